@@ -1,0 +1,963 @@
+// Fully connected layer and recurrent cell (GRU / LSTM) on the 16-bit matrix instructions with the
+// precision of fp32 operands (paper, App. "Model architectures": the FC layer and the core).
+//
+// Arithmetic.  An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 significant bits, each
+// the rounded remainder of the one before), so x * w is the sum of nine exact products.  The six
+// largest are kept: x0w0, x0w1, x1w0, x1w1, x0w2, x2w0; what is dropped is below 2^-25 of the
+// product, i.e. less than the rounding of one fp32 addition.  They run on v_mfma_f32_16x16x32_bf16
+// with fp32 accumulators, smallest products first: 16 times the rate of the fp32 matrix
+// instructions, over six products.  One instruction adds 32 terms to an accumulator, so a sum is
+// rounded 6 times per 32 terms instead of 16 times and comes out nearer to the exact one.  In
+// bf16 configurations the weights are bf16 numbers (one term), the features of the plain stack too
+// (one product), and the state enters with all three terms (three products).
+//
+// Work split.  What bounds these layers is getting the operands into the registers: with few rows
+// the latency of a chain of loads, with many the path from the L2.  So there is no barrier in the K
+// loop: a workgroup of eight waves owns 16*RT rows and 8*U hidden units (FC: 16*U outputs), each
+// wave an eighth of K, its loads running ahead of the products.  The weights are packed in operand
+// order, split ahead of time, and go straight into the registers of the lane that feeds them; the
+// rows are turned into operand order and split into their terms on the way.  The eight partial sums meet in LDS and are added in wave order, where the bias and the gates follow.
+// The order of every sum depends on K alone: the result of a row is the same bits for every choice
+// of RT and U, so these follow the number of rows of the call.  (cell_tile_kernel below, for many
+// rows, sums in another order; which of the two a policy uses is settled at create.)
+//
+// v_mfma_f32_16x16x32_*: lane l supplies A[i = l%16][k = 8*(l/16) + e] and B[k][j = l%16], e = 0..7
+// (16 bytes each); D[i][j] sits in lane j + 16*(i/4), register i%4.  A = weights (i = output
+// column), B = rows: a lane ends up with four neighbouring outputs of one row.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <string.h>
+
+#include <type_traits>
+
+#include "sf_internal.h"
+
+namespace sf {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kWaves = 8;
+constexpr int kThreads = 64 * kWaves;
+
+enum Kind { FC = 0, GRU = 1, LSTM = 2 };
+enum XType { X_F32 = 0, X_BF16 = 1, X_F16 = 2 };
+
+__device__ inline float sigmoid_acc(float a) { return 1.0f / (1.0f + expf(-a)); }
+// (1 - e) / (1 + e) with e = exp(-2|a|), sign restored: e <= 1, nothing overflows
+__device__ inline float tanh_acc(float a) {
+  const float e = expf(-2.0f * fabsf(a));
+  return copysignf((1.0f - e) / (1.0f + e), a);
+}
+
+__device__ inline void cell_gru(float* o, int unit, const float (&sum)[4], const float (&bias)[2][4], float prev) {
+  const float rg = sigmoid_acc(sum[0] + (bias[0][0] + bias[1][0]));
+  const float z = sigmoid_acc(sum[1] + (bias[0][1] + bias[1][1]));
+  const float n = tanh_acc(sum[2] + bias[0][2] + rg * (sum[3] + bias[1][2]));
+  o[unit] = (1.0f - z) * n + z * prev;
+}
+__device__ inline void cell_lstm(float* o, int H, int unit, const float (&sum)[4], const float (&bias)[2][4], float prev) {
+  const float ig = sigmoid_acc(sum[0] + (bias[0][0] + bias[1][0]));
+  const float fg = sigmoid_acc(sum[1] + (bias[0][1] + bias[1][1]));
+  const float gg = tanh_acc(sum[2] + (bias[0][2] + bias[1][2]));
+  const float og = sigmoid_acc(sum[3] + (bias[0][3] + bias[1][3]));
+  const float cn = fg * prev + ig * gg;
+  o[H + unit] = cn;
+  o[unit] = og * tanh_acc(cn);
+}
+
+struct DenseArgs {
+  const void* x1;       // [M][I1] fp32 or 16-bit
+  const float* x2;      // [M][I2] or null (cells)
+  const float* h_in;    // state rows of S floats, row index = row or ids[row] (cells)
+  const uint8_t* done;  // [M] (cells)
+  const int32_t* ids;   // [M] or null
+  const uint8_t* w;     // packed weights
+  const float* b1;      // FC: [N]; cells: b_ih [G*H]
+  const float* b2;      // cells: b_hh [G*H]
+  void* out;            // FC: [M][N]; cells: state rows [M][S]
+  int M, I1, I2, H, S, n_env;
+  int N;                // FC outputs
+  int k1, k2, kn;       // K steps (of 32): of x1, of x1 and x2, all
+  int n_rt, n_cg;       // workgroups along the rows / the columns
+  int rows_per_xcd;     // deal row tiles (1) or column groups (0) to the XCDs
+};
+
+// Rows of the state table: ids[m] where ids are given; an id outside the table reads as a zero
+// state, as after a reset (flag).  One branch for all rows, behind their flag loads: a branch per
+// row makes every row wait for the one before.
+template <int N>
+__device__ inline void state_rows(const DenseArgs& g, int (&row)[N], int (&flag)[N]) {
+  if (!g.ids) return;
+#pragma unroll
+  for (int j = 0; j < N; ++j) row[j] = g.ids[row[j]];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const bool bad = (unsigned)row[j] >= (unsigned)g.n_env;
+    flag[j] |= bad;
+    row[j] = bad ? 0 : row[j];
+  }
+}
+
+// Bytes of one K step and term of a column group: FC 16 columns; cells 8 units, the gates in
+// columns [r z | n] (the 8 n columns of each lane group alone) or [i f | g o].
+constexpr int group_bytes(int kind) { return kind == FC ? 1024 : kind == GRU ? 1536 : 2048; }
+
+// Three terms of two numbers; what is left of them is added to `left`: nothing to speak of, or NaN
+// for an infinity, a NaN and what rounds up to an infinity, which have no terms.
+__device__ inline void split_pair(float r0, float r1, unsigned& t0, unsigned& t1, unsigned& t2, float& left) {
+  const f32x2 v0 = {r0, r1};
+  t0 = __builtin_bit_cast(unsigned, __builtin_convertvector(v0, bf16x2));
+  r0 -= __builtin_bit_cast(float, t0 << 16);
+  r1 -= __builtin_bit_cast(float, t0 & 0xFFFF0000u);
+  const f32x2 v1 = {r0, r1};
+  t1 = __builtin_bit_cast(unsigned, __builtin_convertvector(v1, bf16x2));
+  r0 -= __builtin_bit_cast(float, t1 << 16);
+  r1 -= __builtin_bit_cast(float, t1 & 0xFFFF0000u);
+  const f32x2 v2 = {r0, r1};
+  t2 = __builtin_bit_cast(unsigned, __builtin_convertvector(v2, bf16x2));
+  left += r0 + r1;
+}
+
+// The sums of one row that holds an infinity or a NaN, in plain fp32 arithmetic: the products of
+// such a number with the terms of a weight do not add up to its product with the weight.  q: gate
+// (FC: 0), n: unit (FC: output); the n gate of a GRU has its sums over the features (n_x) and the
+// state (n_h) apart.
+template <int KIND, int XT, int PB>
+__device__ float plain_sum(const DenseArgs& g, int m, int sm, bool reset, int q, int n, int k_from, int k_to) {
+  constexpr int GB = group_bytes(KIND);
+  constexpr int C = KIND == FC ? 16 : 8;
+  float sum = 0.0f;
+  for (int k = 32 * k_from; k < 32 * k_to; ++k) {
+    const int s = k >> 5, lg = (k >> 3) & 3, e = k & 7;
+    float x;
+    if (s < g.k1) {
+      if (XT == X_F32)
+        x = ((const float*)g.x1)[(size_t)m * g.I1 + k];
+      else if (XT == X_BF16)
+        x = __builtin_bit_cast(float, (unsigned)((const uint16_t*)g.x1)[(size_t)m * g.I1 + k] << 16);
+      else
+        x = (float)((const _Float16*)g.x1)[(size_t)m * g.I1 + k];
+    } else if (s < g.k2) {
+      x = g.x2[(size_t)m * g.I2 + (k - 32 * g.k1)];
+    } else {
+      x = reset ? 0.0f : g.h_in[(size_t)sm * g.S + (k - 32 * g.k2)];
+    }
+    int slot;
+    if (KIND == FC)
+      slot = lg * 16 + n % C;
+    else
+      slot = KIND == LSTM || q < 2 ? (q >> 1) * 64 + lg * 16 + (q & 1) * 8 + n % C : 64 + lg * 8 + n % C;
+    const uint8_t* at = g.w + ((size_t)(n / C) * g.kn + s) * PB * GB + slot * 16 + e * 2;
+    float w;
+    if (XT == X_F16) {
+      w = (float)*(const _Float16*)at;
+    } else {
+      w = 0.0f;
+      for (int p = PB - 1; p >= 0; --p) w += __builtin_bit_cast(float, (unsigned)*(const uint16_t*)(at + p * GB) << 16);
+    }
+    sum = fmaf(x, w, sum);
+  }
+  return sum;
+}
+template <int KIND, int XT, int PB>
+__device__ inline void plain_sums(const DenseArgs& g, int m, bool reset, int n, float (&sum)[4]) {
+  const int sm = g.ids && !reset ? g.ids[m] : m;  // (a reset row's state is not read)
+  if (KIND == FC) {
+    sum[0] = plain_sum<KIND, XT, PB>(g, m, sm, reset, 0, n, 0, g.kn);
+  } else {
+    for (int q = 0; q < (KIND == LSTM ? 4 : 2); ++q) sum[q] = plain_sum<KIND, XT, PB>(g, m, sm, reset, q, n, 0, g.kn);
+    if (KIND == GRU) {
+      sum[2] = plain_sum<KIND, XT, PB>(g, m, sm, reset, 2, n, 0, g.k2);
+      sum[3] = plain_sum<KIND, XT, PB>(g, m, sm, reset, 2, n, g.k2, g.kn);
+    }
+  }
+}
+
+// DA, DB: K steps of rows / weights a wave has in flight.
+template <int KIND, int XT, int PB, int RT, int U, int DA, int DB, bool OUT16>
+__global__ __launch_bounds__(kThreads, 2) void dense_split_kernel(DenseArgs g) {
+  constexpr int GB = group_bytes(KIND);
+  constexpr int NB = KIND == FC ? U : KIND == GRU ? U + 1 : 2 * U;  // weight tiles per K step and term
+  constexpr int NA = KIND == FC ? U : KIND == GRU ? U + 2 : 2 * U;  // accumulators per row tile
+  constexpr int RR = RT * NA <= 8 ? RT : 8 / NA;                    // row tiles per round of the sum
+  static_assert(RT % RR == 0, "whole rounds");
+  constexpr int TURN = kWaves * 16 * RT * 36, RED = kWaves * RR * NA * 64 * 4;  // floats
+  __shared__ __attribute__((aligned(16))) float lds[TURN > RED ? TURN : RED];
+  __shared__ int odd_row[16 * RT];  // rows with an infinity or a NaN
+  f32x4(*red)[RR * NA][64] = (f32x4(*)[RR * NA][64])lds;  // after the K loop
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2: an XCD gets column
+  // groups of its own (its share of the weights stays in its L2) or row tiles of its own,
+  // whichever leaves the smaller operand to be read by all of them.
+  int rt0, cg;
+  {
+    const int id = blockIdx.x, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt, n_out = g.rows_per_xcd ? g.n_rt : g.n_cg;
+    const int per = (n_out + 7) / 8, slot = id >> 3;
+    const int o = (id & 7) * per + slot / n_in, i = slot % n_in;
+    if (slot >= per * n_in || o >= n_out) return;
+    rt0 = g.rows_per_xcd ? o : i;
+    cg = g.rows_per_xcd ? i : o;
+  }
+  const int row0 = rt0 * 16 * RT;
+
+  // Rows are loaded with neighbouring lanes on neighbouring bytes (fp32: eight lanes per row, 128
+  // bytes = a K step; 16 bits: four lanes, 64 bytes) and turned into operand order in LDS, in a
+  // corner of the wave's own: no barrier.  Loaded in operand order (lane = row) the same bytes take
+  // 2.5 times as long: 9.6 against 24 TB/s out of the L2, contiguous weights 32.
+  // Row indices of this lane's loads (past the end: the last row again, never stored).
+  constexpr int NL = 2 * RT;                       // loads per K step of fp32 rows
+  if (tid < 16 * RT) odd_row[tid] = 0;
+  int xm[NL], hm[NL], dn[NL] = {}, xm16[XT == X_F32 ? 1 : RT];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    xm[j] = hm[j] = min(row0 + 8 * j + (lane >> 3), g.M - 1);
+    if (KIND != FC) dn[j] = g.done[xm[j]];
+  }
+  if (KIND != FC) state_rows(g, hm, dn);
+  if (XT != X_F32)
+#pragma unroll
+    for (int j = 0; j < RT; ++j) xm16[j] = min(row0 + 16 * j + (lane >> 2), g.M - 1);
+  // this lane's place in the weights of a K step: tile t, lane offset
+  const size_t group_stride = (size_t)g.kn * PB * GB;
+  const uint8_t* wbase = g.w + (size_t)cg * U * group_stride;
+  uint32_t woff[NB];
+#pragma unroll
+  for (int t = 0; t < NB; ++t) {
+    if (KIND == FC)
+      woff[t] = (uint32_t)(t * group_stride) + lane * 16;
+    else if (KIND == LSTM)
+      woff[t] = (uint32_t)((t >> 1) * group_stride) + (t & 1) * 1024 + lane * 16;
+    else if (t < U)
+      woff[t] = (uint32_t)(t * group_stride) + lane * 16;
+    else  // the n columns: 8 per group (one group: twice the same eight)
+      woff[t] = (uint32_t)((U == 2 ? (li >> 3) : 0) * group_stride) + 1024 + (lg * 8 + (li & 7)) * 16;
+  }
+
+  f32x4 acc[RT][NA];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int t = 0; t < NA; ++t) acc[r][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // What the gates need from memory, requested behind the first operands.  Thread -> (element of four
+  // neighbouring outputs, row, four outputs); EPT such elements of a round's row tiles
+  constexpr int ET = 16 * 8 * U;               // cells: threads per row tile
+  const int er = tid & 3, erow = (tid >> 2) & 15, eq = (tid >> 6) & (2 * U - 1), ert = tid / ET;
+  const int unit = (cg * U * 2 + eq) * 4 + er;
+  float bias[2][4] = {}, prev[RT / RR] = {};
+  int gdn[RT / RR] = {};
+  f32x4 fbias = {0, 0, 0, 0};
+  constexpr int ft_per_rt = 64 * U;            // FC: threads per row tile
+  auto load_gates = [&]() __attribute__((always_inline)) {
+    if (KIND == FC) {
+      fbias = *(const f32x4*)(g.b1 + cg * 16 * U + ((tid >> 6) % U) * 16 + 4 * lg);
+    } else {
+  #pragma unroll
+      for (int q = 0; q < (KIND == LSTM ? 4 : 3); ++q) {
+        bias[0][q] = g.b1[q * g.H + unit];
+        bias[1][q] = g.b2[q * g.H + unit];
+      }
+      int ghm[RT / RR];
+  #pragma unroll
+      for (int rd = 0; rd < RT / RR; ++rd) {
+        ghm[rd] = min(row0 + 16 * (rd * RR + (ert < RR ? ert : 0)) + erow, g.M - 1);
+        gdn[rd] = g.done[ghm[rd]];
+      }
+      state_rows(g, ghm, gdn);
+  #pragma unroll
+      for (int rd = 0; rd < RT / RR; ++rd) prev[rd] = g.h_in[(size_t)ghm[rd] * g.S + (KIND == LSTM ? g.H : 0) + unit];
+    }
+  };
+  const int s_begin = g.kn * wave / kWaves, s_end = g.kn * (wave + 1) / kWaves;
+  f32x4 a[DA][NL];
+  u32x4 b[DB][PB][NB];
+  auto load_b = [&](auto slotc, int s) __attribute__((always_inline)) {
+    constexpr int SL = decltype(slotc)::value;
+    s = max(min(s, s_end - 1), 0);
+    const uint8_t* wp = wbase + (size_t)s * (PB * GB);
+#pragma unroll
+    for (int p = 0; p < PB; ++p)
+#pragma unroll
+      for (int t = 0; t < NB; ++t) b[SL][p][t] = *(const u32x4*)(wp + (woff[t] + p * GB));
+  };
+  // F32: one of the fp32 pieces (the row pitches are whole K steps), else 16-bit features.
+  // (selects, not branches: a branch around a load makes the compiler wait for all loads where
+  // the paths join)
+  auto load_a = [&](auto f32c, auto slotc, int s) __attribute__((always_inline)) {
+    constexpr int SL = decltype(slotc)::value;
+    s = max(min(s, s_end - 1), 0);
+    if constexpr (decltype(f32c)::value) {
+      const uint8_t* base = (const uint8_t*)g.x1 + (size_t)s * 128;
+      uint32_t pitch = (uint32_t)g.I1 >> 5;
+      if (KIND != FC) {
+        base = XT == X_F32 && s < g.k1 ? base : (s < g.k2 ? (const uint8_t*)g.x2 + (size_t)(s - g.k1) * 128
+                                                          : (const uint8_t*)g.h_in + (size_t)(s - g.k2) * 128);
+        pitch = (uint32_t)(XT == X_F32 && s < g.k1 ? g.I1 : s < g.k2 ? g.I2 : g.S) >> 5;
+      }
+      base += (lane & 7) * 16;
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        const uint32_t m = KIND == FC || s < g.k2 ? xm[j] : hm[j];
+        a[SL][j] = *(const f32x4*)(base + ((size_t)(m * pitch) << 7));
+      }
+    } else {
+      const uint8_t* base = (const uint8_t*)g.x1 + (size_t)s * 64 + (lane & 3) * 16;
+#pragma unroll
+      for (int j = 0; j < RT; ++j) a[SL][j] = *(const f32x4*)(base + ((size_t)((uint32_t)xm16[j] * ((uint32_t)g.I1 >> 5)) << 6));
+    }
+  };
+  auto mfma = [&](const u32x4& w, const u32x4& x, f32x4& c) __attribute__((always_inline)) {
+    if (XT == X_F16)
+      c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
+    else
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
+  };
+  // one K step, rows in fp32 or (F32 false) in 16 bits
+  constexpr int P32 = 36, P16 = 20;  // pitch of a row in LDS (floats): 16-byte accesses without conflicts
+  float left[RT] = {};
+  float* turn = lds + wave * (16 * RT * P32);
+  auto use = [&](auto f32c, auto slota, auto slotb, bool state) __attribute__((always_inline)) {
+    constexpr int SA = decltype(slota)::value, SB = decltype(slotb)::value;
+    constexpr bool F32 = decltype(f32c)::value;
+    if constexpr (F32) {
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        f32x4 v = a[SA][j];
+        if (KIND != FC) {
+          const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+          v = state && dn[j] ? zero : v;
+        }
+        *(f32x4*)(turn + (8 * j + (lane >> 3)) * P32 + (lane & 7) * 4) = v;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < RT; ++j) *(f32x4*)(turn + (16 * j + (lane >> 2)) * P16 + (lane & 3) * 4) = a[SA][j];
+    }
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      u32x4 x[3];
+      if (F32) {
+        const f32x4 v0 = *(const f32x4*)(turn + (16 * r + li) * P32 + lg * 8);
+        const f32x4 v1 = *(const f32x4*)(turn + (16 * r + li) * P32 + lg * 8 + 4);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          unsigned t0, t1, t2;
+          split_pair(p < 2 ? v0[2 * p] : v1[2 * p - 4], p < 2 ? v0[2 * p + 1] : v1[2 * p - 3], t0, t1, t2, left[r]);
+          x[0][p] = t0;
+          x[1][p] = t1;
+          x[2][p] = t2;
+        }
+      } else {
+        x[0] = __builtin_bit_cast(u32x4, *(const f32x4*)(turn + (16 * r + li) * P16 + lg * 4));
+      }
+      // smallest products first
+      if constexpr (F32 && PB == 3) {
+#pragma unroll
+        for (int t = 0; t < NB; ++t) mfma(b[SB][2][t], x[0], acc[r][t]);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) mfma(b[SB][0][t], x[2], acc[r][t]);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) mfma(b[SB][1][t], x[1], acc[r][t]);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) mfma(b[SB][1][t], x[0], acc[r][t]);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) mfma(b[SB][0][t], x[1], acc[r][t]);
+      } else if constexpr (F32) {
+#pragma unroll
+        for (int t = 0; t < NB; ++t) mfma(b[SB][0][t], x[2], acc[r][t]);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) mfma(b[SB][0][t], x[1], acc[r][t]);
+      }
+#pragma unroll
+      for (int t = 0; t < NB; ++t) mfma(b[SB][0][t], x[0], acc[r][t]);
+    }
+  };
+  // The GRU's n gate needs its sums over the features and over the state apart: at the border
+  // the first moves aside (acc[U] -> acc[U + 1]) and acc[U] starts again.
+  auto move_n = [&]() __attribute__((always_inline)) {
+    if constexpr (KIND == GRU) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        acc[r][U + 1] = acc[r][U];
+        acc[r][U] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    }
+  };
+  auto each = [&](auto f) __attribute__((always_inline)) {
+    f(std::integral_constant<int, 0>{});
+    if constexpr (DA > 1) f(std::integral_constant<int, 1>{});
+    if constexpr (DA > 2) f(std::integral_constant<int, 2>{});
+    if constexpr (DA > 3) f(std::integral_constant<int, 3>{});
+  };
+  static_assert(DA % DB == 0, "weights of a step sit in slot (step % DB)");
+  // K steps [s0, s1) on rows of one type.  Steps in flight are refilled without conditions around
+  // the loads, then come the last DA without loads.
+  auto phase = [&](auto f32c, int s0, int s1) __attribute__((always_inline)) {
+    if (s0 >= s1) {
+      if (XT == X_F32) load_gates();
+      return;
+    }
+    auto step = [&](auto slota, auto slotb, int s) __attribute__((always_inline)) {
+      if (s >= s1) return;
+      if (KIND == GRU && s == g.k2) move_n();
+      use(f32c, slota, slotb, KIND != FC && s >= g.k2);
+    };
+    int s = s0;
+    each([&](auto i) __attribute__((always_inline)) {
+      constexpr int I = decltype(i)::value;
+      load_a(f32c, i, s + I);
+      if constexpr (I < DB) load_b(i, s + I);
+    });
+    if (XT == X_F32) load_gates();
+    for (; s + DA < s1; s += DA)
+      each([&](auto i) __attribute__((always_inline)) {
+        constexpr int I = decltype(i)::value;
+        using SB = std::integral_constant<int, I % DB>;
+        step(i, SB{}, s + I);
+        load_b(SB{}, s + I + DB);
+        load_a(f32c, i, s + I + DA);
+      });
+    each([&](auto i) __attribute__((always_inline)) {
+      constexpr int I = decltype(i)::value;
+      using SB = std::integral_constant<int, I % DB>;
+      step(i, SB{}, s + I);
+      if constexpr (I + DB < DA) load_b(SB{}, s + I + DB);
+    });
+  };
+  if (XT != X_F32) load_gates();
+  if (XT == X_F32) {
+    phase(std::true_type{}, s_begin, s_end);
+  } else {
+    phase(std::false_type{}, s_begin, min(s_end, g.k1));
+    if (KIND != FC) phase(std::true_type{}, max(s_begin, g.k1), s_end);
+  }
+  if (KIND == GRU && s_end <= g.k2) move_n();
+  // The eight partial sums, RR row tiles at a time, added in wave order.
+#pragma unroll
+  for (int rd = 0; rd < RT / RR; ++rd) {
+    __syncthreads();  // (the K loop's LDS, or the last round's sums, are no longer read)
+    if (rd == 0)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+        if (left[r] != left[r]) odd_row[16 * r + li] = 1;
+#pragma unroll
+    for (int r = 0; r < RR; ++r)
+#pragma unroll
+      for (int t = 0; t < NA; ++t) red[wave][r * NA + t][lane] = acc[rd * RR + r][t];
+    __syncthreads();
+    if (KIND == FC) {
+      for (int u = tid; u < RR * ft_per_rt; u += kThreads) {
+        const int r = u / ft_per_rt, t = (u >> 6) % U;
+        f32x4 v = red[0][r * NA + t][lane];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) v += red[w][r * NA + t][lane];
+        const int m = row0 + 16 * (rd * RR + r) + li;
+        if (__builtin_expect(odd_row[16 * (rd * RR + r) + li] != 0, 0) && m < g.M)
+          for (int e = 0; e < 4; ++e)
+            v[e] = plain_sum<KIND, XT, PB>(g, m, m, false, 0, cg * 16 * U + t * 16 + 4 * lg + e, 0, g.kn);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e] + fbias[e], 0.0f);
+        const size_t o = (size_t)m * g.N + cg * 16 * U + t * 16 + 4 * lg;
+        if (m < g.M) {
+          if (OUT16) {
+            const f32x2 lo = {v[0], v[1]}, hi = {v[2], v[3]};
+            u32x2 pk;
+            pk[0] = __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf16x2));
+            pk[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf16x2));
+            *(u32x2*)((uint16_t*)g.out + o) = pk;
+          } else {
+            *(f32x4*)((float*)g.out + o) = v;
+          }
+        }
+      }
+    } else {
+      if (ert < RR) {
+        // the gates of one unit: (tile, lane group) of the four sums
+        const int gq = eq >> 1, hq = eq & 1;
+        int tl[4], ln[4];
+        if (KIND == LSTM) {
+          tl[0] = tl[1] = 2 * gq;
+          tl[2] = tl[3] = 2 * gq + 1;
+          ln[0] = ln[2] = hq;
+          ln[1] = ln[3] = 2 + hq;
+        } else {
+          tl[0] = tl[1] = gq;
+          tl[2] = U + 1;
+          tl[3] = U;
+          ln[0] = hq;
+          ln[1] = 2 + hq;
+          ln[2] = ln[3] = eq;
+        }
+        float sum[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float* src = (const float*)&red[0][ert * NA + tl[q]][16 * ln[q] + erow] + er;
+          float v = src[0];
+#pragma unroll
+          for (int w = 1; w < kWaves; ++w) v += src[w * (RR * NA * 64 * 4)];
+          sum[q] = v;
+        }
+        const int m = row0 + 16 * (rd * RR + ert) + erow;
+        if (m < g.M) {
+          float* o = (float*)g.out + (size_t)m * g.S;
+          const bool rs = gdn[rd] != 0;
+          if (__builtin_expect(odd_row[16 * (rd * RR + ert) + erow] != 0, 0))
+            plain_sums<KIND, XT, PB>(g, m, rs, unit, sum);
+          const float before = rs ? 0.0f : prev[rd];
+          if (KIND == LSTM)
+            cell_lstm(o, g.H, unit, sum, bias, before);
+          else
+            cell_gru(o, unit, sum, bias, before);
+        }
+      }
+    }
+  }
+}
+
+// The cell of an fp32 configuration on many rows: a workgroup owns 64 rows and 32 hidden units in
+// two halves.  Four waves share a half and take every fourth K step; the rows of a chunk of four K
+// steps are split once for all eight waves and wait in LDS in operand order (two buffers, one
+// barrier per chunk), the weights go from memory to the one wave that needs them.
+template <int KIND>
+__global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
+  constexpr int XT = X_F32, PB = 3;
+  constexpr int GB = group_bytes(KIND);
+  constexpr int U = 2;                         // column groups per wave
+  constexpr int NB = KIND == GRU ? U + 1 : 2 * U, NA = 2 * U;
+  constexpr int RT = 4, KW = 4;                // row tiles; K steps per chunk
+  constexpr int RR = 2;                        // row tiles per round of the sum
+  constexpr int NP = 3;                        // terms of a row element
+  constexpr int BUF = NP * RT * KW * 1024;     // bytes of a chunk in LDS
+  constexpr int RED = kWaves * RR * NA * 1024;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * BUF > RED ? 2 * BUF : RED];
+  __shared__ int odd_row[64];                  // rows with an infinity or a NaN
+  f32x4(*red)[RR * NA][64] = (f32x4(*)[RR * NA][64])lds;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kw = wave & 3, half = wave >> 2;
+  const int li = lane & 15, lg = lane >> 4;
+  int rt0, cg;
+  {
+    const int id = blockIdx.x, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt, n_out = g.rows_per_xcd ? g.n_rt : g.n_cg;
+    const int per = (n_out + 7) / 8, slot = id >> 3;
+    const int o = (id & 7) * per + slot / n_in, i = slot % n_in;
+    if (slot >= per * n_in || o >= n_out) return;
+    rt0 = g.rows_per_xcd ? o : i;
+    cg = g.rows_per_xcd ? i : o;
+  }
+  const int row0 = rt0 * 64;
+  const int group0 = (cg * 2 + half) * U;      // this wave's first column group
+
+  // rows of a chunk: thread -> (row tid/32 + 16 j, four floats)
+  constexpr int NL = 4;
+  int xm[NL], hm[NL], dn[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    xm[j] = hm[j] = min(row0 + 16 * j + (tid >> 5), g.M - 1);
+    dn[j] = g.done[xm[j]];
+  }
+  state_rows(g, hm, dn);
+  if (tid < 64) odd_row[tid] = 0;
+
+  const size_t group_stride = (size_t)g.kn * PB * GB;
+  const uint8_t* wbase = g.w + (size_t)group0 * group_stride;
+  uint32_t woff[NB];
+#pragma unroll
+  for (int t = 0; t < NB; ++t) {
+    if (KIND == GRU && t < U)
+      woff[t] = (uint32_t)(t * group_stride) + lane * 16;
+    else if (KIND == LSTM)
+      woff[t] = (uint32_t)((t >> 1) * group_stride) + (t & 1) * 1024 + lane * 16;
+    else
+      woff[t] = (uint32_t)((li >> 3) * group_stride) + 1024 + (lg * 8 + (li & 7)) * 16;
+  }
+
+  f32x4 acc[RT][NA];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int t = 0; t < NA; ++t) acc[r][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  const int nc = g.kn / KW, c1 = g.k1 / KW, c2 = g.k2 / KW;
+  f32x4 a[NL];
+  u32x4 b[2][PB][NB];
+  auto load_b = [&](auto slotc, int c) __attribute__((always_inline)) {
+    constexpr int SL = decltype(slotc)::value;
+    const uint8_t* wp = wbase + (size_t)(min(c, nc - 1) * KW + kw) * (PB * GB);
+#pragma unroll
+    for (int p = 0; p < PB; ++p)
+#pragma unroll
+      for (int t = 0; t < NB; ++t) b[SL][p][t] = *(const u32x4*)(wp + (woff[t] + p * GB));
+  };
+  // Where the next chunk to load has its rows.  Moved on ahead of an iteration's instructions, so
+  // that these stay one block for the scheduler (selects around the loads become branches); it
+  // stays on the last chunk.
+  const uint8_t* from = (const uint8_t*)g.x1;
+  uint32_t from_pitch = (uint32_t)g.I1 >> 5;
+  int from_c = 0, from_state = 0;
+  auto advance = [&]() __attribute__((always_inline)) {
+    if (from_c + 1 >= nc) return;
+    ++from_c;
+    from += 512;
+    if (from_c == c1) {
+      from = (const uint8_t*)g.x2;
+      from_pitch = (uint32_t)g.I2 >> 5;
+    }
+    if (from_c == c2) {
+      from = (const uint8_t*)g.h_in;
+      from_pitch = (uint32_t)g.S >> 5;
+      from_state = 1;
+    }
+  };
+  auto load_a = [&]() __attribute__((always_inline)) {
+    const uint8_t* base = from + (tid & 31) * 16;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const uint32_t m = from_state ? hm[j] : xm[j];
+      a[j] = *(const f32x4*)(base + ((size_t)(m * from_pitch) << 7));
+    }
+  };
+  // Place of (row, K step of the chunk, lane group) in a term's 1 KB operand of (row tile, K step):
+  // rows are exchanged by (lane group, K step), so that the lanes of a store, which differ in
+  // these, spread over the banks.
+  auto slot_of = [&](int row, int ks, int kg) { return 16 * kg + (row ^ ((kg << 2) | ks)); };
+  float left[NL] = {};
+  // piece j of this thread's rows of chunk c into buffer buf
+  auto store_a = [&](int c, int buf, int j) __attribute__((always_inline)) {
+    uint8_t* dst = lds + buf * BUF;
+    const int ks = (tid & 31) >> 3, kg = (tid & 7) >> 1, hf = tid & 1;
+    uint8_t* at = dst + ks * (NP * 1024) + slot_of(tid >> 5, ks, kg) * 16 + hf * 8 + j * KW * (NP * 1024);
+    const unsigned keep = (c >= c2) & (dn[j] != 0) ? 0u : ~0u;
+    u32x2 t[3];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      unsigned t0, t1, t2;
+      float v0 = a[j][2 * p], v1 = a[j][2 * p + 1];
+      v0 = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v0) & keep);
+      v1 = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v1) & keep);
+      split_pair(v0, v1, t0, t1, t2, left[j]);
+      t[0][p] = t0;
+      t[1][p] = t1;
+      t[2][p] = t2;
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *(u32x2*)(at + q * 1024) = t[q];
+  };
+  const int rd_slot = slot_of(li, kw, lg) * 16 + kw * (NP * 1024);
+  // the products of row tile r of a chunk
+  auto products = [&](auto slotc, int r) __attribute__((always_inline)) {
+    constexpr int SL = decltype(slotc)::value;
+    const uint8_t* src = lds + SL * BUF + rd_slot + r * KW * (NP * 1024);
+    bf16x8 x[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) x[q] = *(const bf16x8*)(src + q * 1024);
+    auto term = [&](int wq, int xq) __attribute__((always_inline)) {
+#pragma unroll
+      for (int t = 0; t < NB; ++t)
+        acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[SL][wq][t]), x[xq], acc[r][t], 0, 0, 0);
+    };
+    term(2, 0);
+    term(0, 2);
+    term(1, 1);
+    term(1, 0);
+    term(0, 1);
+    term(0, 0);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  load_a();
+  load_b(I0{}, 0);
+#pragma unroll
+  for (int j = 0; j < NL; ++j) store_a(0, 0, j);
+  advance();
+  load_a();
+  load_b(I1{}, 1);  // (the order of the loop: the waits of its first trip are those of every trip)
+  __syncthreads();
+  // Iteration c: products of chunk c, rows of chunk c + 1 into the other buffer, loads of c + 2
+  // (past the end: the last chunk again, unused; no conditions around the loads).  The two waves
+  // of a SIMD leave the barrier together, so that each has to mix its own matrix and vector
+  // instructions: in separate stretches both would use the one pipe, then both the other.
+  auto iter = [&](auto slotc, int c) __attribute__((always_inline)) {
+    constexpr int SL = decltype(slotc)::value;
+    if (KIND == GRU && c == c2) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        acc[r][NA - 1] = acc[r][NA - 2];
+        acc[r][NA - 2] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    }
+    advance();
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      products(slotc, r);
+      store_a(c + 1, SL ^ 1, r);
+    }
+    load_a();
+    load_b(slotc, c + 2);
+#pragma unroll
+    for (int i = 0; i < RT * NB * 6; ++i) {  // one matrix instruction, two vector instructions
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+    }
+    __syncthreads();
+  };
+  int c = 0;
+  for (; c + 1 < nc; c += 2) {
+    iter(I0{}, c);
+    iter(I1{}, c + 1);
+  }
+  if (c < nc) iter(I0{}, c);
+
+  // What the gates need, requested ahead of the exchange of sums.  Thread -> unit (half, four of
+  // the half's sixteen, one of them), rows lane/4 + 16 j: a wave reads its sums from 64
+  // neighbouring words of LDS.
+  const int un = wave * 4 + (lane & 3), unit = cg * 32 + un, erow = lane >> 2;
+  float bias[2][4] = {}, prev[RT];
+  int gdn[RT], ghm[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    ghm[j] = min(row0 + 16 * j + erow, g.M - 1);
+    gdn[j] = g.done[ghm[j]];
+  }
+  state_rows(g, ghm, gdn);
+#pragma unroll
+  for (int j = 0; j < RT; ++j) prev[j] = g.h_in[(size_t)ghm[j] * g.S + (KIND == LSTM ? g.H : 0) + unit];
+#pragma unroll
+  for (int q = 0; q < (KIND == LSTM ? 4 : 3); ++q) {
+    bias[0][q] = g.b1[q * g.H + unit];
+    bias[1][q] = g.b2[q * g.H + unit];
+  }
+#pragma unroll
+  for (int j = 0; j < NL; ++j)
+    if (left[j] != left[j]) odd_row[16 * j + (tid >> 5)] = 1;
+
+  // the four partial sums of a half, RR row tiles at a time, in wave order
+#pragma unroll
+  for (int rd = 0; rd < RT / RR; ++rd) {
+    if (rd) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RR; ++r)
+#pragma unroll
+      for (int t = 0; t < NA; ++t) red[wave][r * NA + t][lane] = acc[rd * RR + r][t];
+    __syncthreads();
+    {
+      const int hf = wave >> 2, eq = wave & 3, er = lane & 3;
+      const int gq = eq >> 1, hq = eq & 1;
+#pragma unroll
+      for (int r = 0; r < RR; ++r) {
+        int tl[4], ln[4];
+        if (KIND == LSTM) {
+          tl[0] = tl[1] = 2 * gq;
+          tl[2] = tl[3] = 2 * gq + 1;
+          ln[0] = ln[2] = hq;
+          ln[1] = ln[3] = 2 + hq;
+        } else {
+          tl[0] = tl[1] = gq;
+          tl[2] = U + 1;
+          tl[3] = U;
+          ln[0] = hq;
+          ln[1] = 2 + hq;
+          ln[2] = ln[3] = eq;
+        }
+        float sum[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float* src = (const float*)&red[4 * hf][r * NA + tl[q]][16 * ln[q] + erow] + er;
+          float v = src[0];
+#pragma unroll
+          for (int w = 1; w < 4; ++w) v += src[w * (RR * NA * 64 * 4)];
+          sum[q] = v;
+        }
+        const int j = rd * RR + r, m = row0 + 16 * j + erow;
+        if (m < g.M) {
+          float* o = (float*)g.out + (size_t)m * g.S;
+          const bool rs = gdn[j] != 0;
+          if (__builtin_expect(odd_row[16 * j + erow] != 0, 0))
+            plain_sums<KIND, XT, PB>(g, m, rs, unit, sum);
+          const float before = rs ? 0.0f : prev[j];
+          if (KIND == LSTM)
+            cell_lstm(o, g.H, unit, sum, bias, before);
+          else
+            cell_gru(o, unit, sum, bias, before);
+        }
+      }
+    }
+  }
+}
+
+template <int KIND, int XT, int PB, int RT, int U, int DA, int DB, bool OUT16>
+hipError_t launch_cfg(DenseArgs g, hipStream_t st) {
+  g.n_rt = (g.M + 16 * RT - 1) / (16 * RT);
+  g.n_cg = KIND == FC ? g.N / (16 * U) : g.H / (8 * U);
+  // bytes of the rows against bytes of the weights
+  const long long xb = (long long)g.M * g.kn * 32 * (XT == X_F32 ? 4 : 2);
+  const long long wb = (long long)g.n_cg * U * g.kn * PB * group_bytes(KIND);
+  g.rows_per_xcd = xb > wb;
+  const int n_out = g.rows_per_xcd ? g.n_rt : g.n_cg, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt;
+  const unsigned blocks = 8u * ((n_out + 7) / 8) * n_in;
+  dense_split_kernel<KIND, XT, PB, RT, U, DA, DB, OUT16><<<blocks, kThreads, 0, st>>>(g);
+  return hipGetLastError();
+}
+
+template <int KIND>
+hipError_t launch_tile(DenseArgs g, hipStream_t st) {
+  g.n_rt = (g.M + 63) / 64;
+  g.n_cg = g.H / 32;
+  const long long xb = (long long)g.M * g.kn * 128, wb = (long long)(g.H / 8) * g.kn * 3 * group_bytes(KIND);
+  g.rows_per_xcd = xb > wb;
+  const int n_out = g.rows_per_xcd ? g.n_rt : g.n_cg, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt;
+  cell_tile_kernel<KIND><<<8u * ((n_out + 7) / 8) * n_in, kThreads, 0, st>>>(g);
+  return hipGetLastError();
+}
+
+long long split_workgroups(long long M, int n_col, int rt, int u) {
+  return ((M + 16 * rt - 1) / (16 * rt)) * (n_col / u);
+}
+
+// Rows and columns per workgroup: the smallest tile whose grid is one round of workgroups (256, one
+// per CU), since a round takes about as long with one workgroup as with 256.  Launch times (us) of
+// the FC layer 2304 -> 512 / the GRU 512 -> 512 in fp32, one CU tile per column:
+//   rows   16 x 1      32 x 1      32 x 2      64 x 2
+//     64   6.2 /  5.7  8.4 /  8.0 10.0 /  8.3 18.2 / 14.3
+//    256  11.8 / 21.2  9.8 / 16.6 10.9 /  9.5 18.8 / 15.4
+//    512  24.0 / 40    16  / 32   12.3 / 18   19   / 16
+//   1024  62   / 85    35  / 68   25   / 38   23   / 35
+// The bits of a result do not depend on it.
+template <int KIND, int XT, int PB, bool OUT16>
+hipError_t launch_kind(const DenseArgs& g, hipStream_t st) {
+  const int n_col = KIND == FC ? g.N / 16 : g.H / 8;
+  if (split_workgroups(g.M, n_col, 1, 1) <= 256) return launch_cfg<KIND, XT, PB, 1, 1, 4, 4, OUT16>(g, st);
+  if (split_workgroups(g.M, n_col, 2, 1) <= 256) return launch_cfg<KIND, XT, PB, 2, 1, 3, 3, OUT16>(g, st);
+  // (a cell of 64 rows does not fit the registers)
+  if (KIND != FC || split_workgroups(g.M, n_col, 2, 2) <= 256) return launch_cfg<KIND, XT, PB, 2, 2, 2, 2, OUT16>(g, st);
+  if constexpr (KIND == FC) return launch_cfg<KIND, XT, PB, 4, 2, 3, 3, OUT16>(g, st);
+  return hipErrorInvalidValue;
+}
+
+// Eight neighbouring weights -> one operand of a lane per term, `stride` elements apart.  bf16 to
+// nearest, ties to even; what would become infinite is cut off.  (Plain loops over eight: the
+// compiler's vectors.)
+inline void put8(const float* src, int terms, bool f16, uint16_t* dst, size_t stride) {
+  if (f16) {
+    for (int e = 0; e < 8; ++e) dst[e] = conv_weight_bits(src[e], true);
+    return;
+  }
+  typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+  typedef float f32x8 __attribute__((ext_vector_type(8)));
+  typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+  f32x8 r;
+  memcpy(&r, src, sizeof(r));
+  for (int q = 0; q < terms; ++q) {
+    const u32x8 u = __builtin_bit_cast(u32x8, r);
+    const u32x8 up = (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u;
+    const u32x8 inf = (u32x8)((up & 0x7F800000u) == 0x7F800000u);  // all ones where true
+    const u32x8 t = (up & ~inf) | (u & 0xFFFF0000u & inf);
+    const u16x8 h = __builtin_convertvector(t >> 16, u16x8);
+    memcpy(dst + q * stride, &h, sizeof(h));
+    r -= __builtin_bit_cast(f32x8, t);
+  }
+}
+
+}  // namespace
+
+// FC: N outputs from K inputs, whole column groups and whole K steps.
+bool dense_fc_supported(int K, int N) { return K > 0 && (K % 32) == 0 && N > 0 && (N % 32) == 0; }
+bool dense_cell_supported(int I1, int I2, int H) {
+  return I1 > 0 && (I1 % 32) == 0 && (I2 % 32) == 0 && H > 0 && (H % 32) == 0;
+}
+// FC layer on 16-bit rows: up to two rounds of the largest tile the tiled kernel (k_conv_bf16.hip),
+// whose time hardly depends on the batch, is the slower one: 2304 -> 512 in bf16 at 2048 rows 17
+// against 21 us, at 4096 rows 33 against 23; 4608 -> 256 in fp16 at 2048 rows 18 against 41 us, at
+// 8192 rows 62 against 45.
+bool dense_fc_small(int M, int N) { return split_workgroups(M, N / 16, 4, 2) <= 512; }
+// Cells: up to two rounds of the 32-row tile.  Beyond, cell_tile_kernel in fp32 (GRU 512 -> 512 at
+// 512 rows 18 against 21 us, at 1024 rows 38 against 25) and k_rnn_bf16.hip in bf16 (at 512 rows 12
+// against 20 us, at 1024 rows 24 against 21; 256 -> 256 at 1024 rows 10 against 14, at 2048 20
+// against 17).  The kernels' sums run in different orders, so that this is settled once, by the
+// largest batch.
+bool dense_cell_small(int M, int H) { return split_workgroups(M, H / 8, 2, 2) <= 512; }
+bool dense_cell_tile_supported(int I1, int I2, int H) {
+  return I1 > 0 && (I1 % 128) == 0 && (I2 % 128) == 0 && H > 0 && (H % 128) == 0;
+}
+
+// w [N][K] -> [N / 16][K / 32][terms][64][8]; terms: 3 (fp32 weights) or 1 (bf16, or fp16 if f16).
+void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, std::vector<uint16_t>& out) {
+  const int kn = K / 32;
+  out.resize((size_t)N * K * terms);
+  for (int nb = 0; nb < N / 16; ++nb)
+    for (int s = 0; s < kn; ++s)
+      for (int lg = 0; lg < 4; ++lg)
+        for (int i = 0; i < 16; ++i)
+          put8(w + (size_t)(nb * 16 + i) * K + 32 * s + 8 * lg, terms, f16,
+               out.data() + (((size_t)nb * kn + s) * terms * 64 + lg * 16 + i) * 8, 64 * 8);
+}
+
+// w_ih [G*H][I], w_hh [G*H][H] -> [H / 8][(I + H) / 32][terms][operands of a group]: tile columns
+// [i f | g o] (LSTM) or [r z] and the eight n columns of every lane group (GRU).
+void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms,
+                     std::vector<uint16_t>& out) {
+  const int kn = (I + H) / 32, G = lstm ? 4 : 3;
+  const size_t gb = group_bytes(lstm ? LSTM : GRU) / 2;
+  out.resize((size_t)(H / 8) * kn * terms * gb);
+  for (int gr = 0; gr < H / 8; ++gr)
+    for (int s = 0; s < kn; ++s) {
+      uint16_t* dst = out.data() + ((size_t)gr * kn + s) * terms * gb;
+      const float* src = 32 * s < I ? w_ih + 32 * s : w_hh + (32 * s - I);
+      const size_t pitch = 32 * s < I ? I : H;
+      for (int q = 0; q < G; ++q)
+        for (int lg = 0; lg < 4; ++lg)
+          for (int i = 0; i < 8; ++i) {
+            const size_t slot = q < 2 || lstm ? (size_t)(q >> 1) * 64 + lg * 16 + (q & 1) * 8 + i : (size_t)64 + lg * 8 + i;
+            put8(src + ((size_t)q * H + gr * 8 + i) * pitch + 8 * lg, terms, false, dst + slot * 8, gb);
+          }
+    }
+}
+
+// x [M][K] (x_type 0 fp32, 1 bf16, 2 fp16), w packed with three terms for fp32 rows and one for
+// 16-bit rows; out [M][N] = relu(x w^T + bias), fp32 or (out_bf16) bf16.
+hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const float* bias, void* out, int out_bf16,
+                           int M, int K, int N, hipStream_t st) {
+  if (M == 0) return hipSuccess;
+  if (!dense_fc_supported(K, N)) return hipErrorInvalidValue;
+  DenseArgs g{};
+  g.x1 = x; g.w = (const uint8_t*)w; g.b1 = bias; g.out = out;
+  g.M = M; g.I1 = K; g.N = N; g.k1 = g.k2 = g.kn = K / 32;
+  if (x_type == X_F32) return out_bf16 ? hipErrorInvalidValue : launch_kind<FC, X_F32, 3, false>(g, st);
+  if (x_type == X_BF16)
+    return out_bf16 ? launch_kind<FC, X_BF16, 1, true>(g, st) : launch_kind<FC, X_BF16, 1, false>(g, st);
+  return out_bf16 ? hipErrorInvalidValue : launch_kind<FC, X_F16, 1, false>(g, st);
+}
+
+// terms: of the packed weights (3 or 1; bf16 features go with one); tile: cell_tile_kernel.
+hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16, const float* x2,
+                             const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
+                             const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st) {
+  if (B == 0) return hipSuccess;
+  if (!x2) I2 = 0;
+  if (!dense_cell_supported(I1, I2, H) || (x1_bf16 && terms != 1)) return hipErrorInvalidValue;
+  DenseArgs g{};
+  g.x1 = x1; g.x2 = x2; g.h_in = h_in; g.done = done; g.ids = ids; g.w = (const uint8_t*)w;
+  g.b1 = b_ih; g.b2 = b_hh; g.out = h_out;
+  g.M = B; g.I1 = I1; g.I2 = I2; g.H = H; g.S = lstm ? 2 * H : H; g.n_env = n_env;
+  g.k1 = I1 / 32; g.k2 = (I1 + I2) / 32; g.kn = g.k2 + H / 32;
+  if (tile) {
+    if (terms != 3 || !dense_cell_tile_supported(I1, I2, H)) return hipErrorInvalidValue;
+    return lstm ? launch_tile<LSTM>(g, st) : launch_tile<GRU>(g, st);
+  }
+  if (terms == 3) return lstm ? launch_kind<LSTM, X_F32, 3, false>(g, st) : launch_kind<GRU, X_F32, 3, false>(g, st);
+  if (x1_bf16) return lstm ? launch_kind<LSTM, X_BF16, 1, false>(g, st) : launch_kind<GRU, X_BF16, 1, false>(g, st);
+  return lstm ? launch_kind<LSTM, X_F32, 1, false>(g, st) : launch_kind<GRU, X_F32, 1, false>(g, st);
+}
+
+}  // namespace sf

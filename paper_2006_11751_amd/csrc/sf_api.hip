@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 
 #include "sf_internal.h"
@@ -251,8 +252,6 @@ Switches read_switches() {
   sw.conv1_waves = env_int("SF_CONV1_WAVES");
   sw.gemm_tile = env_int("SF_GEMM_TILE");
   sw.fc_tile = env_int("SF_FC_TILE");
-  sw.gru_bm = env_int("SF_GRU_BM");
-  sw.no_rnn_pairs = env_set("SF_NO_RNN_PAIRS");
   sw.no_bf16_path = env_set("SF_NO_BF16_PATH");
   sw.no_rnn_bf16 = env_set("SF_NO_RNN_BF16");
   sw.conv_bf16_tc = env_int("SF_CONV_BF16_TC");
@@ -615,6 +614,9 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
       return SF_ERR_SHAPE;
     }
 
+  std::vector<uint16_t> split;  // FC and core matrices in bf16 terms, one after the other
+  split.reserve((size_t)(bld.bf16 ? 1 : 3) * std::max<size_t>((size_t)p->flat * cfg->fc_dim,
+                                                               (size_t)4 * cfg->rnn_dim * (cfg->fc_dim + 2 * cfg->rnn_dim)));
   // ---- FC: columns permuted from (c, y, x) to the channels-last order (y, x, c), transposed ----
   {
     // u: [fc][flat in channels-last order]
@@ -630,7 +632,15 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
     p->fc_w_t = nullptr;
     const bool fc_mfma = !sw.force_generic && !p->bf16_path &&
                          gemm_mfma_supported(p->flat, 1, 0, cfg->fc_dim);
-    if (fc_mfma) {
+    // fp32 rows: always; 16-bit rows: while the batch is small (see the launcher's rules)
+    p->fc_split_w = nullptr;
+    p->dense_fc = !sw.force_generic && dense_fc_supported(p->flat, cfg->fc_dim) &&
+                  (p->bf16_path ? !p->stream_f32 && sw.conv_bf16_tc == 0 && dense_fc_small(cfg->max_batch, cfg->fc_dim)
+                                : sw.fc_tile == 0 && !bld.bf16);
+    if (p->dense_fc) {
+      dense_pack_fc(u.data(), cfg->fc_dim, p->flat, p->bf16_path ? 1 : 3, p->act_f16, split);
+      p->fc_split_w = bld.upload(split);
+    } else if (fc_mfma) {
       p->fc_wt = bld.upload(u);
       p->fc_tile = sw.fc_tile > 0 ? sw.fc_tile
                                   : gemm_mfma_pick_tile(cfg->max_batch, cfg->fc_dim, p->flat, p->flat);
@@ -642,7 +652,7 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
       p->fc_w_t = bld.upload(t);
     }
     p->fc_wbf = nullptr;
-    if (p->bf16_path) {
+    if (p->bf16_path && !p->dense_fc) {
       // the FC is a 1x1 "convolution" over a 1x1 image with flat channels: u is [fc][flat][1][1]
       std::vector<uint16_t> wt;
       std::vector<float> bb;
@@ -685,40 +695,49 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   const int HG = (lstm ? 4 : 3) * cfg->rnn_dim;
   p->state_dim = (lstm ? 2 : 1) * cfg->rnn_dim;
   p->gru_wih_t = p->gru_whh_t = nullptr;
-  p->gru_wih = p->gru_whh = nullptr;
-  p->rnn_seq_w = nullptr;
   p->rnn_wih_bf = p->rnn_whh_bf = nullptr;
-  if (cfg->dtype == SF_DTYPE_BF16 && !sw.force_generic && !sw.no_rnn_bf16 &&
-      rnn_bf16_supported(cfg->fc_dim, p->meas_out_dim, cfg->rnn_dim)) {
+  p->rnn_split_w = nullptr;
+  // The core with operands split into bf16 terms: in fp32 configurations and for small batches; in
+  // every configuration also for the few rows per time step of sf_policy_unroll.
+  const bool dense = !sw.force_generic && dense_cell_supported(cfg->fc_dim, p->meas_out_dim, cfg->rnn_dim);
+  const bool small = dense_cell_small(cfg->max_batch, cfg->rnn_dim);
+  const bool rnn_bf16 = bld.bf16 && !sw.force_generic && !sw.no_rnn_bf16 &&
+                        rnn_bf16_supported(cfg->fc_dim, p->meas_out_dim, cfg->rnn_dim);
+  p->dense_core = dense && !(rnn_bf16 && !small);
+  p->core_tile = dense && !bld.bf16 && !small &&
+                 dense_cell_tile_supported(cfg->fc_dim, p->meas_out_dim, cfg->rnn_dim);
+  if (rnn_bf16) {
+    // The FC kernel can hand its output over as bf16 (the rounding the bf16 core would apply
+    // while staging it): half the bytes for every unit tile that re-reads the rows.  Not with a
+    // second input (fp32) and not where the 16-bit activations are fp16.
+    p->fc_out_bf16 = p->bf16_path && !p->act_f16 && p->meas_out_dim == 0 && !sw.fc_out_f32;
+  }
+  if (rnn_bf16 && !p->dense_core) {
     // bf16 configuration: gate GEMMs on the 16-bit MFMA, state split into two bf16 terms
     std::vector<uint16_t> t;
     rnn_bf16_pack(w->rnn_w_ih, (size_t)HG * core_in, t);
     p->rnn_wih_bf = bld.upload(t);
     rnn_bf16_pack(w->rnn_w_hh, (size_t)HG * cfg->rnn_dim, t);
     p->rnn_whh_bf = bld.upload(t);
-    // The FC kernel can hand its output over as bf16 (the rounding this kernel would apply
-    // while staging it): half the bytes for every unit tile that re-reads the rows.  Not with a
-    // second input (fp32) and not where the 16-bit activations are fp16.
-    p->fc_out_bf16 = p->fc_wbf && !p->act_f16 && p->meas_out_dim == 0 && !sw.fc_out_f32;
-  } else if (sw.force_generic || !rnn_mfma_supported(cfg->fc_dim, p->meas_out_dim, cfg->rnn_dim)) {
+  }
+  if (!dense && !rnn_bf16) {
     p->gru_wih_t = bld.pack_transposed(w->rnn_w_ih, HG, core_in);
     p->gru_whh_t = bld.pack_transposed(w->rnn_w_hh, HG, cfg->rnn_dim);
-  } else {
-    p->gru_wih = bld.pack_vec(w->rnn_w_ih, (size_t)HG * core_in);
-    p->gru_whh = bld.pack_vec(w->rnn_w_hh, (size_t)HG * cfg->rnn_dim);
-    p->gru_bm = sw.gru_bm > 0 ? sw.gru_bm : rnn_mfma_pick_bm(cfg->max_batch, cfg->rnn_dim);
-    p->rnn_plain_loops = sw.no_rnn_pairs ? 0 : 1;
   }
-  if ((p->gru_wih || p->rnn_wih_bf) && !sw.no_rnn_seq &&
-      rnn_seq_supported(cfg->fc_dim, p->meas_out_dim, cfg->rnn_dim)) {
-    // the same matrices once more (fp32 values; in a bf16 configuration the rounded ones), in the
-    // operand order of the kernel that runs the core on the few rows per time step of
-    // sf_policy_unroll
-    std::vector<float> qi((size_t)HG * core_in), qh((size_t)HG * cfg->rnn_dim), t;
-    for (size_t i = 0; i < qi.size(); ++i) qi[i] = bld.q(w->rnn_w_ih[i]);
-    for (size_t i = 0; i < qh.size(); ++i) qh[i] = bld.q(w->rnn_w_hh[i]);
-    rnn_seq_pack(qi.data(), qh.data(), core_in, cfg->rnn_dim, lstm ? 1 : 0, t);
-    p->rnn_seq_w = bld.upload(t);
+  if (p->dense_core || (dense && !sw.no_rnn_seq)) {
+    // the values as the configuration defines them (rounded in a bf16 one: one term)
+    std::vector<float> qi, qh;
+    const float *wi = w->rnn_w_ih, *wh = w->rnn_w_hh;
+    if (bld.bf16) {
+      qi.resize((size_t)HG * core_in);
+      qh.resize((size_t)HG * cfg->rnn_dim);
+      for (size_t i = 0; i < qi.size(); ++i) qi[i] = bld.q(wi[i]);
+      for (size_t i = 0; i < qh.size(); ++i) qh[i] = bld.q(wh[i]);
+      wi = qi.data();
+      wh = qh.data();
+    }
+    dense_pack_cell(wi, wh, core_in, cfg->rnn_dim, lstm ? 1 : 0, bld.bf16 ? 1 : 3, split);
+    p->rnn_split_w = bld.upload(split);
   }
   p->gru_bih = bld.pack_vec(w->rnn_b_ih, HG);
   p->gru_bhh = bld.pack_vec(w->rnn_b_hh, HG);
@@ -995,8 +1014,9 @@ extern "C" int sf_policy_update_weights(sf_policy* handle, const sf_policy_weigh
                    scratch.stream_f32 == p->stream_f32 && scratch.fc_tile == p->fc_tile &&
                    scratch.fc_out_bf16 == p->fc_out_bf16 && (scratch.fc_wt != nullptr) == (p->fc_wt != nullptr) &&
                    (scratch.fc_wbf != nullptr) == (p->fc_wbf != nullptr) &&
-                   (scratch.gru_wih != nullptr) == (p->gru_wih != nullptr) &&
-                   scratch.rnn_seq_w == p->rnn_seq_w &&
+                   scratch.core_tile == p->core_tile &&
+                   scratch.rnn_split_w == p->rnn_split_w && scratch.fc_split_w == p->fc_split_w &&
+                   scratch.dense_fc == p->dense_fc && scratch.dense_core == p->dense_core &&
                    (scratch.rnn_wih_bf != nullptr) == (p->rnn_wih_bf != nullptr);
   for (size_t i = 0; same_plan && i < p->convs.size(); ++i) {
     const ConvLayer &a = scratch.convs[i], &b = p->convs[i];
@@ -1244,7 +1264,10 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
           SF_LAUNCH(launch_maxpool3x3s2p1(B, op.C, op.H, op.W, buf(op.in_buf), buf(op.out_buf), st));
         break;
       case OP_FC:
-        if (p->fc_wbf)
+        if (p->dense_fc)
+          SF_LAUNCH(launch_dense_fc(buf(op.in_buf), !p->bf16_path ? 0 : p->act_f16 ? 2 : 1, p->fc_split_w, p->fc_b,
+                                    p->fc_out, p->fc_out_bf16, B, p->flat, c.fc_dim, st));
+        else if (p->fc_wbf)
           SF_LAUNCH(launch_conv_bf16(buf(op.in_buf), p->fc_wbf, p->fc_bbf, nullptr, p->fc_out, B, 1, 1,
                                      p->flat, 1, 1, 0, 1, 1, c.fc_dim, p->fc_Kpad, 0, 1,
                                      p->stream_f32, 0, p->fc_out_bf16 ? 0 : 1, p->act_f16,
@@ -1275,18 +1298,17 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
         const float* x1 = (const float*)((const char*)p->fc_out +
                                          feat_row * c.fc_dim * (p->fc_out_bf16 ? 2 : 4));
         const int lstm = c.rnn_type == SF_RNN_LSTM;
-        if (parts == PART_CORE && p->rnn_seq_w && !ids)
-          // (one time step of the pass over trajectories: few rows)
-          SF_LAUNCH(launch_rnn_seq(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1, p->fc_out_bf16, x2, h_in, done,
-                                   p->rnn_seq_w, p->gru_bih, p->gru_bhh, h_out, st));
+        // (PART_CORE alone: one time step of the pass over trajectories, few rows; the step's own
+        // kernel there too if the switch asks for it)
+        const bool few = parts == PART_CORE && !p->sw.no_rnn_seq;
+        if (p->dense_core || (few && p->rnn_split_w))
+          SF_LAUNCH(launch_dense_cell(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1, p->fc_out_bf16, x2, h_in, done,
+                                      p->rnn_split_w, c.dtype == SF_DTYPE_BF16 ? 1 : 3, p->gru_bih, p->gru_bhh, h_out,
+                                      ids, n_env, p->core_tile && !few, st));
         else if (p->rnn_wih_bf)
           SF_LAUNCH(launch_rnn_bf16(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1,
                                     p->fc_out_bf16, x2, h_in, done, p->rnn_wih_bf, p->rnn_whh_bf, p->gru_bih, p->gru_bhh, h_out,
                                     ids, n_env, st));
-        else if (p->gru_wih)
-          SF_LAUNCH(launch_rnn_mfma(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1, x2, h_in,
-                                    done, p->gru_wih, p->gru_whh, p->gru_bih, p->gru_bhh, h_out,
-                                    p->gru_bm, p->rnn_plain_loops, ids, n_env, st));
         else
           SF_LAUNCH(launch_rnn_generic(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1, x2,
                                        h_in, done, p->gru_wih_t, p->gru_whh_t, p->gru_bih, p->gru_bhh,
@@ -1444,8 +1466,8 @@ extern "C" const char* sf_policy_op_pipe(const sf_policy* handle, int i) {
         default: return "valu";
       }
     }
-    case OP_FC: return p->fc_wbf ? mfma16 : (p->fc_wt ? "f32" : "valu");
-    case OP_GRU: return p->rnn_wih_bf ? "bf16" : (p->gru_wih ? "f32" : "valu");
+    case OP_FC: return p->fc_split_w && !p->bf16_path ? "bf16x3" : p->bf16_path ? mfma16 : (p->fc_wt ? "f32" : "valu");
+    case OP_GRU: return p->gru_wih_t ? "valu" : p->cfg.dtype == SF_DTYPE_FP32 ? "bf16x3" : "bf16";
     default: return "valu";
   }
 }

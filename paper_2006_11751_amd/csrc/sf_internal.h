@@ -59,8 +59,7 @@ struct Switches {
   int conv1 = 0;                 // SF_CONV1: 0 = by the admission test of the fixed-point bank,
                                  // 1 = "fp32" (fp32 MFMA forced), 2 = "i8" (digit planes forced)
   int conv1_waves = 0;           // SF_CONV1_WAVES
-  int gemm_tile = 0, fc_tile = 0, gru_bm = 0;  // SF_GEMM_TILE, SF_FC_TILE, SF_GRU_BM (0 = default)
-  bool no_rnn_pairs = false;     // SF_NO_RNN_PAIRS
+  int gemm_tile = 0, fc_tile = 0;  // SF_GEMM_TILE, SF_FC_TILE (0 = default)
   bool no_bf16_path = false;     // SF_NO_BF16_PATH
   bool no_rnn_bf16 = false;      // SF_NO_RNN_BF16
   int conv_bf16_tc = 0;          // SF_CONV_BF16_TC
@@ -116,15 +115,14 @@ struct Policy {
   // recurrent core (GRU: G = 3 gate blocks, LSTM: G = 4); core input = fc_dim + meas_out_dim
   float* gru_wih_t;   // dev [core input][G*H]
   float* gru_whh_t;   // dev [H][G*H]
-  float* gru_wih;     // dev [G*H][core input] (canonical) for the MFMA kernel, or null
-  float* gru_whh;     // dev [G*H][H]
-  float* rnn_seq_w = nullptr;  // dev: both matrices in the operand order of k_rnn_seq.hip, or null
-  int gru_bm;         // rows per workgroup of the MFMA kernel, fixed at create
+  uint16_t* rnn_split_w = nullptr;  // dev: both matrices packed for k_dense_split.hip, or null
+  uint16_t* fc_split_w = nullptr;   // dev: FC matrix packed for k_dense_split.hip, or null
+  bool dense_fc = false, dense_core = false;  // the step's FC layer / core run on k_dense_split.hip
+  bool core_tile = false;           // ... the core on its kernel for many rows
   double conv1_ratio2 = 0, conv1_ratio3 = 0;  // admission test of the first convolution's digit planes
   int conv1_image = 1;      // first convolution: frame-resident variant where it applies
   int fc_out_bf16 = 0;      // the FC kernel hands bf16 values to the 16-bit recurrent kernel
   int conv_bf16_tc = 0;     // 16-bit conv kernel: 0 = channel blocks per workgroup by grid size, 1 / 2 forced
-  int rnn_plain_loops = 1;  // GRU on the MFMA: the two-plain-loops form where the chunk counts allow it
   uint16_t* rnn_wih_bf;  // dev bf16 [G*H][core input] for the 16-bit MFMA kernel, or null
   uint16_t* rnn_whh_bf;  // dev bf16 [G*H][H]
   float* gru_bih;     // dev [G*H]
@@ -256,18 +254,20 @@ void conv3x3_stem_pack(const float* w, const float* bias, int cout, bool f16,
 hipError_t launch_conv3x3_stem(const uint8_t* obs, const uint16_t* wpk, const float* bias32, void* out,
                                int B, int H, int W, int cout, float obs_sub, float obs_mul, int f16,
                                hipStream_t st);
-bool rnn_mfma_supported(int I1, int I2, int H);
-hipError_t launch_rnn_mfma(int lstm, int B, int I1, int I2, int H, const float* x1, const float* x2,
-                           const float* h_in, const uint8_t* done, const float* w_ih,
-                           const float* w_hh, const float* b_ih, const float* b_hh, float* h_out,
-                           int bm, int plain_loops, const int32_t* ids, int n_env, hipStream_t st);
-int rnn_mfma_pick_bm(int max_batch, int H);
-// the cell for the few rows per time step of the pass over trajectories (k_rnn_seq.hip)
-bool rnn_seq_supported(int I1, int I2, int H);
-void rnn_seq_pack(const float* w_ih, const float* w_hh, int I, int H, int lstm, std::vector<float>& out);
-hipError_t launch_rnn_seq(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16, const float* x2,
-                          const float* h_in, const uint8_t* done, const float* wpk, const float* b_ih,
-                          const float* b_hh, float* h_out, hipStream_t st);
+// FC layer and recurrent cell on the 16-bit MFMA with operands split into bf16 terms (k_dense_split.hip)
+bool dense_fc_supported(int K, int N);
+bool dense_cell_supported(int I1, int I2, int H);
+bool dense_fc_small(int M, int N);
+bool dense_cell_small(int M, int H);
+bool dense_cell_tile_supported(int I1, int I2, int H);
+void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, std::vector<uint16_t>& out);
+void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms,
+                     std::vector<uint16_t>& out);
+hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const float* bias, void* out, int out_bf16,
+                           int M, int K, int N, hipStream_t st);
+hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16, const float* x2,
+                             const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
+                             const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);
 bool rnn_bf16_supported(int I1, int I2, int H);
 void rnn_bf16_pack(const float* w, size_t n, std::vector<uint16_t>& out);
 hipError_t launch_rnn_bf16(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16,
