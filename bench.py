@@ -27,8 +27,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # the fp32 vector rate), 16-bit MFMA, int8 MFMA.  An int8 digit-plane launch executes 2 or 3
 # integer multiply-adds per algorithmic one; its figure below is algorithmic work over the
 # int8 peak, i.e. a lower bound of how busy the int8 pipe is.
-# ("bf16x3": fp32 operands as three bf16 terms, six products per multiply-add)
-PEAK_TOPS = {"f32": 157.3, "bf16x3": 2500.0 / 6, "valu": 157.3, "bf16": 2500.0, "f16": 2500.0, "i8x2": 5000.0, "i8x3": 5000.0}
+# ("bf16x3", "f16x2": fp32 operands as three bf16 or two fp16 terms, six or three products per
+# multiply-add)
+PEAK_TOPS = {"f32": 157.3, "bf16x3": 2500.0 / 6, "f16x2": 2500.0 / 3, "valu": 157.3, "bf16": 2500.0, "f16": 2500.0, "i8x2": 5000.0, "i8x3": 5000.0}
 HBM_PEAK_GBPS = 8000.0
 
 

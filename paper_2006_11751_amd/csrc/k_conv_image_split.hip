@@ -1,0 +1,393 @@
+// Strided convolution of the plain encoder in fp32 configurations on the 16-bit matrix instructions
+// (paper, App. "Model architectures": conv layers behind the first one), the frame's input image
+// resident in LDS.
+//
+//   out[b][oy][ox][n] = act(bias[n] + sum_{p,q,c} in[b][oy*s + p][ox*s + q][c] * W[n][c][p][q])
+//
+// Arithmetic.  Scaled by powers of two, an activation is the sum of two fp16 numbers (11 + 11
+// significant bits) and so is a weight; of the four products the three largest are kept: x0w1,
+// x1w0, x0w0.  What is left out is below 2^-22 of a product and of random sign, less than the
+// rounding of an fp32 accumulator over the 512 or 576 terms of these layers, and an accumulator
+// here is rounded 3 times per 32 terms instead of 16 times: the result is nearer to the exact one.
+// fp16 holds 2^-24 .. 65504, so every input channel has a scale of its own that takes the largest
+// value it can have (a bound that follows from the weights of the layers before it, frames being
+// bytes) into [2^14, 2^15], folded into the weights, and every output channel one that does the
+// same for its largest folded weight.  Values are then exact to 22 bits from 2^-18 of the bound
+// upward; below, the absolute error stays at 2^-40 of the bound.  Where that is not small against
+// the rounding errors of the layer (a bound far above the values), the layer keeps the fp32 matrix
+// instructions: conv_split_pack's admission test.
+//
+// The tiled fp32 kernel (k_gemm_mfma.hip) was bound by the fp32 matrix instructions (1/16 of the
+// rate) and staged every pixel once per window that covers it.  Here a workgroup of four waves
+// walks rounds of FR frames: the image goes through registers, where it is scaled and split, into
+// LDS, and after one barrier each wave computes 16 output channels of all pixels, its filter bank
+// (both terms: 128 or 144 registers) resident.  Two workgroups share a CU, one loading while the
+// other computes.  Launch times at B = 1024: see launch_conv_image_split.
+//
+// v_mfma_f32_16x16x32_f16: lane l supplies A[i = l%16][k = 8*(l/16) + e] and B[k][j = l%16], e =
+// 0..7 (16 bytes each); D[i][j] sits in lane j + 16*(i/4), register i%4.  A = weights (i = output
+// channel), B = pixels: a lane ends up with four neighbouring channels of one pixel.  One
+// instruction covers 32 input channels of one filter tap.
+//
+// LDS: a pixel is its CIN first terms, its CIN second terms and 16 bytes of padding (an odd number
+// of 16-byte pieces); rows and frames are padded so that output pixel n of a round reads piece
+// 2 * P4 * n + const modulo 16 also across the end of a row: neighbouring pixels two pieces apart,
+// the four lane groups one, no bank conflicts.
+#include <math.h>
+#include <string.h>
+
+#include <mutex>
+#include <type_traits>
+
+#include "sf_internal.h"
+
+namespace sf {
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kNT = 256;
+constexpr size_t kMaxLds = 80 * 1024;  // two workgroups per CU
+
+struct SplitArgs {
+  const f32x4* in;      // [B][H][W][CIN]
+  const u32x4* wpk;     // [N/16][G][2][64] lane operands, G = KS*KS*CIN/32
+  const float* scale;   // [CIN] input scales, [N] inverse output scales
+  const float* bias;    // [N]
+  float* out;           // [B][Ho*Wo][N]
+  int B, H, W, Ho, Wo, N;
+  int row_pad, frame_pad;  // 16-byte pieces appended to an image row / a frame in LDS
+  int rcp_w, rcp_wo, rcp_npix;  // x / d = x * rcp >> 16, see reciprocal()
+};
+// ceil(65536 / d): exact for x * d < 65536
+int reciprocal(int d) { return (65536 + d - 1) / d; }
+
+// FR frames per round; their FR*Ho*Wo <= 16*MT output pixels form one row-major sequence of MT
+// 16-pixel tiles, computed MP at a time.  NV: 16-byte pieces of a round's input per thread.
+template <int CIN, int KS, int FR, int MT, int MP, int NV>
+__global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
+  constexpr int STRIDE = 2;
+  constexpr int C4 = CIN / 4;       // 16-byte pieces of a pixel in memory
+  constexpr int C8 = CIN / 8;       // ... of one of its terms in LDS
+  constexpr int P4 = 2 * C8 + 1;    // LDS pixel pitch in pieces
+  constexpr int HALVES = CIN / 32;
+  constexpr int G = KS * KS * HALVES;
+  extern __shared__ __attribute__((aligned(16))) u32x4 img[];  // [FR][frame_stride] pieces
+
+  static_assert(FR <= 2 && kNT % C4 == 0, "a thread's pieces: two frames at most, the same channels throughout");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lp = lane & 15, lg = lane >> 4;
+  const int n0 = ((int)blockIdx.y * 4 + wave) * 16;  // the wave's output channels
+  const int npix = g.Ho * g.Wo;
+  const int frame_pieces = g.H * g.W * C4;
+  const int row_stride = g.W * P4 + g.row_pad;
+  const int frame_stride = g.H * row_stride + g.frame_pad;
+
+  u32x4 wf[G][2];
+#pragma unroll
+  for (int t = 0; t < G; ++t)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) wf[t][q] = g.wpk[((size_t)(n0 / 16) * G + t) * 128 + q * 64 + lane];
+  const f32x4 scale = *(const f32x4*)(g.scale + (tid % C4) * 4);  // (a thread's pieces: the same channels)
+  const f32x4 inv = *(const f32x4*)(g.scale + CIN + n0 + 4 * lg);
+  const f32x4 bias = *(const f32x4*)(g.bias + n0 + 4 * lg);
+
+  // this lane's pixel of a tile: LDS piece of its window's first pixel (past the end: the last
+  // pixel again, computed and stored again with the same bits)
+  auto origin = [&](int m) {
+    int n = 16 * m + lp;
+    n = n < FR * npix ? n : FR * npix - 1;
+    const int fr = FR == 1 ? 0 : n * g.rcp_npix >> 16, pix = n - fr * npix;
+    const int oy = pix * g.rcp_wo >> 16, ox = pix - oy * g.Wo;
+    return fr * frame_stride + (oy * STRIDE) * row_stride + (ox * STRIDE) * P4 + lg;
+  };
+  int abase[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) abase[m] = origin(m);
+
+  const int n_rounds = (g.B + FR - 1) / FR;
+  for (int it = blockIdx.x; it < n_rounds; it += gridDim.x) {
+    const int frames = min(g.B - it * FR, FR);
+    {
+      // a last round with fewer frames re-reads its last piece instead of reading past the batch
+      const uint8_t* src = (const uint8_t*)(g.in + (size_t)it * FR * frame_pieces);
+      const uint32_t last = 16u * (uint32_t)(frames * frame_pieces - 1);
+      // (opaque: computed ahead of the loop the places of all pieces would have to be spilled)
+      int first = tid;
+      asm volatile("" : "+v"(first));
+      f32x4 v[NV];
+#pragma unroll
+      for (int u = 0; u < NV; ++u) v[u] = *(const f32x4*)(src + min(16u * (uint32_t)(first + kNT * u), last));
+#pragma unroll
+      for (int u = 0; u < NV; ++u) {
+        const int f = first + kNT * u;
+        const bool second = FR == 2 && f >= frame_pieces;
+        const int pix = (f - (second ? frame_pieces : 0)) / C4;
+        int at = (second ? frame_stride : 0) + pix * P4 + (pix * g.rcp_w >> 16) * g.row_pad;
+        at = min(at, FR * frame_stride);  // (past the end: a pixel behind the images, for no use)
+        u32x2 t0, t1;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const f32x2 s = {v[u][2 * p] * scale[2 * p], v[u][2 * p + 1] * scale[2 * p + 1]};
+          const f16x2 h = __builtin_convertvector(s, f16x2);
+          const f32x2 rest = {fmaf((float)h[0], -1.0f, s[0]), fmaf((float)h[1], -1.0f, s[1])};
+          t0[p] = __builtin_bit_cast(unsigned, h);
+          t1[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(rest, f16x2));
+        }
+        u32x2* dst = (u32x2*)(img + at) + tid % C4;
+        dst[0] = t0;
+        dst[2 * C8] = t1;
+      }
+    }
+    __syncthreads();
+
+    float* dst = g.out + (size_t)it * FR * npix * g.N + n0 + 4 * lg;
+    const int live = frames * npix;
+    auto tap = [&](int t) {
+      const int tp = t / HALVES, half = t % HALVES;
+      return (tp / KS) * row_stride + (tp % KS) * P4 + 4 * half;
+    };
+    auto tiles = [&](auto m0c, auto mnc) __attribute__((always_inline)) {
+      constexpr int M0 = decltype(m0c)::value, MN = decltype(mnc)::value;
+      // (the small products in an accumulator of their own: added to the large ones they would have
+      // them rounded three times as often)
+      f32x4 acc[MN], low[MN];
+      u32x4 x0[MN], x1[MN];
+#pragma unroll
+      for (int m = 0; m < MN; ++m) {
+        acc[m] = low[m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        x0[m] = img[abase[M0 + m] + tap(0)];
+        x1[m] = img[abase[M0 + m] + tap(0) + C8];
+      }
+#pragma unroll
+      for (int t = 0; t < G; ++t) {
+        const int next = tap(t + 1 < G ? t + 1 : t);
+#pragma unroll
+        for (int m = 0; m < MN; ++m) {
+          auto mfma = [&](const u32x4& w, const u32x4& x, f32x4& c) __attribute__((always_inline)) {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
+          };
+          mfma(wf[t][1], x0[m], low[m]);
+          mfma(wf[t][0], x0[m], acc[m]);
+          mfma(wf[t][0], x1[m], low[m]);
+          // the operands of the next tap, MN tiles ahead of their use
+          if (t + 1 < G) {
+            x0[m] = img[abase[M0 + m] + next];
+            x1[m] = img[abase[M0 + m] + next + C8];
+          }
+          __builtin_amdgcn_sched_barrier(0);  // (left alone, the scheduler sinks each read to its use)
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < MN; ++m) {
+        const int n = min(16 * (M0 + m) + lp, FR * npix - 1);
+        f32x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = fmaxf(fmaf(acc[m][e] + low[m][e], inv[e], bias[e]), 0.0f);
+        if (FR == 1 || n < live) *(f32x4*)(dst + (size_t)n * g.N) = r;
+      }
+    };
+    tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, MP>{});
+    if constexpr (MT > MP) tiles(std::integral_constant<int, MP>{}, std::integral_constant<int, MT - MP>{});
+    __syncthreads();  // every wave is done with this round's images
+  }
+}
+
+struct Layout {
+  int row_pad, frame_pad;
+  size_t lds_bytes;
+};
+Layout layout(int Cin, int FR, int H, int W, int Ho, int Wo) {
+  const int P4 = Cin / 4 + 1;
+  Layout L;
+  L.row_pad = (((P4 * Wo - W * P4) % 8) + 8) % 8;
+  const int row = W * P4 + L.row_pad;
+  L.frame_pad = FR > 1 ? (((2 * P4 * Ho * Wo - H * row) % 16) + 16) % 16 : 0;
+  L.lds_bytes = 16 * ((size_t)FR * (H * row + L.frame_pad) + P4);  // and a pixel that nobody reads
+  return L;
+}
+
+// Which instantiation takes a layer: 0 none; 1: 4x4 on 32 channels, one frame per round in seven
+// tiles; 2: 3x3 on 64 channels, two frames per round in three tiles (four frames in five tiles waste
+// less of a tile, but leave room for one workgroup per CU).
+int variant(int Cin, int ksize, int stride, int pad, int H, int W, int N) {
+  if (stride != 2 || pad != 0 || (N % 64) != 0 || H < ksize || W < ksize) return 0;
+  const int Ho = (H - ksize) / 2 + 1, Wo = (W - ksize) / 2 + 1;
+  if (17 * kNT / 8 * W >= 65536 || 128 * Ho * Wo >= 65536) return 0;  // (reciprocal())
+  if (Cin == 32 && ksize == 4) {
+    const int mt = (Ho * Wo + 15) / 16;
+    if (mt == 7 && H * W * 8 <= 17 * kNT && layout(32, 1, H, W, Ho, Wo).lds_bytes <= kMaxLds) return 1;
+  }
+  if (Cin == 64 && ksize == 3)
+    if (2 * Ho * Wo > 32 && 2 * Ho * Wo <= 48 && 2 * H * W * 16 <= 13 * kNT &&
+        layout(64, 2, H, W, Ho, Wo).lds_bytes <= kMaxLds)
+      return 2;
+  return 0;
+}
+
+template <int CIN, int KS, int FR, int MT, int MP, int NV>
+hipError_t launch_t(SplitArgs g, hipStream_t st) {
+  const Layout L = layout(CIN, FR, g.H, g.W, g.Ho, g.Wo);
+  g.row_pad = L.row_pad;
+  g.frame_pad = L.frame_pad;
+  g.rcp_w = reciprocal(g.W);
+  g.rcp_wo = reciprocal(g.Wo);
+  g.rcp_npix = reciprocal(g.Ho * g.Wo);
+  auto kern = conv_image_split_kernel<CIN, KS, FR, MT, MP, NV>;
+  static std::once_flag once;
+  static hipError_t attr_status = hipSuccess;
+  std::call_once(once, [&] {
+    attr_status = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+  });
+  if (attr_status != hipSuccess) return attr_status;
+  const int n_rounds = (g.B + FR - 1) / FR, ny = g.N / 64;
+  const int slots = ny >= 512 ? 1 : 512 / ny;  // two workgroups per CU, each walking its share of the rounds
+  kern<<<dim3((unsigned)(n_rounds < slots ? n_rounds : slots), (unsigned)ny), kNT, L.lds_bytes, st>>>(g);
+  return hipGetLastError();
+}
+
+// the power of two that takes v into [2^14, 2^15)
+int power(double v) {
+  if (!(v > 0.0 && v < 1e300)) return 0;
+  int e;
+  frexp(v, &e);  // v in [2^(e-1), 2^e)
+  return e < -85 ? 100 : e > 115 ? -100 : 15 - e;
+}
+
+// One output channel's weights in two terms (the second build with the host's conversion
+// instructions: packing runs at every weight update).
+inline __attribute__((always_inline)) void pack_channel(const float* wn, int n, int kk, int halves, const double* fold,
+                                                        double up, uint16_t* wpk) {
+  const int G = kk * halves;
+  for (int gi = 0; gi < G; ++gi) {
+    const int t = gi / halves, half = gi % halves;
+    for (int lg = 0; lg < 4; ++lg)
+      for (int i = 0; i < 8; ++i) {
+        const int c = 32 * half + 8 * lg + i;
+        const float v = (float)((double)wn[c * kk + t] * fold[c] * up);
+        const _Float16 h = (_Float16)v, rest = (_Float16)(v - (float)h);
+        const size_t at = ((((size_t)(n / 16) * G + gi) * 2) * 64 + lg * 16 + n % 16) * 8 + i;
+        memcpy(&wpk[at], &h, 2);
+        memcpy(&wpk[at + 64 * 8], &rest, 2);
+      }
+  }
+}
+void pack_channel_plain(const float* wn, int n, int kk, int halves, const double* fold, double up, uint16_t* wpk) {
+  pack_channel(wn, n, kk, halves, fold, up, wpk);
+}
+#if defined(__HIP_DEVICE_COMPILE__) || !defined(__x86_64__)
+bool host_f16c() { return false; }
+void pack_channel_f16c(const float* wn, int n, int kk, int halves, const double* fold, double up, uint16_t* wpk) {
+  pack_channel(wn, n, kk, halves, fold, up, wpk);
+}
+#else
+bool host_f16c() { return __builtin_cpu_supports("avx2") && __builtin_cpu_supports("f16c"); }
+__attribute__((target("avx2,f16c"))) void pack_channel_f16c(const float* wn, int n, int kk, int halves,
+                                                            const double* fold, double up, uint16_t* wpk) {
+  pack_channel(wn, n, kk, halves, fold, up, wpk);
+}
+#endif
+
+}  // namespace
+
+bool conv_image_split_supported(int Cin, int ksize, int stride, int pad, int H, int W, int N) {
+  return variant(Cin, ksize, stride, pad, H, W, N) != 0;
+}
+
+// Bound and mean square of every output channel of a ReLU'd convolution, from those of its input
+// channels (w [cout][cin][k][k]; the mean square takes the terms of a sum as independent).
+void conv_activation_range(const float* w, const float* bias, int cout, int cin, int k, std::vector<double>& bound,
+                           std::vector<double>& mean_sq) {
+  std::vector<double> b(cout), m(cout);
+  for (int o = 0; o < cout; ++o) {
+    double sb = fabs((double)bias[o]), sm = (double)bias[o] * bias[o];
+    for (int c = 0; c < cin; ++c) {
+      double l1 = 0.0, l2 = 0.0;
+      for (int t = 0; t < k * k; ++t) {
+        const double v = w[((size_t)o * cin + c) * k * k + t];
+        l1 += fabs(v);
+        l2 += v * v;
+      }
+      sb += l1 * bound[c];
+      sm += l2 * mean_sq[c];
+    }
+    b[o] = sb;
+    m[o] = sm;
+  }
+  bound.swap(b);
+  mean_sq.swap(m);
+}
+
+// Weights in operand order, [N/16][G][2][64][8] fp16 bits: lane l of tap group gi holds, for e =
+// 0..7, both terms of W[16 nt + l%16][c = 32 half + 8 (l/16) + e][p][q], gi = (p k + q)(cin/32) +
+// half, times 2^(e_in[c]) and the output channel's scale; scale: [cin] input scales, [cout] inverse
+// output scales.  bound, mean_sq: of the input channels.
+// Returns the admission ratio: the largest over the output channels of
+//     (what the fixed part of the splitting errors, 2^-40 of an input bound and 2^-39 of the largest
+//      folded weight, can add up to)
+//   / (the rounding errors of an fp32 sum of the typical terms: sqrt(K) 2^-24 times their root mean
+//      square, K terms);
+// the split runs where it is <= 1.  (Infinite or NaN bounds give a ratio that is not <= 1.)
+double conv_image_split_pack(const float* w, int cout, int cin, int k, const std::vector<double>& bound,
+                             const std::vector<double>& mean_sq, std::vector<uint16_t>& wpk, std::vector<float>& scale) {
+  const int halves = cin / 32, kk = k * k, G = kk * halves, K = cin * kk;
+  wpk.assign((size_t)cout * K * 2, 0);
+  scale.assign(cin + cout, 1.0f);
+  std::vector<double> fold(cin);  // 1 / input scale
+  for (int c = 0; c < cin; ++c) {
+    const int e = power(bound[c]);
+    scale[c] = (float)ldexp(1.0, e);
+    fold[c] = ldexp(1.0, -e);
+  }
+  double worst = 0.0;
+  for (int n = 0; n < cout; ++n) {
+    const float* wn = w + (size_t)n * K;
+    double top = 0.0, typ = 0.0, spread = 0.0;
+    for (int c = 0; c < cin; ++c) {
+      if (!(bound[c] < 1e30)) worst = INFINITY;
+      for (int t = 0; t < kk; ++t) {
+        const double v = fabs((double)wn[c * kk + t]);
+        top = fmax(top, v * fold[c]);
+        typ += v * v * mean_sq[c];
+        spread += v * bound[c];
+      }
+    }
+    const int e = power(top);
+    const double up = ldexp(1.0, e);
+    scale[cin + n] = (float)ldexp(1.0, -e);
+    // folded weights have an absolute error of 2^-25 at a largest value of 2^14 or more; an input
+    // of scaled size 2^15 multiplies it
+    const double fixed = ldexp(spread, -40) + K * ldexp(1.0, 15 - 25 - e);
+    const double ref = sqrt((double)K) * ldexp(1.0, -24) * sqrt(typ);
+    // (a channel without weights has nothing to get wrong)
+    if (top > 0.0) worst = fmax(worst, ref > 0.0 ? fixed / ref : INFINITY);
+    (host_f16c() ? pack_channel_f16c : pack_channel_plain)(wn, n, kk, halves, fold.data(), up, wpk.data());
+  }
+  return worst;
+}
+
+// in [B][H][W][Cin] fp32 -> out [B][Ho*Wo][N] fp32, ReLU'd.
+// Launch times (us) against k_gemm_mfma.hip, conv2 / conv3 of the standard network: 16 rows 6.8 / 4.7
+// (7.2 / 7.6), 333 rows 13.7 / 9.2 (26 / 16), 1024 rows 27 / 15 (72 / 34), 2048 rows 50 / 26
+// (126 / 57).  At 1024 rows conv2 reads 70 MB and writes 26: 3.5 TB/s.
+hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const float* scale, const float* bias,
+                                   float* out, int B, int H, int W, int Cin, int ksize, int N, hipStream_t st) {
+  if (B == 0) return hipSuccess;
+  SplitArgs g;
+  g.in = (const f32x4*)in; g.wpk = (const u32x4*)wpk; g.scale = scale; g.bias = bias; g.out = out;
+  g.B = B; g.H = H; g.W = W; g.Ho = (H - ksize) / 2 + 1; g.Wo = (W - ksize) / 2 + 1; g.N = N;
+  g.row_pad = g.frame_pad = 0;
+  switch (variant(Cin, ksize, 2, 0, H, W, N)) {
+    case 1: return launch_t<32, 4, 1, 7, 4, 17>(g, st);
+    case 2: return launch_t<64, 3, 2, 3, 3, 13>(g, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace sf

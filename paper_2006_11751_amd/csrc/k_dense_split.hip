@@ -845,10 +845,25 @@ hipError_t launch_kind(const DenseArgs& g, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
+// Packing runs at every weight update, 24 results per eight weights: two builds of the loops, the
+// second with 256-bit vectors where the host has them.
+#define SF_INLINE inline __attribute__((always_inline))
+#if defined(__HIP_DEVICE_COMPILE__) || !defined(__x86_64__)
+#define SF_AVX2
+#else
+#define SF_AVX2 __attribute__((target("avx2")))
+#endif
+bool host_avx2() {
+#if defined(__HIP_DEVICE_COMPILE__) || !defined(__x86_64__)
+  return false;
+#else
+  return __builtin_cpu_supports("avx2");
+#endif
+}
+
 // Eight neighbouring weights -> one operand of a lane per term, `stride` elements apart.  bf16 to
-// nearest, ties to even; what would become infinite is cut off.  (Plain loops over eight: the
-// compiler's vectors.)
-inline void put8(const float* src, int terms, bool f16, uint16_t* dst, size_t stride) {
+// nearest, ties to even; what would become infinite is cut off.
+SF_INLINE void put8(const float* src, int terms, bool f16, uint16_t* dst, size_t stride) {
   if (f16) {
     for (int e = 0; e < 8; ++e) dst[e] = conv_weight_bits(src[e], true);
     return;
@@ -867,6 +882,42 @@ inline void put8(const float* src, int terms, bool f16, uint16_t* dst, size_t st
     memcpy(dst + q * stride, &h, sizeof(h));
     r -= __builtin_bit_cast(f32x8, t);
   }
+}
+
+SF_INLINE void pack_fc_loops(const float* w, int N, int K, int terms, bool f16, uint16_t* out) {
+  const int kn = K / 32;
+  for (int nb = 0; nb < N / 16; ++nb)
+    for (int s = 0; s < kn; ++s)
+      for (int lg = 0; lg < 4; ++lg)
+        for (int i = 0; i < 16; ++i)
+          put8(w + (size_t)(nb * 16 + i) * K + 32 * s + 8 * lg, terms, f16,
+               out + (((size_t)nb * kn + s) * terms * 64 + lg * 16 + i) * 8, 64 * 8);
+}
+SF_INLINE void pack_cell_loops(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms, uint16_t* out) {
+  const int kn = (I + H) / 32, G = lstm ? 4 : 3;
+  const size_t gb = group_bytes(lstm ? LSTM : GRU) / 2;
+  for (int gr = 0; gr < H / 8; ++gr)
+    for (int s = 0; s < kn; ++s) {
+      uint16_t* dst = out + ((size_t)gr * kn + s) * terms * gb;
+      const float* src = 32 * s < I ? w_ih + 32 * s : w_hh + (32 * s - I);
+      const size_t pitch = 32 * s < I ? I : H;
+      for (int q = 0; q < G; ++q)
+        for (int lg = 0; lg < 4; ++lg)
+          for (int i = 0; i < 8; ++i) {
+            const size_t slot = q < 2 || lstm ? (size_t)(q >> 1) * 64 + lg * 16 + (q & 1) * 8 + i : (size_t)64 + lg * 8 + i;
+            put8(src + ((size_t)q * H + gr * 8 + i) * pitch + 8 * lg, terms, false, dst + slot * 8, gb);
+          }
+    }
+}
+void pack_fc_plain(const float* w, int N, int K, int terms, bool f16, uint16_t* out) { pack_fc_loops(w, N, K, terms, f16, out); }
+SF_AVX2 void pack_fc_avx2(const float* w, int N, int K, int terms, bool f16, uint16_t* out) {
+  pack_fc_loops(w, N, K, terms, f16, out);
+}
+void pack_cell_plain(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms, uint16_t* out) {
+  pack_cell_loops(w_ih, w_hh, I, H, lstm, terms, out);
+}
+SF_AVX2 void pack_cell_avx2(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms, uint16_t* out) {
+  pack_cell_loops(w_ih, w_hh, I, H, lstm, terms, out);
 }
 
 }  // namespace
@@ -892,36 +943,18 @@ bool dense_cell_tile_supported(int I1, int I2, int H) {
 }
 
 // w [N][K] -> [N / 16][K / 32][terms][64][8]; terms: 3 (fp32 weights) or 1 (bf16, or fp16 if f16).
-void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, std::vector<uint16_t>& out) {
-  const int kn = K / 32;
-  out.resize((size_t)N * K * terms);
-  for (int nb = 0; nb < N / 16; ++nb)
-    for (int s = 0; s < kn; ++s)
-      for (int lg = 0; lg < 4; ++lg)
-        for (int i = 0; i < 16; ++i)
-          put8(w + (size_t)(nb * 16 + i) * K + 32 * s + 8 * lg, terms, f16,
-               out.data() + (((size_t)nb * kn + s) * terms * 64 + lg * 16 + i) * 8, 64 * 8);
+size_t dense_fc_pack_size(int N, int K, int terms) { return (size_t)N * K * terms; }
+void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, uint16_t* out) {
+  (host_avx2() ? pack_fc_avx2 : pack_fc_plain)(w, N, K, terms, f16, out);
 }
 
 // w_ih [G*H][I], w_hh [G*H][H] -> [H / 8][(I + H) / 32][terms][operands of a group]: tile columns
 // [i f | g o] (LSTM) or [r z] and the eight n columns of every lane group (GRU).
-void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms,
-                     std::vector<uint16_t>& out) {
-  const int kn = (I + H) / 32, G = lstm ? 4 : 3;
-  const size_t gb = group_bytes(lstm ? LSTM : GRU) / 2;
-  out.resize((size_t)(H / 8) * kn * terms * gb);
-  for (int gr = 0; gr < H / 8; ++gr)
-    for (int s = 0; s < kn; ++s) {
-      uint16_t* dst = out.data() + ((size_t)gr * kn + s) * terms * gb;
-      const float* src = 32 * s < I ? w_ih + 32 * s : w_hh + (32 * s - I);
-      const size_t pitch = 32 * s < I ? I : H;
-      for (int q = 0; q < G; ++q)
-        for (int lg = 0; lg < 4; ++lg)
-          for (int i = 0; i < 8; ++i) {
-            const size_t slot = q < 2 || lstm ? (size_t)(q >> 1) * 64 + lg * 16 + (q & 1) * 8 + i : (size_t)64 + lg * 8 + i;
-            put8(src + ((size_t)q * H + gr * 8 + i) * pitch + 8 * lg, terms, false, dst + slot * 8, gb);
-          }
-    }
+size_t dense_cell_pack_size(int I, int H, int lstm, int terms) {
+  return (size_t)(H / 8) * ((I + H) / 32) * terms * (group_bytes(lstm ? LSTM : GRU) / 2);
+}
+void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms, uint16_t* out) {
+  (host_avx2() ? pack_cell_avx2 : pack_cell_plain)(w_ih, w_hh, I, H, lstm, terms, out);
 }
 
 // x [M][K] (x_type 0 fp32, 1 bf16, 2 fp16), w packed with three terms for fp32 rows and one for

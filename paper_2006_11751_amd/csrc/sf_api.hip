@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <new>
 
 #include "sf_internal.h"
@@ -87,9 +88,15 @@ struct Builder {
 
   template <typename T>
   T* upload(const std::vector<T>& host) {
-    T* d = (T*)dev_alloc(host.size() * sizeof(T));
+    return upload_packed<T>(host.size(), [&](T* out) { memcpy(out, host.data(), host.size() * sizeof(T)); });
+  }
+
+  // fill(out) writes n elements: in replay mode straight into the staging area.
+  template <typename T, typename F>
+  T* upload_packed(size_t count, F fill) {
+    T* d = (T*)dev_alloc(count * sizeof(T));
     if (!d) return nullptr;
-    const size_t n = host.size() * sizeof(T);
+    const size_t n = count * sizeof(T);
     if (target) {
       const size_t off = (stage_off + 15) & ~(size_t)15;
       if (off + n > target->stage_bytes) {
@@ -99,19 +106,34 @@ struct Builder {
         }
         return nullptr;
       }
-      memcpy(target->stage + off, host.data(), n);
+      fill((T*)(target->stage + off));
       stage_off = off + n;
       copies.push_back(Copy{d, off, n});
       return d;
     }
     p->upload_bytes += n + 16;
-    hipError_t e = hipMemcpy(d, host.data(), n, hipMemcpyHostToDevice);
+    std::unique_ptr<T[]> host(new (std::nothrow) T[count]);
+    if (!host) {
+      set_error("out of host memory for %zu bytes of packed weights", n);
+      status = SF_ERR_OOM;
+      return nullptr;
+    }
+    fill(host.get());
+    hipError_t e = hipMemcpy(d, host.get(), n, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
       set_error("hipMemcpy to device failed: %s", hipGetErrorString(e));
       status = SF_ERR_DEVICE;
       return nullptr;
     }
     return d;
+  }
+
+  // Room for n elements without their values: a bank that the present parameters do not use (a weight
+  // update may come to use it).
+  template <typename T>
+  T* reserve(size_t n) {
+    if (!target) p->upload_bytes += n * sizeof(T) + 16;
+    return (T*)dev_alloc(n * sizeof(T));
   }
 
   float q(float v) const { return bf16 ? bf16_round(v) : v; }
@@ -338,6 +360,15 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   {
     int C = cfg->obs_c, H = cfg->obs_h, W = cfg->obs_w;
     int ti = 0;
+    // plain stack in fp32: largest possible value and mean square (of uniform bytes) of the channels
+    // of the current activation, which decide how a layer may split its operands
+    std::vector<double> act_bound, act_mean_sq;
+    if (cfg->encoder == SF_ENCODER_CONV) {
+      const double sub = cfg->obs_sub, mul = cfg->obs_mul;
+      const double mean_sq = mul * mul * (sub * sub - 255.0 * sub + 255.0 * 511.0 / 6.0);
+      act_bound.assign(C, fabs(mul) * std::max(fabs(sub), fabs(255.0 - sub)));
+      act_mean_sq.assign(C, mean_sq);
+    }
     auto add_conv = [&](const char* name, int cout, int k, int s, int pad, int relu_in,
                         int relu_out, int in_buf, int out_buf, int resid_buf) {
       ConvLayer L{};
@@ -430,20 +461,36 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
       }
       if (in_buf >= 0 && allow_mfma && !relu_in && resid_buf < 0 &&
           gemm_mfma_supported(C, k, pad, cout)) {
-        // [cout][cin][k][k] -> [cout][k][k][cin]: K ordered (filter row, filter column, channel)
-        std::vector<float> t((size_t)cout * C * k * k);
-        for (int o = 0; o < cout; ++o)
-          for (int c2 = 0; c2 < C; ++c2)
-            for (int a = 0; a < k; ++a)
-              for (int b2 = 0; b2 < k; ++b2)
-                t[(((size_t)o * k + a) * k + b2) * C + c2] =
-                    bld.q(w->conv_w[ti][(((size_t)o * C + c2) * k + a) * k + b2]);
-        L.wpk = bld.upload(t);
-        L.bpk = L.bias;
+        const size_t n_w = (size_t)cout * C * k * k;
         L.impl = CONV_GEMM_MFMA;
         L.tile = sw.gemm_tile > 0 ? sw.gemm_tile
                                   : gemm_mfma_pick_tile((long long)cfg->max_batch * L.Ho * L.Wo, cout,
                                                         k * k * C, k * C);
+        if (!bld.bf16 && relu_out && sw.gemm_tile == 0 && !sw.no_conv_image &&
+            conv_image_split_supported(C, k, s, pad, H, W, cout)) {
+          // Whether the layer may split its operands depends on the parameter values, and a weight
+          // update may change it: there is room for both banks.
+          std::vector<uint16_t> wt;
+          std::vector<float> sc;
+          const double ratio = conv_image_split_pack(w->conv_w[ti], cout, C, k, act_bound, act_mean_sq, wt, sc);
+          L.wsp = bld.upload(wt);
+          L.ssc = bld.upload(sc);
+          if (ratio <= 1.0) L.impl = CONV_IMAGE_SPLIT;
+        }
+        if (L.impl == CONV_IMAGE_SPLIT) {
+          L.wpk = bld.reserve<float>(n_w);
+        } else {
+          // [cout][cin][k][k] -> [cout][k][k][cin]: K ordered (filter row, filter column, channel)
+          std::vector<float> t(n_w);
+          for (int o = 0; o < cout; ++o)
+            for (int c2 = 0; c2 < C; ++c2)
+              for (int a = 0; a < k; ++a)
+                for (int b2 = 0; b2 < k; ++b2)
+                  t[(((size_t)o * k + a) * k + b2) * C + c2] =
+                      bld.q(w->conv_w[ti][(((size_t)o * C + c2) * k + a) * k + b2]);
+          L.wpk = bld.upload(t);
+        }
+        L.bpk = L.bias;
       }
       if (in_buf < 0 && allow_mfma && conv1_i8_supported(L) && conv1_mfma_supported(L)) {
         // First convolution of an fp32 network: three int8 digit planes of the folded filter
@@ -467,6 +514,8 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
         p->conv1_ratio2 = info.ratio2;
         p->conv1_ratio3 = info.ratio3;
       }
+      if (!act_bound.empty() && !bld.bf16)
+        conv_activation_range(w->conv_w[ti], w->conv_b[ti], cout, C, k, act_bound, act_mean_sq);
       if (L.impl == CONV_GENERIC) L.w_khwc_o = bld.pack_conv(w->conv_w[ti], cout, C, k);
       ++ti;
       int64_t m = (int64_t)L.Ho * L.Wo * cout * C * k * k;
@@ -614,9 +663,6 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
       return SF_ERR_SHAPE;
     }
 
-  std::vector<uint16_t> split;  // FC and core matrices in bf16 terms, one after the other
-  split.reserve((size_t)(bld.bf16 ? 1 : 3) * std::max<size_t>((size_t)p->flat * cfg->fc_dim,
-                                                               (size_t)4 * cfg->rnn_dim * (cfg->fc_dim + 2 * cfg->rnn_dim)));
   // ---- FC: columns permuted from (c, y, x) to the channels-last order (y, x, c), transposed ----
   {
     // u: [fc][flat in channels-last order]
@@ -624,8 +670,8 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
     for (int o = 0; o < cfg->fc_dim; ++o) {
       const float* src = w->fc_w + (size_t)o * p->flat;
       float* dst = u.data() + (size_t)o * p->flat;
-      for (int c = 0; c < Cf; ++c)
-        for (int yx = 0; yx < Hf * Wf; ++yx) dst[(size_t)yx * Cf + c] = bld.q(src[(size_t)c * Hf * Wf + yx]);
+      for (int yx = 0; yx < Hf * Wf; ++yx)
+        for (int c = 0; c < Cf; ++c) dst[(size_t)yx * Cf + c] = bld.q(src[(size_t)c * Hf * Wf + yx]);
     }
     p->fc_b = bld.pack_vec(w->fc_b, cfg->fc_dim);
     p->fc_wt = nullptr;
@@ -638,8 +684,10 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
                   (p->bf16_path ? !p->stream_f32 && sw.conv_bf16_tc == 0 && dense_fc_small(cfg->max_batch, cfg->fc_dim)
                                 : sw.fc_tile == 0 && !bld.bf16);
     if (p->dense_fc) {
-      dense_pack_fc(u.data(), cfg->fc_dim, p->flat, p->bf16_path ? 1 : 3, p->act_f16, split);
-      p->fc_split_w = bld.upload(split);
+      const int terms = p->bf16_path ? 1 : 3;
+      p->fc_split_w = bld.upload_packed<uint16_t>(dense_fc_pack_size(cfg->fc_dim, p->flat, terms), [&](uint16_t* out) {
+        dense_pack_fc(u.data(), cfg->fc_dim, p->flat, terms, p->act_f16, out);
+      });
     } else if (fc_mfma) {
       p->fc_wt = bld.upload(u);
       p->fc_tile = sw.fc_tile > 0 ? sw.fc_tile
@@ -736,8 +784,10 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
       wi = qi.data();
       wh = qh.data();
     }
-    dense_pack_cell(wi, wh, core_in, cfg->rnn_dim, lstm ? 1 : 0, bld.bf16 ? 1 : 3, split);
-    p->rnn_split_w = bld.upload(split);
+    const int terms = bld.bf16 ? 1 : 3;
+    p->rnn_split_w = bld.upload_packed<uint16_t>(dense_cell_pack_size(core_in, cfg->rnn_dim, lstm, terms), [&](uint16_t* out) {
+      dense_pack_cell(wi, wh, core_in, cfg->rnn_dim, lstm, terms, out);
+    });
   }
   p->gru_bih = bld.pack_vec(w->rnn_b_ih, HG);
   p->gru_bhh = bld.pack_vec(w->rnn_b_hh, HG);
@@ -1023,7 +1073,10 @@ extern "C" int sf_policy_update_weights(sf_policy* handle, const sf_policy_weigh
     // the first convolution's arithmetic (digit planes or fp32) follows the parameter values
     const bool conv1_pair = (a.impl == CONV1_U8_I8 || a.impl == CONV1_U8_MFMA) &&
                             (b.impl == CONV1_U8_I8 || b.impl == CONV1_U8_MFMA) && a.ipk && a.wpk;
-    same_plan = (a.impl == b.impl || conv1_pair) && a.tile == b.tile && a.wpk == b.wpk && a.wbf == b.wbf &&
+    // and so does a later one's (split operands or fp32)
+    const bool split_pair = (a.impl == CONV_IMAGE_SPLIT || a.impl == CONV_GEMM_MFMA) &&
+                            (b.impl == CONV_IMAGE_SPLIT || b.impl == CONV_GEMM_MFMA) && a.ssc && a.ssc == b.ssc;
+    same_plan = (a.impl == b.impl || conv1_pair || split_pair) && a.tile == b.tile && a.wpk == b.wpk && a.wbf == b.wbf &&
                 a.ipk == b.ipk && a.w_khwc_o == b.w_khwc_o && a.wsp == b.wsp;
   }
   if (!same_plan) {
@@ -1199,6 +1252,10 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
             SF_LAUNCH(launch_gemm_mfma((const float*)in, L.wpk, L.bpk, buf(op.out_buf), B, L.H, L.W,
                                        L.cin, L.k, L.s, L.Ho, L.Wo, L.cout, L.relu_out, L.tile,
                                        op.conv + 1, st));
+            break;
+          case CONV_IMAGE_SPLIT:
+            SF_LAUNCH(launch_conv_image_split((const float*)in, L.wsp, L.ssc, L.bias, buf(op.out_buf), B, L.H, L.W,
+                                              L.cin, L.k, L.cout, st));
             break;
           case CONV_IMAGE_BF16:
             SF_LAUNCH(launch_conv_image_bf16(in, L.wbf, L.bbf, buf(op.out_buf), B, L.H, L.W, L.cin,
@@ -1422,6 +1479,7 @@ extern "C" const char* sf_policy_op_kernel(const sf_policy* handle, int i) {
         case RES_BLOCK: return "res_block";
         case RES_STAGE: return "res_stage";
         case CONV_IMAGE_BF16: return "conv_image_bf16";
+        case CONV_IMAGE_SPLIT: return "conv_image_split";
         default: return "generic";
       }
     case OP_POOL: return "pool";
@@ -1454,6 +1512,7 @@ extern "C" const char* sf_policy_op_pipe(const sf_policy* handle, int i) {
           return L.planes == 2 ? "i8x2" : "i8x3";
         case CONV1_U8_MFMA:
         case CONV_GEMM_MFMA: return "f32";
+        case CONV_IMAGE_SPLIT: return "f16x2";
         case CONV_BF16:
         case CONV3X3_PATCH:
         case CONV3X3_STEM:

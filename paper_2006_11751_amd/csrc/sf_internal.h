@@ -35,7 +35,9 @@ struct ConvLayer {
   int in_f32, out_f32;    // bf16 kernel: element type of its input / output tensors
   float* w_cpqo;          // dev, fp32 [c][p][q][cout] for the byte-input 3x3 kernel
   uint16_t* wsp;          // dev, A operands in a second layout: of the register-pooled first convolution,
-                          // or of a 16 -> 16 channel block convolution for the stage kernel (or null)
+                          // of a 16 -> 16 channel block convolution for the stage kernel, or in two
+                          // fp16 terms for k_conv_image_split.hip (or null)
+  float* ssc;             // dev, that kernel's scales
 };
 enum ConvImpl {
   CONV_GENERIC = 0, CONV1_U8_MFMA = 1, CONV_GEMM_MFMA = 2, CONV1_U8_I8 = 3,
@@ -48,6 +50,7 @@ enum ConvImpl {
   RES_STAGE = 11,       // all residual blocks of a stage in one kernel, frame resident in LDS
   STEM_POOL = 12,       // first convolution of the residual encoder and its max-pool, pooled in registers
   CONV_POOL_REGS = 13,  // stage convolution (16 or 32 -> 32 channels) and its max-pool, pooled in registers
+  CONV_IMAGE_SPLIT = 14,  // fp32 operands in two fp16 terms, the frame's input image resident in LDS
   CONV_IMAGE_BF16 = 10  // 16-bit MFMA with the frame's input image resident in LDS
 };
 
@@ -260,9 +263,10 @@ bool dense_cell_supported(int I1, int I2, int H);
 bool dense_fc_small(int M, int N);
 bool dense_cell_small(int M, int H);
 bool dense_cell_tile_supported(int I1, int I2, int H);
-void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, std::vector<uint16_t>& out);
-void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms,
-                     std::vector<uint16_t>& out);
+size_t dense_fc_pack_size(int N, int K, int terms);  // elements
+size_t dense_cell_pack_size(int I, int H, int lstm, int terms);
+void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, uint16_t* out);
+void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms, uint16_t* out);
 hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const float* bias, void* out, int out_bf16,
                            int M, int K, int N, hipStream_t st);
 hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16, const float* x2,
@@ -284,6 +288,14 @@ hipError_t launch_conv_image_bf16(const void* in, const uint16_t* wpk, const flo
 bool conv12_fused_bf16_supported(int cin, int H, int W, const sf_conv& c1, const sf_conv& c2);
 hipError_t launch_conv12_fused_bf16(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs,
                                     void* out, hipStream_t st);
+// fp32 convolution on operands split into two fp16 terms (k_conv_image_split.hip)
+bool conv_image_split_supported(int Cin, int ksize, int stride, int pad, int H, int W, int N);
+void conv_activation_range(const float* w, const float* bias, int cout, int cin, int k, std::vector<double>& bound,
+                           std::vector<double>& mean_sq);
+double conv_image_split_pack(const float* w, int cout, int cin, int k, const std::vector<double>& bound,
+                             const std::vector<double>& mean_sq, std::vector<uint16_t>& wpk, std::vector<float>& scale);
+hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const float* scale, const float* bias,
+                                   float* out, int B, int H, int W, int Cin, int ksize, int N, hipStream_t st);
 bool gemm_mfma_supported(int Cin, int ksize, int pad, int N);
 int gemm_mfma_pick_tile(long long M, int N, int K, int seg_len);
 hipError_t launch_gemm_mfma(const float* A, const float* Wt, const float* bias, float* out, int B,
