@@ -128,6 +128,16 @@ EXPORTS = ("sf_policy_create", "sf_policy_step", "sf_policy_destroy", "sf_last_e
            "sf_appo_loss_static", "sf_appo_loss_static_max_trajectories", "sf_policy_op_kernel", "sf_policy_unroll")
 
 _lib = None
+_torch_module = None
+
+
+def _torch():
+    """torch, imported when it is first needed (an import statement costs half a microsecond a call)."""
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 class SfError(RuntimeError):
@@ -355,16 +365,14 @@ def sf_policy_update_weights(handle, weights, hip_stream=None):
         raise SfError(rc, sf_last_error())
 
 
+_HEAD_ARRAY = C.c_int32 * SF_MAX_HEADS
+
+
 def make_loss_config(hp):
     """hp: dict(T, N, heads, gamma, rho_bar, c_bar, clip, critic_coef, entropy_coef)."""
-    c = SfLossConfig()
-    c.struct_size = C.sizeof(SfLossConfig)
-    c.T, c.N, c.n_heads = hp["T"], hp["N"], len(hp["heads"])
-    for i, a in enumerate(hp["heads"]):
-        c.head_sizes[i] = a
-    for k in ("gamma", "rho_bar", "c_bar", "clip", "critic_coef", "entropy_coef"):
-        setattr(c, k, hp[k])
-    return c
+    heads = hp["heads"]
+    return SfLossConfig(C.sizeof(SfLossConfig), hp["T"], hp["N"], len(heads), _HEAD_ARRAY(*heads), hp["gamma"],
+                        hp["rho_bar"], hp["c_bar"], hp["clip"], hp["critic_coef"], hp["entropy_coef"])
 
 
 def sf_appo_loss_workspace_bytes(cfg):
@@ -395,14 +403,22 @@ def sf_appo_loss_static(cfg, logits, actions, logp_mu, values, rewards, dones, v
 def appo_loss(hp, tr, want_grads=True, stream=None, out=None):
     """tr: dict of contiguous CUDA tensors (logits, actions, logp_mu, values, rewards, dones),
     time-major.  Returns dict(vs, adv, loss[4], dlogits, dvalues) of CUDA tensors."""
-    import torch
+    # (called once per batch of a learner, where the launches take about as long as this function:
+    # the checks are written out)
+    torch = _torch()
     cfg = make_loss_config(hp)
-    T, N, sumA = tr["logits"].shape
-    d = tr["logits"].device
-    for k, dt in (("logits", torch.float32), ("actions", torch.int32), ("logp_mu", torch.float32),
-                  ("values", torch.float32), ("rewards", torch.float32), ("dones", torch.uint8)):
-        assert tr[k].dtype == dt and tr[k].is_contiguous() and tr[k].is_cuda, k
-    assert (T, N) == (hp["T"], hp["N"]) and sumA == sum(hp["heads"]) and tuple(tr["values"].shape) == (T + 1, N)
+    logits, actions, logp_mu = tr["logits"], tr["actions"], tr["logp_mu"]
+    values, rewards, dones = tr["values"], tr["rewards"], tr["dones"]
+    T, N, sumA = logits.shape
+    d = logits.device
+    f32 = torch.float32
+    assert logits.dtype == f32 and logits.is_contiguous() and logits.is_cuda, "logits"
+    assert actions.dtype == torch.int32 and actions.is_contiguous() and actions.is_cuda, "actions"
+    assert logp_mu.dtype == f32 and logp_mu.is_contiguous() and logp_mu.is_cuda, "logp_mu"
+    assert values.dtype == f32 and values.is_contiguous() and values.is_cuda, "values"
+    assert rewards.dtype == f32 and rewards.is_contiguous() and rewards.is_cuda, "rewards"
+    assert dones.dtype == torch.uint8 and dones.is_contiguous() and dones.is_cuda, "dones"
+    assert T == hp["T"] and N == hp["N"] and sumA == sum(hp["heads"]) and values.shape == (T + 1, N)
     if out is None:
         out = dict(vs=torch.empty((T, N), device=d), adv=torch.empty((T, N), device=d),
                    loss=torch.empty(4, device=d),
@@ -410,10 +426,12 @@ def appo_loss(hp, tr, want_grads=True, stream=None, out=None):
                    dvalues=torch.empty((T, N), device=d) if want_grads else None,
                    workspace=torch.empty(sf_appo_loss_workspace_bytes(cfg), dtype=torch.uint8, device=d))
     s = stream if stream is not None else torch.cuda.current_stream(d)
-    p = lambda x: None if x is None else x.data_ptr()
-    sf_appo_loss(cfg, p(tr["logits"]), p(tr["actions"]), p(tr["logp_mu"]), p(tr["values"]), p(tr["rewards"]),
-                 p(tr["dones"]), p(out["vs"]), p(out["adv"]), p(out["loss"]), p(out["dlogits"]),
-                 p(out["dvalues"]), p(out["workspace"]), s.cuda_stream)
+    dlogits, dvalues, workspace = out["dlogits"], out["dvalues"], out["workspace"]
+    sf_appo_loss(cfg, logits.data_ptr(), actions.data_ptr(), logp_mu.data_ptr(), values.data_ptr(),
+                 rewards.data_ptr(), dones.data_ptr(), out["vs"].data_ptr(), out["adv"].data_ptr(),
+                 out["loss"].data_ptr(), None if dlogits is None else dlogits.data_ptr(),
+                 None if dvalues is None else dvalues.data_ptr(),
+                 None if workspace is None else workspace.data_ptr(), s.cuda_stream)
     return out
 
 

@@ -9,23 +9,19 @@
 //   L_pi = -mean min(ratio adv, clamp(ratio, 1/clip, clip) adv),  L_v = c_v mean (V - vs)^2,
 //   L_ent = -c_H mean entropy
 //
-// One 64-lane wavefront per trajectory, one lane per time step.  A lane first reduces its
-// sample's logits to the joint log-probability and the entropy; the backward recursion over
-// time then runs across the lanes of the wave (the 64 coefficient pairs are broadcast one
-// by one, last step first); trajectories longer than 64 steps are walked in 64-step chunks
-// from the end, carrying the recursion's value.  The lane then writes targets, advantages
-// and gradients for its sample, and the wave its three partial sums.  A second, single-wave
-// launch adds the per-trajectory partial sums in a fixed order, so the result does not
-// depend on scheduling.
+// A sample's logits are reduced to the joint log-probability and the entropy; the backward recursion
+// over time runs across the 32 or 64 lanes of a trajectory (the coefficient pairs are broadcast one
+// by one, last step first); longer trajectories are walked in chunks from the end, carrying the
+// recursion's value.  Targets, advantages, gradients and partial sums follow.  A second,
+// single-workgroup launch adds the partial sums in a fixed order, so the result does not depend on
+// scheduling.
 //
-// Memory side: the arrays are time-major, so the 64 samples of a wave lie N * sumA floats apart
+// Memory side: the arrays are time-major, so the samples of a trajectory lie N * sumA floats apart
 // and per-lane reads of a sample's logits touch a cache line per lane and element.  A workgroup
-// therefore owns four consecutive trajectories: for every time step their logits (and actions)
-// are one contiguous run in memory, which the 256 threads copy into LDS with coalesced loads
-// (row pitch odd: the per-lane walks over a sample's logits are then free of bank conflicts);
-// the lanes compute out of LDS, leave the logit gradients there in place, and the workgroup
-// writes them back as contiguous runs.  Logits and actions cross the memory bus once.  Tiles
-// that do not fit LDS (several hundred logits per sample) take the direct kernel.
+// therefore copies its trajectories' logits (and actions; one contiguous run of memory per time
+// step) into LDS with coalesced loads (row pitch odd: walks over a sample's logits are free of bank
+// conflicts), and the gradients leave for memory as contiguous runs again.  Tiles that do not fit
+// LDS take the direct kernel (one wave per trajectory, one lane per time step).
 #include <math.h>
 
 #include <mutex>
@@ -59,6 +55,8 @@ struct LossArgs {
   float* partials;        // [N][4]
   int T, N, n_heads, sumA;
   int head_sizes[SF_MAX_HEADS];
+  int head_off[SF_MAX_HEADS];    // first logit of each head
+  int head_order[SF_MAX_HEADS];  // heads by size, largest first
   float gamma, rho_bar, c_bar, clip, critic_coef, entropy_coef;
 };
 
@@ -175,24 +173,23 @@ __device__ inline uint32_t div_magic(uint32_t e, uint32_t d, uint32_t m) { retur
 
 struct LdsPlan {
   int pitch;             // floats per sample row of the logits tile (odd, >= sumA)
-  uint32_t m_sumA, m_nh; // multipliers for division by sumA and by n_heads
+  uint32_t m_sumA, m_nh; // multipliers for division by sumA and by n_heads,
+  uint32_t m_row, m_row4, m_arow;  // by the length of a whole tile row (floats, 16-byte pieces; actions)
   int vec4;              // logits rows may be copied as 16-byte pieces (pitch == sumA, alignment)
 };
 
 constexpr int kLossThreads = kWave * kTrajPerBlock;
 
-// Tile copies between memory and LDS.  Row tt of the chunk holds, for time step t0 + tt, the nb
-// trajectories' values side by side: memory run of nb * per elements at ((t0 + tt) * N + n0) * per,
-// LDS sample (tt, j) at (tt * TPB + j) * pitch.  TO_LDS: memory -> LDS, else LDS -> memory.
-// Loads are issued in batches of kCopyBatch per thread before the first of them is stored: a
-// loop of load-then-store pays one memory latency per iteration.
+// Tile copies into LDS.  Row tt of the chunk holds, for time step t0 + tt, the nb trajectories'
+// values side by side: memory run of nb * per elements at ((t0 + tt) * N + n0) * per, LDS sample
+// (tt, j) at (tt * TPB + j) * pitch.  Loads are issued in batches of kCopyBatch per thread before
+// the first of them is stored: a loop of load-then-store pays one memory latency per iteration.
 constexpr int kCopyBatch = 8;
 
-template <bool TO_LDS, int TPB, int NT, typename T>
-__device__ inline void copy_tile(T* mem, T* tile, int t0, int nt, int N, int n0, int nb, int per,
-                                 int pitch, uint32_t m_per) {
+template <int TPB, int NT, typename T>
+__device__ inline void copy_tile(const T* mem, T* tile, int t0, int nt, int N, int n0, int nb, int per,
+                                 int pitch, uint32_t m_per, uint32_t m_row) {
   const int rowlen = nb * per;
-  const uint32_t m_row = magic_of((uint32_t)rowlen);
   const int total = nt * rowlen;
   for (int e0 = threadIdx.x; e0 < total; e0 += NT * kCopyBatch) {
     T v[kCopyBatch];
@@ -204,11 +201,8 @@ __device__ inline void copy_tile(T* mem, T* tile, int t0, int nt, int N, int n0,
       const int tt = (int)div_magic((uint32_t)ec, (uint32_t)rowlen, m_row);
       const int r = ec - tt * rowlen;
       const int j = (int)div_magic((uint32_t)r, (uint32_t)per, m_per);
-      const int i = r - j * per;
-      T* gp = mem + ((size_t)(t0 + tt) * N + n0) * per + r;
-      T* lp = tile + (tt * TPB + j) * pitch + i;
-      v[u] = TO_LDS ? *gp : *lp;
-      dst[u] = TO_LDS ? lp : gp;
+      v[u] = mem[((size_t)(t0 + tt) * N + n0) * per + r];
+      dst[u] = tile + (tt * TPB + j) * pitch + (r - j * per);
     }
 #pragma unroll
     for (int u = 0; u < kCopyBatch; ++u)
@@ -219,10 +213,10 @@ __device__ inline void copy_tile(T* mem, T* tile, int t0, int nt, int N, int n0,
 // The same for a full-width tile (nb == TPB) whose rows are contiguous in LDS as in memory
 // (pitch == per) and 16-byte aligned on both sides: 16-byte pieces.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <bool TO_LDS, int TPB, int NT>
-__device__ inline void copy_tile_vec4(float* mem, float* tile, int t0, int nt, int N, int n0, int per) {
+template <int TPB, int NT>
+__device__ inline void copy_tile_vec4(const float* mem, float* tile, int t0, int nt, int N, int n0, int per,
+                                      uint32_t m_row4) {
   const int row4 = TPB * per / 4;  // pieces per row
-  const uint32_t m_row = magic_of((uint32_t)row4);
   const int total = nt * row4;
   for (int e0 = threadIdx.x; e0 < total; e0 += NT * kCopyBatch) {
     f32x4 v[kCopyBatch];
@@ -231,12 +225,10 @@ __device__ inline void copy_tile_vec4(float* mem, float* tile, int t0, int nt, i
     for (int u = 0; u < kCopyBatch; ++u) {
       const int e = e0 + u * NT;
       const int ec = e < total ? e : total - 1;
-      const int tt = (int)div_magic((uint32_t)ec, (uint32_t)row4, m_row);
+      const int tt = (int)div_magic((uint32_t)ec, (uint32_t)row4, m_row4);
       const int r = ec - tt * row4;
-      f32x4* gp = (f32x4*)(mem + ((size_t)(t0 + tt) * N + n0) * per) + r;
-      f32x4* lp = (f32x4*)(tile + (size_t)tt * TPB * per) + r;
-      v[u] = TO_LDS ? *gp : *lp;
-      dst[u] = TO_LDS ? lp : gp;
+      v[u] = *((const f32x4*)(mem + ((size_t)(t0 + tt) * N + n0) * per) + r);
+      dst[u] = (f32x4*)(tile + (size_t)tt * TPB * per) + r;
     }
 #pragma unroll
     for (int u = 0; u < kCopyBatch; ++u)
@@ -244,32 +236,60 @@ __device__ inline void copy_tile_vec4(float* mem, float* tile, int t0, int nt, i
   }
 }
 
-// LW lanes per trajectory: 64, or 32 when T <= 32 (two trajectories per wave, no idle half);
-// NT threads per workgroup (LW = 32: two waves, so that the grid has several workgroups per CU
-// and one's tile copies overlap another's arithmetic).
-// Per head the forward pass takes one exponential per logit:
+// A workgroup of NT threads owns TPB trajectories, LW (32 when T <= 32, else 64) time steps of them
+// at a time.  What bounds it is the latency of a few dependent stretches, so each of them is spread
+// over all threads:
+//   1. tiles of logits and actions into LDS, coalesced;
+//   2. one thread per (sample, head), largest heads first: log-sum-exp, entropy, log-probability;
+//   3. one thread per sample: ratio, the backward recursion across the lanes of a trajectory,
+//      targets, advantages, partial sums;
+//   4. one thread per logit (four neighbouring ones where the rows allow): gradients straight from
+//      the tile to memory.
+// (One lane per sample through all of it, two waves per workgroup, took 14.5 us at 64 trajectories of
+// 32 steps and seven heads, 19.6 at 2048; now 9.4 and 15.7, 1.6 TB/s of logits, actions and gradients.)
+// Per head one exponential per logit forward,
 //   d_i = l_i - max, e_i = exp(d_i), se = sum e_i, sd = sum e_i d_i
 //   lse = max + log se,  entropy = log se - sd / se   (= -sum p_i (l_i - lse))
-// (lse, entropy) of every head of every sample are kept in LDS for the gradient pass, which takes
-// one more exponential per logit (p_i = exp(l_i - lse)).  These exponentials (arguments <= 0,
+// and one more for the gradient (p_i = exp(l_i - lse)).  These exponentials (arguments <= 0,
 // results only ever summed or multiplied into terms of the 1e-4 tolerance) use the hardware
 // exp2 (about 2 ulp for arguments of a few units); the logarithm per head and the importance
 // ratio stay on the accurate routines.
-template <int LW, int NT>
+template <int LW, int TPB, int NT>
 __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan plan) {
-  constexpr int TPB = NT / LW;  // trajectories per workgroup
+  constexpr int S = LW * TPB;  // samples per chunk; sample (tt, j) of the tile is tt * TPB + j
+  static_assert(S <= NT, "one thread per sample");
   extern __shared__ __attribute__((aligned(16))) float lds_tile[];
-  float* ltile = lds_tile;                                   // [LW][TPB][pitch] logits, then gradients
-  float* htile = ltile + LW * TPB * plan.pitch;              // [LW][TPB][n_heads][2] (lse, entropy)
-  int32_t* atile = (int32_t*)(htile + LW * TPB * g.n_heads * 2);  // [LW][TPB][n_heads]
-  const int lane = threadIdx.x % LW, j = threadIdx.x / LW;
+  const int hp = g.n_heads | 1;                              // odd pitch of the per-head values
+  float* ltile = lds_tile;                                   // [S][pitch] logits
+  float* t_lse = ltile + S * plan.pitch;                     // [S][hp]
+  float* t_ent = t_lse + S * hp;                             // [S][hp]
+  float* t_lp = t_ent + S * hp;                              // [S][hp] log-probability of the action taken
+  int32_t* t_act = (int32_t*)(t_lp + S * hp);                // [S][hp] actions, then their place among the logits
+  float* t_dlp = (float*)(t_act + S * hp);                   // [S] d L_pi / d logp_pi
+  float* t_sum = t_dlp + S;                                  // [TPB][4] partial sums
+  int32_t* head_of = (int32_t*)(t_sum + TPB * 4);            // [sumA] head of a logit
+  // time step, trajectory of a sample (threads from S on ask for the same scalars again)
+  const int tid = threadIdx.x, lane = tid % LW, j = tid / LW % TPB;
   const int n0 = blockIdx.x * TPB;
   const int nb = g.N - n0 < TPB ? g.N - n0 : TPB;
   const int n = n0 + j;
-  const bool have = n < g.N;  // lanes without a trajectory only help with the copies
+  const bool have = tid < S && n < g.N;
   const bool vec4 = plan.vec4 && nb == TPB;
+  uint32_t m_row = plan.m_row, m_arow = plan.m_arow;
+  if (nb != TPB) {
+    m_row = magic_of((uint32_t)(nb * g.sumA));
+    m_arow = magic_of((uint32_t)(nb * g.n_heads));
+  }
   const float inv_m = 1.0f / ((float)g.T * (float)g.N);
   const float lo = 1.0f / g.clip, hi = g.clip;
+  const float ce = g.entropy_coef * inv_m;
+  // (the arguments' tables, read by a lane's own index, are a chain of memory latencies)
+  __shared__ int t_size[SF_MAX_HEADS], t_off[SF_MAX_HEADS], t_order[SF_MAX_HEADS];
+  if (tid < SF_MAX_HEADS) {
+    t_size[tid] = g.head_sizes[tid];
+    t_off[tid] = g.head_off[tid];
+    t_order[tid] = g.head_order[tid];
+  }
   float sum_pi = 0.0f, sum_v = 0.0f, sum_ent = 0.0f;
   float carry = 0.0f;
   const int n_chunks = (g.T + LW - 1) / LW;
@@ -278,67 +298,71 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
     const int nt = g.T - t0 < LW ? g.T - t0 : LW;
     // the sample's scalars are requested first: their latency passes under the tile copies
     const int tt = t0 + lane < g.T ? lane : nt - 1;  // idle lanes re-read the chunk's last step
-    const size_t s = (size_t)(t0 + tt) * g.N + (have ? n : g.N - 1);
+    const size_t s = (size_t)(t0 + tt) * g.N + (n < g.N ? n : g.N - 1);
     const float v = g.values[s], vn = g.values[s + g.N], r = g.rewards[s], lmu = g.logp_mu[s];
     const float gm = g.dones[s] ? 0.0f : g.gamma;
     if (vec4)
-      copy_tile_vec4<true, TPB, NT>(const_cast<float*>(g.logits), ltile, t0, nt, g.N, n0, g.sumA);
+      copy_tile_vec4<TPB, NT>(g.logits, ltile, t0, nt, g.N, n0, g.sumA, plan.m_row4);
     else
-      copy_tile<true, TPB, NT>(const_cast<float*>(g.logits), ltile, t0, nt, g.N, n0, nb, g.sumA, plan.pitch,
-                           plan.m_sumA);
-    copy_tile<true, TPB, NT>(const_cast<int32_t*>(g.actions), atile, t0, nt, g.N, n0, nb, g.n_heads, g.n_heads,
-                         plan.m_nh);
+      copy_tile<TPB, NT>(g.logits, ltile, t0, nt, g.N, n0, nb, g.sumA, plan.pitch, plan.m_sumA, m_row);
+    copy_tile<TPB, NT>(g.actions, t_act, t0, nt, g.N, n0, nb, g.n_heads, hp, plan.m_nh, m_arow);
+    __syncthreads();
+    if (ch == n_chunks - 1)
+      for (int i = tid; i < g.sumA; i += NT) {
+        int k = 0;
+        for (int q = 1; q < g.n_heads; ++q) k += i >= t_off[q];
+        head_of[i] = k;
+      }
+    for (int w = tid; w < g.n_heads * S; w += NT) {
+      const int k = t_order[w / S], smp = w % S;
+      if (smp / TPB >= nt || smp % TPB >= nb) continue;
+      const int A = t_size[k], off = t_off[k];
+      const float* l = ltile + smp * plan.pitch + off;
+      // four independent chains per pass: nobody else hides the latency of an LDS read or of an
+      // exponential
+      float m4[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      int i = 0;
+      for (; i + 4 <= A; i += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m4[u] = fmaxf(m4[u], l[i + u]);
+      }
+      for (; i < A; ++i) m4[0] = fmaxf(m4[0], l[i]);
+      const float mx = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+      float se4[4] = {0.0f, 0.0f, 0.0f, 0.0f}, sd4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (i = 0; i + 4 <= A; i += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float d = l[i + u] - mx;
+          const float e = __expf(d);
+          se4[u] += e;
+          sd4[u] = fmaf(e, d, sd4[u]);
+        }
+      }
+      for (; i < A; ++i) {
+        const float d = l[i] - mx;
+        const float e = __expf(d);
+        se4[0] += e;
+        sd4[0] = fmaf(e, d, sd4[0]);
+      }
+      const float se = (se4[0] + se4[1]) + (se4[2] + se4[3]);
+      const float sd = (sd4[0] + sd4[1]) + (sd4[2] + sd4[3]);
+      const float lg = logf(se);
+      const float lse = mx + lg;
+      const int at = smp * hp + k;
+      const int a = min(max(t_act[at], 0), A - 1);
+      t_lse[at] = lse;
+      t_ent[at] = lg - sd / se;
+      t_lp[at] = l[a] - lse;
+      t_act[at] = off + a;
+    }
     __syncthreads();
     if (have) {
       const bool live = t0 + lane < g.T;
       const int smp = tt * TPB + j;
-      float* l0 = ltile + smp * plan.pitch;
-      float* h0 = htile + smp * g.n_heads * 2;
-      const int32_t* a0 = atile + smp * g.n_heads;
       float logp = 0.0f, ent = 0.0f;
-      {
-        const float* l = l0;
-        for (int k = 0; k < g.n_heads; ++k) {
-          const int A = g.head_sizes[k];
-          // four independent chains per pass: with one wave per SIMD there is nobody else to
-          // hide the latency of an LDS read or of an exponential behind
-          float m4[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-          int i = 0;
-          for (; i + 4 <= A; i += 4) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) m4[u] = fmaxf(m4[u], l[i + u]);
-          }
-          for (; i < A; ++i) m4[0] = fmaxf(m4[0], l[i]);
-          const float mx = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
-          float se4[4] = {0.0f, 0.0f, 0.0f, 0.0f}, sd4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-          for (i = 0; i + 4 <= A; i += 4) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const float d = l[i + u] - mx;
-              const float e = __expf(d);
-              se4[u] += e;
-              sd4[u] = fmaf(e, d, sd4[u]);
-            }
-          }
-          for (; i < A; ++i) {
-            const float d = l[i] - mx;
-            const float e = __expf(d);
-            se4[0] += e;
-            sd4[0] = fmaf(e, d, sd4[0]);
-          }
-          const float se = (se4[0] + se4[1]) + (se4[2] + se4[3]);
-          const float sd = (sd4[0] + sd4[1]) + (sd4[2] + sd4[3]);
-          const float lg = logf(se);
-          const float lse = mx + lg, hk = lg - sd / se;
-          if (live) {  // (idle lanes share the last step's slot with its owner)
-            h0[2 * k] = lse;
-            h0[2 * k + 1] = hk;
-          }
-          const int a = min(max(a0[k], 0), A - 1);
-          logp += l[a] - lse;
-          ent += hk;
-          l += A;
-        }
+      for (int k = 0; k < g.n_heads; ++k) {
+        logp += t_lp[smp * hp + k];
+        ent += t_ent[smp * hp + k];
       }
       const float ratio = expf(logp - lmu);
       const float rho = fminf(g.rho_bar, ratio), c = fminf(g.c_bar, ratio);
@@ -364,46 +388,43 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
         sum_v += dv * dv;
         sum_ent -= ent;
         if (g.dvalues) g.dvalues[s] = 2.0f * g.critic_coef * dv * inv_m;
-        if (g.dlogits) {
-          const float dlp = a <= b ? -adv * ratio * inv_m : 0.0f;  // d L_pi / d logp_pi
-          const float ce = g.entropy_coef * inv_m;
-          float* l = l0;  // the gradient replaces the logits in the tile
-          for (int k = 0; k < g.n_heads; ++k) {
-            const int A = g.head_sizes[k];
-            const float lse = h0[2 * k], hk = h0[2 * k + 1];
-            const int act = min(max(a0[k], 0), A - 1);
-            int i = 0;
-            for (; i + 4 <= A; i += 4) {
-              float q[4];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) q[u] = l[i + u];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const float ls = q[u] - lse;
-                const float p = __expf(ls);
-                q[u] = dlp * ((i + u == act ? 1.0f : 0.0f) - p) + ce * p * (ls + hk);
-              }
-#pragma unroll
-              for (int u = 0; u < 4; ++u) l[i + u] = q[u];
-            }
-            for (; i < A; ++i) {
-              const float ls = l[i] - lse;
-              const float p = __expf(ls);
-              l[i] = dlp * ((i == act ? 1.0f : 0.0f) - p) + ce * p * (ls + hk);
-            }
-            l += A;
-          }
-        }
+        t_dlp[smp] = a <= b ? -adv * ratio * inv_m : 0.0f;
       }
     }
     __syncthreads();
     if (g.dlogits) {
-      if (vec4)
-        copy_tile_vec4<false, TPB, NT>(g.dlogits, ltile, t0, nt, g.N, n0, g.sumA);
-      else
-        copy_tile<false, TPB, NT>(g.dlogits, ltile, t0, nt, g.N, n0, nb, g.sumA, plan.pitch, plan.m_sumA);
+      auto gradient = [&](int smp, int i) {
+        const int k = head_of[i], at = smp * hp + k;
+        const float ls = ltile[smp * plan.pitch + i] - t_lse[at];
+        const float p = __expf(ls);
+        return t_dlp[smp] * ((i == t_act[at] ? 1.0f : 0.0f) - p) + ce * p * (ls + t_ent[at]);
+      };
+      if (vec4) {
+        const int row4 = TPB * g.sumA / 4;
+        for (int e = tid; e < nt * row4; e += NT) {
+          const int gt = (int)div_magic((uint32_t)e, (uint32_t)row4, plan.m_row4), q = e - gt * row4;
+          int jj = (int)div_magic((uint32_t)(4 * q), (uint32_t)g.sumA, plan.m_sumA), i = 4 * q - jj * g.sumA;
+          f32x4 d;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            d[u] = gradient(gt * TPB + jj, i);
+            if (++i == g.sumA) {
+              i = 0;
+              ++jj;
+            }
+          }
+          *((f32x4*)(g.dlogits + ((size_t)(t0 + gt) * g.N + n0) * g.sumA) + q) = d;
+        }
+      } else {
+        const int row = nb * g.sumA;
+        for (int e = tid; e < nt * row; e += NT) {
+          const int gt = (int)div_magic((uint32_t)e, (uint32_t)row, m_row), q = e - gt * row;
+          const int jj = (int)div_magic((uint32_t)q, (uint32_t)g.sumA, plan.m_sumA), i = q - jj * g.sumA;
+          g.dlogits[((size_t)(t0 + gt) * g.N + n0) * g.sumA + q] = gradient(gt * TPB + jj, i);
+        }
+      }
     }
-    __syncthreads();  // the tiles are free for the next chunk
+    if (ch) __syncthreads();  // the tiles are free for the next chunk
   }
   if (have) {
 #pragma unroll
@@ -413,16 +434,22 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
       sum_ent += __shfl_xor(sum_ent, m, LW);
     }
     if (lane == 0) {
-      float* o = g.partials + (size_t)n * 4;
-      o[0] = sum_pi;
-      o[1] = sum_v;
-      o[2] = sum_ent;
-      o[3] = 0.0f;
+      t_sum[j * 4] = sum_pi;
+      t_sum[j * 4 + 1] = sum_v;
+      t_sum[j * 4 + 2] = sum_ent;
     }
+  }
+  __syncthreads();
+  if (tid < 4) {  // one entry per workgroup, trajectories in order
+    float a = 0.0f;
+    if (tid < 3)
+      for (int q = 0; q < nb; ++q) a += t_sum[q * 4 + tid];
+    g.partials[(size_t)blockIdx.x * 4 + tid] = a;
   }
 }
 
-// Adds the per-trajectory partial sums in an order that depends on N only: thread i takes
+// Adds the partial sums (one entry per workgroup of the first launch) in an order that depends on
+// their number only: thread i takes
 // entries i, i + 256, ... (independent 16-byte loads), then a fixed binary tree over the 256
 // threads' sums in LDS.
 constexpr int kReduceThreads = 256;
@@ -526,43 +553,67 @@ int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const flo
   for (int k = 0; k < SF_MAX_HEADS; ++k) g.head_sizes[k] = k < cfg->n_heads ? cfg->head_sizes[k] : 0;
   g.gamma = cfg->gamma; g.rho_bar = cfg->rho_bar; g.c_bar = cfg->c_bar; g.clip = cfg->clip;
   g.critic_coef = cfg->critic_coef; g.entropy_coef = cfg->entropy_coef;
-  // the LDS-staged kernel where a chunk's tiles fit LDS, with 32 lanes per trajectory (eight
-  // trajectories per workgroup) when the trajectories are no longer than that
+  {
+    int off = 0;
+    for (int k = 0; k < SF_MAX_HEADS; ++k) {
+      g.head_off[k] = off;
+      off += g.head_sizes[k];
+      g.head_order[k] = k;
+    }
+    for (int k = 1; k < g.n_heads; ++k)  // (a stable insertion sort: equal heads keep their order)
+      for (int q = k; q > 0 && g.head_sizes[g.head_order[q]] > g.head_sizes[g.head_order[q - 1]]; --q) {
+        const int o = g.head_order[q];
+        g.head_order[q] = g.head_order[q - 1];
+        g.head_order[q - 1] = o;
+      }
+  }
+  // The LDS-staged kernel where a chunk's tiles fit LDS.  A workgroup takes four trajectories (the rows
+  // it copies are long runs of memory), but with too few of them to give every CU a workgroup one.
   const int LW = cfg->T <= 32 ? 32 : 64;
-  const int NT = LW == 32 ? 128 : 256;
-  const int TPB = NT / LW;
+  // (32 steps, seven heads, whole call: 64 trajectories 12.0 against 12.7 us, 512 13.1 against 13.4,
+  // 1024 17.3 against 14.2)
+  const bool few = cfg->N < 1024;
+  const int TPB = few ? 1 : 4, S = LW * TPB;
   LdsPlan plan;
   plan.pitch = sumA | 1;
   plan.m_sumA = magic_of((uint32_t)sumA);
   plan.m_nh = magic_of((uint32_t)cfg->n_heads);
+  plan.m_row = magic_of((uint32_t)(TPB * sumA));
+  plan.m_row4 = magic_of((uint32_t)(TPB * sumA / 4));
+  plan.m_arow = magic_of((uint32_t)(TPB * cfg->n_heads));
   plan.vec4 = plan.pitch == sumA && (TPB * sumA) % 4 == 0 && ((size_t)cfg->N * sumA) % 4 == 0 &&
               ((uintptr_t)logits & 15) == 0 && (!dlogits_opt || ((uintptr_t)dlogits_opt & 15) == 0);
-  const size_t lds = sizeof(float) * NT * ((size_t)plan.pitch + 3 * (size_t)cfg->n_heads);
+  const size_t lds = sizeof(float) * ((size_t)S * (plan.pitch + 4 * (size_t)(cfg->n_heads | 1) + 1) + TPB * 4 + sumA);
+  constexpr size_t kMaxLds = 144 * 1024;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
-    attr_status = hipFuncSetAttribute((const void*)appo_traj_lds_kernel<32, 128>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-    if (attr_status == hipSuccess)
-      attr_status = hipFuncSetAttribute((const void*)appo_traj_lds_kernel<64, 256>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+    for (const void* k : {(const void*)appo_traj_lds_kernel<32, 4, 512>, (const void*)appo_traj_lds_kernel<32, 1, 256>,
+                          (const void*)appo_traj_lds_kernel<64, 4, 512>, (const void*)appo_traj_lds_kernel<64, 1, 256>})
+      if (attr_status == hipSuccess)
+        attr_status = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   });
   if (attr_status != hipSuccess) {
     set_error("%s: hipFuncSetAttribute failed: %s", fn, hipGetErrorString(attr_status));
     return SF_ERR_DEVICE;
   }
-  const unsigned blocks = (unsigned)((cfg->N + TPB - 1) / TPB);
-  if (lds <= 128 * 1024) {
-    if (LW == 32)
-      appo_traj_lds_kernel<32, 128><<<blocks, 128, lds, st>>>(g, plan);
+  unsigned n_partials = (unsigned)((cfg->N + TPB - 1) / TPB);
+  if (lds <= kMaxLds) {
+    if (LW == 32 && few)
+      appo_traj_lds_kernel<32, 1, 256><<<n_partials, 256, lds, st>>>(g, plan);
+    else if (LW == 32)
+      appo_traj_lds_kernel<32, 4, 512><<<n_partials, 512, lds, st>>>(g, plan);
+    else if (few)
+      appo_traj_lds_kernel<64, 1, 256><<<n_partials, 256, lds, st>>>(g, plan);
     else
-      appo_traj_lds_kernel<64, 256><<<blocks, 256, lds, st>>>(g, plan);
+      appo_traj_lds_kernel<64, 4, 512><<<n_partials, 512, lds, st>>>(g, plan);
   } else {
+    n_partials = (unsigned)cfg->N;
     appo_traj_kernel<<<(unsigned)((cfg->N + kTrajPerBlock - 1) / kTrajPerBlock), kLossThreads, 0, st>>>(g);
   }
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) {
-    appo_reduce_kernel<<<1, kReduceThreads, 0, st>>>(g.partials, cfg->N, 1.0f / ((float)cfg->T * (float)cfg->N),
+    appo_reduce_kernel<<<1, kReduceThreads, 0, st>>>(g.partials, (int)n_partials, 1.0f / ((float)cfg->T * (float)cfg->N),
                                             cfg->critic_coef, cfg->entropy_coef, loss);
     e = hipGetLastError();
   }

@@ -1,0 +1,34 @@
+"""The loss kernels at the edges of their dispatch: one and four trajectories per workgroup (from
+1024 trajectories on), ragged last workgroups, 32 and 64 lanes per trajectory with partial chunks,
+16-byte and element-wise gradients, heads in every order of size, tiles too large for LDS."""
+import numpy as np
+import pytest
+
+from paper_2006_11751_amd import workloads as wl
+from tests import parity
+from tests.test_gpu_loss import RTOL, _ratios, _run
+
+pytestmark = pytest.mark.gpu
+
+FULL = (3, 3, 2, 2, 2, 8, 21)
+CASES = [(FULL, 1, 1), (FULL, 32, 1023), (FULL, 32, 1024), (FULL, 31, 1027), (FULL, 33, 1026), (FULL, 65, 5),
+         ((21, 1, 8), 7, 1025), ((4, 4), 5, 1030), ((2,) * 16, 40, 3), ((500,), 3, 1024), ((1000, 23), 2, 3)]
+
+
+@pytest.mark.parametrize("heads,T,N", CASES, ids=["%s-%d-%d" % ("+".join(map(str, h)), t, n) for h, t, n in CASES])
+def test_shapes(torch_cuda, ref, heads, T, N):
+    hp = wl.loss_config(heads, T, N)
+    tr = wl.trajectories(hp, 6100)
+    g = _run(torch_cuda, hp, tr)
+    o = ref.appo_loss(hp, **tr)
+    for k in ("vs", "adv", "dvalues"):
+        parity.assert_close(k, g[k], o[k], RTOL)
+    scale = np.abs(o["loss"][:3]).max()
+    assert np.all(np.abs(g["loss"] - o["loss"]) <= RTOL * (np.abs(o["loss"]) + scale)), (g["loss"], o["loss"])
+    # (samples on a boundary of the clipping range may fall on either side in fp32)
+    r, clip = _ratios(hp, tr), float(np.float32(hp["clip"]))
+    sure = np.minimum(np.abs(r - clip), np.abs(r - 1.0 / clip)) > 1e-4
+    parity.assert_close("dlogits", g["dlogits"][sure], o["dlogits"][sure], RTOL)
+    again = _run(torch_cuda, hp, tr)
+    for k in ("vs", "adv", "dvalues", "dlogits", "loss"):
+        assert np.array_equal(g[k], again[k]), k
