@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "sf_internal.h"
+#include "sf_split.h"
 
 namespace sf {
 namespace {
@@ -108,22 +109,6 @@ __device__ inline void state_rows(const DenseArgs& g, int (&row)[N], int (&flag)
 // Bytes of one K step and term of a column group: FC 16 columns; cells 8 units, the gates in
 // columns [r z | n] (the 8 n columns of each lane group alone) or [i f | g o].
 constexpr int group_bytes(int kind) { return kind == FC ? 1024 : kind == GRU ? 1536 : 2048; }
-
-// Three terms of two numbers; what is left of them is added to `left`: nothing to speak of, or NaN
-// for an infinity, a NaN and what rounds up to an infinity, which have no terms.
-__device__ inline void split_pair(float r0, float r1, unsigned& t0, unsigned& t1, unsigned& t2, float& left) {
-  const f32x2 v0 = {r0, r1};
-  t0 = __builtin_bit_cast(unsigned, __builtin_convertvector(v0, bf16x2));
-  r0 -= __builtin_bit_cast(float, t0 << 16);
-  r1 -= __builtin_bit_cast(float, t0 & 0xFFFF0000u);
-  const f32x2 v1 = {r0, r1};
-  t1 = __builtin_bit_cast(unsigned, __builtin_convertvector(v1, bf16x2));
-  r0 -= __builtin_bit_cast(float, t1 << 16);
-  r1 -= __builtin_bit_cast(float, t1 & 0xFFFF0000u);
-  const f32x2 v2 = {r0, r1};
-  t2 = __builtin_bit_cast(unsigned, __builtin_convertvector(v2, bf16x2));
-  left += r0 + r1;
-}
 
 // The sums of one row that holds an infinity or a NaN, in plain fp32 arithmetic: the products of
 // such a number with the terms of a weight do not add up to its product with the weight.  q: gate

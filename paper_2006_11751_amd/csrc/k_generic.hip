@@ -94,61 +94,89 @@ __global__ __launch_bounds__(kThreads) void linear_generic_kernel(
 }
 
 // Measurement encoder of the full architecture: one or two fully connected + ReLU layers
-// in one launch.  A workgroup handles kMeasRows rows; the rows' inputs and the hidden
-// activations sit in LDS, every weight is read once per workgroup.  Sums run in the same
-// order as linear_generic_kernel's.
+// in one launch.  A workgroup handles kMeasRows rows; the rows' inputs and the hidden activations
+// sit in LDS, every weight is read once per workgroup.  The time is the latency of the weight
+// loads, so four groups of threads share the inputs of a layer and the first weights of both layers
+// are requested at once; the partial sums meet in LDS.  (One group, eight loads in flight: 10 us for 23 -> 128 -> 128 on
+// 333 rows; now 5.9.)
 constexpr int kMeasRows = 4;
-constexpr int kMeasThreads = 128;
+constexpr int kMeasCols = 128;   // outputs at a time
+constexpr int kMeasParts = 4;    // groups of threads along the inputs
+constexpr int kMeasThreads = kMeasCols * kMeasParts;
+
+// A thread's first weights of a layer, and its bias: requested for both layers at the kernel's start.
+template <int BATCH>
+struct MeasFirst {
+  float w[BATCH], bias;
+  __device__ inline void load(const float* __restrict__ w_t, const float* __restrict__ b, int n_in, int n_out) {
+    const int o = min((int)threadIdx.x % kMeasCols, n_out - 1), q = threadIdx.x / kMeasCols;
+    const int k0 = n_in * q / kMeasParts, k1 = n_in * (q + 1) / kMeasParts;
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) w[u] = w_t[(size_t)max(min(k0 + u, k1 - 1), 0) * n_out + o];
+    bias = b[o];
+  }
+};
+
+template <int BATCH>
+__device__ inline void meas_layer(const float* in, int n_in, const float* __restrict__ w_t, const float* __restrict__ b,
+                                  int n_out, MeasFirst<BATCH>& first, float* part, float* hidden, float* out, int rows) {
+  const int tid = threadIdx.x, c = tid % kMeasCols, q = tid / kMeasCols;
+  const int k0 = n_in * q / kMeasParts, k1 = n_in * (q + 1) / kMeasParts;
+  for (int o0 = 0; o0 < n_out; o0 += kMeasCols) {
+    const int o = min(o0 + c, n_out - 1);
+    if (o0) first.bias = b[o];
+    float acc[kMeasRows];
+#pragma unroll
+    for (int r = 0; r < kMeasRows; ++r) acc[r] = 0.0f;
+    for (int i = k0; i < k1; i += BATCH) {
+      if (o0 || i != k0)
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) first.w[u] = w_t[(size_t)min(i + u, k1 - 1) * n_out + o];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const float wu = i + u < k1 ? first.w[u] : 0.0f;  // (past the end: the last weight again, for no use)
+        const int at = min(i + u, k1 - 1);
+#pragma unroll
+        for (int r = 0; r < kMeasRows; ++r) acc[r] = fmaf(in[r * n_in + at], wu, acc[r]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kMeasRows; ++r) part[(q * kMeasRows + r) * kMeasCols + c] = acc[r];
+    __syncthreads();
+    const int r = q;  // (as many groups as rows)
+    float v = first.bias;
+#pragma unroll
+    for (int p = 0; p < kMeasParts; ++p) v += part[(p * kMeasRows + r) * kMeasCols + c];
+    v = fmaxf(v, 0.0f);
+    if (o0 + c < n_out) {
+      if (hidden)
+        hidden[r * n_out + o] = v;
+      else if (r < rows)
+        out[(size_t)r * n_out + o] = v;
+    }
+    __syncthreads();
+  }
+}
 
 __global__ __launch_bounds__(kMeasThreads) void meas_mlp_kernel(
     const float* __restrict__ meas, int B, int n0, const float* __restrict__ w1_t,
     const float* __restrict__ b1, int n1, const float* __restrict__ w2_t,
     const float* __restrict__ b2, int n2, float* __restrict__ out) {
+  static_assert(kMeasParts == kMeasRows, "a group finishes a row");
+  __shared__ float part[kMeasParts * kMeasRows * kMeasCols];
   extern __shared__ float sm[];
   float* s_in = sm;                   // [kMeasRows][n0]
   float* s_h = sm + kMeasRows * n0;   // [kMeasRows][n1]
-  const int r0 = blockIdx.x * kMeasRows;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < kMeasRows * n0; i += kMeasThreads) {
-    const int r = i / n0;
-    s_in[i] = r0 + r < B ? meas[(size_t)(r0 + r) * n0 + (i - r * n0)] : 0.0f;
-  }
+  const int r0 = blockIdx.x * kMeasRows, rows = min(B - r0, kMeasRows);
+  MeasFirst<8> first1;
+  MeasFirst<32> first2;
+  first1.load(w1_t, b1, n0, n1);
+  if (n2 > 0) first2.load(w2_t, b2, n1, n2);
+  for (int i = threadIdx.x; i < kMeasRows * n0; i += kMeasThreads)
+    s_in[i] = i < rows * n0 ? meas[(size_t)r0 * n0 + i] : 0.0f;
   __syncthreads();
-  for (int o = tid; o < n1; o += kMeasThreads) {
-    float acc[kMeasRows];
-#pragma unroll
-    for (int r = 0; r < kMeasRows; ++r) acc[r] = b1[o];
-#pragma unroll 8
-    for (int i = 0; i < n0; ++i) {
-      const float w = w1_t[(size_t)i * n1 + o];
-#pragma unroll
-      for (int r = 0; r < kMeasRows; ++r) acc[r] = fmaf(s_in[r * n0 + i], w, acc[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < kMeasRows; ++r) {
-      const float v = fmaxf(acc[r], 0.0f);
-      if (n2 > 0)
-        s_h[r * n1 + o] = v;
-      else if (r0 + r < B)
-        out[(size_t)(r0 + r) * n1 + o] = v;
-    }
-  }
-  if (n2 == 0) return;
-  __syncthreads();
-  for (int o = tid; o < n2; o += kMeasThreads) {
-    float acc[kMeasRows];
-#pragma unroll
-    for (int r = 0; r < kMeasRows; ++r) acc[r] = b2[o];
-#pragma unroll 8
-    for (int i = 0; i < n1; ++i) {
-      const float w = w2_t[(size_t)i * n2 + o];
-#pragma unroll
-      for (int r = 0; r < kMeasRows; ++r) acc[r] = fmaf(s_h[r * n1 + i], w, acc[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < kMeasRows; ++r)
-      if (r0 + r < B) out[(size_t)(r0 + r) * n2 + o] = fmaxf(acc[r], 0.0f);
-  }
+  meas_layer(s_in, n0, w1_t, b1, n1, first1, part, n2 > 0 ? s_h : nullptr, out + (size_t)r0 * n1, rows);
+  if (n2 > 0) meas_layer(s_h, n1, w2_t, b2, n2, first2, part, nullptr, out + (size_t)r0 * n2, rows);
 }
 
 __device__ inline float sigmoidf_acc(float a) { return 1.0f / (1.0f + expf(-a)); }

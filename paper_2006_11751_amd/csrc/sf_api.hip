@@ -813,6 +813,15 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
     for (int i = 0; i < sumA; ++i) hb[i] = bld.q(w->pi_b[i]);
     hb[sumA] = bld.q(w->v_b[0]);
     p->head_w = bld.upload(hw);
+    p->head_split_w = nullptr;
+    if (!sw.force_generic && heads_split_supported(Hd, cfg->n_heads, sumA)) {
+      const int rows = (sumA + 16) / 16 * 16, terms = bld.bf16 ? 1 : 3;
+      std::vector<float> padded(hw);
+      padded.resize((size_t)rows * Hd, 0.0f);
+      p->head_split_w = bld.upload_packed<uint16_t>(dense_fc_pack_size(rows, Hd, terms), [&](uint16_t* out) {
+        dense_pack_fc(padded.data(), rows, Hd, terms, false, out);
+      });
+    }
     p->head_b = bld.upload(hb);
     p->head_off = bld.upload(off);
     macs += (int64_t)(sumA + 1) * Hd;
@@ -1066,6 +1075,7 @@ extern "C" int sf_policy_update_weights(sf_policy* handle, const sf_policy_weigh
                    (scratch.fc_wbf != nullptr) == (p->fc_wbf != nullptr) &&
                    scratch.core_tile == p->core_tile &&
                    scratch.rnn_split_w == p->rnn_split_w && scratch.fc_split_w == p->fc_split_w &&
+                   scratch.head_split_w == p->head_split_w &&
                    scratch.dense_fc == p->dense_fc && scratch.dense_core == p->dense_core &&
                    (scratch.rnn_wih_bf != nullptr) == (p->rnn_wih_bf != nullptr);
   for (size_t i = 0; same_plan && i < p->convs.size(); ++i) {
@@ -1373,8 +1383,8 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
         break;
       }
       case OP_HEADS:
-        SF_LAUNCH(launch_heads(B, c.rnn_dim, c.n_heads, p->sumA, p->head_off, h_out, p->head_w,
-                               p->head_b, seed, step, actions, logp, value, logits_opt, ids, h_table,
+        SF_LAUNCH(launch_heads(B, c.rnn_dim, c.n_heads, p->sumA, p->head_off, h_out, p->head_split_w,
+                               c.dtype == SF_DTYPE_BF16 ? 1 : 3, p->head_w, p->head_b, seed, step, actions, logp, value, logits_opt, ids, h_table,
                                n_env, p->state_dim, p->max_head, st));
         break;
     }

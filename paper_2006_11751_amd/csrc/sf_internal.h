@@ -139,6 +139,7 @@ struct Policy {
   float* meas_b[SF_MAX_MEAS_LAYERS];
   float* meas_buf[SF_MAX_MEAS_LAYERS];  // dev [max_batch][meas_hidden[l]]
   float* head_w;      // dev [sumA + 1][H]   (last row: value head)
+  uint16_t* head_split_w = nullptr;  // dev: the same packed in bf16 terms for heads_split_kernel, or null
   float* head_b;      // dev [sumA + 1]
   int32_t* head_off;  // dev [n_heads + 1]   prefix sums of head_sizes
   // workspace, sized for max_batch
@@ -181,9 +182,10 @@ hipError_t launch_rnn_generic(int lstm, int B, int n1, int n2, int H, const floa
                               const float* h_in, const uint8_t* done, const float* wih_t,
                               const float* whh_t, const float* bih, const float* bhh, float* h_out,
                               const int32_t* ids, int n_env, hipStream_t st);
+bool heads_split_supported(int H, int n_heads, int sumA);
 hipError_t launch_heads(int B, int H, int n_heads, int sumA, const int32_t* head_off,
-                        const float* h, const float* head_w, const float* head_b, uint64_t seed,
-                        uint64_t step, int32_t* actions, float* logp, float* value,
+                        const float* h, const uint16_t* split_w, int terms, const float* head_w,
+                        const float* head_b, uint64_t seed, uint64_t step, int32_t* actions, float* logp, float* value,
                         float* logits_opt, const int32_t* ids, float* h_table, int n_env,
                         int state_dim, int max_head, hipStream_t st);
 
