@@ -165,12 +165,13 @@ __device__ inline void plain_sums(const DenseArgs& g, int m, bool reset, int n, 
   }
 }
 
-// DA, DB: K steps of rows / weights a wave has in flight.
+// DA, DB: K steps of rows / weights a wave has in flight; 1: in turn with a second workgroup of the CU.
 template <int KIND, int XT, int PB, int RT, int U, int DA, int DB, bool OUT16>
-__global__ __launch_bounds__(kThreads, 2) void dense_split_kernel(DenseArgs g) {
+__global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(DenseArgs g) {
   constexpr int GB = group_bytes(KIND);
   constexpr int NB = KIND == FC ? U : KIND == GRU ? U + 1 : 2 * U;  // weight tiles per K step and term
   constexpr int NA = KIND == FC ? U : KIND == GRU ? U + 2 : 2 * U;  // accumulators per row tile
+  constexpr bool LATE = DA == 1;
   constexpr int RR = RT * NA <= 8 ? RT : 8 / NA;                    // row tiles per round of the sum
   static_assert(RT % RR == 0, "whole rounds");
   constexpr int TURN = kWaves * 16 * RT * 36, RED = kWaves * RR * NA * 64 * 4;  // floats
@@ -234,7 +235,8 @@ __global__ __launch_bounds__(kThreads, 2) void dense_split_kernel(DenseArgs g) {
 #pragma unroll
     for (int t = 0; t < NA; ++t) acc[r][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // What the gates need from memory, requested behind the first operands.  Thread -> (element of four
+  // What the gates need from memory, requested behind the first operands (LATE: behind the last, for
+  // want of registers).  Thread -> (element of four
   // neighbouring outputs, row, four outputs); EPT such elements of a round's row tiles
   constexpr int ET = 16 * 8 * U;               // cells: threads per row tile
   const int er = tid & 3, erow = (tid >> 2) & 15, eq = (tid >> 6) & (2 * U - 1), ert = tid / ET;
@@ -389,7 +391,7 @@ __global__ __launch_bounds__(kThreads, 2) void dense_split_kernel(DenseArgs g) {
   // the loads, then come the last DA without loads.
   auto phase = [&](auto f32c, int s0, int s1) __attribute__((always_inline)) {
     if (s0 >= s1) {
-      if (XT == X_F32) load_gates();
+      if (XT == X_F32 && !LATE) load_gates();
       return;
     }
     auto step = [&](auto slota, auto slotb, int s) __attribute__((always_inline)) {
@@ -403,7 +405,7 @@ __global__ __launch_bounds__(kThreads, 2) void dense_split_kernel(DenseArgs g) {
       load_a(f32c, i, s + I);
       if constexpr (I < DB) load_b(i, s + I);
     });
-    if (XT == X_F32) load_gates();
+    if (XT == X_F32 && !LATE) load_gates();
     for (; s + DA < s1; s += DA)
       each([&](auto i) __attribute__((always_inline)) {
         constexpr int I = decltype(i)::value;
@@ -419,7 +421,7 @@ __global__ __launch_bounds__(kThreads, 2) void dense_split_kernel(DenseArgs g) {
       if constexpr (I + DB < DA) load_b(SB{}, s + I + DB);
     });
   };
-  if (XT != X_F32) load_gates();
+  if (XT != X_F32 && !LATE) load_gates();
   if (XT == X_F32) {
     phase(std::true_type{}, s_begin, s_end);
   } else {
@@ -427,6 +429,7 @@ __global__ __launch_bounds__(kThreads, 2) void dense_split_kernel(DenseArgs g) {
     if (KIND != FC) phase(std::true_type{}, max(s_begin, g.k1), s_end);
   }
   if (KIND == GRU && s_end <= g.k2) move_n();
+  if (LATE) load_gates();
   // The eight partial sums, RR row tiles at a time, added in wave order.
 #pragma unroll
   for (int rd = 0; rd < RT / RR; ++rd) {
@@ -623,7 +626,7 @@ __global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
     uint8_t* dst = lds + buf * BUF;
     const int ks = (tid & 31) >> 3, kg = (tid & 7) >> 1, hf = tid & 1;
     uint8_t* at = dst + ks * (NP * 1024) + slot_of(tid >> 5, ks, kg) * 16 + hf * 8 + j * KW * (NP * 1024);
-    const unsigned keep = (c >= c2) & (dn[j] != 0) ? 0u : ~0u;
+    const unsigned keep = ((c >= c2) & (dn[j] != 0)) ? 0u : ~0u;
     u32x2 t[3];
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
@@ -818,16 +821,26 @@ long long split_workgroups(long long M, int n_col, int rt, int u) {
 //    256  11.8 / 21.2  9.8 / 16.6 10.9 /  9.5 18.8 / 15.4
 //    512  24.0 / 40    16  / 32   12.3 / 18   19   / 16
 //   1024  62   / 85    35  / 68   25   / 38   23   / 35
-// The bits of a result do not depend on it.
+// Beyond one round two workgroups of the 32 x 2 tile share a CU (DA = DB = 1, 128 registers), so that
+// one's loads run behind the other's products.  Launch times (us, the launch's own few included)
+// against the tile that was there, one workgroup per CU with two or three steps in flight:
+//   FC in fp32, 600 / 1024 / 2048 rows: 24 -> 21.5, 26.8 -> 24.6, 47 -> 46 (was 64 x 2)
+//   GRU 512 -> 512 in fp32, 333 / 512 rows: 21.4 -> 19.8, 22.6 -> 21.3; LSTM equal
+//   GRU 512 -> 512 in bf16, 512 rows: 16.5 -> 13.3
+//   GRU 256 -> 256 on 16-bit features, 512 / 1000 rows: 9.4 -> 8.6, 14.0 -> 11.4
+// Within one round it is worse in fp32 (GRU at 160 rows 14.1 against 12.9), better for cells in 16 bits
+// (the figure at 512 rows is one).  FC rows in 16 bits keep 64 x 2.
+// The bits of a result do not depend on any of this.
 template <int KIND, int XT, int PB, bool OUT16>
 hipError_t launch_kind(const DenseArgs& g, hipStream_t st) {
   const int n_col = KIND == FC ? g.N / 16 : g.H / 8;
+  const bool one_round = split_workgroups(g.M, n_col, 2, 2) <= 256;
   if (split_workgroups(g.M, n_col, 1, 1) <= 256) return launch_cfg<KIND, XT, PB, 1, 1, 4, 4, OUT16>(g, st);
   if (split_workgroups(g.M, n_col, 2, 1) <= 256) return launch_cfg<KIND, XT, PB, 2, 1, 3, 3, OUT16>(g, st);
-  // (a cell of 64 rows does not fit the registers)
-  if (KIND != FC || split_workgroups(g.M, n_col, 2, 2) <= 256) return launch_cfg<KIND, XT, PB, 2, 2, 2, 2, OUT16>(g, st);
-  if constexpr (KIND == FC) return launch_cfg<KIND, XT, PB, 4, 2, 3, 3, OUT16>(g, st);
-  return hipErrorInvalidValue;
+  if constexpr (KIND == FC || PB == 3)
+    if (one_round) return launch_cfg<KIND, XT, PB, 2, 2, 2, 2, OUT16>(g, st);
+  if constexpr (KIND == FC && XT != X_F32) return launch_cfg<KIND, XT, PB, 4, 2, 3, 3, OUT16>(g, st);
+  else return launch_cfg<KIND, XT, PB, 2, 2, 1, 1, OUT16>(g, st);
 }
 
 // Packing runs at every weight update, 24 results per eight weights: two builds of the loops, the
@@ -918,10 +931,9 @@ bool dense_cell_supported(int I1, int I2, int H) {
 // 8192 rows 62 against 45.
 bool dense_fc_small(int M, int N) { return split_workgroups(M, N / 16, 4, 2) <= 512; }
 // Cells: up to two rounds of the 32-row tile.  Beyond, cell_tile_kernel in fp32 (GRU 512 -> 512 at
-// 512 rows 18 against 21 us, at 1024 rows 38 against 25) and k_rnn_bf16.hip in bf16 (at 512 rows 12
-// against 20 us, at 1024 rows 24 against 21; 256 -> 256 at 1024 rows 10 against 14, at 2048 20
-// against 17).  The kernels' sums run in different orders, so that this is settled once, by the
-// largest batch.
+// 512 rows 17.5 against 21 us, at 1024 rows 38 against 25) and k_rnn_bf16.hip in bf16 (at 512 rows 10
+// against 20 us, at 1024 rows 24 against 21; 256 -> 256 at 1000 rows 8 against 14).  The kernels'
+// sums run in different orders, so that this is settled once, by the largest batch.
 bool dense_cell_small(int M, int H) { return split_workgroups(M, H / 8, 2, 2) <= 512; }
 bool dense_cell_tile_supported(int I1, int I2, int H) {
   return I1 > 0 && (I1 % 128) == 0 && (I2 % 128) == 0 && H > 0 && (H % 128) == 0;
