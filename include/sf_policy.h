@@ -174,14 +174,15 @@ int sf_policy_create(const sf_policy_config* cfg, const sf_policy_weights* weigh
  * network runs the layer on the fp32 matrix cores (about three times slower for that
  * launch) and a bf16 network takes the third digit plane.  The decision depends on the
  * parameter values only, never on the batch.  sf_policy_op_pipe tells which arithmetic a
- * launch uses ("i8x3", "i8x2", "f32", "bf16", "f16", "valu"); ..._ratio returns the worst
+ * launch uses ("i8x3", "i8x2", "f32", "bf16", "f16", "valu"; "f16x2": fp32 operands in two
+ * scaled fp16 terms, "bf16x3": in three bf16 terms); ..._ratio returns the worst
  * channel's E_fix / E_ref for 2 or 3 planes (0 if the layer has another shape, -1 for a
  * null handle). */
 const char* sf_policy_op_pipe(const sf_policy* p, int i); /* static storage; "" if out of range */
 /* The kernel family launch i runs, for tests and benchmarks that must know which code path a
  * shape took: one of "generic", "conv1_mfma", "gemm_mfma", "conv1_i8", "conv_bf16",
  * "conv3x3_u8", "conv3x3_patch", "conv3x3_stem", "conv3x3_pool", "stem_pool", "conv_pool_regs", "res_block",
- * "res_stage", "conv_image_bf16", "conv12_fused" for a convolution launch, and "pool", "fc",
+ * "res_stage", "conv_image_bf16", "conv_image_split", "conv12_fused" for a convolution launch, and "pool", "fc",
  * "meas", "rnn", "heads" for the others.  Static storage; "" if out of range or null. */
 const char* sf_policy_op_kernel(const sf_policy* p, int i);
 double sf_policy_conv1_fixed_point_ratio(const sf_policy* p, int planes);
@@ -283,10 +284,11 @@ int sf_policy_unroll(sf_policy* p, int32_t T, int32_t N, const uint8_t* obs, con
  * waits for the previous update's copies.  The whole set is packed and checked before the
  * first copy is enqueued: after an error other than SF_ERR_DEVICE the policy still holds its
  * previous parameters.  The kernels are those chosen at create (environment switches are not
- * read again), with one exception: the first convolution's admission test (see
- * sf_policy_op_pipe) is repeated on the new values, and later steps run the arithmetic it
- * selects.  A HIP graph captured before the update keeps the kernel it recorded, which then
- * reads the new bank of its own kind: capture again if the selection changed.
+ * read again), with one exception: the admission tests of the convolutions' fixed-point and
+ * split arithmetic (see sf_policy_op_pipe) are repeated on the new values, and later steps run
+ * what they select.  A HIP graph captured before the update keeps the kernels it recorded,
+ * which then read the new bank of their own kind: capture again if the selection changed (a
+ * layer captured as "f16x2" and no longer admitted computes in fp32 by itself, slowly).
  * Errors: SF_ERR_ARG (null handle or weight pointer), SF_ERR_OOM (staging area),
  * SF_ERR_DEVICE, SF_ERR_SHAPE (internal mismatch). */
 int sf_policy_update_weights(sf_policy* p, const sf_policy_weights* weights, void* hip_stream);

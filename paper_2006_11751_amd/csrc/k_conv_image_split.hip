@@ -58,7 +58,8 @@ constexpr size_t kMaxLds = 80 * 1024;  // two workgroups per CU
 struct SplitArgs {
   const f32x4* in;      // [B][H][W][CIN]
   const u32x4* wpk;     // [N/16][G][2][64] lane operands, G = KS*KS*CIN/32
-  const float* scale;   // [CIN] input scales, [N] inverse output scales
+  const float* scale;   // [CIN] input scales, [N] inverse output scales, 1 if the split is not admitted
+  const float* w32;     // [N][KS][KS][CIN]
   const float* bias;    // [N]
   float* out;           // [B][Ho*Wo][N]
   int B, H, W, Ho, Wo, N;
@@ -97,6 +98,7 @@ __global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
   const f32x4 scale = *(const f32x4*)(g.scale + (tid % C4) * 4);  // (a thread's pieces: the same channels)
   const f32x4 inv = *(const f32x4*)(g.scale + CIN + n0 + 4 * lg);
   const f32x4 bias = *(const f32x4*)(g.bias + n0 + 4 * lg);
+  const float refused = g.scale[CIN + g.N];
 
   // this lane's pixel of a tile: LDS piece of its window's first pixel (past the end: the last
   // pixel again, computed and stored again with the same bits)
@@ -146,6 +148,7 @@ __global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
       }
     }
     __syncthreads();
+    asm volatile("" ::"s"(refused));  // (requested with the scales, here long since)
 
     float* dst = g.out + (size_t)it * FR * npix * g.N + n0 + 4 * lg;
     const int live = frames * npix;
@@ -196,6 +199,27 @@ __global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
     tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, MP>{});
     if constexpr (MT > MP) tiles(std::integral_constant<int, MP>{}, std::integral_constant<int, MT - MP>{});
     __syncthreads();  // every wave is done with this round's images
+  }
+  // The host launches this kernel while the split is admitted; a graph recorded then may run it after
+  // an update that is not, and gets the layer by its definition in fp32 (slow, every wave its own
+  // outputs once more).
+  if (__builtin_expect(refused != 0.0f, 0)) {
+    __syncthreads();
+    for (int it = blockIdx.x; it < n_rounds; it += gridDim.x) {
+      const int todo = min(g.B - it * FR, FR) * npix * 16;
+#pragma unroll 1
+      for (int i = lane; i < todo; i += 64) {
+        const int n = n0 + (i & 15), at = i >> 4, fr = at / npix, pix = at % npix, oy = pix / g.Wo, ox = pix % g.Wo;
+        const float* x = (const float*)g.in +
+                         (((size_t)(it * FR + fr) * g.H + oy * STRIDE) * g.W + ox * STRIDE) * CIN;
+        const float* w = g.w32 + (size_t)n * (KS * KS * CIN);
+        float sum = 0.0f;
+#pragma unroll 1
+        for (int k = 0; k < KS * KS * CIN; ++k)
+          sum = fmaf(x[(size_t)(k / (KS * CIN)) * g.W * CIN + k % (KS * CIN)], w[k], sum);
+        g.out[((size_t)it * FR * npix + at) * g.N + n] = fmaxf(sum + g.bias[n], 0.0f);
+      }
+    }
   }
 }
 
@@ -327,7 +351,7 @@ void conv_activation_range(const float* w, const float* bias, int cout, int cin,
 // Weights in operand order, [N/16][G][2][64][8] fp16 bits: lane l of tap group gi holds, for e =
 // 0..7, both terms of W[16 nt + l%16][c = 32 half + 8 (l/16) + e][p][q], gi = (p k + q)(cin/32) +
 // half, times 2^(e_in[c]) and the output channel's scale; scale: [cin] input scales, [cout] inverse
-// output scales.  bound, mean_sq: of the input channels.
+// output scales, 0 or (not admitted) 1.  bound, mean_sq: of the input channels.
 // Returns the admission ratio: the largest over the output channels of
 //     (what the fixed part of the splitting errors, 2^-40 of an input bound and 2^-39 of the largest
 //      folded weight, can add up to)
@@ -336,9 +360,9 @@ void conv_activation_range(const float* w, const float* bias, int cout, int cin,
 // the split runs where it is <= 1.  (Infinite or NaN bounds give a ratio that is not <= 1.)
 double conv_image_split_pack(const float* w, int cout, int cin, int k, const std::vector<double>& bound,
                              const std::vector<double>& mean_sq, std::vector<uint16_t>& wpk, std::vector<float>& scale) {
-  const int halves = cin / 32, kk = k * k, G = kk * halves, K = cin * kk;
+  const int halves = cin / 32, kk = k * k, K = cin * kk;
   wpk.assign((size_t)cout * K * 2, 0);
-  scale.assign(cin + cout, 1.0f);
+  scale.assign(cin + cout + 1, 1.0f);
   std::vector<double> fold(cin);  // 1 / input scale
   for (int c = 0; c < cin; ++c) {
     const int e = power(bound[c]);
@@ -369,18 +393,19 @@ double conv_image_split_pack(const float* w, int cout, int cin, int k, const std
     if (top > 0.0) worst = fmax(worst, ref > 0.0 ? fixed / ref : INFINITY);
     (host_f16c() ? pack_channel_f16c : pack_channel_plain)(wn, n, kk, halves, fold.data(), up, wpk.data());
   }
+  scale[cin + cout] = worst <= 1.0 ? 0.0f : 1.0f;
   return worst;
 }
 
-// in [B][H][W][Cin] fp32 -> out [B][Ho*Wo][N] fp32, ReLU'd.
+// in [B][H][W][Cin] fp32; w32 the fp32 weights [N][k][k][Cin] -> out [B][Ho*Wo][N] fp32, ReLU'd.
 // Launch times (us) against k_gemm_mfma.hip, conv2 / conv3 of the standard network: 16 rows 6.8 / 4.7
 // (7.2 / 7.6), 333 rows 13.7 / 9.2 (26 / 16), 1024 rows 27 / 15 (72 / 34), 2048 rows 50 / 26
 // (126 / 57).  At 1024 rows conv2 reads 70 MB and writes 26: 3.5 TB/s.
-hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const float* scale, const float* bias,
-                                   float* out, int B, int H, int W, int Cin, int ksize, int N, hipStream_t st) {
+hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const float* scale, const float* w32,
+                                   const float* bias, float* out, int B, int H, int W, int Cin, int ksize, int N, hipStream_t st) {
   if (B == 0) return hipSuccess;
   SplitArgs g;
-  g.in = (const f32x4*)in; g.wpk = (const u32x4*)wpk; g.scale = scale; g.bias = bias; g.out = out;
+  g.in = (const f32x4*)in; g.wpk = (const u32x4*)wpk; g.scale = scale; g.w32 = w32; g.bias = bias; g.out = out;
   g.B = B; g.H = H; g.W = W; g.Ho = (H - ksize) / 2 + 1; g.Wo = (W - ksize) / 2 + 1; g.N = N;
   g.row_pad = g.frame_pad = 0;
   switch (variant(Cin, ksize, 2, 0, H, W, N)) {

@@ -128,14 +128,6 @@ struct Builder {
     return d;
   }
 
-  // Room for n elements without their values: a bank that the present parameters do not use (a weight
-  // update may come to use it).
-  template <typename T>
-  T* reserve(size_t n) {
-    if (!target) p->upload_bytes += n * sizeof(T) + 16;
-    return (T*)dev_alloc(n * sizeof(T));
-  }
-
   float q(float v) const { return bf16 ? bf16_round(v) : v; }
 
   // [cout][cin][k][k] -> [k][k][cin][cout]
@@ -469,7 +461,7 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
         if (!bld.bf16 && relu_out && sw.gemm_tile == 0 && !sw.no_conv_image &&
             conv_image_split_supported(C, k, s, pad, H, W, cout)) {
           // Whether the layer may split its operands depends on the parameter values, and a weight
-          // update may change it: there is room for both banks.
+          // update may change it: both banks are packed, for launches that a graph has recorded.
           std::vector<uint16_t> wt;
           std::vector<float> sc;
           const double ratio = conv_image_split_pack(w->conv_w[ti], cout, C, k, act_bound, act_mean_sq, wt, sc);
@@ -477,19 +469,15 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
           L.ssc = bld.upload(sc);
           if (ratio <= 1.0) L.impl = CONV_IMAGE_SPLIT;
         }
-        if (L.impl == CONV_IMAGE_SPLIT) {
-          L.wpk = bld.reserve<float>(n_w);
-        } else {
-          // [cout][cin][k][k] -> [cout][k][k][cin]: K ordered (filter row, filter column, channel)
-          std::vector<float> t(n_w);
-          for (int o = 0; o < cout; ++o)
-            for (int c2 = 0; c2 < C; ++c2)
-              for (int a = 0; a < k; ++a)
-                for (int b2 = 0; b2 < k; ++b2)
-                  t[(((size_t)o * k + a) * k + b2) * C + c2] =
-                      bld.q(w->conv_w[ti][(((size_t)o * C + c2) * k + a) * k + b2]);
-          L.wpk = bld.upload(t);
-        }
+        // [cout][cin][k][k] -> [cout][k][k][cin]: K ordered (filter row, filter column, channel)
+        std::vector<float> t(n_w);
+        for (int o = 0; o < cout; ++o)
+          for (int c2 = 0; c2 < C; ++c2)
+            for (int a = 0; a < k; ++a)
+              for (int b2 = 0; b2 < k; ++b2)
+                t[(((size_t)o * k + a) * k + b2) * C + c2] =
+                    bld.q(w->conv_w[ti][(((size_t)o * C + c2) * k + a) * k + b2]);
+        L.wpk = bld.upload(t);
         L.bpk = L.bias;
       }
       if (in_buf < 0 && allow_mfma && conv1_i8_supported(L) && conv1_mfma_supported(L)) {
@@ -1264,8 +1252,8 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
                                        op.conv + 1, st));
             break;
           case CONV_IMAGE_SPLIT:
-            SF_LAUNCH(launch_conv_image_split((const float*)in, L.wsp, L.ssc, L.bias, buf(op.out_buf), B, L.H, L.W,
-                                              L.cin, L.k, L.cout, st));
+            SF_LAUNCH(launch_conv_image_split((const float*)in, L.wsp, L.ssc, L.wpk, L.bias, buf(op.out_buf), B, L.H,
+                                              L.W, L.cin, L.k, L.cout, st));
             break;
           case CONV_IMAGE_BF16:
             SF_LAUNCH(launch_conv_image_bf16(in, L.wbf, L.bbf, buf(op.out_buf), B, L.H, L.W, L.cin,

@@ -296,8 +296,9 @@ void conv_activation_range(const float* w, const float* bias, int cout, int cin,
                            std::vector<double>& mean_sq);
 double conv_image_split_pack(const float* w, int cout, int cin, int k, const std::vector<double>& bound,
                              const std::vector<double>& mean_sq, std::vector<uint16_t>& wpk, std::vector<float>& scale);
-hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const float* scale, const float* bias,
-                                   float* out, int B, int H, int W, int Cin, int ksize, int N, hipStream_t st);
+hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const float* scale, const float* w32,
+                                   const float* bias, float* out, int B, int H, int W, int Cin, int ksize, int N,
+                                   hipStream_t st);
 bool gemm_mfma_supported(int Cin, int ksize, int pad, int N);
 int gemm_mfma_pick_tile(long long M, int N, int K, int seg_len);
 hipError_t launch_gemm_mfma(const float* A, const float* Wt, const float* bias, float* out, int B,

@@ -86,3 +86,37 @@ def test_admission_follows_the_parameters(torch_cuda, ref):
     for k in first:
         assert np.array_equal(first[k], again[k]), k
     pol.close()
+
+
+@pytest.mark.parametrize("factor", [-110, 110])
+def test_recorded_step_after_an_update(torch_cuda, ref, factor):
+    """A graph keeps its kernels: recorded with the split admitted and replayed with parameters for
+    which it is not (factor < 0: the other way round), it computes the new parameters' network."""
+    torch = torch_cuda
+    net = _net()
+    w = wl.weights(net)
+    huge = {k: [a.copy() for a in v] if isinstance(v, list) else v.copy() for k, v in w.items()}
+    huge["conv_w"][0] *= np.float32(2.0 ** 110)
+    huge["conv_b"][0] *= np.float32(2.0 ** 110)
+    huge["conv_w"][1] *= np.float32(2.0 ** -110)
+    before, after = (w, huge) if factor > 0 else (huge, w)
+    B = 37
+    pol = binding.Policy(net, before, max_batch=B)
+    o_, s_, d_ = wl.observations(net, 0, B), wl.initial_state(net, B), wl.done_mask(net, 0, B)
+    obs, st, dn = (torch.from_numpy(a).cuda() for a in (o_, s_, d_))
+    out = pol.step(obs, st, dn, 7, 11)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pol.step(obs, st, dn, 7, 11, out=out, stream=torch.cuda.current_stream())
+    pol.update_weights(after)
+    torch.cuda.synchronize()
+    want = ref.policy_step(net, after, o_, s_, d_, 7, 11)
+    for _ in range(3):
+        for v in out.values():
+            v.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in ("logits", "value", "h_out"):
+            parity.assert_close(k, out[k].cpu().numpy(), want[k], 1e-4)
+    pol.close()
