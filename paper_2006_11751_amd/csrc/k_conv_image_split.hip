@@ -99,6 +99,7 @@ __global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
   const f32x4 inv = *(const f32x4*)(g.scale + CIN + n0 + 4 * lg);
   const f32x4 bias = *(const f32x4*)(g.bias + n0 + 4 * lg);
   const float refused = g.scale[CIN + g.N];
+  const int wave_n0 = __builtin_amdgcn_readfirstlane(n0);  // (kept in a scalar register for the fallback)
 
   // this lane's pixel of a tile: LDS piece of its window's first pixel (past the end: the last
   // pixel again, computed and stored again with the same bits)
@@ -205,11 +206,12 @@ __global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
   // outputs once more).
   if (__builtin_expect(refused != 0.0f, 0)) {
     __syncthreads();
+    const int fallback_lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     for (int it = blockIdx.x; it < n_rounds; it += gridDim.x) {
       const int todo = min(g.B - it * FR, FR) * npix * 16;
 #pragma unroll 1
-      for (int i = lane; i < todo; i += 64) {
-        const int n = n0 + (i & 15), at = i >> 4, fr = at / npix, pix = at % npix, oy = pix / g.Wo, ox = pix % g.Wo;
+      for (int i = fallback_lane; i < todo; i += 64) {
+        const int n = wave_n0 + (i & 15), at = i >> 4, fr = at / npix, pix = at % npix, oy = pix / g.Wo, ox = pix % g.Wo;
         const float* x = (const float*)g.in +
                          (((size_t)(it * FR + fr) * g.H + oy * STRIDE) * g.W + ox * STRIDE) * CIN;
         const float* w = g.w32 + (size_t)n * (KS * KS * CIN);
