@@ -17,6 +17,8 @@
  * sf_policy_step is a pure function of (weights, obs, h_in, done, seed, step):
  * row b of every output depends on row b of the inputs and on b itself (the
  * sampler's counter word) only, and is bitwise reproducible from call to call.
+ * (Some kernels are chosen at create by max_batch: handles of different max_batch may
+ * add the same sums in another order.)
  *
  * Conventions
  *   - every function returns an int status (SF_OK or a negative SF_ERR_*),

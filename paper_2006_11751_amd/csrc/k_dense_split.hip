@@ -8,8 +8,11 @@
 // with fp32 accumulators, smallest products first: 16 times the rate of the fp32 matrix
 // instructions, over six products.  One instruction adds 32 terms to an accumulator, so a sum is
 // rounded 6 times per 32 terms instead of 16 times and comes out nearer to the exact one.  In
-// bf16 configurations the weights are bf16 numbers (one term), the features of the plain stack too
-// (one product), and the state enters with all three terms (three products).
+// bf16 configurations the weights are bf16 numbers (one term), and the state enters with all three
+// terms (three products).  The features are activations of 16 bits there: in the step they are
+// bf16 numbers (one product), as they come from the FC layer or rounded here (X_ROUND), as
+// k_rnn_bf16.hip, which takes larger batches, rounds them; in the pass over trajectories fp32
+// features keep all their bits.
 //
 // Work split.  What bounds these layers is getting the operands into the registers: with few rows
 // the latency of a chain of loads, with many the path from the L2.  So there is no barrier in the K
@@ -48,7 +51,7 @@ constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 
 enum Kind { FC = 0, GRU = 1, LSTM = 2 };
-enum XType { X_F32 = 0, X_BF16 = 1, X_F16 = 2 };
+enum XType { X_F32 = 0, X_BF16 = 1, X_F16 = 2, X_ROUND = 3 };  // X_ROUND: fp32, one bf16 term is used
 
 __device__ inline float sigmoid_acc(float a) { return 1.0f / (1.0f + expf(-a)); }
 // (1 - e) / (1 + e) with e = exp(-2|a|), sign restored: e <= 1, nothing overflows
@@ -110,6 +113,8 @@ __device__ inline void state_rows(const DenseArgs& g, int (&row)[N], int (&flag)
 // columns [r z | n] (the 8 n columns of each lane group alone) or [i f | g o].
 constexpr int group_bytes(int kind) { return kind == FC ? 1024 : kind == GRU ? 1536 : 2048; }
 
+constexpr bool in_f32(int xt) { return xt == X_F32 || xt == X_ROUND; }
+
 // The sums of one row that holds an infinity or a NaN, in plain fp32 arithmetic: the products of
 // such a number with the terms of a weight do not add up to its product with the weight.  q: gate
 // (FC: 0), n: unit (FC: output); the n gate of a GRU has its sums over the features (n_x) and the
@@ -123,7 +128,7 @@ __device__ float plain_sum(const DenseArgs& g, int m, int sm, bool reset, int q,
     const int s = k >> 5, lg = (k >> 3) & 3, e = k & 7;
     float x;
     if (s < g.k1) {
-      if (XT == X_F32)
+      if (in_f32(XT))
         x = ((const float*)g.x1)[(size_t)m * g.I1 + k];
       else if (XT == X_BF16)
         x = __builtin_bit_cast(float, (unsigned)((const uint16_t*)g.x1)[(size_t)m * g.I1 + k] << 16);
@@ -134,6 +139,7 @@ __device__ float plain_sum(const DenseArgs& g, int m, int sm, bool reset, int q,
     } else {
       x = reset ? 0.0f : g.h_in[(size_t)sm * g.S + (k - 32 * g.k2)];
     }
+    if (XT == X_ROUND && s < g.k2) x = (float)(__bf16)x;
     int slot;
     if (KIND == FC)
       slot = lg * 16 + n % C;
@@ -172,6 +178,7 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
   constexpr int NB = KIND == FC ? U : KIND == GRU ? U + 1 : 2 * U;  // weight tiles per K step and term
   constexpr int NA = KIND == FC ? U : KIND == GRU ? U + 2 : 2 * U;  // accumulators per row tile
   constexpr bool LATE = DA == 1;
+  constexpr int R16 = 0, R32 = 1, R32_ONE = 2;                      // kinds of rows of a K step: see load_a
   constexpr int RR = RT * NA <= 8 ? RT : 8 / NA;                    // row tiles per round of the sum
   static_assert(RT % RR == 0, "whole rounds");
   constexpr int TURN = kWaves * 16 * RT * 36, RED = kWaves * RR * NA * 64 * 4;  // floats
@@ -203,14 +210,14 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
   // Row indices of this lane's loads (past the end: the last row again, never stored).
   constexpr int NL = 2 * RT;                       // loads per K step of fp32 rows
   if (tid < 16 * RT) odd_row[tid] = 0;
-  int xm[NL], hm[NL], dn[NL] = {}, xm16[XT == X_F32 ? 1 : RT];
+  int xm[NL], hm[NL], dn[NL] = {}, xm16[in_f32(XT) ? 1 : RT];
 #pragma unroll
   for (int j = 0; j < NL; ++j) {
     xm[j] = hm[j] = min(row0 + 8 * j + (lane >> 3), g.M - 1);
     if (KIND != FC) dn[j] = g.done[xm[j]];
   }
   if (KIND != FC) state_rows(g, hm, dn);
-  if (XT != X_F32)
+  if (!in_f32(XT))
 #pragma unroll
     for (int j = 0; j < RT; ++j) xm16[j] = min(row0 + 16 * j + (lane >> 2), g.M - 1);
   // this lane's place in the weights of a K step: tile t, lane offset
@@ -277,19 +284,20 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
 #pragma unroll
       for (int t = 0; t < NB; ++t) b[SL][p][t] = *(const u32x4*)(wp + (woff[t] + p * GB));
   };
-  // F32: one of the fp32 pieces (the row pitches are whole K steps), else 16-bit features.
+  // Rows as 16-bit features, or one of the fp32 pieces (the row pitches are whole K steps) with all
+  // terms or with one.
   // (selects, not branches: a branch around a load makes the compiler wait for all loads where
   // the paths join)
-  auto load_a = [&](auto f32c, auto slotc, int s) __attribute__((always_inline)) {
+  auto load_a = [&](auto kindc, auto slotc, int s) __attribute__((always_inline)) {
     constexpr int SL = decltype(slotc)::value;
     s = max(min(s, s_end - 1), 0);
-    if constexpr (decltype(f32c)::value) {
+    if constexpr (decltype(kindc)::value != R16) {
       const uint8_t* base = (const uint8_t*)g.x1 + (size_t)s * 128;
       uint32_t pitch = (uint32_t)g.I1 >> 5;
       if (KIND != FC) {
-        base = XT == X_F32 && s < g.k1 ? base : (s < g.k2 ? (const uint8_t*)g.x2 + (size_t)(s - g.k1) * 128
+        base = in_f32(XT) && s < g.k1 ? base : (s < g.k2 ? (const uint8_t*)g.x2 + (size_t)(s - g.k1) * 128
                                                           : (const uint8_t*)g.h_in + (size_t)(s - g.k2) * 128);
-        pitch = (uint32_t)(XT == X_F32 && s < g.k1 ? g.I1 : s < g.k2 ? g.I2 : g.S) >> 5;
+        pitch = (uint32_t)(in_f32(XT) && s < g.k1 ? g.I1 : s < g.k2 ? g.I2 : g.S) >> 5;
       }
       base += (lane & 7) * 16;
 #pragma unroll
@@ -309,13 +317,13 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
     else
       c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
   };
-  // one K step, rows in fp32 or (F32 false) in 16 bits
+  // one K step
   constexpr int P32 = 36, P16 = 20;  // pitch of a row in LDS (floats): 16-byte accesses without conflicts
   float left[RT] = {};
   float* turn = lds + wave * (16 * RT * P32);
-  auto use = [&](auto f32c, auto slota, auto slotb, bool state) __attribute__((always_inline)) {
+  auto use = [&](auto kindc, auto slota, auto slotb, bool state) __attribute__((always_inline)) {
     constexpr int SA = decltype(slota)::value, SB = decltype(slotb)::value;
-    constexpr bool F32 = decltype(f32c)::value;
+    constexpr bool F32 = decltype(kindc)::value != R16, TERMS = decltype(kindc)::value == R32;
     if constexpr (F32) {
 #pragma unroll
       for (int j = 0; j < NL; ++j) {
@@ -338,8 +346,14 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
         const f32x4 v1 = *(const f32x4*)(turn + (16 * r + li) * P32 + lg * 8 + 4);
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
+          const float e0 = p < 2 ? v0[2 * p] : v1[2 * p - 4], e1 = p < 2 ? v0[2 * p + 1] : v1[2 * p - 3];
+          if constexpr (!TERMS) {
+            const f32x2 e = {e0, e1};
+            x[0][p] = __builtin_bit_cast(unsigned, __builtin_convertvector(e, bf16x2));
+            continue;
+          }
           unsigned t0, t1, t2;
-          split_pair(p < 2 ? v0[2 * p] : v1[2 * p - 4], p < 2 ? v0[2 * p + 1] : v1[2 * p - 3], t0, t1, t2, left[r]);
+          split_pair(e0, e1, t0, t1, t2, left[r]);
           x[0][p] = t0;
           x[1][p] = t1;
           x[2][p] = t2;
@@ -348,7 +362,7 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
         x[0] = __builtin_bit_cast(u32x4, *(const f32x4*)(turn + (16 * r + li) * P16 + lg * 4));
       }
       // smallest products first
-      if constexpr (F32 && PB == 3) {
+      if constexpr (TERMS && PB == 3) {
 #pragma unroll
         for (int t = 0; t < NB; ++t) mfma(b[SB][2][t], x[0], acc[r][t]);
 #pragma unroll
@@ -359,7 +373,7 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
         for (int t = 0; t < NB; ++t) mfma(b[SB][1][t], x[0], acc[r][t]);
 #pragma unroll
         for (int t = 0; t < NB; ++t) mfma(b[SB][0][t], x[1], acc[r][t]);
-      } else if constexpr (F32) {
+      } else if constexpr (TERMS) {
 #pragma unroll
         for (int t = 0; t < NB; ++t) mfma(b[SB][0][t], x[2], acc[r][t]);
 #pragma unroll
@@ -387,9 +401,9 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
     if constexpr (DA > 3) f(std::integral_constant<int, 3>{});
   };
   static_assert(DA % DB == 0, "weights of a step sit in slot (step % DB)");
-  // K steps [s0, s1) on rows of one type.  Steps in flight are refilled without conditions around
+  // K steps [s0, s1) on rows of one kind.  Steps in flight are refilled without conditions around
   // the loads, then come the last DA without loads.
-  auto phase = [&](auto f32c, int s0, int s1) __attribute__((always_inline)) {
+  auto phase = [&](auto kindc, int s0, int s1) __attribute__((always_inline)) {
     if (s0 >= s1) {
       if (XT == X_F32 && !LATE) load_gates();
       return;
@@ -397,12 +411,12 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
     auto step = [&](auto slota, auto slotb, int s) __attribute__((always_inline)) {
       if (s >= s1) return;
       if (KIND == GRU && s == g.k2) move_n();
-      use(f32c, slota, slotb, KIND != FC && s >= g.k2);
+      use(kindc, slota, slotb, KIND != FC && s >= g.k2);
     };
     int s = s0;
     each([&](auto i) __attribute__((always_inline)) {
       constexpr int I = decltype(i)::value;
-      load_a(f32c, i, s + I);
+      load_a(kindc, i, s + I);
       if constexpr (I < DB) load_b(i, s + I);
     });
     if (XT == X_F32 && !LATE) load_gates();
@@ -412,7 +426,7 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
         using SB = std::integral_constant<int, I % DB>;
         step(i, SB{}, s + I);
         load_b(SB{}, s + I + DB);
-        load_a(f32c, i, s + I + DA);
+        load_a(kindc, i, s + I + DA);
       });
     each([&](auto i) __attribute__((always_inline)) {
       constexpr int I = decltype(i)::value;
@@ -422,11 +436,16 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
     });
   };
   if (XT != X_F32 && !LATE) load_gates();
+  using All = std::integral_constant<int, R32>;
+  using One = std::integral_constant<int, R32_ONE>;
   if (XT == X_F32) {
-    phase(std::true_type{}, s_begin, s_end);
+    phase(All{}, s_begin, s_end);
+  } else if (XT == X_ROUND) {
+    phase(One{}, s_begin, min(s_end, g.k2));
+    phase(All{}, max(s_begin, g.k2), s_end);
   } else {
-    phase(std::false_type{}, s_begin, min(s_end, g.k1));
-    if (KIND != FC) phase(std::true_type{}, max(s_begin, g.k1), s_end);
+    phase(std::integral_constant<int, R16>{}, s_begin, min(s_end, g.k1));
+    if (KIND != FC) phase(All{}, max(s_begin, g.k1), s_end);
   }
   if (KIND == GRU && s_end <= g.k2) move_n();
   if (LATE) load_gates();
@@ -789,7 +808,7 @@ hipError_t launch_cfg(DenseArgs g, hipStream_t st) {
   g.n_rt = (g.M + 16 * RT - 1) / (16 * RT);
   g.n_cg = KIND == FC ? g.N / (16 * U) : g.H / (8 * U);
   // bytes of the rows against bytes of the weights
-  const long long xb = (long long)g.M * g.kn * 32 * (XT == X_F32 ? 4 : 2);
+  const long long xb = (long long)g.M * g.kn * 32 * (in_f32(XT) ? 4 : 2);
   const long long wb = (long long)g.n_cg * U * g.kn * PB * group_bytes(KIND);
   g.rows_per_xcd = xb > wb;
   const int n_out = g.rows_per_xcd ? g.n_rt : g.n_cg, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt;
@@ -969,13 +988,14 @@ hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const f
   return out_bf16 ? hipErrorInvalidValue : launch_kind<FC, X_F16, 1, false>(g, st);
 }
 
-// terms: of the packed weights (3 or 1; bf16 features go with one); tile: cell_tile_kernel.
-hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16, const float* x2,
+// terms: of the packed weights (3 or 1); x_type: features in fp32 (0), or with one term: x1 in bf16
+// (1), fp32 features to be rounded to bf16 (2); tile: cell_tile_kernel.
+hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st) {
   if (B == 0) return hipSuccess;
   if (!x2) I2 = 0;
-  if (!dense_cell_supported(I1, I2, H) || (x1_bf16 && terms != 1)) return hipErrorInvalidValue;
+  if (!dense_cell_supported(I1, I2, H) || (x_type && terms != 1) || (x_type == 1 && I2)) return hipErrorInvalidValue;
   DenseArgs g{};
   g.x1 = x1; g.x2 = x2; g.h_in = h_in; g.done = done; g.ids = ids; g.w = (const uint8_t*)w;
   g.b1 = b_ih; g.b2 = b_hh; g.out = h_out;
@@ -986,7 +1006,8 @@ hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void*
     return lstm ? launch_tile<LSTM>(g, st) : launch_tile<GRU>(g, st);
   }
   if (terms == 3) return lstm ? launch_kind<LSTM, X_F32, 3, false>(g, st) : launch_kind<GRU, X_F32, 3, false>(g, st);
-  if (x1_bf16) return lstm ? launch_kind<LSTM, X_BF16, 1, false>(g, st) : launch_kind<GRU, X_BF16, 1, false>(g, st);
+  if (x_type == 1) return lstm ? launch_kind<LSTM, X_BF16, 1, false>(g, st) : launch_kind<GRU, X_BF16, 1, false>(g, st);
+  if (x_type == 2) return lstm ? launch_kind<LSTM, X_ROUND, 1, false>(g, st) : launch_kind<GRU, X_ROUND, 1, false>(g, st);
   return lstm ? launch_kind<LSTM, X_F32, 1, false>(g, st) : launch_kind<GRU, X_F32, 1, false>(g, st);
 }
 

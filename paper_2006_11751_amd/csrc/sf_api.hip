@@ -742,6 +742,8 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   p->dense_core = dense && !(rnn_bf16 && !small);
   p->core_tile = dense && !bld.bf16 && !small &&
                  dense_cell_tile_supported(cfg->fc_dim, p->meas_out_dim, cfg->rnn_dim);
+  // The core's input is a 16-bit activation there, whichever kernel the batch size selects.
+  p->core_round = rnn_bf16;
   if (rnn_bf16) {
     // The FC kernel can hand its output over as bf16 (the rounding the bf16 core would apply
     // while staging it): half the bytes for every unit tile that re-reads the rows.  Not with a
@@ -1061,7 +1063,7 @@ extern "C" int sf_policy_update_weights(sf_policy* handle, const sf_policy_weigh
                    scratch.stream_f32 == p->stream_f32 && scratch.fc_tile == p->fc_tile &&
                    scratch.fc_out_bf16 == p->fc_out_bf16 && (scratch.fc_wt != nullptr) == (p->fc_wt != nullptr) &&
                    (scratch.fc_wbf != nullptr) == (p->fc_wbf != nullptr) &&
-                   scratch.core_tile == p->core_tile &&
+                   scratch.core_tile == p->core_tile && scratch.core_round == p->core_round &&
                    scratch.rnn_split_w == p->rnn_split_w && scratch.fc_split_w == p->fc_split_w &&
                    scratch.head_split_w == p->head_split_w &&
                    scratch.dense_fc == p->dense_fc && scratch.dense_core == p->dense_core &&
@@ -1356,8 +1358,9 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
         // (PART_CORE alone: one time step of the pass over trajectories, few rows; the step's own
         // kernel there too if the switch asks for it)
         const bool few = parts == PART_CORE && !p->sw.no_rnn_seq;
+        const int x_type = p->fc_out_bf16 ? 1 : p->core_round && !few ? 2 : 0;
         if (p->dense_core || (few && p->rnn_split_w))
-          SF_LAUNCH(launch_dense_cell(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1, p->fc_out_bf16, x2, h_in, done,
+          SF_LAUNCH(launch_dense_cell(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1, x_type, x2, h_in, done,
                                       p->rnn_split_w, c.dtype == SF_DTYPE_BF16 ? 1 : 3, p->gru_bih, p->gru_bhh, h_out,
                                       ids, n_env, p->core_tile && !few, st));
         else if (p->rnn_wih_bf)

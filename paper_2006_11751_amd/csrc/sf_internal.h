@@ -122,6 +122,7 @@ struct Policy {
   uint16_t* fc_split_w = nullptr;   // dev: FC matrix packed for k_dense_split.hip, or null
   bool dense_fc = false, dense_core = false;  // the step's FC layer / core run on k_dense_split.hip
   bool core_tile = false;           // ... the core on its kernel for many rows
+  bool core_round = false;          // the step's core takes its features as bf16 numbers
   double conv1_ratio2 = 0, conv1_ratio3 = 0;  // admission test of the first convolution's digit planes
   int conv1_image = 1;      // first convolution: frame-resident variant where it applies
   int fc_out_bf16 = 0;      // the FC kernel hands bf16 values to the 16-bit recurrent kernel
@@ -271,7 +272,7 @@ void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, uint16_t* 
 void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms, uint16_t* out);
 hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const float* bias, void* out, int out_bf16,
                            int M, int K, int N, hipStream_t st);
-hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16, const float* x2,
+hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);
 bool rnn_bf16_supported(int I1, int I2, int H);

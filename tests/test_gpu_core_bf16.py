@@ -1,0 +1,59 @@
+"""The recurrent core of 16-bit configurations on either side of the rule that picks its kernel from
+the handle's largest batch (k_dense_split.hip up to two rounds of its 32-row tile, k_rnn_bf16.hip
+beyond): the features enter it as bf16 numbers on both."""
+import numpy as np
+import pytest
+
+from paper_2006_11751_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+_SMALL = dict(obs=(3, 36, 64), dtype="bf16", fc=256, rnn=256)
+# networks whose FC layer hands over fp32 numbers (256 units: the border is 1024 rows)
+NETS = [wl.network(4, name="residual", **_SMALL),
+        wl.network(6, name="measurements", meas_hidden=[40, 64], **_SMALL),
+        wl.network(5, name="lstm_measurements", meas_dim=9, meas_hidden=[128], **_SMALL)]
+
+
+def _run(torch, pol, net, B):
+    d = pol.device
+    t = lambda a: None if a is None else torch.from_numpy(a).to(d)
+    out = pol.step(t(wl.observations(net, 0, B)), t(wl.initial_state(net, B)), t(wl.done_mask(net, 0, B)), 7, 11,
+                   meas=t(wl.measurements(net, 0, B)))
+    torch.cuda.synchronize()
+    return {k: v.cpu().numpy() for k, v in out.items()}
+
+
+@pytest.mark.parametrize("net", NETS, ids=lambda n: n["name"])
+def test_both_kernels_round_the_features(torch_cuda, net):
+    """The same row from a small handle and from a large one.  What may differ: the order of the
+    sums, one rounding of the state (2^-17 of it), and, where another order of the FC layer's sum
+    moves a feature over a rounding border (a few in 10^4 features), 2^-8 of that feature.  Features
+    with all their bits on one side would differ by 2^-10 of every feature: about 2e-3 of the result."""
+    w = wl.weights(net)
+    got = []
+    for max_batch in (100, 1100):
+        pol = binding.Policy(net, w, max_batch=max_batch)
+        got.append(_run(torch_cuda, pol, net, 100))
+        pol.close()
+    for k in ("h_out", "logits", "value"):
+        a, b = (g[k].astype(np.float64) for g in got)
+        assert np.linalg.norm(a - b) <= 3e-4 * np.linalg.norm(b), k
+
+
+def test_rounding_before_or_inside_the_core(torch_cuda, monkeypatch):
+    """The FC layer hands over bf16 numbers, or (by the switch) fp32 ones that the core rounds: the
+    same bits."""
+    net = wl.network(2, name="features", obs=(3, 36, 64), fc=128, rnn=128)
+    w = wl.weights(net)
+    for B in (1, 40, 300):
+        pol = binding.Policy(net, w, max_batch=B)
+        a = _run(torch_cuda, pol, net, B)
+        pol.close()
+        with monkeypatch.context() as m:
+            m.setenv("SF_FC_OUT_F32", "1")
+            pol = binding.Policy(net, w, max_batch=B)
+        b = _run(torch_cuda, pol, net, B)
+        pol.close()
+        for k in a:
+            assert np.array_equal(a[k], b[k]), (B, k)
