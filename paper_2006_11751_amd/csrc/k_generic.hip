@@ -134,10 +134,10 @@ __device__ inline void meas_layer(const float* in, int n_in, const float* __rest
         for (int u = 0; u < BATCH; ++u) first.w[u] = w_t[(size_t)min(i + u, k1 - 1) * n_out + o];
 #pragma unroll
       for (int u = 0; u < BATCH; ++u) {
-        const float wu = i + u < k1 ? first.w[u] : 0.0f;  // (past the end: the last weight again, for no use)
+        // past the end: 0 times the last weight again (the input is the one to leave out: it may be infinite)
         const int at = min(i + u, k1 - 1);
 #pragma unroll
-        for (int r = 0; r < kMeasRows; ++r) acc[r] = fmaf(in[r * n_in + at], wu, acc[r]);
+        for (int r = 0; r < kMeasRows; ++r) acc[r] = fmaf(i + u < k1 ? in[r * n_in + at] : 0.0f, first.w[u], acc[r]);
       }
     }
 #pragma unroll
