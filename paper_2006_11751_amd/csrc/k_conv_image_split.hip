@@ -6,16 +6,20 @@
 //
 // Arithmetic.  Scaled by powers of two, an activation is the sum of two fp16 numbers (11 + 11
 // significant bits) and so is a weight; of the four products the three largest are kept: x0w1,
-// x1w0, x0w0.  What is left out is below 2^-22 of a product and of random sign, less than the
-// rounding of an fp32 accumulator over the 512 or 576 terms of these layers, and an accumulator
-// here is rounded 3 times per 32 terms instead of 16 times: the result is nearer to the exact one.
+// x1w0, x0w0.  What is left out is at most 2^-21 of a product, 2^-23.8 root mean square, of random
+// sign: less than what an fp32 accumulator is off after the 512 or 576 terms of these layers, and
+// an accumulator here is rounded 3 times per 32 terms instead of 16 times: the result is nearer to
+// the exact one.  That needs a sum that fp32 rounds often: with 16 taps other than zero the split is
+// 1.5 times as far off as an fp32 sum in one piece, with one tap 2 to 5 times, with 128 of 512 0.6
+// to 0.8 times, with all 0.4 times.  Banks with channels of few such roundings keep the fp32
+// instructions (conv_image_split_pack).
 // fp16 holds 2^-24 .. 65504, so every input channel has a scale of its own that takes the largest
 // value it can have (a bound that follows from the weights of the layers before it, frames being
 // bytes) into [2^14, 2^15], folded into the weights, and every output channel one that does the
 // same for its largest folded weight.  Values are then exact to 22 bits from 2^-18 of the bound
 // upward; below, the absolute error stays at 2^-40 of the bound.  Where that is not small against
 // the rounding errors of the layer (a bound far above the values), the layer keeps the fp32 matrix
-// instructions: conv_split_pack's admission test.
+// instructions: the admission test of conv_image_split_pack.
 //
 // The tiled fp32 kernel (k_gemm_mfma.hip) was bound by the fp32 matrix instructions (1/16 of the
 // rate) and staged every pixel once per window that covers it.  Here a workgroup of four waves
@@ -36,6 +40,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -354,45 +359,67 @@ void conv_activation_range(const float* w, const float* bias, int cout, int cin,
 // 0..7, both terms of W[16 nt + l%16][c = 32 half + 8 (l/16) + e][p][q], gi = (p k + q)(cin/32) +
 // half, times 2^(e_in[c]) and the output channel's scale; scale: [cin] input scales, [cout] inverse
 // output scales, 0 or (not admitted) 1.  bound, mean_sq: of the input channels.
-// Returns the admission ratio: the largest over the output channels of
-//     (what the fixed part of the splitting errors, 2^-40 of an input bound and 2^-39 of the largest
-//      folded weight, can add up to)
-//   / (the rounding errors of an fp32 sum of the typical terms: sqrt(K) 2^-24 times their root mean
-//      square, K terms);
-// the split runs where it is <= 1.  (Infinite or NaN bounds give a ratio that is not <= 1.)
+// Returns the admission ratio; the split runs where it is <= 1.  (Infinite or NaN bounds give a ratio
+// that is not <= 1.)  With P_k the mean square of a channel's sum after k terms (in the order tap,
+// input channel) and R = (sum of P_k over the terms that can round an accumulator: 2^-20 of the
+// whole or more) / P_K, an fp32 sum is off by about sqrt(2 R) 2^-24 of its size (R = K / 2 where all taps are
+// alike, 1 for a single tap).  The ratio is the largest over the channels of
+//   - what the fixed part of the splitting errors can add up to, 2^-40 of an input bound and 2^-39
+//     of the largest folded weight, over that error;
+//   - 192 / R: what is left out of the products is proportional to the sum's size, so it has to be
+//     rounded often to be as far off in fp32.  Error of the new state against 64 bits, split over
+//     fp32 kernel, 64 hidden units, R of 230 and more (random weights: normal, Laplace, uniform): 0.80
+//     to 0.84 where k_gemm_mfma.hip takes K in one piece (handles for 1100 rows), 0.93 to 0.99 in two
+//     pieces (400 rows), 0.99 to 1.06 in four (64 rows); R = 160: 0.93, 1.04, 1.09.
 double conv_image_split_pack(const float* w, int cout, int cin, int k, const std::vector<double>& bound,
                              const std::vector<double>& mean_sq, std::vector<uint16_t>& wpk, std::vector<float>& scale) {
+  constexpr double kRounds = 192.0;
   const int halves = cin / 32, kk = k * k, K = cin * kk;
   wpk.assign((size_t)cout * K * 2, 0);
   scale.assign(cin + cout + 1, 1.0f);
   std::vector<double> fold(cin);  // 1 / input scale
+  double worst = 0.0;
   for (int c = 0; c < cin; ++c) {
     const int e = power(bound[c]);
     scale[c] = (float)ldexp(1.0, e);
     fold[c] = ldexp(1.0, -e);
+    if (!(bound[c] < 1e30)) worst = INFINITY;
   }
-  double worst = 0.0;
+  std::vector<double> sq(K);  // mean squares of a channel's terms, [tap][input channel]
   for (int n = 0; n < cout; ++n) {
     const float* wn = w + (size_t)n * K;
-    double top = 0.0, typ = 0.0, spread = 0.0;
-    for (int c = 0; c < cin; ++c) {
-      if (!(bound[c] < 1e30)) worst = INFINITY;
+    double top = 0.0, whole = 0.0, spread = 0.0;
+    for (int c = 0; c < cin; ++c)
       for (int t = 0; t < kk; ++t) {
-        const double v = fabs((double)wn[c * kk + t]);
-        top = fmax(top, v * fold[c]);
-        typ += v * v * mean_sq[c];
+        const double v = fabs((double)wn[c * kk + t]), q = v * v * mean_sq[c];
+        top = std::max(top, v * fold[c]);
         spread += v * bound[c];
+        whole += q;
+        sq[(size_t)t * cin + c] = q;
       }
+    // R, tap by tap: a tap's terms are seen by the later taps' roundings and half of its own
+    double seen = 0.0, before = 0.0;
+    for (int t = 0; t < kk; ++t) {
+      double part = 0.0;
+      int roundings = 0;
+      for (int c = 0; c < cin; ++c) {
+        const double q = sq[(size_t)t * cin + c];
+        part += q;
+        roundings += q >= 0x1p-40 * whole;
+      }
+      seen += roundings * (before + 0.5 * part);
+      before += part;
     }
+    const double rounds = seen / whole;
     const int e = power(top);
     const double up = ldexp(1.0, e);
     scale[cin + n] = (float)ldexp(1.0, -e);
     // folded weights have an absolute error of 2^-25 at a largest value of 2^14 or more; an input
     // of scaled size 2^15 multiplies it
     const double fixed = ldexp(spread, -40) + K * ldexp(1.0, 15 - 25 - e);
-    const double ref = sqrt((double)K) * ldexp(1.0, -24) * sqrt(typ);
+    const double ref = sqrt(2.0 * rounds) * ldexp(1.0, -24) * sqrt(whole);
     // (a channel without weights has nothing to get wrong)
-    if (top > 0.0) worst = fmax(worst, ref > 0.0 ? fixed / ref : INFINITY);
+    if (top > 0.0) worst = std::max(worst, ref > 0.0 ? std::max(fixed / ref, kRounds / rounds) : INFINITY);
     (host_f16c() ? pack_channel_f16c : pack_channel_plain)(wn, n, kk, halves, fold.data(), up, wpk.data());
   }
   scale[cin + cout] = worst <= 1.0 ? 0.0f : 1.0f;
