@@ -12,7 +12,7 @@
 // A sample's logits are reduced to the joint log-probability and the entropy; the backward recursion
 // over time runs across the 32 or 64 lanes of a trajectory (the coefficient pairs are broadcast one
 // by one, last step first); longer trajectories are walked in chunks from the end, carrying the
-// recursion's value.  Targets, advantages, gradients and partial sums follow.  A second,
+// recursion's value.  Targets, advantages, gradients and a workgroup's partial sums follow.  A second,
 // single-workgroup launch adds the partial sums in a fixed order, so the result does not depend on
 // scheduling.
 //
@@ -52,7 +52,7 @@ struct LossArgs {
   float* adv;             // [T][N]
   float* dlogits;         // [T][N][sumA] or null
   float* dvalues;         // [T][N] or null
-  float* partials;        // [N][4]
+  float* partials;        // [workgroups of the trajectory kernel][4], at most [N][4]
   int T, N, n_heads, sumA;
   int head_sizes[SF_MAX_HEADS];
   int head_off[SF_MAX_HEADS];    // first logit of each head
@@ -246,7 +246,8 @@ __device__ inline void copy_tile_vec4(const float* mem, float* tile, int t0, int
 //   4. one thread per logit (four neighbouring ones where the rows allow): gradients straight from
 //      the tile to memory.
 // (One lane per sample through all of it, two waves per workgroup, took 14.5 us at 64 trajectories of
-// 32 steps and seven heads, 19.6 at 2048; now 9.4 and 15.7, 1.6 TB/s of logits, actions and gradients.)
+// 32 steps and seven heads, 19.6 at 2048; now 9.4 and 15.7, 1.6 TB/s of logits, actions and gradients:
+// see pick_tile for whole calls.)
 // Per head one exponential per logit forward,
 //   d_i = l_i - max, e_i = exp(d_i), se = sum e_i, sd = sum e_i d_i
 //   lse = max + log se,  entropy = log se - sd / se   (= -sum p_i (l_i - lse))
@@ -527,6 +528,64 @@ extern "C" int64_t sf_appo_loss_workspace_bytes(const sf_loss_config* cfg) {
 
 namespace {
 
+// The instantiations of the LDS-staged kernel: lanes per trajectory, trajectories per workgroup,
+// threads.
+struct LossTile {
+  int lw, tpb, threads;
+  void (*kernel)(LossArgs, LdsPlan);
+};
+template <int LW, int TPB, int NT>
+constexpr LossTile loss_tile() { return LossTile{LW, TPB, NT, appo_traj_lds_kernel<LW, TPB, NT>}; }
+const LossTile kTiles[] = {loss_tile<32, 8, 256>(), loss_tile<32, 4, 256>(), loss_tile<32, 8, 512>(),
+                           loss_tile<32, 4, 512>(), loss_tile<32, 1, 256>(), loss_tile<64, 8, 512>(),
+                           loss_tile<64, 4, 512>(), loss_tile<64, 2, 512>(), loss_tile<64, 1, 256>()};
+constexpr size_t kMaxLds = 144 * 1024;
+
+size_t tile_lds(const LossTile& k, int n_heads, int sumA) {
+  const size_t pitch = sumA | 1, hp = n_heads | 1;
+  return sizeof(float) * ((size_t)k.lw * k.tpb * (pitch + 4 * hp + 1) + k.tpb * 4 + sumA);
+}
+
+// Which of them takes a call: null if no chunk of a single trajectory fits LDS (the direct kernel
+// does).  Several trajectories make the rows that a workgroup copies long runs of memory and its stages
+// full, but too few workgroups leave CUs without one, and a large tile leaves a CU one workgroup.
+// Whole calls, replayed from a graph (us; the kernel before had one lane per sample, 2 or 4
+// waves):
+//   logits x heads, steps x trajectories   before   1 of 256   4 of 256   4 of 512   8 of 256   8 of 512
+//     7 x 1   32 x  700                       10.1       11.4        9.4        9.6       10.0        9.9
+//     7 x 1   32 x 2048                       12.9       21.6       11.8       12.7       10.8       10.8
+//     7 x 1   32 x 8192                       28.9       65.0       28.4       37.9       18.7       23.9
+//    41 x 7   32 x   64                       15.8       11.0       14.1       12.5       18.9       15.2
+//    41 x 7   32 x  700                       17.1       14.6       14.6       13.0       19.6       15.9
+//    41 x 7   32 x 2048                       22.4       28.1       19.3       18.6       21.3       18.3
+//    41 x 7   32 x 8192                       57.5       85.2       47.1       55.7       48.3       42.5
+//    90 x 1   32 x 4096                       76.8       66.9       53.5       48.5       75.3       54.8
+//    32 x 16  32 x 4096                       64.5       45.1       37.4       33.8       54.2       37.9
+//    64 x 16  32 x  512                       34.0       13.6       22.5       16.8       35.9       24.6
+//     7 x 1   64 x 4096                       30.0       49.0       26.4       31.9          -       23.0
+//    15 x 1  128 x  600                       20.3       23.6       21.4       20.5          -       25.4
+//    41 x 7   64 x 1024                       21.0       24.7       23.4       19.8          -       26.1
+//    78 x 16  40 x 1024                       37.6       25.2   (four trajectories do not fit: 96 by the direct kernel)
+// and 7 x 1, 64 x 300: 11.1, 11.4 one of 256, 10.7 two of 512.
+const LossTile* pick_tile(int T, int N, int n_heads, int sumA) {
+  const int lw = T <= 32 ? 32 : 64;
+  const bool small = sumA <= 16, many = N >= 1536;
+  int tpb, threads = 512;
+  if (small) {
+    tpb = many ? 8 : lw == 32 || N >= 512 ? 4 : 2;
+    if (lw == 32) threads = 256;
+  } else if (lw == 32) {
+    tpb = many && sumA <= 48 ? 8 : N >= 640 ? 4 : 1;
+  } else {
+    tpb = N >= 1024 ? 4 : 1;
+  }
+  for (const LossTile& k : kTiles) {
+    if (k.lw != lw || k.tpb > tpb || (k.tpb > 1 && k.threads != threads)) continue;
+    if (tile_lds(k, n_heads, sumA) <= (k.tpb == 8 ? kMaxLds / 2 : kMaxLds)) return &k;
+  }
+  return nullptr;
+}
+
 // Argument checks and the two launches shared by the entry points; `partials` is device
 // memory for N x 4 floats.
 int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const float* logits,
@@ -567,13 +626,8 @@ int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const flo
         g.head_order[q - 1] = o;
       }
   }
-  // The LDS-staged kernel where a chunk's tiles fit LDS.  A workgroup takes four trajectories (the rows
-  // it copies are long runs of memory), but with too few of them to give every CU a workgroup one.
-  const int LW = cfg->T <= 32 ? 32 : 64;
-  // (32 steps, seven heads, whole call: 64 trajectories 12.0 against 12.7 us, 512 13.1 against 13.4,
-  // 1024 17.3 against 14.2)
-  const bool few = cfg->N < 1024;
-  const int TPB = few ? 1 : 4, S = LW * TPB;
+  const LossTile* tile = pick_tile(cfg->T, cfg->N, cfg->n_heads, sumA);
+  const int TPB = tile ? tile->tpb : 1;
   LdsPlan plan;
   plan.pitch = sumA | 1;
   plan.m_sumA = magic_of((uint32_t)sumA);
@@ -583,30 +637,20 @@ int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const flo
   plan.m_arow = magic_of((uint32_t)(TPB * cfg->n_heads));
   plan.vec4 = plan.pitch == sumA && (TPB * sumA) % 4 == 0 && ((size_t)cfg->N * sumA) % 4 == 0 &&
               ((uintptr_t)logits & 15) == 0 && (!dlogits_opt || ((uintptr_t)dlogits_opt & 15) == 0);
-  const size_t lds = sizeof(float) * ((size_t)S * (plan.pitch + 4 * (size_t)(cfg->n_heads | 1) + 1) + TPB * 4 + sumA);
-  constexpr size_t kMaxLds = 144 * 1024;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
-    for (const void* k : {(const void*)appo_traj_lds_kernel<32, 4, 512>, (const void*)appo_traj_lds_kernel<32, 1, 256>,
-                          (const void*)appo_traj_lds_kernel<64, 4, 512>, (const void*)appo_traj_lds_kernel<64, 1, 256>})
+    for (const LossTile& k : kTiles)
       if (attr_status == hipSuccess)
-        attr_status = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+        attr_status = hipFuncSetAttribute((const void*)k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   });
   if (attr_status != hipSuccess) {
     set_error("%s: hipFuncSetAttribute failed: %s", fn, hipGetErrorString(attr_status));
     return SF_ERR_DEVICE;
   }
   unsigned n_partials = (unsigned)((cfg->N + TPB - 1) / TPB);
-  if (lds <= kMaxLds) {
-    if (LW == 32 && few)
-      appo_traj_lds_kernel<32, 1, 256><<<n_partials, 256, lds, st>>>(g, plan);
-    else if (LW == 32)
-      appo_traj_lds_kernel<32, 4, 512><<<n_partials, 512, lds, st>>>(g, plan);
-    else if (few)
-      appo_traj_lds_kernel<64, 1, 256><<<n_partials, 256, lds, st>>>(g, plan);
-    else
-      appo_traj_lds_kernel<64, 4, 512><<<n_partials, 512, lds, st>>>(g, plan);
+  if (tile) {
+    tile->kernel<<<n_partials, tile->threads, tile_lds(*tile, cfg->n_heads, sumA), st>>>(g, plan);
   } else {
     n_partials = (unsigned)cfg->N;
     appo_traj_kernel<<<(unsigned)((cfg->N + kTrajPerBlock - 1) / kTrajPerBlock), kLossThreads, 0, st>>>(g);
@@ -693,7 +737,7 @@ extern "C" int sf_appo_loss_static(const sf_loss_config* cfg, const float* logit
   float* partials = nullptr;
   rc = static_scratch(fn, &partials);
   if (rc != SF_OK) return rc;
-  // every trajectory's wave writes its slot before the reduction reads it: nothing to clear
+  // every slot that the reduction reads is written first: nothing to clear
   return run_appo_loss(fn, cfg, sumA, logits, actions, logp_mu, values, rewards, dones, vs, adv, loss,
                        dlogits_opt, dvalues_opt, partials, reinterpret_cast<hipStream_t>(hip_stream));
 }

@@ -1,6 +1,6 @@
-"""The loss kernels at the edges of their dispatch: one and four trajectories per workgroup (from
-1024 trajectories on), ragged last workgroups, 32 and 64 lanes per trajectory with partial chunks,
-16-byte and element-wise gradients, heads in every order of size, tiles too large for LDS."""
+"""The loss kernels at the edges of their dispatch: one, two, four and eight trajectories per workgroup,
+ragged last workgroups, 32 and 64 lanes per trajectory with partial chunks, 16-byte and element-wise
+gradients, heads in every order of size, tiles too large for LDS with several trajectories or with one."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 
 FULL = (3, 3, 2, 2, 2, 8, 21)
 CASES = [(FULL, 1, 1), (FULL, 32, 1023), (FULL, 32, 1024), (FULL, 31, 1027), (FULL, 33, 1026), (FULL, 65, 5),
-         ((21, 1, 8), 7, 1025), ((4, 4), 5, 1030), ((2,) * 16, 40, 3), ((500,), 3, 1024), ((1000, 23), 2, 3)]
+         ((21, 1, 8), 7, 1025), ((4, 4), 5, 1030), ((2,) * 16, 40, 3), ((500,), 3, 1024), ((1000, 23), 2, 3),
+         ((7,), 32, 1535), ((7,), 32, 1537), ((3, 3, 2, 2, 2, 11), 9, 1543), ((40, 9), 4, 1540), (FULL, 31, 639), (FULL, 31, 641),
+         ((1,) * 16, 40, 1537), ((15,), 40, 511), ((15,), 40, 513), ((7,), 65, 1541), ((1200,), 3, 3)]
 
 
 @pytest.mark.parametrize("heads,T,N", CASES, ids=["%s-%d-%d" % ("+".join(map(str, h)), t, n) for h, t, n in CASES])
@@ -32,3 +34,19 @@ def test_shapes(torch_cuda, ref, heads, T, N):
     again = _run(torch_cuda, hp, tr)
     for k in ("vs", "adv", "dvalues", "dlogits", "loss"):
         assert np.array_equal(g[k], again[k]), k
+
+
+@pytest.mark.parametrize("heads,T", [((7,), 32), (FULL, 20), ((7,), 70), (FULL, 40), ((5,) * 15 + (3,), 40), ((150,), 40),
+                                     ((200,), 32)], ids=lambda v: "+".join(map(str, v)) if isinstance(v, tuple) else None)
+def test_trajectories_do_not_depend_on_their_number(torch_cuda, heads, T):
+    """Targets and advantages of a trajectory are the same bits in every batch: with one, four or eight of
+    them in a workgroup, and also where several do not fit LDS and one does (the kernel without LDS, with
+    other exponentials, is for tiles that never fit)."""
+    hp = wl.loss_config(heads, T, 1537)
+    tr = wl.trajectories(hp, 6200)
+    full = _run(torch_cuda, hp, tr)
+    for n in (3, 511, 600, 1024):
+        part = {k: np.ascontiguousarray(v[:, :n]) for k, v in tr.items()}
+        g = _run(torch_cuda, dict(hp, N=n), part)
+        for k in ("vs", "adv"):
+            assert np.array_equal(g[k], full[k][:, :n]), (n, k)
