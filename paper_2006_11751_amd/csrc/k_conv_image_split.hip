@@ -291,39 +291,102 @@ int power(double v) {
   return e < -85 ? 100 : e > 115 ? -100 : 15 - e;
 }
 
-// One output channel's weights in two terms (the second build with the host's conversion
-// instructions: packing runs at every weight update).
-inline __attribute__((always_inline)) void pack_channel(const float* wn, int n, int kk, int halves, const double* fold,
-                                                        double up, uint16_t* wpk) {
-  const int G = kk * halves;
-  for (int gi = 0; gi < G; ++gi) {
-    const int t = gi / halves, half = gi % halves;
-    for (int lg = 0; lg < 4; ++lg)
-      for (int i = 0; i < 8; ++i) {
-        const int c = 32 * half + 8 * lg + i;
-        const float v = (float)((double)wn[c * kk + t] * fold[c] * up);
-        const _Float16 h = (_Float16)v, rest = (_Float16)(v - (float)h);
-        const size_t at = ((((size_t)(n / 16) * G + gi) * 2) * 64 + lg * 16 + n % 16) * 8 + i;
-        memcpy(&wpk[at], &h, 2);
-        memcpy(&wpk[at + 64 * 8], &rest, 2);
-      }
-  }
-}
-void pack_channel_plain(const float* wn, int n, int kk, int halves, const double* fold, double up, uint16_t* wpk) {
-  pack_channel(wn, n, kk, halves, fold, up, wpk);
-}
+// Packing runs at every weight update: vectors over the input channels, and two builds of the loops, the
+// second with the host's conversion instructions.
+#define SF_INLINE inline __attribute__((always_inline))
 #if defined(__HIP_DEVICE_COMPILE__) || !defined(__x86_64__)
+#define SF_F16C
 bool host_f16c() { return false; }
-void pack_channel_f16c(const float* wn, int n, int kk, int halves, const double* fold, double up, uint16_t* wpk) {
-  pack_channel(wn, n, kk, halves, fold, up, wpk);
-}
 #else
+#define SF_F16C __attribute__((target("avx2,f16c")))
 bool host_f16c() { return __builtin_cpu_supports("avx2") && __builtin_cpu_supports("f16c"); }
-__attribute__((target("avx2,f16c"))) void pack_channel_f16c(const float* wn, int n, int kk, int halves,
-                                                            const double* fold, double up, uint16_t* wpk) {
-  pack_channel(wn, n, kk, halves, fold, up, wpk);
-}
 #endif
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+
+struct Channel {
+  double top;     // largest folded weight
+  double spread;  // sum of |weight| * input bound
+  double whole;   // sum of the mean squares of the terms
+  double rounds;  // R of conv_image_split_pack
+};
+
+// The filter bank of an output channel as [tap][input channel], and what the admission test asks of it.
+SF_INLINE Channel channel_loops(const float* wn, int cin, int kk, const double* fold, const double* bound,
+                                const double* mean_sq, float* x) {
+  for (int c = 0; c < cin; ++c)
+    for (int t = 0; t < kk; ++t) x[(size_t)t * cin + c] = wn[(size_t)c * kk + t];
+  auto vec = [](const double* v, int c) __attribute__((always_inline)) {
+    f64x4 r;
+    memcpy(&r, v + c, sizeof(r));
+    return r;
+  };
+  auto size = [&](int t, int c) __attribute__((always_inline)) {
+    f32x4 r;
+    memcpy(&r, x + (size_t)t * cin + c, sizeof(r));
+    return __builtin_convertvector(__builtin_elementwise_abs(r), f64x4);
+  };
+  auto sum = [](f64x4 v) __attribute__((always_inline)) { return (v[0] + v[1]) + (v[2] + v[3]); };
+  f64x4 top = {0, 0, 0, 0}, spread = top, whole = top;
+  for (int t = 0; t < kk; ++t)
+    for (int c = 0; c < cin; c += 4) {
+      const f64x4 v = size(t, c);
+      top = __builtin_elementwise_max(top, v * vec(fold, c));
+      spread += v * vec(bound, c);
+      whole += v * v * vec(mean_sq, c);
+    }
+  Channel r{std::max(std::max(top[0], top[1]), std::max(top[2], top[3])), sum(spread), sum(whole), 0.0};
+  // tap by tap: a tap's terms are seen by the later taps' roundings and half of its own
+  double seen = 0.0, before = 0.0;
+  const double least = 0x1p-40 * r.whole;
+  for (int t = 0; t < kk; ++t) {
+    f64x4 part = {0, 0, 0, 0}, roundings = part;
+    for (int c = 0; c < cin; c += 4) {
+      const f64x4 v = size(t, c), q = v * v * vec(mean_sq, c);
+      part += q;
+      roundings -= __builtin_convertvector(q >= least, f64x4);
+    }
+    const double own = sum(part);
+    seen += sum(roundings) * (before + 0.5 * own);
+    before += own;
+  }
+  r.rounds = seen / r.whole;
+  return r;
+}
+
+// The same bank, scaled, in two terms.  (Two loops: from fp64 to fp16 without the stop there is no vector
+// instruction.)
+SF_INLINE void pack_loops(float* x, int n, int cin, int kk, const double* fold, double up, uint16_t* wpk) {
+  const int halves = cin / 32, G = kk * halves;
+  for (int t = 0; t < kk; ++t)
+    for (int c = 0; c < cin; ++c) x[(size_t)t * cin + c] = (float)(x[(size_t)t * cin + c] * fold[c] * up);
+  for (int gi = 0; gi < G; ++gi)
+    for (int lg = 0; lg < 4; ++lg) {
+      const int c = 32 * (gi % halves) + 8 * lg;
+      f32x8 v;
+      memcpy(&v, x + (size_t)(gi / halves) * cin + c, sizeof(v));
+      const f16x8 h = __builtin_convertvector(v, f16x8);
+      const f16x8 rest = __builtin_convertvector(v - __builtin_convertvector(h, f32x8), f16x8);
+      uint16_t* at = wpk + ((((size_t)(n / 16) * G + gi) * 2) * 64 + lg * 16 + n % 16) * 8;
+      memcpy(at, &h, sizeof(h));
+      memcpy(at + 64 * 8, &rest, sizeof(rest));
+    }
+}
+Channel channel_plain(const float* wn, int cin, int kk, const double* fold, const double* bound, const double* mean_sq,
+                      float* x) {
+  return channel_loops(wn, cin, kk, fold, bound, mean_sq, x);
+}
+SF_F16C Channel channel_f16c(const float* wn, int cin, int kk, const double* fold, const double* bound,
+                             const double* mean_sq, float* x) {
+  return channel_loops(wn, cin, kk, fold, bound, mean_sq, x);
+}
+void pack_plain(float* x, int n, int cin, int kk, const double* fold, double up, uint16_t* wpk) {
+  pack_loops(x, n, cin, kk, fold, up, wpk);
+}
+SF_F16C void pack_f16c(float* x, int n, int cin, int kk, const double* fold, double up, uint16_t* wpk) {
+  pack_loops(x, n, cin, kk, fold, up, wpk);
+}
 
 }  // namespace
 
@@ -374,7 +437,7 @@ void conv_activation_range(const float* w, const float* bias, int cout, int cin,
 double conv_image_split_pack(const float* w, int cout, int cin, int k, const std::vector<double>& bound,
                              const std::vector<double>& mean_sq, std::vector<uint16_t>& wpk, std::vector<float>& scale) {
   constexpr double kRounds = 192.0;
-  const int halves = cin / 32, kk = k * k, K = cin * kk;
+  const int kk = k * k, K = cin * kk;
   wpk.assign((size_t)cout * K * 2, 0);
   scale.assign(cin + cout + 1, 1.0f);
   std::vector<double> fold(cin);  // 1 / input scale
@@ -385,42 +448,21 @@ double conv_image_split_pack(const float* w, int cout, int cin, int k, const std
     fold[c] = ldexp(1.0, -e);
     if (!(bound[c] < 1e30)) worst = INFINITY;
   }
-  std::vector<double> sq(K);  // mean squares of a channel's terms, [tap][input channel]
+  std::vector<float> x(K);
+  const bool f16c = host_f16c();
   for (int n = 0; n < cout; ++n) {
-    const float* wn = w + (size_t)n * K;
-    double top = 0.0, whole = 0.0, spread = 0.0;
-    for (int c = 0; c < cin; ++c)
-      for (int t = 0; t < kk; ++t) {
-        const double v = fabs((double)wn[c * kk + t]), q = v * v * mean_sq[c];
-        top = std::max(top, v * fold[c]);
-        spread += v * bound[c];
-        whole += q;
-        sq[(size_t)t * cin + c] = q;
-      }
-    // R, tap by tap: a tap's terms are seen by the later taps' roundings and half of its own
-    double seen = 0.0, before = 0.0;
-    for (int t = 0; t < kk; ++t) {
-      double part = 0.0;
-      int roundings = 0;
-      for (int c = 0; c < cin; ++c) {
-        const double q = sq[(size_t)t * cin + c];
-        part += q;
-        roundings += q >= 0x1p-40 * whole;
-      }
-      seen += roundings * (before + 0.5 * part);
-      before += part;
-    }
-    const double rounds = seen / whole;
-    const int e = power(top);
+    const Channel ch = (f16c ? channel_f16c : channel_plain)(w + (size_t)n * K, cin, kk, fold.data(), bound.data(),
+                                                            mean_sq.data(), x.data());
+    const int e = power(ch.top);
     const double up = ldexp(1.0, e);
     scale[cin + n] = (float)ldexp(1.0, -e);
     // folded weights have an absolute error of 2^-25 at a largest value of 2^14 or more; an input
     // of scaled size 2^15 multiplies it
-    const double fixed = ldexp(spread, -40) + K * ldexp(1.0, 15 - 25 - e);
-    const double ref = sqrt(2.0 * rounds) * ldexp(1.0, -24) * sqrt(whole);
+    const double fixed = ldexp(ch.spread, -40) + K * ldexp(1.0, 15 - 25 - e);
+    const double ref = sqrt(2.0 * ch.rounds) * ldexp(1.0, -24) * sqrt(ch.whole);
     // (a channel without weights has nothing to get wrong)
-    if (top > 0.0) worst = std::max(worst, ref > 0.0 ? std::max(fixed / ref, kRounds / rounds) : INFINITY);
-    (host_f16c() ? pack_channel_f16c : pack_channel_plain)(wn, n, kk, halves, fold.data(), up, wpk.data());
+    if (ch.top > 0.0) worst = std::max(worst, ref > 0.0 ? std::max(fixed / ref, kRounds / ch.rounds) : INFINITY);
+    (f16c ? pack_f16c : pack_plain)(x.data(), n, cin, kk, fold.data(), up, wpk.data());
   }
   scale[cin + cout] = worst <= 1.0 ? 0.0f : 1.0f;
   return worst;
