@@ -113,10 +113,12 @@ __device__ inline void state_rows(const DenseArgs& g, int (&row)[N], int (&flag)
 // columns [r z | n] (the 8 n columns of each lane group alone) or [i f | g o].
 constexpr int group_bytes(int kind) { return kind == FC ? 1024 : kind == GRU ? 1536 : 2048; }
 
+__device__ inline bool finite(float v) { return fabsf(v) < INFINITY; }
 constexpr bool in_f32(int xt) { return xt == X_F32 || xt == X_ROUND; }
 
-// The sums of one row that holds an infinity or a NaN, in plain fp32 arithmetic: the products of
-// such a number with the terms of a weight do not add up to its product with the weight.  q: gate
+// The sums of one row that holds an infinity or a NaN, or of a row whose sum came out as one, in plain
+// fp32 arithmetic: the products of such a number with the terms of a weight do not add up to its
+// product with the weight, and neither do those of terms whose largest product overflows.  q: gate
 // (FC: 0), n: unit (FC: output); the n gate of a GRU has its sums over the features (n_x) and the
 // state (n_h) apart.
 template <int KIND, int XT, int PB>
@@ -469,7 +471,10 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) v += red[w][r * NA + t][lane];
         const int m = row0 + 16 * (rd * RR + r) + li;
-        if (__builtin_expect(odd_row[16 * (rd * RR + r) + li] != 0, 0) && m < g.M)
+        bool odd = odd_row[16 * (rd * RR + r) + li] != 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) odd |= !finite(v[e]);
+        if (__builtin_expect(odd, 0) && m < g.M)
           for (int e = 0; e < 4; ++e)
             v[e] = plain_sum<KIND, XT, PB>(g, m, m, false, 0, cg * 16 * U + t * 16 + 4 * lg + e, 0, g.kn);
 #pragma unroll
@@ -518,7 +523,10 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
         if (m < g.M) {
           float* o = (float*)g.out + (size_t)m * g.S;
           const bool rs = gdn[rd] != 0;
-          if (__builtin_expect(odd_row[16 * (rd * RR + ert) + erow] != 0, 0))
+          bool odd = odd_row[16 * (rd * RR + ert) + erow] != 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) odd |= !finite(sum[q]);
+          if (__builtin_expect(odd, 0))
             plain_sums<KIND, XT, PB>(g, m, rs, unit, sum);
           const float before = rs ? 0.0f : prev[rd];
           if (KIND == LSTM)
@@ -790,7 +798,10 @@ __global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
         if (m < g.M) {
           float* o = (float*)g.out + (size_t)m * g.S;
           const bool rs = gdn[j] != 0;
-          if (__builtin_expect(odd_row[16 * j + erow] != 0, 0))
+          bool odd = odd_row[16 * j + erow] != 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) odd |= !finite(sum[q]);
+          if (__builtin_expect(odd, 0))
             plain_sums<KIND, XT, PB>(g, m, rs, unit, sum);
           const float before = rs ? 0.0f : prev[j];
           if (KIND == LSTM)

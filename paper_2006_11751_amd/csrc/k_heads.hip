@@ -327,12 +327,14 @@ __global__ __launch_bounds__(kHeadThreads) void heads_split_kernel(HeadsArgs g) 
     f32x4 v = red[0][tid >> 6][lane];
 #pragma unroll
     for (int w = 1; w < kHeadWaves; ++w) v += red[w][tid >> 6][lane];
-    const bool odd = odd_row[li] != 0;
+    bool odd = odd_row[li] != 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) odd |= !(fabsf(v[e]) < INFINITY);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int a = (tid >> 6) * 16 + 4 * lg + e;
       const int ac = min(a, g.sumA);
-      if (__builtin_expect(odd, 0)) {  // an infinity or a NaN in the state: plain arithmetic
+      if (__builtin_expect(odd, 0)) {  // an infinity or a NaN in the state or as a sum: plain arithmetic
         const float* hr = g.h + (size_t)min(row0 + li, g.B - 1) * g.S;
         float sum = 0.0f;
         for (int k = 0; k < g.H; ++k) sum = fmaf(hr[k], g.head_w[(size_t)ac * g.H + k], sum);

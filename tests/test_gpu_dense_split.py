@@ -120,3 +120,48 @@ def test_states_without_terms(torch_cuda, ref, max_batch, B, rnn_type):
         assert m.sum() >= 200 and np.max(np.abs(a[m] - b[m])) < 1e-4, row
     assert np.isnan(got["h_out"][33]).all()
     pol.close()
+
+
+@pytest.mark.parametrize("max_batch", [40, 200, 600])
+@pytest.mark.parametrize("rnn_type", ["gru", "lstm"])
+def test_sums_that_overflow(torch_cuda, ref, max_batch, rnn_type):
+    """Finite operands whose products overflow: the infinity of the definition, in the FC layer, in a cell
+    and in the heads, and not the NaN that terms of both signs would add up to."""
+    torch = torch_cuda
+    B = max_batch
+    net = _net(fc=128, rnn=512, rnn_type=rnn_type)
+    w = wl.weights(net)
+    obs, state, done = wl.observations(net, 0, B), wl.initial_state(net, B), np.zeros(B, np.uint8)
+    # FC: activations of 2^118, one unit with positive weights only, the others go to zero
+    v = {k: [a.copy() for a in x] if isinstance(x, list) else x.copy() for k, x in w.items()}
+    v["conv_w"][1] *= np.float32(2.0 ** 118)
+    v["conv_b"][1] *= np.float32(2.0 ** 118)
+    v["fc_w"] = -np.abs(v["fc_w"]) * np.float32(2.0 ** 24)
+    v["fc_w"][17] *= -1
+    # cell: a state of 2^127 in one place (with an open r gate everywhere, so that no unit is 0 * infinity,
+    # and at that unit an open z gate), and zero there in the other rows
+    u = {k: [a.copy() for a in x] if isinstance(x, list) else x.copy() for k, x in w.items()}
+    c, H, rows = 77, 512, np.array([0, 15, 16, B - 1])
+    u["rnn_w_hh"][:, c] *= np.float32(2.0 ** 16)
+    if rnn_type == "gru":
+        u["rnn_w_hh"][:H, c] = np.abs(u["rnn_w_hh"][:H, c])
+        u["rnn_w_hh"][H + c, c] = np.abs(u["rnn_w_hh"][H + c, c])
+        u["pi_w"][:, c] *= np.float32(2.0 ** 16)
+        u["v_w"][c] = 2.0 ** 16
+    big = state.copy()
+    big[:, c] = 0
+    big[rows, c] = 1.703 * 2.0 ** 127
+    for weights, st in ((v, state), (u, big)):
+        pol = binding.Policy(net, weights, max_batch=max_batch)
+        g = _run(torch, pol, net, obs, st, done, None)
+        pol.close()
+        with np.errstate(all="ignore"):
+            o = ref.policy_step(net, weights, obs, st, done, 7, 11)
+        for k in ("h_out", "logits", "value"):
+            a, b = g[k].astype(np.float64), o[k].astype(np.float64)
+            m = np.isfinite(b) & (np.abs(b) < 1e30)
+            assert np.array_equal(a[~m], b[~m]), k
+            # (heads with weights of 2^16: what they make of a state's last bits is not looked at)
+            assert (weights is u and k != "h_out") or np.max(np.abs(a[m] - b[m])) < 1e-4, k
+    if rnn_type == "gru":
+        assert np.isinf(o["logits"][rows]).all() and np.isfinite(o["logits"]).sum() == (B - 4) * 6
