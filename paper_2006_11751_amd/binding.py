@@ -480,7 +480,8 @@ class Policy:
                 for i in range(L.sf_policy_op_count(self.handle))]
 
     def op_pipes(self):
-        """The arithmetic of each launch: "i8x3", "i8x2", "f32", "bf16", "f16" or "valu"."""
+        """The arithmetic of each launch: "i8x3", "i8x2", "f32", "bf16", "f16", "f16x2",
+        "bf16x3" or "valu"."""
         L = load_library()
         return [L.sf_policy_op_pipe(self.handle, i).decode()
                 for i in range(L.sf_policy_op_count(self.handle))]

@@ -1528,6 +1528,7 @@ extern "C" const char* sf_policy_op_pipe(const sf_policy* handle, int i) {
     }
     case OP_FC: return p->fc_split_w && !p->bf16_path ? "bf16x3" : p->bf16_path ? mfma16 : (p->fc_wt ? "f32" : "valu");
     case OP_GRU: return p->gru_wih_t ? "valu" : p->cfg.dtype == SF_DTYPE_FP32 ? "bf16x3" : "bf16";
+    case OP_HEADS: return !p->head_split_w ? "valu" : p->cfg.dtype == SF_DTYPE_FP32 ? "bf16x3" : "bf16";
     default: return "valu";
   }
 }

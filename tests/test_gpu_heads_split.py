@@ -56,3 +56,13 @@ def test_rows_without_terms(torch_cuda):
         plain = (h[None, :] * w["pi_w"].astype(np.float64)).sum(1) + w["pi_b"]
     assert np.array_equal(np.isnan(got["logits"][17]), np.isnan(plain))
     pol.close()
+
+
+@pytest.mark.parametrize("kw,pipe", [(dict(heads=[63], rnn=64), "bf16x3"), (dict(heads=[64], rnn=64), "valu"),
+                                     (dict(heads=[7], rnn=64, dtype="bf16"), "bf16"), (dict(heads=[7], rnn=48), "valu")])
+def test_pipe_of_the_heads(torch_cuda, kw, pipe):
+    """The arithmetic that the library reports for the heads' launch (the benchmark's peak follows it)."""
+    net = dict(_BASE, fc=64, **kw)
+    pol = binding.Policy(net, wl.weights(net), max_batch=3)
+    assert pol.op_pipes()[-1] == pipe
+    pol.close()
