@@ -426,11 +426,13 @@ def appo_loss(hp, tr, want_grads=True, stream=None, out=None):
                    dvalues=torch.empty((T, N), device=d) if want_grads else None,
                    workspace=torch.empty(sf_appo_loss_workspace_bytes(cfg), dtype=torch.uint8, device=d))
     s = stream if stream is not None else torch.cuda.current_stream(d)
-    dlogits, dvalues, workspace = out["dlogits"], out["dvalues"], out["workspace"]
+    # (a buffer that is None is the library's to refuse, or to leave out)
+    vs, adv, loss, dlogits, dvalues, workspace = (out["vs"], out["adv"], out["loss"], out["dlogits"], out["dvalues"],
+                                                  out["workspace"])
     sf_appo_loss(cfg, logits.data_ptr(), actions.data_ptr(), logp_mu.data_ptr(), values.data_ptr(),
-                 rewards.data_ptr(), dones.data_ptr(), out["vs"].data_ptr(), out["adv"].data_ptr(),
-                 out["loss"].data_ptr(), None if dlogits is None else dlogits.data_ptr(),
-                 None if dvalues is None else dvalues.data_ptr(),
+                 rewards.data_ptr(), dones.data_ptr(), None if vs is None else vs.data_ptr(),
+                 None if adv is None else adv.data_ptr(), None if loss is None else loss.data_ptr(),
+                 None if dlogits is None else dlogits.data_ptr(), None if dvalues is None else dvalues.data_ptr(),
                  None if workspace is None else workspace.data_ptr(), s.cuda_stream)
     return out
 

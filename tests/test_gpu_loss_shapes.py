@@ -50,3 +50,14 @@ def test_trajectories_do_not_depend_on_their_number(torch_cuda, heads, T):
         g = _run(torch_cuda, dict(hp, N=n), part)
         for k in ("vs", "adv"):
             assert np.array_equal(g[k], full[k][:, :n]), (n, k)
+
+
+@pytest.mark.parametrize("missing", ["vs", "adv", "loss", "workspace"])
+def test_a_missing_buffer_is_refused_by_the_library(torch_cuda, missing):
+    from paper_2006_11751_amd import binding
+    hp = wl.loss_config((7,), 4, 3)
+    tr = {k: torch_cuda.from_numpy(v).cuda() for k, v in wl.trajectories(hp).items()}
+    out = dict(binding.appo_loss(hp, tr), **{missing: None})
+    with pytest.raises(binding.SfError) as e:
+        binding.appo_loss(hp, tr, out=out)
+    assert e.value.code == binding.SF_ERR_ARG
