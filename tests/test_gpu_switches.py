@@ -1,7 +1,7 @@
 """Every kernel-selection switch still gives the oracle's result: the fallback kernels
 (shape-agnostic kernels, fp32 kernels on bf16 weights, per-layer residual-encoder kernels,
-fp32-MFMA core in bf16 configurations, fp32 first convolution) are exercised on small
-networks through the C ABI.  The switches are read when a policy is created, once: a weight
+the core with unrounded features in bf16 configurations, the FC layer on the tiled fp32 kernel, fp32
+first convolution) are exercised on small networks through the C ABI.  The switches are read when a policy is created, once: a weight
 update on such a policy, made after the variable has been removed, still packs for the kernels
 chosen at create.
 """
@@ -27,8 +27,10 @@ CASES = [
     ("SF_CONV1", "fp32", STD_SMALL),
     ("SF_CONV1", "i8", STD_SMALL),
     ("SF_GEMM_TILE", "4", STD_SMALL),
-    ("SF_GRU_BM", "64", STD_SMALL),
-    ("SF_NO_RNN_PAIRS", "1", STD_SMALL),
+    ("SF_FC_TILE", "2", STD_SMALL),
+    ("SF_FC_TILE", "4", STD_SMALL),
+    ("SF_CONV1_WAVES", "100", STD_SMALL),
+    ("SF_NO_CONV1_IMAGE", "1", dict(STD_SMALL, B=2060)),  # (the frame-resident kernel is for 2048 frames and more)
     ("SF_NO_BF16_PATH", "1", STD_BF16_SMALL),
     ("SF_NO_RNN_BF16", "1", STD_BF16_SMALL),
     ("SF_CONV_BF16_TC", "2", STD_BF16_SMALL),
@@ -36,12 +38,15 @@ CASES = [
     ("SF_NO_CONV_IMAGE", "1", STD_BF16_SMALL),
     ("SF_NO_CONV12_FUSE", "1", STD_BF16_SMALL),
     ("SF_NO_RNN_BF16", "1", BY_NAME["lstm_bf16_mfma"]),
+    # 512 hidden units and more than 512 rows: the core is on k_rnn_bf16.hip without the switch
+    ("SF_NO_RNN_BF16", "1", dict(BY_NAME["lstm_bf16_mfma"], name="lstm_bf16_many_rows", B=520, rnn=512)),
     ("SF_NO_FUSED_RESNET", "1", RESNET_BF16_MID),
     ("SF_NO_RES_STAGE", "1", dict(RESNET_BF16_POW2, B=9)),
     ("SF_NO_STEM_POOL", "1", RESNET_BF16_MID),
     ("SF_NO_CONV_POOL_REGS", "1", RESNET_BF16_MID),
     ("SF_NO_PATCH_CONV", "1", RESNET_BF16_SMALL),
     ("SF_STREAM_F32", "1", RESNET_BF16_SMALL),
+    ("SF_ACT_BF16", "1", RESNET_BF16_SMALL),
 ]
 
 
