@@ -23,7 +23,8 @@ NETS = [
     dict(_BASE, name="full_mfma", fc=64, rnn=64, meas_dim=23, meas_hidden=[40, 32], heads=[3, 3, 2, 2, 2, 8, 21], index=6),
     dict(_BASE, name="full_lstm_mfma", fc=96, rnn=32, rnn_type="lstm", meas_dim=5, meas_hidden=[64], heads=[7], index=6),
     dict(_BASE, name="full_mixed", fc=64, rnn=64, meas_dim=9, meas_hidden=[17], heads=[2, 3], index=6),  # x2 not a K chunk
-    # bf16 configurations whose core runs on the 16-bit MFMA (64-wide K chunks), ragged batch of 137
+    # bf16 configurations, ragged batch of 137 (k_dense_split.hip; k_rnn_bf16.hip, for larger handles, is in
+    # test_gpu_core_bf16.py)
     dict(_BASE, name="lstm_bf16_mfma", B=137, fc=64, rnn=128, rnn_type="lstm", heads=[4, 4], index=5, dtype="bf16"),
     dict(_BASE, name="gru_bf16_mfma", B=137, fc=128, rnn=64, heads=[9], index=5, dtype="bf16"),
     dict(_BASE, name="full_bf16_mfma", B=137, fc=64, rnn=64, meas_dim=11, meas_hidden=[20, 64], heads=[3, 2], index=6,
