@@ -33,11 +33,15 @@ def test_heads(torch_cuda, ref, kw, B):
 
 
 def test_rows_without_terms(torch_cuda):
-    """A row whose state holds a NaN has NaN logits, one with an infinity the plain sums; the other
-    rows keep their bits."""
+    """A row whose state holds a NaN has NaN logits; one with a number that rounds up to an infinity in bf16,
+    in one unit, has the plain sums; the other rows keep their bits."""
     torch = torch_cuda
     net = dict(_BASE, fc=64, rnn=64, heads=[7])
     w = wl.weights(net)
+    # unit 9 keeps a large state: its z gate opens with it, and every r gate (no 0 * infinity in an n gate)
+    H, unit, most = 64, 9, np.finfo(np.float32).max
+    w["rnn_w_hh"][:H, unit] = np.abs(w["rnn_w_hh"][:H, unit])
+    w["rnn_w_hh"][H + unit, unit] = np.abs(w["rnn_w_hh"][H + unit, unit])
     pol = binding.Policy(net, w, max_batch=20)
     d = pol.device
     obs, state, done = wl.observations(net, 0, 20), wl.initial_state(net, 20), np.zeros(20, np.uint8)
@@ -45,16 +49,22 @@ def test_rows_without_terms(torch_cuda):
                                                              torch.from_numpy(done).to(d), 7, 11).items()}
     clean = run(state)
     odd = state.copy()
-    odd[3, 5], odd[17, 9] = np.nan, np.inf
+    odd[3, 5], odd[16, unit] = np.nan, most
+    odd[17] = 0.0
+    odd[17, unit] = most
     got = run(odd)
-    rest = [i for i in range(20) if i not in (3, 17)]
+    rest = [i for i in range(20) if i not in (3, 16, 17)]
     for k in got:
         assert np.array_equal(got[k][rest], clean[k][rest]), k
-    assert np.isnan(got["logits"][3]).all()
-    h = got["h_out"][17].astype(np.float64)
-    with np.errstate(all="ignore"):
-        plain = (h[None, :] * w["pi_w"].astype(np.float64)).sum(1) + w["pi_b"]
-    assert np.array_equal(np.isnan(got["logits"][17]), np.isnan(plain))
+    assert np.isnan(got["logits"][3]).all() and np.isnan(got["value"][3])
+    h = got["h_out"][[16, 17]].astype(np.float64)
+    assert np.isfinite(h).all() and np.all(h[:, unit] == most)
+    with np.errstate(all="raise"):
+        logits = h @ w["pi_w"].astype(np.float64).T + w["pi_b"]
+        value = h @ w["v_w"].astype(np.float64).ravel() + w["v_b"].ravel()
+    # one term beyond all others: its product is rounded once and the others vanish behind it
+    assert np.allclose(got["logits"][[16, 17]], logits, rtol=1e-6, atol=0)
+    assert np.allclose(got["value"][[16, 17]], value, rtol=1e-6, atol=0)
     pol.close()
 
 
