@@ -21,12 +21,11 @@ CASES = [
     ("one_sample", wl.loss_config((2,), 1, 1), 6004),
     ("exact_chunk", wl.loss_config((6,), 64, 5), 6005),
     ("large", wl.loss_config((7,), 32, 2048), 6006),
-    # 133 logits per sample: the tiles do not fit LDS, the kernel that reads memory directly runs
-    ("wide_head_direct_kernel", wl.loss_config((130, 3), 20, 5), 6007),
-    # an even number of logits (padded LDS rows, element-wise tile copies), three chunks of 64
-    # steps, and a last workgroup with 3 of its 4 trajectories
+    # 133 logits per sample (the kernel for tiles that do not fit LDS is in test_gpu_loss_shapes.py)
+    ("wide_head", wl.loss_config((130, 3), 20, 5), 6007),
+    # an even number of logits (padded LDS rows, element-wise tile copies), three chunks of 64 steps
     ("even_width_staged", wl.loss_config((60, 4), 150, 7), 6008),
-    # 32 lanes per trajectory, eight per workgroup, the last workgroup with 3; 16-byte tile copies
+    # 32 lanes per trajectory, four per workgroup, the last workgroup with 3; 16-byte tile copies
     ("short_trajectories", wl.loss_config((5, 4), 32, 19), 6010),
     ("short_trajectories_scalar_copies", wl.loss_config((5, 4), 17, 19), 6011),
     ("full_action_space_large", wl.loss_config((3, 3, 2, 2, 2, 8, 21), 32, 515), 6009),
