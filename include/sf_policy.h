@@ -177,7 +177,11 @@ int sf_policy_create(const sf_policy_config* cfg, const sf_policy_weights* weigh
  * launch) and a bf16 network takes the third digit plane.  The decision depends on the
  * parameter values only, never on the batch.  sf_policy_op_pipe tells which arithmetic a
  * launch uses ("i8x3", "i8x2", "f32", "bf16", "f16", "valu"; "f16x2": fp32 operands in two
- * scaled fp16 terms, "bf16x3": in three bf16 terms); ..._ratio returns the worst
+ * scaled fp16 terms, "bf16x3": in three bf16 terms).  "f16x2" too is admitted by the parameter
+ * values, channel by channel: what the terms lose below fp16's range has to stay under the
+ * rounding of an fp32 sum of the layer's typical terms, and that sum has to be rounded 192 times
+ * at its full size (all taps alike: 384 taps other than zero), since what two terms leave out of
+ * a product shows in a sum of few.  ..._ratio returns the worst
  * channel's E_fix / E_ref for 2 or 3 planes (0 if the layer has another shape, -1 for a
  * null handle). */
 const char* sf_policy_op_pipe(const sf_policy* p, int i); /* static storage; "" if out of range */
@@ -412,8 +416,8 @@ int sf_appo_loss(const sf_loss_config* cfg, const float* logits, const int32_t* 
 
 /* The same loss for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving or training loops, harnesses that forbid allocation.  The
- * per-trajectory partial sums (N x 16 bytes) live in an array inside the library's device
- * image, 256 KiB per GPU for as long as the process runs, so N is limited to
+ * partial sums (at most N x 16 bytes) live in an array inside the library's device image, 256 KiB
+ * per GPU for as long as the process runs, so N is limited to
  * sf_appo_loss_static_max_trajectories() = 16384; a larger N is refused with SF_ERR_SHAPE.  The
  * call allocates and frees nothing, runs on the current HIP device, and is otherwise
  * sf_appo_loss (same kernels, same bits).  All calls on one GPU share the one array, which

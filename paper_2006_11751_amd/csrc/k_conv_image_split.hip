@@ -246,7 +246,10 @@ Layout layout(int Cin, int FR, int H, int W, int Ho, int Wo) {
 
 // Which instantiation takes a layer: 0 none; 1: 4x4 on 32 channels, one frame per round in seven
 // tiles; 2: 3x3 on 64 channels, two frames per round in three tiles (four frames in five tiles waste
-// less of a tile, but leave room for one workgroup per CU).
+// less of a tile, but leave room for one workgroup per CU).  The numbers of tiles, and of pieces per
+// thread, are those of frames of 72 x 128 and their like, because a tile's place is a register and its
+// loop is unrolled; nothing else stands against other frames, which need instantiations of their
+// own (84 x 84: six and two tiles) and stay on k_gemm_mfma.hip, up to 2.7 times slower, without.
 int variant(int Cin, int ksize, int stride, int pad, int H, int W, int N) {
   if (stride != 2 || pad != 0 || (N % 64) != 0 || H < ksize || W < ksize) return 0;
   const int Ho = (H - ksize) / 2 + 1, Wo = (W - ksize) / 2 + 1;

@@ -3,8 +3,8 @@
 //
 // Arithmetic.  An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 significant bits, each
 // the rounded remainder of the one before), so x * w is the sum of nine exact products.  The six
-// largest are kept: x0w0, x0w1, x1w0, x1w1, x0w2, x2w0; what is dropped is below 2^-25 of the
-// product, i.e. less than the rounding of one fp32 addition.  They run on v_mfma_f32_16x16x32_bf16
+// largest are kept: x0w0, x0w1, x1w0, x1w1, x0w2, x2w0; what is dropped is at most 2^-23 of the
+// product and 2^-27 root mean square, less than the rounding of one fp32 addition.  They run on v_mfma_f32_16x16x32_bf16
 // with fp32 accumulators, smallest products first: 16 times the rate of the fp32 matrix
 // instructions, over six products.  One instruction adds 32 terms to an accumulator, so a sum is
 // rounded 6 times per 32 terms instead of 16 times and comes out nearer to the exact one.  In
@@ -852,10 +852,13 @@ long long split_workgroups(long long M, int n_col, int rt, int u) {
 //    512  24.0 / 40    16  / 32   12.3 / 18   19   / 16
 //   1024  62   / 85    35  / 68   25   / 38   23   / 35
 // Beyond one round two workgroups of the 32 x 2 tile share a CU (DA = DB = 1, 128 registers), so that
-// one's loads run behind the other's products.  Launch times (us, the launch's own few included)
+// one's loads run behind the other's products.  The cells in fp32 do not quite fit: the GRU spills 14
+// registers, the LSTM 20, and both read some of them back in every K step.  Launch times (us, the launch's own few included)
 // against the tile that was there, one workgroup per CU with two or three steps in flight:
 //   FC in fp32, 600 / 1024 / 2048 rows: 24 -> 21.5, 26.8 -> 24.6, 47 -> 46 (was 64 x 2)
-//   GRU 512 -> 512 in fp32, 333 / 512 rows: 21.4 -> 19.8, 22.6 -> 21.3; LSTM equal
+//   GRU 512 -> 512 in fp32, 333 / 512 rows: 21.4 -> 19.8, 22.6 -> 21.3
+//   LSTM 512 -> 512 in fp32, 300 / 400 / 512 rows: 22.6 -> 22.5, 23.2 -> 23.6, 24.0 -> 24.9; with 128
+//   measurement features more 25.7 -> 24.7, 26.4 -> 25.5, 27.5 -> 27.1: a draw, and one form for both
 //   GRU 512 -> 512 in bf16, 512 rows: 16.5 -> 13.3
 //   GRU 256 -> 256 on 16-bit features, 512 / 1000 rows: 9.4 -> 8.6, 14.0 -> 11.4
 // Within one round it is worse in fp32 (GRU at 160 rows 14.1 against 12.9), better for cells in 16 bits
@@ -963,7 +966,8 @@ bool dense_fc_small(int M, int N) { return split_workgroups(M, N / 16, 4, 2) <= 
 // Cells: up to two rounds of the 32-row tile.  Beyond, cell_tile_kernel in fp32 (GRU 512 -> 512 at
 // 512 rows 17.5 against 21 us, at 1024 rows 38 against 25) and k_rnn_bf16.hip in bf16 (at 512 rows 10
 // against 20 us, at 1024 rows 24 against 21; 256 -> 256 at 1000 rows 8 against 14).  The kernels'
-// sums run in different orders, so that this is settled once, by the largest batch.
+// sums run in different orders (and the state enters k_rnn_bf16.hip in two terms), so that this is
+// settled once, by the largest batch.
 bool dense_cell_small(int M, int H) { return split_workgroups(M, H / 8, 2, 2) <= 512; }
 bool dense_cell_tile_supported(int I1, int I2, int H) {
   return I1 > 0 && (I1 % 128) == 0 && (I2 % 128) == 0 && H > 0 && (H % 128) == 0;
