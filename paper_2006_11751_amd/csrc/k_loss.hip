@@ -668,7 +668,7 @@ int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const flo
   return SF_OK;
 }
 
-// Scratch of the entry point that allocates nothing: the per-trajectory partial sums.  One copy
+// Scratch of the entry point that allocates nothing: the partial sums.  One copy
 // of this array exists on every GPU the library is loaded on, at an address of its own; host
 // code never uses the symbol's name as an address but the pointer that hipGetSymbolAddress
 // returns for the current device, looked up once per device.
