@@ -43,12 +43,13 @@ def test_both_kernels_round_the_features(torch_cuda, net):
         assert np.linalg.norm(a - b) <= 3e-4 * np.linalg.norm(b), k
 
 
-def test_rounding_before_or_inside_the_core(torch_cuda, monkeypatch):
+@pytest.mark.parametrize("rnn_type", ["gru", "lstm"])
+def test_rounding_before_or_inside_the_core(torch_cuda, monkeypatch, rnn_type):
     """The FC layer hands over bf16 numbers, or (by the switch) fp32 ones that the core rounds: the
-    same bits."""
-    net = wl.network(2, name="features", obs=(3, 36, 64), fc=128, rnn=128)
+    same bits, in each of its tiles (16 x 8, 32 x 8, 32 x 16)."""
+    net = wl.network(2, name="features", obs=(3, 36, 64), fc=128, rnn=128, rnn_type=rnn_type)
     w = wl.weights(net)
-    for B in (1, 40, 300):
+    for B in (1, 40, 300, 600):
         pol = binding.Policy(net, w, max_batch=B)
         a = _run(torch_cuda, pol, net, B)
         pol.close()
