@@ -539,6 +539,10 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
         a.out_buf = b.out_buf;
         p->ops.erase(p->ops.begin() + 1);
       }
+      // fp32: the first two layers run as one launch while the parameters admit both to their split
+      // arithmetic (see fuses_conv12); the operations stay two
+      p->conv12_split = cfg->n_conv >= 2 && !sw.no_conv12_fuse && !p->bf16_path && p->convs[0].ipk && p->convs[1].ssc &&
+                        conv12_split_supported(cfg->obs_c, cfg->obs_h, cfg->obs_w, cfg->conv[0], cfg->conv[1]);
     } else {
       // buffer roles rotate: x holds the stage state, t and u are scratch
       int x = 0, t = 1, u = 2;
@@ -1131,6 +1135,12 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
              float* value, float* h_out, float* logits_opt, const int32_t* ids, float* h_table,
              int n_env, hipStream_t st, unsigned parts = PART_ALL, size_t feat_row = 0);
 
+// The first two convolutions of an fp32 plain stack in one launch, with the present parameters (16-byte
+// aligned frames).
+bool fuses_conv12(const Policy* p) {
+  return p->conv12_split && p->convs[0].impl == CONV1_U8_I8 && p->convs[1].impl == CONV_IMAGE_SPLIT;
+}
+
 bool misaligned(const void* q, uintptr_t a) { return (reinterpret_cast<uintptr_t>(q) & (a - 1)) != 0; }
 
 }  // namespace
@@ -1215,6 +1225,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
   const sf_policy_config& c = p->cfg;
   auto buf = [&](int i) -> float* { return i < 0 ? nullptr : p->act[i]; };
   const bool timing = p->timing && parts == PART_ALL;
+  const bool conv12 = fuses_conv12(p) && !misaligned(obs, 16);
   if (timing) SF_LAUNCH(hipEventRecord(p->events[0], st));
   for (size_t i = 0; i < p->ops.size(); ++i) {
     const Op& op = p->ops[i];
@@ -1241,6 +1252,10 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
               }
               break;
             }
+            if (conv12) {
+              SF_LAUNCH(launch_conv12_split(L, p->convs[1], B, obs, buf(op.out_buf), buf(p->ops[1].out_buf), st));
+              break;
+            }
             SF_LAUNCH(launch_conv1_i8(L, B, obs, L.ipk, L.spk, L.bpk8, buf(op.out_buf), p->bf16_path,
                                       L.planes, p->conv1_waves, p->conv1_image, st));
             break;
@@ -1254,6 +1269,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
                                        op.conv + 1, st));
             break;
           case CONV_IMAGE_SPLIT:
+            if (conv12 && op.conv == 1) break;  // (in the first layer's launch)
             SF_LAUNCH(launch_conv_image_split((const float*)in, L.wsp, L.ssc, L.wpk, L.bias, buf(op.out_buf), B, L.H,
                                               L.W, L.cin, L.k, L.cout, st));
             break;
@@ -1466,6 +1482,7 @@ extern "C" const char* sf_policy_op_kernel(const sf_policy* handle, int i) {
   switch (op.kind) {
     case OP_CONV:
       if (op.mid_buf >= 0) return "conv12_fused";
+      if (op.conv == 0 && fuses_conv12(p)) return "conv12_split";
       switch (p->convs[op.conv].impl) {
         case CONV1_U8_MFMA: return "conv1_mfma";
         case CONV_GEMM_MFMA: return "gemm_mfma";

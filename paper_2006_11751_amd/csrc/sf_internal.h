@@ -124,6 +124,7 @@ struct Policy {
   bool core_tile = false;           // ... the core on its kernel for many rows
   bool core_round = false;          // the step's core takes its features as bf16 numbers
   double conv1_ratio2 = 0, conv1_ratio3 = 0;  // admission test of the first convolution's digit planes
+  bool conv12_split = false;  // fp32: the first two convolutions may run as one launch (k_conv12_split.hip)
   int conv1_image = 1;      // first convolution: frame-resident variant where it applies
   int fc_out_bf16 = 0;      // the FC kernel hands bf16 values to the 16-bit recurrent kernel
   int conv_bf16_tc = 0;     // 16-bit conv kernel: 0 = channel blocks per workgroup by grid size, 1 / 2 forced
@@ -300,6 +301,10 @@ double conv_image_split_pack(const float* w, int cout, int cin, int k, const std
 hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const float* scale, const float* w32,
                                    const float* bias, float* out, int B, int H, int W, int Cin, int ksize, int N,
                                    hipStream_t st);
+// the first two convolutions of an fp32 plain stack in one launch (k_conv12_split.hip)
+bool conv12_split_supported(int cin, int H, int W, const sf_conv& c1, const sf_conv& c2);
+hipError_t launch_conv12_split(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs, float* mid, float* out,
+                               hipStream_t st);
 bool gemm_mfma_supported(int Cin, int ksize, int pad, int N);
 int gemm_mfma_pick_tile(long long M, int N, int K, int seg_len);
 hipError_t launch_gemm_mfma(const float* A, const float* Wt, const float* bias, float* out, int B,

@@ -1,0 +1,42 @@
+"""The first two convolutions of an fp32 network in one launch (k_conv12_split.hip) against the two separate
+launches and the oracle: one and several frames per workgroup, a frame height that leaves rows over, frames
+at an address that only the separate kernels take."""
+import numpy as np
+import pytest
+
+from paper_2006_11751_amd import binding, workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("height", [72, 75])
+def test_one_launch_and_two(torch_cuda, ref, monkeypatch, height):
+    torch = torch_cuda
+    net = wl.network(1, fc=64, rnn=64, name="conv12_split", obs=(3, height, 128))
+    w = wl.weights(net)
+    B = 600  # two and three frames per workgroup
+    one = binding.Policy(net, w, max_batch=B)
+    with monkeypatch.context() as m:
+        m.setenv("SF_NO_CONV12_FUSE", "1")
+        two = binding.Policy(net, w, max_batch=B)
+    assert one.op_kernels()[0] == "conv12_split" and two.op_kernels()[0] == "conv1_i8"
+    o_, s_, d_ = wl.observations(net, 0, B), wl.initial_state(net, B), wl.done_mask(net, 0, B)
+    raw = torch.empty(o_.size + 4, dtype=torch.uint8, device="cuda")
+    shifted = raw[4:].view(o_.shape).copy_(torch.from_numpy(o_))
+    obs, st, dn = (torch.from_numpy(a).cuda() for a in (o_, s_, d_))
+    step = lambda pol, n, x: {k: v.cpu().numpy() for k, v in pol.step(x[:n], st[:n], dn[:n], 7, 11).items()}
+    full, apart, moved = step(one, B, obs), step(two, B, obs), step(one, B, shifted)
+    rows = np.array([0, 1, 255, 256, 257, 511, 512, 599])
+    want = ref.policy_step(net, w, o_[rows], s_[rows], d_[rows], 7, 11)
+    for k in ("logits", "value", "h_out"):
+        parity.assert_close(k, full[k][rows], want[k], 1e-4)
+        # the same products in another order: a few roundings of an fp32 sum of 512 terms, then of the rest
+        assert np.abs(full[k] - apart[k]).max() <= 2e-5 * np.abs(apart[k]).max(), k
+        assert np.array_equal(moved[k], apart[k]), k  # (the separate kernels)
+    for n in (257, 256, 1):  # a frame's bits do not depend on the batch
+        part = step(one, n, obs)
+        for k in full:
+            assert np.array_equal(part[k], full[k][:n]), (n, k)
+    one.close()
+    two.close()
