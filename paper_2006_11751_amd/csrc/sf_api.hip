@@ -279,6 +279,7 @@ Switches read_switches() {
   sw.no_stem_pool = env_set("SF_NO_STEM_POOL");
   sw.no_conv_pool_regs = env_set("SF_NO_CONV_POOL_REGS");
   sw.no_rnn_seq = env_set("SF_NO_RNN_SEQ");
+  sw.core_seq_limit = env_int("SF_CORE_SEQ_LIMIT");
   sw.act_bf16 = env_set("SF_ACT_BF16");
   sw.stream_f32 = env_set("SF_STREAM_F32");
   return sw;
@@ -828,6 +829,7 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   for (int i = 0; i < 3; ++i)
     p->act[i] = i < n_act ? (float*)bld.dev_alloc(act_row_bytes * cfg->max_batch)
                           : nullptr;
+  p->seq_words = (unsigned*)bld.dev_alloc(256);
   p->trash = (float*)bld.dev_alloc(256);
   p->fc_out = (float*)bld.dev_alloc(sizeof(float) * (size_t)cfg->fc_dim * cfg->max_batch);
   p->h_new = (float*)bld.dev_alloc(sizeof(float) * (size_t)p->state_dim * cfg->max_batch);
@@ -1445,12 +1447,26 @@ extern "C" int sf_policy_unroll(sf_policy* handle, int32_t T, int32_t N, const u
   // the encoder on all T * N frames at once (their features stay in the handle's workspace) ...
   int rc = run_step(p, rows, obs, meas, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr,
                     nullptr, nullptr, 0, st, PART_ENCODER);
-  // ... the core one time step after the other, each reading the state rows the previous wrote ...
-  for (int32_t t = 0; t < T && rc == SF_OK; ++t) {
-    const size_t r = (size_t)t * N;
-    const float* h_prev = t == 0 ? h0 : h_seq + (r - N) * p->state_dim;
-    rc = run_step(p, N, nullptr, nullptr, h_prev, done + r, 0, 0, nullptr, nullptr, nullptr,
-                  h_seq + r * p->state_dim, nullptr, nullptr, nullptr, 0, st, PART_CORE, r);
+  // ... the core over all steps in one launch ...
+  const int x_type = p->fc_out_bf16 ? 1 : 0;
+  if (rc == SF_OK && T > 1 && p->rnn_split_w && !p->sw.no_rnn_seq &&
+      core_seq_supported(c.fc_dim, p->meas_out_dim, c.rnn_dim, x_type)) {
+    const int limit = p->sw.core_seq_limit ? p->sw.core_seq_limit : 1 << 17;
+    hipError_t e = launch_core_seq(c.rnn_type == SF_RNN_LSTM, T, N, c.fc_dim, p->meas_out_dim, c.rnn_dim, p->fc_out, x_type,
+                                   p->n_meas ? p->meas_buf[p->n_meas - 1] : nullptr, h0, done, p->rnn_split_w,
+                                   c.dtype == SF_DTYPE_BF16 ? 1 : 3, p->gru_bih, p->gru_bhh, h_seq, p->seq_words, limit, st);
+    if (e != hipSuccess) {
+      set_error("sf_policy_unroll: launch failed: %s", hipGetErrorString(e));
+      rc = SF_ERR_DEVICE;
+    }
+  } else {
+    // ... or one time step after the other, each reading the state rows the previous wrote ...
+    for (int32_t t = 0; t < T && rc == SF_OK; ++t) {
+      const size_t r = (size_t)t * N;
+      const float* h_prev = t == 0 ? h0 : h_seq + (r - N) * p->state_dim;
+      rc = run_step(p, N, nullptr, nullptr, h_prev, done + r, 0, 0, nullptr, nullptr, nullptr,
+                    h_seq + r * p->state_dim, nullptr, nullptr, nullptr, 0, st, PART_CORE, r);
+    }
   }
   // ... and the heads on all T * N states at once (no action is drawn)
   if (rc == SF_OK)

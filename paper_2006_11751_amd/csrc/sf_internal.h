@@ -76,6 +76,7 @@ struct Switches {
   bool no_stem_pool = false;     // SF_NO_STEM_POOL
   bool no_conv_pool_regs = false;  // SF_NO_CONV_POOL_REGS
   bool no_rnn_seq = false;         // SF_NO_RNN_SEQ
+  int core_seq_limit = 0;          // SF_CORE_SEQ_LIMIT (0 = default; negative: the exchange is given up at once)
   bool act_bf16 = false;         // SF_ACT_BF16
   bool stream_f32 = false;       // SF_STREAM_F32
 };
@@ -149,6 +150,7 @@ struct Policy {
   size_t act_elems;
   float* fc_out;      // dev [max_batch][fc_dim]
   float* h_new;       // dev [max_batch][state_dim]: new states of an indexed step before the scatter
+  unsigned* seq_words;  // dev, counters of the core over time (k_core_seq.hip)
   float* trash;       // dev, 64 floats: target of stores that fall outside a tensor
   std::vector<void*> allocations;
   std::vector<size_t> alloc_bytes;   // size of each allocation, in allocation order
@@ -276,6 +278,11 @@ hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const f
 hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);
+// the core over all steps of N trajectories in one launch (k_core_seq.hip)
+bool core_seq_supported(int I1, int I2, int H, int x_type);
+hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
+                           const float* h0, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
+                           const float* b_hh, float* h_seq, unsigned* words, int limit, hipStream_t st);
 bool rnn_bf16_supported(int I1, int I2, int H);
 void rnn_bf16_pack(const float* w, size_t n, std::vector<uint16_t>& out);
 hipError_t launch_rnn_bf16(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16,

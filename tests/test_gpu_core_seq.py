@@ -1,0 +1,79 @@
+"""The recurrent core over all time steps in one launch (k_core_seq.hip): every number of K steps per wave,
+one and two row tiles per workgroup, ragged rows, more workgroups than the chip has CUs, states that are
+not finite, and the pass that gives up its exchange and is computed again without one."""
+import numpy as np
+import pytest
+
+from paper_2006_11751_amd import binding, workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+BASE = dict(obs=(3, 36, 64), convs=[(16, 8, 4, 0), (32, 4, 2, 0)], p_done=0.2)
+# name, T, N, network: features + state -> K steps per wave (32 numbers each, eight waves)
+CASES = {
+    "gru-1-1": (5, 20, dict(fc=96, rnn=32)),
+    "gru-1-1-two-tiles": (4, 300, dict(fc=128, rnn=128)),
+    "lstm-2-1": (6, 7, dict(fc=288, rnn=64, rnn_type="lstm")),
+    "gru-2-2-rounds": (4, 132, dict(fc=512, rnn=512)),
+    "lstm-2-2": (5, 12, dict(fc=512, rnn=288, rnn_type="lstm")),
+    "gru-3-2": (5, 12, dict(fc=512, rnn=320, meas_dim=23, meas_hidden=[64, 128])),
+    "bf16-gru-2-2-two-tiles": (4, 132, dict(fc=512, rnn=512, dtype="bf16")),
+    "bf16-lstm-1-1": (5, 24, dict(fc=128, rnn=96, rnn_type="lstm", dtype="bf16")),
+}
+
+
+def _pass(torch, net, w, T, N, env, monkeypatch, h0=None):
+    with monkeypatch.context() as m:
+        for k, v in env.items():
+            m.setenv(k, v)
+        pol = binding.Policy(net, w, max_batch=T * N)
+    obs, h, done, meas = wl.trajectory_inputs(net, T, N)
+    h = h if h0 is None else h0
+    out = pol.unroll(*(torch.from_numpy(a).cuda() for a in (obs, h, done)),
+                     meas=None if meas is None else torch.from_numpy(meas).cuda())
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in out.items()}
+    pol.close()
+    return got, (obs, h, done, meas)
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_one_launch_for_all_steps(torch_cuda, ref, monkeypatch, name):
+    torch = torch_cuda
+    T, N, kw = CASES[name]
+    net = wl.network(0, **dict(BASE, name=name, **kw))
+    w = wl.weights(net)
+    got, (obs, h0, done, meas) = _pass(torch, net, w, T, N, {}, monkeypatch)
+    rtol = parity.RTOL[net["dtype"]]
+    sel = np.unique(np.array([0, N // 3, N - 1]))
+    want = ref.policy_unroll(net, w, obs[:, sel], h0[sel], done[:, sel],
+                             meas=None if meas is None else meas[:, sel])
+    for k in ("h_seq", "logits", "value"):
+        parity.assert_close(k, got[k][:, sel], want[k], rtol)
+    # every element: a launch per step, and the pass that gives up; both add the same terms in other orders
+    for env in ({"SF_NO_RNN_SEQ": "1"}, {"SF_CORE_SEQ_LIMIT": "-1"}):
+        other, _ = _pass(torch, net, w, T, N, env, monkeypatch)
+        for k in ("h_seq", "logits", "value"):
+            parity.assert_close(k, got[k], other[k], rtol)
+
+
+@pytest.mark.parametrize("kind", ["gru", "lstm"])
+def test_states_that_are_not_finite(torch_cuda, monkeypatch, kind):
+    """A row that starts with an infinity, a NaN or the NaN that marks a state as still to come: the same
+    kind of number everywhere as with a launch per step, and no other row is touched."""
+    torch = torch_cuda
+    T, N = 4, 24
+    net = wl.network(0, **dict(BASE, name="odd_" + kind, fc=96, rnn=64, rnn_type=kind, p_done=0.0))
+    w = wl.weights(net)
+    h0 = wl.trajectory_inputs(net, T, N)[1].copy()
+    h0[3, 5] = np.inf
+    h0[9, 60] = np.nan
+    h0.view(np.uint32)[17, :] = 0xFFFFFFFF
+    got, _ = _pass(torch, net, w, T, N, {}, monkeypatch, h0)
+    other, _ = _pass(torch, net, w, T, N, {"SF_NO_RNN_SEQ": "1"}, monkeypatch, h0)
+    for k in got:
+        assert np.array_equal(np.isnan(got[k]), np.isnan(other[k])), k
+        parity.assert_close(k, np.nan_to_num(got[k]), np.nan_to_num(other[k]), 1e-4)
+    rows = [r for r in range(N) if r not in (3, 9, 17)]
+    assert np.isfinite(got["h_seq"][:, rows]).all()
