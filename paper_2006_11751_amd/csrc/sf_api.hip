@@ -1449,8 +1449,8 @@ extern "C" int sf_policy_unroll(sf_policy* handle, int32_t T, int32_t N, const u
                     nullptr, nullptr, 0, st, PART_ENCODER);
   // ... the core over all steps in one launch ...
   const int x_type = p->fc_out_bf16 ? 1 : 0;
-  if (rc == SF_OK && T > 1 && p->rnn_split_w && !p->sw.no_rnn_seq &&
-      core_seq_supported(c.fc_dim, p->meas_out_dim, c.rnn_dim, x_type)) {
+  if (rc == SF_OK && p->rnn_split_w && !p->sw.no_rnn_seq &&
+      core_seq_supported(T, N, c.fc_dim, p->meas_out_dim, c.rnn_dim, x_type)) {
     const int limit = p->sw.core_seq_limit ? p->sw.core_seq_limit : 1 << 17;
     hipError_t e = launch_core_seq(c.rnn_type == SF_RNN_LSTM, T, N, c.fc_dim, p->meas_out_dim, c.rnn_dim, p->fc_out, x_type,
                                    p->n_meas ? p->meas_buf[p->n_meas - 1] : nullptr, h0, done, p->rnn_split_w,

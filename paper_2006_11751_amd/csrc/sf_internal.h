@@ -279,7 +279,7 @@ hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void*
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);
 // the core over all steps of N trajectories in one launch (k_core_seq.hip)
-bool core_seq_supported(int I1, int I2, int H, int x_type);
+bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type);
 hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                            const float* h0, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                            const float* b_hh, float* h_seq, unsigned* words, int limit, hipStream_t st);

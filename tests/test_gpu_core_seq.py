@@ -13,12 +13,13 @@ BASE = dict(obs=(3, 36, 64), convs=[(16, 8, 4, 0), (32, 4, 2, 0)], p_done=0.2)
 # name, T, N, network: features + state -> K steps per wave (32 numbers each, eight waves)
 CASES = {
     "gru-1-1": (5, 20, dict(fc=96, rnn=32)),
-    "gru-1-1-two-tiles": (4, 300, dict(fc=128, rnn=128)),
+    "gru-1-1-two-tiles": (4, 500, dict(fc=128, rnn=128)),
     "lstm-2-1": (6, 7, dict(fc=288, rnn=64, rnn_type="lstm")),
-    "gru-2-2-rounds": (4, 132, dict(fc=512, rnn=512)),
+    "gru-2-2-two-tiles": (4, 116, dict(fc=512, rnn=512)),
     "lstm-2-2": (5, 12, dict(fc=512, rnn=288, rnn_type="lstm")),
-    "gru-3-2": (5, 12, dict(fc=512, rnn=320, meas_dim=23, meas_hidden=[64, 128])),
-    "bf16-gru-2-2-two-tiles": (4, 132, dict(fc=512, rnn=512, dtype="bf16")),
+    "gru-3-2-two-rounds": (5, 120, dict(fc=512, rnn=512, meas_dim=23, meas_hidden=[64, 128])),
+    "bf16-gru-2-2-two-tiles": (4, 124, dict(fc=512, rnn=512, dtype="bf16")),
+    "one-launch-per-step": (3, 20, dict(fc=96, rnn=32)),
     "bf16-lstm-1-1": (5, 24, dict(fc=128, rnn=96, rnn_type="lstm", dtype="bf16")),
 }
 
