@@ -118,9 +118,11 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
   float* bias_lds = (float*)(lds + 2 * img_bytes);  // [n_convs][32]: a convolution's first MFMA
                                                     // must not wait for a load from memory
 
-  // both images start as zeros: the ring is never written again
-  for (int i = tid; i < 2 * img_bytes / 16; i += kNT) ((u32x4*)lds)[i] = u32x4{0u, 0u, 0u, 0u};
-  for (int i = tid; i < g.n_convs * 32; i += kNT) bias_lds[i] = g.bias[i >> 5][i & 31];
+  // both images start as zeros: the ring is never written again (called behind the first requests)
+  auto clear = [&]() {
+    for (int i = tid; i < g.n_convs * 32; i += kNT) bias_lds[i] = g.bias[i >> 5][i & 31];
+    for (int i = tid; i < 2 * img_bytes / 16; i += kNT) ((u32x4*)lds)[i] = u32x4{0u, 0u, 0u, 0u};
+  };
 
   // this thread's pieces: LDS byte offset of piece tid + k * kNT (past the end: piece 0, unused)
   // (shifts and masks: computed where it is used rather than kept in registers)
@@ -449,9 +451,11 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     if constexpr (resident) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) load_bank(c < g.n_convs ? c : 0, wk[c]);
+      clear();
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the banks (and the first frame) have arrived
     } else {
       load_bank(0, wA);
+      clear();
     }
     __syncthreads();  // zeros in place
     for (; b < g.B; b += gridDim.x) {
@@ -506,6 +510,7 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
   int b = blockIdx.x;
   load_frame(b, xs);
   load_bank(0, wA);
+  clear();
   __syncthreads();  // zeros in place
   for (; b < n_groups; b += gridDim.x) {
 #pragma unroll
@@ -557,6 +562,203 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
   }
 }
 
+// The same for 32 channels, up to two blocks, with the filter banks in LDS too.  In the kernel above a
+// wave takes its next filter bank (18 KB, the same for all eight) from the caches between two
+// convolutions: 147 KB per convolution through the CU's one port, 1.4 k cycles to issue and as much again at
+// the barriers, of 27 k per frame at 18 x 32.  Here the banks wait in LDS (18 KB each; the images without
+// padding, 64 bytes per pixel, the 16-byte pieces of a pixel exchanged by the pixel's column so that 16
+// neighbouring pixels read different banks), a convolution's fragments are read beside the pixels', and
+// all RT tiles of a wave are computed together, so that a fragment is used RT times and not kept.
+// The residual stream stays in registers in the accumulator layout, like the 16-channel stream above: the
+// rows of the weights are dealt so that a lane's 16 accumulators are 16 neighbouring channels (32 bytes: two
+// pieces) of its pixel, conv_b adds to them and writes relu of the sum for the next block: no pass of its
+// own for the sum, one barrier fewer per block.
+// Cycles per frame and launch times: see launch_res_stage.
+template <int LW, int RT>
+__global__ __launch_bounds__(kNT, 2) void res_stage32_kernel(StageArgs g) {
+  constexpr int W = 1 << LW, PIX = 64, ROW = (W + 2) * PIX, S = 18;
+  auto swz = [](int col) { return ((col >> 2) & 3) << 4; };
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 31, lh = lane >> 5;
+  const int HS = g.F * (g.H + 1) - 1;  // rows of the stack
+  const int n_tiles = (HS * W + 31) >> 5;
+  const int img_bytes = (((n_tiles << 5) + W - 1) / W + 2) * ROW;
+  unsigned char* const X = lds;
+  unsigned char* const T = lds + img_bytes;
+  u32x4* const bank = (u32x4*)(lds + 2 * img_bytes);           // [n_convs][S][64]
+  float* const bias_lds = (float*)(bank + g.n_convs * S * 64);  // [n_convs][32]
+
+  // accumulator v = 4 a + u of lane half h is row 8 a + 4 h + u of the product: channel 16 h + 4 a + u
+  // (all requests ahead of the first store: one trip to memory)
+  constexpr int NB = 4 * S * 64 / kNT;
+  u32x4 banks[NB];
+  const int n_bank = g.n_convs * S * 64;
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int i = min(tid + kNT * j, n_bank - 1), row = i & 31, ch = 16 * ((row >> 2) & 1) + 4 * (row >> 3) + (row & 3);
+    banks[j] = g.w[i / (S * 64)][(i % (S * 64) & ~31) + ch];
+  }
+  auto store_banks = [&]() {
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      if (tid + kNT * j < n_bank) bank[tid + kNT * j] = banks[j];
+  };
+
+  // this lane's pixel of tile t: image pixel (y, x) is ring pixel (y + 1, x + 1)
+  const int lane_row = (li >> LW) * ROW, lane_col = li & (W - 1);
+  int lane_q[3][2], lane_o[2];
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      lane_q[q][s] = lane_row + (lane_col + q) * PIX + ((32 * s + 16 * lh) ^ swz(lane_col + q));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    lane_o[i] = lane_row + ROW + (lane_col + 1) * PIX + ((32 * lh + 16 * i) ^ swz(lane_col + 1));
+  auto tile_off = [&](int t) {
+    if (LW >= 5) return ((t << 5) >> LW) * ROW + ((t << 5) & (W - 1)) * PIX;
+    return (t * (32 >> LW)) * ROW;
+  };
+  const int n_groups = (g.B + g.F - 1) / g.F;
+  const int own = min((n_tiles - wave + kNW - 1) / kNW, RT);  // tiles wave, wave + 8, ...
+  // does the lane's pixel of round r exist in stack b (no separating row, no missing frame), and where
+  // its 32 bytes lie in the stack's memory
+  auto place = [&](int r, int b, bool& ok) {
+    int t = wave + kNW * r;
+    asm volatile("" : "+s"(t));  // (opaque: computed where it is used, not kept for all rounds)
+    const int ys = ((t << 5) >> LW) + (li >> LW), col = ((t << 5) & (W - 1)) + lane_col;
+    const int f = (ys > g.H) + (ys > 2 * g.H + 1) + (ys > 3 * g.H + 2);
+    const int y = ys - f * (g.H + 1);
+    ok = r < own && y < g.H && f < g.F && b * g.F + f < g.B;
+    return ok ? (uint32_t)(((f * g.H + y) * W + col) * PIX + 32 * lh) : 0u;
+  };
+  const size_t stack_bytes = (size_t)g.F * g.H * W * PIX;
+
+  u32x4 x[RT][2], nx[RT][2];
+  auto load_tile = [&](int r, int b, u32x4 (&dst)[2]) __attribute__((always_inline)) {
+    const unsigned char* src = (const unsigned char*)g.x + (size_t)b * stack_bytes;
+    bool ok;
+    const uint32_t at = place(r, b, ok);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) dst[i] = *(const u32x4*)(src + at + 16 * i);
+  };
+
+  // a convolution over the wave's N tiles; done(r, accumulators)
+  auto conv = [&](auto cnt, int k, const unsigned char* src, auto done) __attribute__((always_inline)) {
+    constexpr int N = decltype(cnt)::value;
+    f32x16 acc[N];
+    const unsigned char* base[N];
+    {
+      f32x16 a;
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4 bv = *(const f32x4*)(bias_lds + 32 * k + 16 * lh + 4 * q4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[4 * q4 + u] = bv[u];
+      }
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        acc[n] = a;
+        base[n] = src + tile_off(wave + kNW * n);
+      }
+    }
+    const u32x4* w = bank + k * (S * 64) + lane;
+    // step: filter tap step / 2, 16 input channels step % 2; fragments two steps ahead
+    u32x4 wf[2], pf[2][N];
+    auto request = [&](int step, int n) __attribute__((always_inline)) {
+      const int tap = step / 2;
+      pf[step & 1][n] = *(const u32x4*)(base[n] + lane_q[tap % 3][step % 2] + (tap / 3) * ROW);
+    };
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      wf[d] = w[d * 64];
+#pragma unroll
+      for (int n = 0; n < N; ++n) request(d, n);
+    }
+#pragma unroll
+    for (int step = 0; step < S; ++step) {
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, wf[step & 1]),
+                                                        __builtin_bit_cast(f16x8, pf[step & 1][n]), acc[n], 0, 0, 0);
+        if (step + 2 < S) request(step + 2, n);
+        if (n == N - 1 && step + 2 < S) wf[step & 1] = w[(step + 2) * 64];
+        __builtin_amdgcn_sched_barrier(0);  // (left alone, the scheduler sinks each read to its use)
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      u32x4 v[2];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e / 4][e % 4] = pk_f16(acc[n][2 * e], acc[n][2 * e + 1]);
+      done(n, v);
+    }
+  };
+  auto conv_any = [&](int k, const unsigned char* src, auto done) __attribute__((always_inline)) {
+    if constexpr (RT >= 3) {
+      if (own == 3) return conv(std::integral_constant<int, 3>{}, k, src, done);
+    }
+    if constexpr (RT >= 2) {
+      if (own == 2) return conv(std::integral_constant<int, 2>{}, k, src, done);
+    }
+    if (own == 1) conv(std::integral_constant<int, 1>{}, k, src, done);
+  };
+  auto put = [&](unsigned char* image, int r, int b, const u32x4 (&v)[2]) __attribute__((always_inline)) {
+    bool ok;
+    place(r, b, ok);
+    if (!ok) return;
+    unsigned char* o = image + tile_off(wave + kNW * r);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *(u32x4*)(o + lane_o[i]) = relu8(v[i]);
+  };
+
+  const int stride = (int)gridDim.x;
+  int b = blockIdx.x;
+#pragma unroll
+  for (int r = 0; r < RT; ++r) load_tile(r, b, x[r]);
+#pragma unroll
+  for (int r = 0; r < RT; ++r) load_tile(r, min(b + stride, n_groups - 1), nx[r]);
+  for (int i = tid; i < 2 * img_bytes / 16; i += kNT) ((u32x4*)lds)[i] = u32x4{0u, 0u, 0u, 0u};
+  for (int i = tid; i < g.n_convs * 32; i += kNT) bias_lds[i] = g.bias[i >> 5][i & 31];
+  store_banks();
+  __syncthreads();  // zeros, banks and biases in place
+#pragma unroll
+  for (int r = 0; r < RT; ++r) put(X, r, b, x[r]);
+  __syncthreads();
+  for (; b < n_groups; b += stride) {
+    // (no stack left: the last one again, for no use)
+    const int next = min(b + stride, n_groups - 1), after = min(b + 2 * stride, n_groups - 1);
+    unsigned char* dst = (unsigned char*)g.out + (size_t)b * stack_bytes;
+    for (int k = 0; k < g.n_convs; k += 2) {
+      conv_any(k, X, [&](int r, const u32x4 (&v)[2]) __attribute__((always_inline)) { put(T, r, b, v); });
+      __syncthreads();
+      const bool more = k + 2 < g.n_convs;
+      conv_any(k + 1, T, [&](int r, const u32x4 (&v)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[r][i][e] = pk_add(x[r][i][e], v[i][e]);
+        if (!more) {
+          // the tile leaves, the next stack's takes its place (X is not read in this convolution), and the one
+          // after that is asked for
+          bool ok;
+          const uint32_t at = place(r, b, ok);
+          if (ok)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) *(u32x4*)(dst + at + 16 * i) = g.relu_out ? relu8(x[r][i]) : x[r][i];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) x[r][i] = nx[r][i];
+          load_tile(r, after, nx[r]);
+        }
+        put(X, r, more ? b : next, x[r]);
+      });
+      __syncthreads();  // X complete for the next block or the next stack
+    }
+  }
+}
+
 // (H: rows of the stack)
 size_t stage_lds_bytes(int c, int H, int W) {
   const int pitch = c == 16 ? 32 : 80;
@@ -579,6 +781,34 @@ hipError_t launch_stage_r(const StageArgs& g, size_t lds, hipStream_t st) {
   const int blocks = groups < 256 ? groups : 256;
   kern<<<blocks, kNT, lds, st>>>(g);
   return hipGetLastError();
+}
+
+// 32 channels with the filter banks in LDS: tiles per wave, 0 where it does not take the shape
+int stage32_rounds(int H, int W, int n_convs) {
+  const int n_tiles = (H * W + 31) / 32, rows = (n_tiles * 32 + W - 1) / W + 2;
+  const size_t lds = 2 * (size_t)rows * (W + 2) * 64 + n_convs * (18 * 1024 + 32 * sizeof(float));
+  const int rounds = (n_tiles + kNW - 1) / kNW;
+  return n_convs <= 4 && rounds <= 3 && lds <= 160 * 1024 ? rounds : 0;
+}
+template <int LW, int RT>
+hipError_t launch_stage32(const StageArgs& g, hipStream_t st) {
+  auto kern = res_stage32_kernel<LW, RT>;
+  static std::once_flag once;
+  static hipError_t attr_status = hipSuccess;
+  std::call_once(once, [&] {
+    attr_status = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  });
+  if (attr_status != hipSuccess) return attr_status;
+  constexpr int W = 1 << LW;
+  const int n_tiles = ((g.F * (g.H + 1) - 1) * W + 31) / 32, rows = (n_tiles * 32 + W - 1) / W + 2;
+  const size_t lds = 2 * (size_t)rows * (W + 2) * 64 + g.n_convs * (18 * 1024 + 32 * sizeof(float));
+  const int groups = (g.B + g.F - 1) / g.F;
+  kern<<<groups < 256 ? groups : 256, kNT, lds, st>>>(g);  // one workgroup per CU, each walking its share
+  return hipGetLastError();
+}
+template <int LW>
+hipError_t launch_stage32(const StageArgs& g, int rounds, hipStream_t st) {
+  return rounds == 1 ? launch_stage32<LW, 1>(g, st) : rounds == 2 ? launch_stage32<LW, 2>(g, st) : launch_stage32<LW, 3>(g, st);
 }
 
 template <int C, int LW, int PPT>
@@ -669,6 +899,11 @@ hipError_t launch_res_stage(const void* x, void* out, const uint16_t* const* wpk
     if (W == 64) SF_STAGE(16, 6);
     if (W == 32) SF_STAGE(16, 5);
     SF_STAGE(16, 4);
+  }
+  if (const int rounds = stage32_rounds(g.F * (H + 1) - 1, W, n_convs)) {
+    if (W == 64) return launch_stage32<6>(g, rounds, st);
+    if (W == 32) return launch_stage32<5>(g, rounds, st);
+    return launch_stage32<4>(g, rounds, st);
   }
   if (W == 64) SF_STAGE(32, 6);
   if (W == 32) SF_STAGE(32, 5);

@@ -1,0 +1,40 @@
+"""32-channel stages of the residual encoder in one launch: one to three tiles per wave with the filter
+banks in LDS, and the stages whose banks do not fit there (three blocks, wide frames)."""
+import numpy as np
+import pytest
+
+from paper_2006_11751_amd import binding, workloads as wl
+from tests import parity
+from tests.test_gpu_parity import RESNET_BF16_SMALL, _gpu_step
+
+pytestmark = pytest.mark.gpu
+
+# second stage frames (32 channels): 8 x 32 (one tile per wave), 12 x 32 with a ragged wave, 18 x 32 (three),
+# 11 x 16 stacked; 600 frames: several per workgroup; three blocks: the kernel that streams its banks
+CASES = [((3, 32, 128), 2, 5), ((3, 45, 128), 2, 600), ((3, 72, 128), 1, 259), ((3, 44, 64), 2, 13),
+         ((3, 72, 128), 3, 3), ((3, 24, 256), 2, 4)]
+
+
+@pytest.mark.parametrize("obs,blocks,B", CASES, ids=["%dx%d-%d-%d" % (o[1], o[2], n, b) for o, n, b in CASES])
+def test_stage_with_its_banks_in_lds(torch_cuda, ref, monkeypatch, obs, blocks, B):
+    torch = torch_cuda
+    net = dict(RESNET_BF16_SMALL, name="res_stage_%dx%d" % obs[1:], B=B, obs=obs, blocks_per_stage=blocks)
+    if blocks == 3:  # (at most 20 convolutions)
+        net["stages"] = [16, 32]
+    w = wl.weights(net)
+    o_, h_, d_ = wl.observations(net, 0, B), wl.initial_state(net, B), wl.done_mask(net, 0, B)
+    pol = binding.Policy(net, w)
+    assert "res_stage" in pol.op_kernels(), pol.op_kernels()
+    g = _gpu_step(torch, pol, o_, h_, d_, 7, 11)
+    pol.close()
+    rows = np.unique(np.array([0, B // 2, B - 1]))
+    o = ref.policy_step(net, w, o_[rows], h_[rows], d_[rows], 7, 11)
+    monkeypatch.setenv("SF_NO_RES_STAGE", "1")
+    old = binding.Policy(net, w)
+    monkeypatch.delenv("SF_NO_RES_STAGE")
+    g2 = _gpu_step(torch, old, o_, h_, d_, 7, 11)
+    old.close()
+    for k in ("h_out", "value"):
+        parity.assert_close(k, g[k][rows], o[k], 1e-2)
+        # (fp16 streams rounded at different points, each about 1e-3 from the oracle)
+        parity.assert_close(k + " vs per-block kernels", g[k], g2[k], 1e-2)
