@@ -111,11 +111,19 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
 
   // ---- the first bank in LDS: [channel half][channel][digit] operands of 64 lanes ----
   u32x4* const bank1 = (u32x4*)(lds + g.bank_at);
-  for (int i = tid; i < 2 * kCin * 3 * 64; i += kNT) {
-    const int l = i & 63, d = (i >> 6) % 3, s = (i >> 6) / 3 % 3, half = (i >> 6) / 9;
-    const int* from = g.wpk1 + ((2 * s + (l >> 5)) * 3 + d) * (4 * 64) + 32 * ((l >> 4) & 1) + 16 * half + (l & 15);
-    const u32x4 v = {(unsigned)from[0], (unsigned)from[64], (unsigned)from[128], (unsigned)from[192]};
-    bank1[i] = v;
+  {
+    // (all requests ahead of the first store: one trip to memory)
+    constexpr int N = 2 * kCin * 3 * 64, NB = (N + kNT - 1) / kNT;
+    u32x4 v[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int i = min(tid + kNT * j, N - 1), l = i & 63, d = (i >> 6) % 3, s = (i >> 6) / 3 % 3, half = (i >> 6) / 9;
+      const int* from = g.wpk1 + ((2 * s + (l >> 5)) * 3 + d) * (4 * 64) + 32 * ((l >> 4) & 1) + 16 * half + (l & 15);
+      v[j] = u32x4{(unsigned)from[0], (unsigned)from[64], (unsigned)from[128], (unsigned)from[192]};
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      if (tid + kNT * j < N) bank1[tid + kNT * j] = v[j];
   }
   // its scales and bias, the second layer's input scales (powers of two: the same bits) folded in
   float* const affine1 = (float*)(bank1 + 2 * kCin * 3 * 64);  // [2][32]

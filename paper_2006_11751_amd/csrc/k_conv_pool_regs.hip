@@ -110,7 +110,11 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
   for (int i = tid; i < FPW * FB / 16; i += kNT) ((u32x4*)lds)[i] = u32x4{0u, 0u, 0u, 0u};
   // the filter bank behind the frames (the registers are needed for three accumulator sets)
   const u32x4* wl = (const u32x4*)(lds + FPW * FB) + lane;
-  for (int i = tid; i < 9 * NS * 64; i += kNT) ((u32x4*)(lds + FPW * FB))[i] = g.wpk[i];
+  // (all requests ahead of the first store: one trip to memory)
+  constexpr int NBANK = 9 * NS * 64, NBP = (NBANK + kNT - 1) / kNT;
+  u32x4 bank[NBP];
+#pragma unroll
+  for (int k = 0; k < NBP; ++k) bank[k] = g.wpk[min(tid + kNT * k, NBANK - 1)];
   // the bias in the accumulator layout: register 4*q4 + u holds channel 8*q4 + 4*lh + u
   f32x16 bias_acc;
 #pragma unroll
@@ -119,12 +123,6 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) bias_acc[4 * q4 + u] = bv[u];
   }
-  // The parameters have arrived before the first frame is requested (vmcnt(0), other counters
-  // untouched).  Otherwise the compiler, which must assume their loads pending on some path,
-  // drains the load counter ahead of every row loop that uses them, and that wait would catch
-  // the next frame's pixels right after they have been requested.
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-
   // The threads cover step_rows image rows at a time, one 16-byte piece each: thread tid has
   // piece tid % row_pieces (pixel x, channels 8*c8..) of row tid / row_pieces of the step.  In LDS:
   // plane x%2, row y + 1, plane column x/2 (even plane) or x/2 + 1 (odd plane: its column 0 is
@@ -261,6 +259,14 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
 
   int b0 = blockIdx.x * FPW;
   load_frames(b0);
+#pragma unroll
+  for (int k = 0; k < NBP; ++k)
+    if (tid + kNT * k < NBANK) ((u32x4*)(lds + FPW * FB))[tid + kNT * k] = bank[k];
+  // Parameters and first frame, requested together, have arrived before the loop (vmcnt(0), other counters
+  // untouched).  Otherwise the compiler, which must assume the parameters' loads pending on some path,
+  // drains the load counter ahead of every row loop that uses them, and that wait would catch the next
+  // frame's pixels right after they have been requested.
+  __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();  // zeros in place
   for (; b0 < g.B; b0 += gridDim.x * FPW) {
     stage();

@@ -96,18 +96,11 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   const int j = lane & 15, grp = lane >> 4;
   const size_t plane = (size_t)g.H * g.W;
 
-  // zeros once: the ring is never written again
-  for (int i = tid; i < (g.H + 2) * g.RP / 16; i += kNT) ((u32x4*)patch)[i] = u32x4{0u, 0u, 0u, 0u};
-
   const u32x4 a_lo1 = g.wpk[lane], a_lo2 = g.wpk[64 + lane];
   const u32x4 a_hi1 = g.wpk[128 + lane], a_hi2 = g.wpk[192 + lane];
   const f32x4 bias = *(const f32x4*)(g.bias + 4 * grp);
-  // The parameters have arrived before the first frame is requested (vmcnt(0), other counters
-  // untouched).  Otherwise the compiler, which must assume their loads pending on some path,
-  // drains the load counter ahead of every row loop that uses them, and that wait would catch
-  // the next frame's bytes right after they have been requested.
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-
+  // zeros once: the ring is never written again
+  for (int i = tid; i < (g.H + 2) * g.RP / 16; i += kNT) ((u32x4*)patch)[i] = u32x4{0u, 0u, 0u, 0u};
   // Item i = tid + it * kNT is the four pixels at byte 4*i of each colour plane: image row
   // i / (W/4), columns 4*(i % (W/4)) ..; in LDS, row + 1 and column + 2.
   const int Q = g.W >> 2;
@@ -221,6 +214,11 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
 
   int b = blockIdx.x;
   load_frame(b);
+  // Parameters and first frame, requested together, have arrived before the loop (vmcnt(0), other counters
+  // untouched).  Otherwise the compiler, which must assume the parameters' loads pending on some path,
+  // drains the load counter ahead of every row loop that uses them, and that wait would catch the next
+  // frame's bytes right after they have been requested.
+  __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();  // zeros in place
   for (; b < g.B; b += gridDim.x) {
     stage();
