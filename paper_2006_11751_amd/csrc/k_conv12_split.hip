@@ -48,7 +48,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kNT = 512;
 constexpr int kCin = 3, kK1 = 8, kS1 = 4, kC1 = 32;  // first layer: planes, filter, stride, channels
 constexpr int kK2 = 4, kS2 = 2, kC2 = 64;            // second layer: filter, stride, channels
-constexpr int kMT = 7;                               // 16-pixel tiles of the second layer
+constexpr int kMaxTiles = 7;                         // 16-pixel tiles of the second layer
 constexpr int kP4 = kC1 / 4 + 1;                     // image pixel in 16-byte pieces: both terms and padding
 constexpr int kPitch = 160;                          // byte-frame row in LDS, see layout()
 constexpr int kNV = 4;                               // 16-byte pieces of a byte frame per thread
@@ -75,28 +75,52 @@ struct Args {
   int row_stride;        // image row in pieces
   int image_at, sums_at, bank_at; // LDS offsets
   int rcp_wo2, rcp_row;  // x / d = x * rcp >> 16 for Wo2, W / 16
+  int parts;             // workgroups per frame
 };
 
 int reciprocal(int d) { return (65536 + d - 1) / d; }  // exact for x * d < 65536
 
+// MT: 16-pixel tiles of the second layer per workgroup.  Few frames are dealt to two or four workgroups
+// each, by rows of the second layer's output: a workgroup then takes the image rows that these need (the
+// first layer's rows at a border are computed twice) and MT = 4 or 2 tiles.
+template <int MT>
 __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
+  constexpr bool WHOLE = MT == kMaxTiles;
+  constexpr int OWN0 = (MT + 1) / 2;  // tiles finished by the first half of the waves
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   uint8_t* const image = lds + g.image_at;
-  f32x4* const sums = (f32x4*)(lds + g.sums_at);  // [4][kMT][64]
+  f32x4* const sums = (f32x4*)(lds + g.sums_at);  // [4][MT][64]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lp = lane & 15, lg = lane >> 4;
   const int half1 = wave & 1;                  // first layer: channel half
   const int ct = wave & 3, kh = wave >> 2;     // second layer: channel tile, half of the filter
 
-  const int pieces = kCin * g.H * g.W / 16;
+  // rows [row0, row0 + n2) of the second layer's output, n1 of the first layer's, in_rows of the image
+  const int part = WHOLE ? 0 : (int)blockIdx.x % g.parts;
+  const int row0 = WHOLE ? 0 : part * g.Ho2 / g.parts;
+  const int n2 = WHOLE ? g.Ho2 : (part + 1) * g.Ho2 / g.parts - row0;
+  const int n1 = WHOLE ? g.Ho1 : kS2 * (n2 - 1) + kK2;
+  const int in_rows = WHOLE ? g.H : kS1 * (n1 - 1) + kK1;
+  const int first_frame = WHOLE ? (int)blockIdx.x : (int)blockIdx.x / g.parts;
+  const int frame_step = WHOLE ? (int)gridDim.x : (int)gridDim.x / g.parts;  // (the same part of every frame)
+
+  const int row_pieces = g.W >> 4, pieces = kCin * in_rows * row_pieces;
   u32x4 fv[kNV];
   auto load_frame = [&](int b) {
-    const uint8_t* src = g.obs + (size_t)b * (16 * (size_t)pieces);
+    const uint8_t* src = g.obs + (size_t)b * ((size_t)kCin * g.H * g.W);
     int first = tid;
     asm volatile("" : "+v"(first));  // (opaque: the places are computed in place, not kept)
 #pragma unroll
-    for (int u = 0; u < kNV; ++u) fv[u] = *(const u32x4*)(src + 16u * (uint32_t)min(first + kNT * u, pieces - 1));
+    for (int u = 0; u < kNV; ++u) {
+      const int f = min(first + kNT * u, pieces - 1);
+      uint32_t at = 16u * (uint32_t)f;
+      if (!WHOLE) {
+        const int plane = (f >= in_rows * row_pieces) + (f >= 2 * in_rows * row_pieces);
+        at += (uint32_t)((plane * (g.H - in_rows) + kS1 * kS2 * row0) * g.W);
+      }
+      fv[u] = *(const u32x4*)(src + at);
+    }
   };
   auto store_frame = [&]() {
     int first = tid;
@@ -104,10 +128,10 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
 #pragma unroll
     for (int u = 0; u < kNV; ++u) {
       const int f = min(first + kNT * u, pieces - 1), row = f * g.rcp_row >> 16;
-      *(u32x4*)(lds + (row * kPitch + (f - row * (g.W >> 4)) * 16)) = fv[u] ^ 0x80808080u;
+      *(u32x4*)(lds + (row * kPitch + (f - row * row_pieces) * 16)) = fv[u] ^ 0x80808080u;
     }
   };
-  load_frame(blockIdx.x);
+  load_frame(first_frame);
 
   // ---- the first bank in LDS: [channel half][channel][digit] operands of 64 lanes ----
   u32x4* const bank1 = (u32x4*)(lds + g.bank_at);
@@ -138,12 +162,12 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
   const f32x4 inv = *(const f32x4*)(g.scale2 + kC1 + c2), bias = *(const f32x4*)(g.bias2 + c2);
   const float refused = g.scale2[kC1 + kC2];
 
-  const int npix1 = g.Ho1 * g.Wo1, npix2 = g.Ho2 * g.Wo2;
+  const int npix2 = n2 * g.Wo2;  // of this workgroup
   // second layer: this lane's pixel of every tile, its window's first pixel (past the end: the last
   // pixel again, computed and stored again with the same bits)
-  int abase[kMT];
+  int abase[MT];
 #pragma unroll
-  for (int m = 0; m < kMT; ++m) {
+  for (int m = 0; m < MT; ++m) {
     const int n = min(16 * m + lp, npix2 - 1);
     const int oy = n * g.rcp_wo2 >> 16, ox = n - oy * g.Wo2;
     abase[m] = 16 * ((oy * kS2 + kh * 2) * g.row_stride + (ox * kS2) * kP4 + lg);
@@ -153,20 +177,20 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
   const int ox1 = min(16 * ((wave >> 1) & 1) + lp, g.Wo1 - 1);
   int from[kCin];
 #pragma unroll
-  for (int s = 0; s < kCin; ++s) from[s] = (s * g.H + 2 * lg) * kPitch + ox1 * kS1;
+  for (int s = 0; s < kCin; ++s) from[s] = (s * in_rows + 2 * lg) * kPitch + ox1 * kS1;
   const int to = 16 * ox1 * kP4 + 2 * c1;
   float minus_one = -1.0f;  // (opaque: a product by a known -1 becomes a conversion and a subtraction)
   asm volatile("" : "+v"(minus_one));
 
   // both halves of a frame's sums, bias, ReLU
-  f32x4 own[4];
+  f32x4 own[OWN0];
   auto finish = [&](int b) __attribute__((always_inline)) {
-    float* dst = g.out + (size_t)b * npix2 * kC2 + c2;
-    const int m0 = kh == 0 ? 0 : 4;
+    float* dst = g.out + ((size_t)b * g.Ho2 + row0) * g.Wo2 * kC2 + c2;
+    const int m0 = kh == 0 ? 0 : OWN0;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      if (m == kMT - 4 && kh != 0) break;
-      const f32x4 other = sums[(ct * kMT + m0 + m) * 64 + lane];
+    for (int m = 0; m < OWN0; ++m) {
+      if (m == MT - OWN0 && kh != 0) break;
+      const f32x4 other = sums[(ct * MT + m0 + m) * 64 + lane];
       const int n = min(16 * (m0 + m) + lp, npix2 - 1);
       f32x4 r;
 #pragma unroll
@@ -178,8 +202,9 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
   store_frame();
   __syncthreads();
   int done = -1;  // the frame whose sums wait to be finished
-  for (int b = blockIdx.x; b < g.B; b += gridDim.x) {
-    load_frame(min(b + (int)gridDim.x, g.B - 1));  // (last round: a frame for no use)
+  for (int b = first_frame; b < g.B; b += frame_step) {
+    const bool more = WHOLE || b + frame_step < g.B;
+    if (more) load_frame(min(b + frame_step, g.B - 1));  // (last round: a frame for no use)
 
     // (the last frame's outputs: half of the waves before the first layer, half behind it)
     if (kh != 0 && done >= 0) finish(done);
@@ -195,7 +220,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
       U2 rb[kCin][2];
       i32x4 even[3], odd[3];
       auto load_row = [&](int oy) __attribute__((always_inline)) {
-        const int row = min(oy, g.Ho1 - 1) * (kS1 * kPitch);  // (past the end: the last row, for no use)
+        const int row = min(oy, n1 - 1) * (kS1 * kPitch);  // (past the end: the last row, for no use)
 #pragma unroll
         for (int s = 0; s < kCin; ++s)
 #pragma unroll
@@ -250,13 +275,13 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
         put(even, oy);
         mix();
         oy += 2;
-        if (oy >= g.Ho1) break;
+        if (oy >= n1) break;
         multiply(even);
         load_row(oy + 4);
         put(odd, oy);
         mix();
         oy += 2;
-        if (oy >= g.Ho1) break;
+        if (oy >= n1) break;
       }
     }
     if (kh == 0 && done >= 0) finish(done);
@@ -264,16 +289,16 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
 
     // ---- second layer ----
     {
-      f32x4 acc[kMT], low[kMT];
-      u32x4 x0[kMT], x1[kMT];
+      f32x4 acc[MT], low[MT];
+      u32x4 x0[MT], x1[MT];
       auto tap = [&](int t) { return 16 * ((t / kK2) * g.row_stride + (t % kK2) * kP4); };
       auto mfma = [&](const u32x4& w, const u32x4& x, f32x4& c) __attribute__((always_inline)) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
       };
 #pragma unroll
-      for (int m = 0; m < kMT; ++m) x0[m] = *(const u32x4*)(image + abase[m]);
+      for (int m = 0; m < MT; ++m) x0[m] = *(const u32x4*)(image + abase[m]);
 #pragma unroll
-      for (int m = 0; m < kMT; ++m) {
+      for (int m = 0; m < MT; ++m) {
         x1[m] = *(const u32x4*)(image + abase[m] + 2 * kC1);
         acc[m] = low[m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       }
@@ -283,38 +308,38 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
         // (a term of the next tap is requested behind its last use; left alone, the scheduler sinks each
         // read to its use)
 #pragma unroll
-        for (int m = 0; m < kMT; ++m) {
+        for (int m = 0; m < MT; ++m) {
           mfma(wf[t][1], x0[m], low[m]);
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int m = 0; m < kMT; ++m) {
+        for (int m = 0; m < MT; ++m) {
           mfma(wf[t][0], x0[m], acc[m]);
           if (t + 1 < kG2) x0[m] = *(const u32x4*)(image + abase[m] + next);
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int m = 0; m < kMT; ++m) {
+        for (int m = 0; m < MT; ++m) {
           mfma(wf[t][0], x1[m], low[m]);
           if (t + 1 < kG2) x1[m] = *(const u32x4*)(image + abase[m] + next + 2 * kC1);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
 #pragma unroll
-      for (int m = 0; m < kMT; ++m) acc[m] += low[m];
+      for (int m = 0; m < MT; ++m) acc[m] += low[m];
       if (kh == 0) {
 #pragma unroll
-        for (int m = 4; m < kMT; ++m) sums[(ct * kMT + m) * 64 + lane] = acc[m];
+        for (int m = OWN0; m < MT; ++m) sums[(ct * MT + m) * 64 + lane] = acc[m];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) own[m] = acc[m];
+        for (int m = 0; m < OWN0; ++m) own[m] = acc[m];
       } else {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) sums[(ct * kMT + m) * 64 + lane] = acc[m];
+        for (int m = 0; m < OWN0; ++m) sums[(ct * MT + m) * 64 + lane] = acc[m];
 #pragma unroll
-        for (int m = 4; m < kMT; ++m) own[m - 4] = acc[m];
+        for (int m = OWN0; m < MT; ++m) own[m - OWN0] = acc[m];
       }
     }
-    store_frame();
+    if (more) store_frame();
     __syncthreads();  // the sums and the next frame's bytes are there, the image is used up
     asm volatile("" ::"s"(refused));  // (requested with the scales, here long since)
     done = b;
@@ -326,11 +351,13 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // the stores above are done
     const int8_t* digits = (const int8_t*)g.wpk1;
-    for (int b = blockIdx.x; b < g.B; b += gridDim.x) {
-      const uint8_t* frame = g.obs + (size_t)b * (16 * (size_t)pieces);
-      float* mid = g.mid + (size_t)b * npix1 * kC1;
+    for (int b = first_frame; b < g.B; b += frame_step) {
+      const uint8_t* frame = g.obs + (size_t)b * ((size_t)kCin * g.H * g.W);
+      float* mid = g.mid + (size_t)b * g.Ho1 * g.Wo1 * kC1;
+      // (rows at a border of two workgroups: both write the same values)
+      const int mid0 = kS2 * row0 * g.Wo1 * kC1;
 #pragma unroll 1
-      for (int i = tid; i < npix1 * kC1; i += kNT) {
+      for (int i = mid0 + tid; i < mid0 + n1 * g.Wo1 * kC1; i += kNT) {
         const int n = i % kC1, pix = i / kC1, oy = pix / g.Wo1, ox = pix % g.Wo1;
         int d1 = 0, d2 = 0, d3 = 0;
 #pragma unroll 1
@@ -346,8 +373,9 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
+      const int out0 = row0 * g.Wo2 * kC2;
 #pragma unroll 1
-      for (int i = tid; i < npix2 * kC2; i += kNT) {
+      for (int i = out0 + tid; i < out0 + npix2 * kC2; i += kNT) {
         const int n = i % kC2, pix = i / kC2, oy = pix / g.Wo2, ox = pix % g.Wo2;
         const float* x = mid + ((size_t)oy * kS2 * g.Wo1 + ox * kS2) * kC1;
         const float* w = g.w32 + (size_t)n * (kK2 * kK2 * kC1);
@@ -355,7 +383,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
 #pragma unroll 1
         for (int k = 0; k < kK2 * kK2 * kC1; ++k)
           sum = fmaf(x[(size_t)(k / (kK2 * kC1)) * g.Wo1 * kC1 + k % (kK2 * kC1)], w[k], sum);
-        g.out[(size_t)b * npix2 * kC2 + i] = fmaxf(sum + g.bias2[n], 0.0f);
+        g.out[(size_t)b * g.Ho2 * g.Wo2 * kC2 + i] = fmaxf(sum + g.bias2[n], 0.0f);
       }
     }
   }
@@ -374,7 +402,7 @@ Layout layout(int H, int Ho1, int Wo1, int Wo2) {
   L.row_stride = Wo1 * kP4 + (((kP4 * Wo2 - Wo1 * kP4) % 8) + 8) % 8;
   L.image_at = kCin * H * kPitch;
   L.sums_at = L.image_at + 16 * Ho1 * L.row_stride;
-  L.bank_at = L.sums_at + 16 * 4 * kMT * 64;
+  L.bank_at = L.sums_at + 16 * 4 * kMaxTiles * 64;
   L.bytes = (size_t)L.bank_at + 16 * 2 * kCin * 3 * 64 + 4 * 2 * kC1;
   return L;
 }
@@ -390,7 +418,7 @@ bool conv12_split_supported(int cin, int H, int W, const sf_conv& a, const sf_co
   const int Ho1 = (H - kK1) / kS1 + 1, Wo1 = (W - kK1) / kS1 + 1;
   if (Ho1 < kK2 || Wo1 < kK2 || Wo1 > 32) return false;
   const int Ho2 = (Ho1 - kK2) / kS2 + 1, Wo2 = (Wo1 - kK2) / kS2 + 1, pieces = kCin * H * W / 16;
-  if ((Ho2 * Wo2 + 15) / 16 != kMT || pieces > kNV * kNT) return false;
+  if ((Ho2 * Wo2 + 15) / 16 != kMaxTiles || pieces > kNV * kNT) return false;
   if (Ho2 * Wo2 * Wo2 >= 65536 || pieces * (W / 16) >= 65536) return false;  // (reciprocal())
   return layout(H, Ho1, Wo1, Wo2).bytes <= kMaxLds;
 }
@@ -400,7 +428,7 @@ bool conv12_split_supported(int cin, int H, int W, const sf_conv& a, const sf_co
 hipError_t launch_conv12_split(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs, float* mid, float* out,
                                hipStream_t st) {
   if (B == 0) return hipSuccess;
-  if (((uintptr_t)obs & 15) != 0 || L1.planes != 3 || (L2.Ho * L2.Wo + 15) / 16 != kMT) return hipErrorInvalidValue;
+  if (((uintptr_t)obs & 15) != 0 || L1.planes != 3 || (L2.Ho * L2.Wo + 15) / 16 != kMaxTiles) return hipErrorInvalidValue;
   const Layout L = layout(L1.H, L1.Ho, L1.Wo, L2.Wo);
   Args g;
   g.obs = obs; g.wpk1 = L1.ipk; g.scale1 = L1.spk; g.bias1 = L1.bpk8;
@@ -411,10 +439,24 @@ hipError_t launch_conv12_split(const ConvLayer& L1, const ConvLayer& L2, int B, 
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
-    attr_status = hipFuncSetAttribute((const void*)conv12_split_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+    for (const void* k : {(const void*)conv12_split_kernel<7>, (const void*)conv12_split_kernel<4>, (const void*)conv12_split_kernel<2>})
+      if (attr_status == hipSuccess) attr_status = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   });
   if (attr_status != hipSuccess) return attr_status;
-  conv12_split_kernel<<<B < 256 ? B : 256, kNT, L.bytes, st>>>(g);  // one workgroup per CU
+  // Workgroups per frame.  A half takes 0.6 of a frame's time, a quarter 0.4: the fewest parts of the least
+  // time over the rounds of 256 workgroups (a quarter up to 64 frames, a half up to 128 and from 257 to 384).
+  const int limit[] = {0, 7, 4, 0, 2}, cost[] = {0, 10, 6, 0, 4};
+  g.parts = 1;
+  int blocks = B < 256 ? B : 256, least = (B + 255) / 256 * cost[1];
+  for (int parts : {2, 4}) {
+    const int items = B * parts, time = (items + 255) / 256 * cost[parts];
+    if ((L2.Ho + parts - 1) / parts * L2.Wo > 16 * limit[parts] || time >= least) continue;
+    g.parts = parts;
+    blocks = items < 256 ? items : 256;
+    least = time;
+  }
+  auto kern = g.parts == 4 ? conv12_split_kernel<2> : g.parts == 2 ? conv12_split_kernel<4> : conv12_split_kernel<7>;
+  kern<<<blocks, kNT, L.bytes, st>>>(g);
   return hipGetLastError();
 }
 

@@ -34,7 +34,8 @@ def test_one_launch_and_two(torch_cuda, ref, monkeypatch, height):
         # the same products in another order: a few roundings of an fp32 sum of 512 terms, then of the rest
         assert np.abs(full[k] - apart[k]).max() <= 2e-5 * np.abs(apart[k]).max(), k
         assert np.array_equal(moved[k], apart[k]), k  # (the separate kernels)
-    for n in (257, 256, 1):  # a frame's bits do not depend on the batch
+    # a frame's bits depend neither on the batch nor on whether one, two or four workgroups share it
+    for n in (385, 384, 257, 256, 129, 128, 65, 64, 1):
         part = step(one, n, obs)
         for k in full:
             assert np.array_equal(part[k], full[k][:n]), (n, k)
