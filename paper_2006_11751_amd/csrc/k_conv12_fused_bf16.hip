@@ -44,7 +44,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kNT = 512;
 constexpr int kCin = 3, kK1 = 8, kS1 = 4, kC1 = 32;  // first layer: planes, filter, stride, channels
 constexpr int kK2 = 4, kS2 = 2, kC2 = 64;            // second layer: filter, stride, channels
-constexpr int kMT = 7;                               // 16-pixel tiles of the second layer
+constexpr int kMaxTiles = 7;                         // 16-pixel tiles of the second layer
 constexpr int kP4 = kC1 / 8 + 1;                     // LDS pixel pitch of the image in 16-byte pieces
 constexpr int kNV = 4;                               // 16-byte pieces of a byte frame per thread
 constexpr int kG2 = kK2 * kK2;                       // filter taps of the second layer
@@ -68,6 +68,7 @@ struct Conv12Args {
   int row_stride;       // image row pitch in pieces
   int image_at;         // LDS offset of the two images
   int rcp_wo2, rcp_row; // x / d = x * rcp >> 16 for Wo2, W / 16
+  int parts;            // workgroups per frame
 };
 
 int reciprocal(int d) { return (65536 + d - 1) / d; }  // exact for x * d < 65536
@@ -75,8 +76,13 @@ int reciprocal(int d) { return (65536 + d - 1) / d; }  // exact for x * d < 6553
 // FLAT: the byte frame lies in LDS as in memory; otherwise (rows of whole 16-byte pieces) its rows are
 // kPitch bytes apart: two of them 64 bytes modulo 256, so that the four lane groups of a tile (filter
 // rows 2 lg, 2 lg + 1) read different banks, and at offsets known to the compiler.
-template <bool FLAT>
+// MT: 16-pixel tiles of the second layer per workgroup.  Few frames are dealt to two or four workgroups
+// each, by rows of the second layer's output (the first layer's rows at a border are computed twice), with
+// MT = 4 or 2 tiles.
+template <bool FLAT, int MT>
 __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g) {
+  constexpr bool WHOLE = MT == kMaxTiles;
+  constexpr int TILES = (MT + 1) / 2;  // of the first half of the waves
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lp = lane & 15, lg = lane >> 4;
@@ -84,12 +90,29 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
   const int ct = wave & 3, hi = wave >> 2;  // second layer: channel tile, first or last pixel tiles
   const int pitch = FLAT ? g.W : kPitch;
 
-  const int pieces = kCin * g.H * g.W / 16;
+  // rows [row0, row0 + n2) of the second layer's output, n1 of the first layer's, in_rows of the image
+  const int part = WHOLE ? 0 : (int)blockIdx.x % g.parts;
+  const int row0 = WHOLE ? 0 : part * g.Ho2 / g.parts;
+  const int n2 = WHOLE ? g.Ho2 : (part + 1) * g.Ho2 / g.parts - row0;
+  const int n1 = WHOLE ? g.Ho1 : kS2 * (n2 - 1) + kK2;
+  const int in_rows = WHOLE ? g.H : kS1 * (n1 - 1) + kK1;
+  const int first_frame = WHOLE ? (int)blockIdx.x : (int)blockIdx.x / g.parts;
+  const int stride = WHOLE ? (int)gridDim.x : (int)gridDim.x / g.parts;  // (the same part of every frame)
+
+  const int row_pieces = g.W >> 4, pieces = WHOLE ? kCin * g.H * g.W / 16 : kCin * in_rows * row_pieces;
   u32x4 fv[kNV];
   auto load_frame = [&](int b) {
-    const uint8_t* src = g.obs + (size_t)b * (16 * (size_t)pieces);
+    const uint8_t* src = g.obs + (size_t)b * ((size_t)kCin * g.H * g.W);
 #pragma unroll
-    for (int u = 0; u < kNV; ++u) fv[u] = *(const u32x4*)(src + 16u * (uint32_t)min(tid + kNT * u, pieces - 1));
+    for (int u = 0; u < kNV; ++u) {
+      const int f = min(tid + kNT * u, pieces - 1);
+      uint32_t at = 16u * (uint32_t)f;
+      if (!WHOLE) {
+        const int plane = (f >= in_rows * row_pieces) + (f >= 2 * in_rows * row_pieces);
+        at += (uint32_t)((plane * (g.H - in_rows) + kS1 * kS2 * row0) * g.W);
+      }
+      fv[u] = *(const u32x4*)(src + at);
+    }
   };
   auto store_frame = [&]() {
 #pragma unroll
@@ -103,7 +126,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
       *(u32x4*)(lds + at) = fv[u] ^ 0x80808080u;
     }
   };
-  load_frame(blockIdx.x);
+  load_frame(first_frame);
 
   // ---- operands that stay in registers ----
   i32x4 wd[kCin][2];
@@ -125,15 +148,15 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
   const int ox1 = min(16 * ((wave >> 1) & 1) + lp, g.Wo1 - 1);
   int from[kCin];
 #pragma unroll
-  for (int s = 0; s < kCin; ++s) from[s] = (s * g.H + 2 * lg) * pitch + ox1 * kS1;
+  for (int s = 0; s < kCin; ++s) from[s] = (s * in_rows + 2 * lg) * pitch + ox1 * kS1;
   const int to = 16 * ox1 * kP4 + 2 * c1;
   // second layer: this lane's pixel of the wave's tiles, its window's first pixel (past the end: the last
   // pixel again, computed and stored again with the same bits)
-  const int npix2 = g.Ho2 * g.Wo2;
-  auto pixel = [&](int m) { return min(16 * (4 * hi + m) + lp, npix2 - 1); };
-  int abase[4];
+  const int npix2 = n2 * g.Wo2;
+  auto pixel = [&](int m) { return min(16 * (TILES * hi + m) + lp, npix2 - 1); };
+  int abase[TILES];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
+  for (int m = 0; m < TILES; ++m) {
     const int n = pixel(m), oy = n * g.rcp_wo2 >> 16, ox = n - oy * g.Wo2;
     abase[m] = 16 * ((oy * kS2) * g.row_stride + (ox * kS2) * kP4 + lg);
   }
@@ -143,7 +166,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
     U2 rb[kCin][2];
     i32x4 even[2], odd[2];
     auto load_row = [&](int oy) __attribute__((always_inline)) {
-      const int row = min(oy, g.Ho1 - 1) * (kS1 * pitch);  // (past the end: the last row, for no use)
+      const int row = min(oy, n1 - 1) * (kS1 * pitch);  // (past the end: the last row, for no use)
 #pragma unroll
       for (int s = 0; s < kCin; ++s)
 #pragma unroll
@@ -184,12 +207,12 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
       load_row(oy + 4);
       put(even, oy);
       oy += 2;
-      if (oy >= g.Ho1) break;
+      if (oy >= n1) break;
       multiply(even);
       load_row(oy + 4);
       put(odd, oy);
       oy += 2;
-      if (oy >= g.Ho1) break;
+      if (oy >= n1) break;
     }
   };
 
@@ -216,7 +239,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
           if (t + 2 < kG2) load_tap(t + 2, m);
           __builtin_amdgcn_sched_barrier(0);  // (left alone, the scheduler sinks each read to its use)
         }
-      uint8_t* dst = (uint8_t*)g.out + (size_t)b * npix2 * (2 * kC2);
+      uint8_t* dst = (uint8_t*)g.out + ((size_t)b * g.Ho2 + row0) * g.Wo2 * (2 * kC2);
 #pragma unroll
       for (int m = 0; m < MN; ++m) {
         float r[4];
@@ -230,33 +253,35 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
       }
     };
     if (hi)
-      tiles(std::integral_constant<int, kMT - 4>{});
+      tiles(std::integral_constant<int, MT - TILES>{});
     else
-      tiles(std::integral_constant<int, 4>{});
+      tiles(std::integral_constant<int, TILES>{});
   };
 
   uint8_t* image = lds + g.image_at;        // of the frame whose second layer is next
   uint8_t* other = image + image_bytes;
-  const int stride = (int)gridDim.x;
-  int b = blockIdx.x;
+  int b = first_frame;
   store_frame();
   __syncthreads();
-  load_frame(min(b + stride, g.B - 1));  // (no frame left: one for no use)
+  if (WHOLE || b + stride < g.B) load_frame(min(b + stride, g.B - 1));  // (no frame left: one for no use)
   first_layer(image);
   __syncthreads();
-  store_frame();
-  __syncthreads();
+  if (WHOLE || b + stride < g.B) {
+    store_frame();
+    __syncthreads();
+  }
   for (; b < g.B; b += stride) {
     const bool more = b + stride < g.B;
-    load_frame(min(b + 2 * stride, g.B - 1));
+    if (WHOLE || more) load_frame(min(b + 2 * stride, g.B - 1));
 #pragma unroll 1
-    for (int part = 0; part < 2; ++part) {
-      if (part == hi) {
+    for (int turn = 0; turn < 2; ++turn) {
+      if (turn == hi) {
         if (more) first_layer(other);
       } else {
         second_layer(image, b);
       }
     }
+    if (!WHOLE && !more) break;
     __syncthreads();  // one image is used up, the other complete; the frame's bytes are used up
     store_frame();
     __syncthreads();
@@ -290,7 +315,7 @@ bool conv12_fused_bf16_supported(int cin, int H, int W, const sf_conv& c1, const
   if (Wo1 > 32 || Ho1 < kK2 || Wo1 < kK2) return false;
   const int Ho2 = (Ho1 - kK2) / kS2 + 1, Wo2 = (Wo1 - kK2) / kS2 + 1;
   // seven 16-pixel tiles
-  if ((Ho2 * Wo2 + 15) / 16 != kMT) return false;
+  if ((Ho2 * Wo2 + 15) / 16 != kMaxTiles) return false;
   const int frame_bytes = cin * H * W;
   if (frame_bytes % 16 != 0 || frame_bytes > kNV * kNT * 16) return false;
   if (Ho2 * Wo2 * Wo2 >= 65536 || frame_bytes / 16 * (W / 16) >= 65536) return false;  // (reciprocal())
@@ -302,7 +327,7 @@ bool conv12_fused_bf16_supported(int cin, int H, int W, const sf_conv& c1, const
 hipError_t launch_conv12_fused_bf16(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs,
                                     void* out, hipStream_t st) {
   if (B == 0) return hipSuccess;
-  if (((uintptr_t)obs & 15) != 0 || L1.planes != 2 || (L2.Ho * L2.Wo + 15) / 16 != kMT) return hipErrorInvalidValue;
+  if (((uintptr_t)obs & 15) != 0 || L1.planes != 2 || (L2.Ho * L2.Wo + 15) / 16 != kMaxTiles) return hipErrorInvalidValue;
   Conv12Args g;
   g.obs = obs; g.wpk1 = L1.ipk; g.scale1 = L1.spk; g.bias1 = L1.bpk8;
   g.wpk2 = (const u32x4*)L2.wbf; g.bias2 = L2.bbf; g.out = (uint16_t*)out;
@@ -311,18 +336,24 @@ hipError_t launch_conv12_fused_bf16(const ConvLayer& L1, const ConvLayer& L2, in
   g.image_at = (frame_lds_bytes(L1.H, L1.W) + 15) & ~15;
   g.rcp_wo2 = reciprocal(L2.Wo); g.rcp_row = L1.W >= 16 ? reciprocal(L1.W / 16) : 0;
   const size_t lds = (size_t)g.image_at + 2 * 16 * (size_t)L1.Ho * g.row_stride;
-  auto kern = flat(L1.W) ? conv12_fused_bf16_kernel<true> : conv12_fused_bf16_kernel<false>;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
-    attr_status = hipFuncSetAttribute((const void*)conv12_fused_bf16_kernel<true>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-    if (attr_status == hipSuccess)
-      attr_status = hipFuncSetAttribute((const void*)conv12_fused_bf16_kernel<false>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+    for (const void* k : {(const void*)conv12_fused_bf16_kernel<true, 7>, (const void*)conv12_fused_bf16_kernel<false, 7>,
+                          (const void*)conv12_fused_bf16_kernel<false, 4>, (const void*)conv12_fused_bf16_kernel<false, 2>})
+      if (attr_status == hipSuccess) attr_status = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   });
   if (attr_status != hipSuccess) return attr_status;
-  kern<<<B < 256 ? B : 256, kNT, lds, st>>>(g);  // one workgroup per CU
+  // Workgroups per frame: as many as run at once (one per CU), rows of whole 16-byte pieces.
+  auto fits = [&](int parts, int tiles) {
+    return !flat(L1.W) && B * parts <= 256 && (L2.Ho + parts - 1) / parts * L2.Wo <= 16 * tiles;
+  };
+  g.parts = fits(4, 2) ? 4 : fits(2, 4) ? 2 : 1;
+  auto kern = flat(L1.W) ? conv12_fused_bf16_kernel<true, 7>
+              : g.parts == 4 ? conv12_fused_bf16_kernel<false, 2>
+              : g.parts == 2 ? conv12_fused_bf16_kernel<false, 4>
+                             : conv12_fused_bf16_kernel<false, 7>;
+  kern<<<g.parts > 1 ? B * g.parts : B < 256 ? B : 256, kNT, lds, st>>>(g);
   return hipGetLastError();
 }
 

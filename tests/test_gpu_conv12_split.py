@@ -41,3 +41,23 @@ def test_one_launch_and_two(torch_cuda, ref, monkeypatch, height):
             assert np.array_equal(part[k], full[k][:n]), (n, k)
     one.close()
     two.close()
+
+
+@pytest.mark.parametrize("height", [72, 74])
+def test_bf16_frames_shared_by_workgroups(torch_cuda, height):
+    """The same of the bf16 network, whose one launch gives the bits of the two separate kernels
+    (test_gpu_parity.py)."""
+    torch = torch_cuda
+    net = wl.network(2, fc=64, rnn=64, name="conv12_bf16", obs=(3, height, 128))
+    B = 300
+    pol = binding.Policy(net, wl.weights(net), max_batch=B)
+    assert pol.op_kernels()[0] == "conv12_fused"
+    obs, st, dn = (torch.from_numpy(a).cuda() for a in (wl.observations(net, 0, B), wl.initial_state(net, B),
+                                                       wl.done_mask(net, 0, B)))
+    step = lambda n: {k: v.cpu().numpy() for k, v in pol.step(obs[:n], st[:n], dn[:n], 7, 11).items()}
+    full = step(B)
+    for n in (257, 256, 129, 128, 65, 64, 1):
+        part = step(n)
+        for k in full:
+            assert np.array_equal(part[k], full[k][:n]), (n, k)
+    pol.close()
