@@ -80,6 +80,25 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv_image_bf16_kern
   const int frame_stride = g.H * row_stride + g.frame_pad;
   const int full_pieces = FR * frame_pieces, full_pix = FR * npix_out;
 
+  // Rounds it, it + gridDim.x, ...: while round i is computed out of LDS, the images of the
+  // workgroup's next round are on their way into registers; two barriers per round hand the
+  // LDS over.  A last round with fewer than FR frames re-reads its last valid piece instead of
+  // reading past the batch, and stores under a predicate.
+  const int n_rounds = (g.B + FR - 1) / FR;
+  u32x4 v[NV];
+  auto load_round = [&](int it) {
+    const int frames = g.B - it * FR < FR ? g.B - it * FR : FR;
+    const int valid = frames * frame_pieces;
+    const u32x4* src = g.in + (size_t)it * full_pieces;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int f = tid + NT * u;
+      v[u] = src[f < valid ? f : valid - 1];
+    }
+  };
+  int it = blockIdx.x;
+  load_round(it);
+
   // The wave's fragments start at a wave-uniform address (kept in scalar registers, so that
   // the unrolled K loop does not hold one vector address pair per fragment); fragment (j, gi)
   // of this lane is at byte (j*G + gi)*1024 + lane*16.
@@ -131,24 +150,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv_image_bf16_kern
     abase[m] = fr * frame_stride + (oy * STRIDE) * row_stride + (ox * STRIDE) * P4 + lg;
   }
 
-  // Rounds it, it + gridDim.x, ...: while round i is computed out of LDS, the images of the
-  // workgroup's next round are on their way into registers; two barriers per round hand the
-  // LDS over.  A last round with fewer than FR frames re-reads its last valid piece instead of
-  // reading past the batch, and stores under a predicate.
-  const int n_rounds = (g.B + FR - 1) / FR;
-  u32x4 v[NV];
-  auto load_round = [&](int it) {
-    const int frames = g.B - it * FR < FR ? g.B - it * FR : FR;
-    const int valid = frames * frame_pieces;
-    const u32x4* src = g.in + (size_t)it * full_pieces;
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int f = tid + NT * u;
-      v[u] = src[f < valid ? f : valid - 1];
-    }
-  };
-  int it = blockIdx.x;
-  load_round(it);
   for (; it < n_rounds; it += gridDim.x) {
 #pragma unroll
     for (int u = 0; u < NV; ++u) img[lds_idx[u]] = v[u];
@@ -358,7 +359,10 @@ hipError_t launch_conv_image_bf16(const void* in, const uint16_t* wpk, const flo
   switch (image_variant(Cin, ksize, stride, 0, H, W, Ho, Wo, N)) {
     case 1: return launch_t<32, 4, 1, 7, 1, true, 9, 4>(g, st);
     case 2: return launch_t<32, 4, 1, 8, 1, true, 9, 4>(g, st);
-    case 3: return launch_t<64, 3, 4, 5, 1, true, 7, 8>(g, st);
+    case 3:
+      // few frames: one per round, 64 output channels per workgroup
+      if ((long long)B * (N / 64) <= 256) return launch_t<64, 3, 1, 2, 1, true, 4, 4>(g, st);
+      return launch_t<64, 3, 4, 5, 1, true, 7, 8>(g, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -57,7 +57,6 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kNT = 256;
 constexpr size_t kMaxLds = 80 * 1024;  // two workgroups per CU
 
 struct SplitArgs {
@@ -75,9 +74,11 @@ struct SplitArgs {
 int reciprocal(int d) { return (65536 + d - 1) / d; }
 
 // FR frames per round; their FR*Ho*Wo <= 16*MT output pixels form one row-major sequence of MT
-// 16-pixel tiles, computed MP at a time.  NV: 16-byte pieces of a round's input per thread.
-template <int CIN, int KS, int FR, int MT, int MP, int NV>
-__global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
+// 16-pixel tiles, computed MP at a time.  NW: waves, 16 output channels each; NV: 16-byte pieces of a
+// round's input per thread.
+template <int CIN, int KS, int FR, int MT, int MP, int NW, int NV>
+__global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs g) {
+  constexpr int kNT = 64 * NW;
   constexpr int STRIDE = 2;
   constexpr int C4 = CIN / 4;       // 16-byte pieces of a pixel in memory
   constexpr int C8 = CIN / 8;       // ... of one of its terms in LDS
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(kNT, 2) void conv_image_split_kernel(SplitArgs g) {
   static_assert(FR <= 2 && kNT % C4 == 0, "a thread's pieces: two frames at most, the same channels throughout");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lp = lane & 15, lg = lane >> 4;
-  const int n0 = ((int)blockIdx.y * 4 + wave) * 16;  // the wave's output channels
+  const int n0 = ((int)blockIdx.y * NW + wave) * 16;  // the wave's output channels
   const int npix = g.Ho * g.Wo;
   const int frame_pieces = g.H * g.W * C4;
   const int row_stride = g.W * P4 + g.row_pad;
@@ -253,19 +254,19 @@ Layout layout(int Cin, int FR, int H, int W, int Ho, int Wo) {
 int variant(int Cin, int ksize, int stride, int pad, int H, int W, int N) {
   if (stride != 2 || pad != 0 || (N % 64) != 0 || H < ksize || W < ksize) return 0;
   const int Ho = (H - ksize) / 2 + 1, Wo = (W - ksize) / 2 + 1;
-  if (17 * kNT / 8 * W >= 65536 || 128 * Ho * Wo >= 65536) return 0;  // (reciprocal())
+  if (17 * 256 / 8 * W >= 65536 || 128 * Ho * Wo >= 65536) return 0;  // (reciprocal())
   if (Cin == 32 && ksize == 4) {
     const int mt = (Ho * Wo + 15) / 16;
-    if (mt == 7 && H * W * 8 <= 17 * kNT && layout(32, 1, H, W, Ho, Wo).lds_bytes <= kMaxLds) return 1;
+    if (mt == 7 && H * W * 8 <= 17 * 256 && layout(32, 1, H, W, Ho, Wo).lds_bytes <= kMaxLds) return 1;
   }
   if (Cin == 64 && ksize == 3)
-    if (2 * Ho * Wo > 32 && 2 * Ho * Wo <= 48 && 2 * H * W * 16 <= 13 * kNT &&
+    if (2 * Ho * Wo > 32 && 2 * Ho * Wo <= 48 && 2 * H * W * 16 <= 13 * 256 &&
         layout(64, 2, H, W, Ho, Wo).lds_bytes <= kMaxLds)
       return 2;
   return 0;
 }
 
-template <int CIN, int KS, int FR, int MT, int MP, int NV>
+template <int CIN, int KS, int FR, int MT, int MP, int NW, int NV>
 hipError_t launch_t(SplitArgs g, hipStream_t st) {
   const Layout L = layout(CIN, FR, g.H, g.W, g.Ho, g.Wo);
   g.row_pad = L.row_pad;
@@ -273,16 +274,17 @@ hipError_t launch_t(SplitArgs g, hipStream_t st) {
   g.rcp_w = reciprocal(g.W);
   g.rcp_wo = reciprocal(g.Wo);
   g.rcp_npix = reciprocal(g.Ho * g.Wo);
-  auto kern = conv_image_split_kernel<CIN, KS, FR, MT, MP, NV>;
+  auto kern = conv_image_split_kernel<CIN, KS, FR, MT, MP, NW, NV>;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
     attr_status = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   });
   if (attr_status != hipSuccess) return attr_status;
-  const int n_rounds = (g.B + FR - 1) / FR, ny = g.N / 64;
-  const int slots = ny >= 512 ? 1 : 512 / ny;  // two workgroups per CU, each walking its share of the rounds
-  kern<<<dim3((unsigned)(n_rounds < slots ? n_rounds : slots), (unsigned)ny), kNT, L.lds_bytes, st>>>(g);
+  const int n_rounds = (g.B + FR - 1) / FR, ny = g.N / (16 * NW);
+  // eight waves per CU, each workgroup walking its share of the rounds
+  const int per_chip = 2048 / NW, slots = ny >= per_chip ? 1 : per_chip / ny;
+  kern<<<dim3((unsigned)(n_rounds < slots ? n_rounds : slots), (unsigned)ny), 64 * NW, L.lds_bytes, st>>>(g);
   return hipGetLastError();
 }
 
@@ -483,8 +485,11 @@ hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const f
   g.B = B; g.H = H; g.W = W; g.Ho = (H - ksize) / 2 + 1; g.Wo = (W - ksize) / 2 + 1; g.N = N;
   g.row_pad = g.frame_pad = 0;
   switch (variant(Cin, ksize, 2, 0, H, W, N)) {
-    case 1: return launch_t<32, 4, 1, 7, 4, 17>(g, st);
-    case 2: return launch_t<64, 3, 2, 3, 3, 13>(g, st);
+    case 1: return launch_t<32, 4, 1, 7, 4, 4, 17>(g, st);
+    case 2:
+      // few frames: one per round and two waves, so that a CU has half of the filter bank to fetch
+      if ((long long)B * (N / 32) <= 256) return launch_t<64, 3, 1, 2, 2, 2, 13>(g, st);
+      return launch_t<64, 3, 2, 3, 3, 4, 13>(g, st);
     default: return hipErrorInvalidValue;
   }
 }
