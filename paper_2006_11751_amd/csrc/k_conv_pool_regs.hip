@@ -83,7 +83,8 @@ struct CprArgs {
   int B, H, W, Ho, Wo;
   int PC;             // pixels per LDS plane row: W/2 + 1
   int PB;             // bytes per LDS plane: (H + 2) * PC * pitch
-  int n_seg;          // row segments of a frame (one wave each at a time)
+  int n_seg;          // row segments of a workgroup's pooled rows (one wave each at a time)
+  int parts;          // workgroups per round (few frames): each a share of the pooled rows
   int row_pieces;     // 16-byte pieces per image row: W * CIN / 8
   int step_rows;      // image rows that the workgroup's threads cover at once: kNT / row_pieces
 };
@@ -127,13 +128,17 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
   // piece tid % row_pieces (pixel x, channels 8*c8..) of row tid / row_pieces of the step.  In LDS:
   // plane x%2, row y + 1, plane column x/2 (even plane) or x/2 + 1 (odd plane: its column 0 is
   // image column -1).  Threads past step_rows * row_pieces idle.
+  // pooled rows [p0, p1) and the image rows [ya, yb) that they need
+  const int part = g.parts > 1 ? (int)blockIdx.x % g.parts : 0;
+  const int p0 = part * g.Ho / g.parts, p1 = (part + 1) * g.Ho / g.parts;
+  const int ya = max(2 * p0 - 2, 0), yb = min(2 * p1 + 1, g.H);
   const int srow = tid / g.row_pieces, scol = tid - srow * g.row_pieces;
   const bool loader = srow < g.step_rows;
   const int pieces = g.H * g.row_pieces;
   int lds_off0;
   {
     const int px = scol / C8, c8 = scol - px * C8;
-    lds_off0 = (px & 1) * g.PB + ((srow + 1) * g.PC + (px >> 1) + (px & 1)) * P + c8 * 16;
+    lds_off0 = (px & 1) * g.PB + ((ya + srow + 1) * g.PC + (px >> 1) + (px & 1)) * P + c8 * 16;
   }
   u32x4 nx[FPW][PPT];
   auto load_frames = [&](int b0) {
@@ -146,7 +151,8 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
         int p = tid;
         asm volatile("" : "+v"(p));
         p += k * g.step_rows * g.row_pieces;
-        nx[f][k] = src[loader && p < pieces ? p : pieces - 1];
+        const bool here = loader && p < (yb - ya) * g.row_pieces;
+        nx[f][k] = src[here ? p + ya * g.row_pieces : pieces - 1];
       }
     }
   };
@@ -155,7 +161,7 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
     for (int f = 0; f < FPW; ++f)
 #pragma unroll
       for (int k = 0; k < PPT; ++k)
-        if (loader && srow + k * g.step_rows < g.H)
+        if (loader && ya + srow + k * g.step_rows < yb)
           *(u32x4*)(lds + f * FB + lds_off0 + k * g.step_rows * RPB) = nx[f][k];
   };
 
@@ -232,7 +238,7 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
       }
     };
     for (int seg = wave; seg < g.n_seg; seg += kNW) {
-      const int oy0 = seg * g.Ho / g.n_seg, oy1 = (seg + 1) * g.Ho / g.n_seg;
+      const int oy0 = p0 + seg * (p1 - p0) / g.n_seg, oy1 = p0 + (seg + 1) * (p1 - p0) / g.n_seg;
       // Three accumulator sets take the roles carry (row 2y-1), row 2y, row 2y+1 in turn; the
       // maximum lands in the carry's set and the set of row 2y+1 is the next carry: two pooled
       // rows per trip, no copies.
@@ -257,7 +263,8 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
     }
   };
 
-  int b0 = blockIdx.x * FPW;
+  const int stride = (int)gridDim.x / g.parts * FPW;
+  int b0 = (int)blockIdx.x / g.parts * FPW;
   load_frames(b0);
 #pragma unroll
   for (int k = 0; k < NBP; ++k)
@@ -268,10 +275,10 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
   // frame's pixels right after they have been requested.
   __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();  // zeros in place
-  for (; b0 < g.B; b0 += gridDim.x * FPW) {
+  for (; b0 < g.B; b0 += stride) {
     stage();
     __syncthreads();
-    if (b0 + (int)gridDim.x * FPW < g.B) load_frames(b0 + (int)gridDim.x * FPW);
+    if (b0 + stride < g.B) load_frames(b0 + stride);
     compute(b0);
     __syncthreads();  // every read of these frames done before the next ones are staged
   }
@@ -290,7 +297,7 @@ size_t lds_bytes_of(int cin, int H, int W) {
 }
 
 template <int CIN, int PPT, int FPW>
-hipError_t launch_t(const CprArgs& g, size_t lds_bytes, hipStream_t st) {
+hipError_t launch_t(CprArgs g, size_t lds_bytes, hipStream_t st) {
   auto kern = conv_pool_regs_kernel<CIN, PPT, FPW>;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
@@ -299,7 +306,13 @@ hipError_t launch_t(const CprArgs& g, size_t lds_bytes, hipStream_t st) {
   });
   if (attr_status != hipSuccess) return attr_status;
   const int rounds = (g.B + FPW - 1) / FPW;
-  const int blocks = rounds < 256 ? rounds : 256;  // one workgroup per CU, each walking its share of the frames
+  // Few frames: a share of the pooled rows per workgroup while all run at once (one per CU).
+  g.parts = 1;
+  while (2 * g.parts * rounds <= 256 && g.parts < 4 && g.Ho >= 4 * g.parts) g.parts *= 2;
+  const int rows = (g.Ho + g.parts - 1) / g.parts;
+  g.n_seg = g.Ho / g.parts < kNW ? (g.parts > 1 ? g.Ho / g.parts : rows) : kNW;
+  // one workgroup per CU, each walking its share of the frames
+  const int blocks = g.parts * rounds < 256 ? g.parts * rounds : 256;
   kern<<<blocks, kNT, lds_bytes, st>>>(g);
   return hipGetLastError();
 }
@@ -337,7 +350,6 @@ hipError_t launch_conv_pool_regs(const void* in, const uint16_t* wpk, const floa
   g.B = B; g.H = H; g.W = W; g.Ho = (H - 1) / 2 + 1; g.Wo = W / 2;
   g.PC = W / 2 + 1;
   g.PB = (int)plane_bytes(cin, H, W);
-  g.n_seg = g.Ho < kNW ? g.Ho : kNW;
   g.row_pieces = W * (cin / 8);
   g.step_rows = step_rows_of(cin, W);
   const int fpw = frames_per_round(W);

@@ -77,7 +77,25 @@ struct StageArgs {
   const float* bias[kMaxConvs];  // [32] each
   int B, H, n_convs, relu_out;
   int F;  // frames stacked into one LDS image (32 channels; 1 otherwise)
+  // Few frames: workgroups per frame (F = 1).  Each stores its share of the rows and computes it out of a
+  // strip that has n_convs rows more at a border: what zero padding at the strip's edge makes wrong moves on
+  // by one row per convolution.
+  int parts;
 };
+
+// Rows of a workgroup: it stores [r0, r1) and computes the strip [first, first + H).
+struct Strip {
+  int r0, r1, first, H;
+};
+__device__ inline Strip strip_of(const StageArgs& g) {
+  const int part = g.parts > 1 ? (int)blockIdx.x % g.parts : 0;
+  Strip s;
+  s.r0 = part * g.H / g.parts;
+  s.r1 = (part + 1) * g.H / g.parts;
+  s.first = s.r0 == 0 ? 0 : max(s.r0 - g.n_convs, 0);
+  s.H = (s.r1 == g.H ? g.H : min(s.r1 + g.n_convs, g.H)) - s.first;
+  return s;
+}
 
 // C channels (16 or 32), frame width 1 << LW, PPT 16-byte pieces of a frame per thread; RES: the
 // filter banks of all (at most four) convolutions stay in registers (16 channels only).
@@ -105,7 +123,8 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
   // the convolutions run over the stack as over one tall frame and store nothing into the
   // separating rows, and the pieces of the F frames (contiguous in memory) skip them.
   const int frame_pieces = g.H * W * C8;
-  const int HS = g.F * (g.H + 1) - 1;  // rows of the stack
+  const Strip strip = strip_of(g);
+  const int HS = g.F * (strip.H + 1) - 1;  // rows of the stack (more than one workgroup per frame: of the strip)
   const int npix = HS * W;
   const int pieces = g.F * frame_pieces;  // of a full stack
   const int n_groups = (g.B + g.F - 1) / g.F;
@@ -363,7 +382,7 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     const int lane_g = j16 * 32 + g16 * 8;  // the lane's 8 bytes within a tile's 512 in memory
     // (part p of `parts`: rounds p, p + parts, ...)
     auto load_tiles = [&](int bb, u32x2 (&dst)[RT], int part = 0, int parts = 1) {
-      const unsigned char* src = (const unsigned char*)g.x + (size_t)bb * pieces * 16;
+      const unsigned char* src = (const unsigned char*)g.x + (size_t)bb * pieces * 16 + (size_t)strip.first * W * 32;
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         if (r % parts != part) continue;
@@ -438,7 +457,8 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
       }
     };
 
-    int b = blockIdx.x;
+    const int stride = (int)gridDim.x / g.parts;
+    int b = (int)blockIdx.x / g.parts;
     load_tiles(b, xt);
     // Up to two blocks: all four filter banks stay in registers (80), so that the next frame's
     // tiles are the only loads in flight while a frame is computed.  The load counter completes in
@@ -458,14 +478,14 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
       clear();
     }
     __syncthreads();  // zeros in place
-    for (; b < g.B; b += gridDim.x) {
+    for (; b < g.B; b += stride) {
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         const int t = wave + kNW * r;
         if (t < n16) *(u32x2*)(X + tile_off16(t) + lane_o16) = relu2(xt[r]);
       }
       __syncthreads();
-      const int bn = b + (int)gridDim.x < g.B ? b + (int)gridDim.x : b;  // (last round: its own again)
+      const int bn = b + stride < g.B ? b + stride : b;  // (last round: its own again)
       if constexpr (resident) {
         // the next frame is requested in three parts between the convolutions: the requests of
         // all workgroups in one burst kept the last waves of a workgroup 10 k cycles at issuing theirs
@@ -493,13 +513,14 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
           __syncthreads();
         }
       }
-      unsigned char* dst = (unsigned char*)g.out + (size_t)b * pieces * 16;
+      unsigned char* dst = (unsigned char*)g.out + (size_t)b * pieces * 16 + (size_t)strip.first * W * 32;
+      const int t0 = (strip.r0 - strip.first) * (W / 16), t1 = (strip.r1 - strip.first) * (W / 16);  // its own rows
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         int o = lane_g;
         asm volatile("" : "+v"(o));
         const int t = wave + kNW * r;
-        if (t < n16) *(u32x2*)(dst + (size_t)t * 512 + o) = g.relu_out ? relu2(xt[r]) : xt[r];
+        if (t >= t0 && t < t1) *(u32x2*)(dst + (size_t)t * 512 + o) = g.relu_out ? relu2(xt[r]) : xt[r];
       }
 #pragma unroll
       for (int r = 0; r < RT; ++r) xt[r] = nt[r];
@@ -582,7 +603,9 @@ __global__ __launch_bounds__(kNT, 2) void res_stage32_kernel(StageArgs g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
-  const int HS = g.F * (g.H + 1) - 1;  // rows of the stack
+  const Strip strip = strip_of(g);
+  const int H = strip.H;
+  const int HS = g.F * (H + 1) - 1;  // rows of the stack
   const int n_tiles = (HS * W + 31) >> 5;
   const int img_bytes = (((n_tiles << 5) + W - 1) / W + 2) * ROW;
   unsigned char* const X = lds;
@@ -629,10 +652,10 @@ __global__ __launch_bounds__(kNT, 2) void res_stage32_kernel(StageArgs g) {
     int t = wave + kNW * r;
     asm volatile("" : "+s"(t));  // (opaque: computed where it is used, not kept for all rounds)
     const int ys = ((t << 5) >> LW) + (li >> LW), col = ((t << 5) & (W - 1)) + lane_col;
-    const int f = (ys > g.H) + (ys > 2 * g.H + 1) + (ys > 3 * g.H + 2);
-    const int y = ys - f * (g.H + 1);
-    ok = r < own && y < g.H && f < g.F && b * g.F + f < g.B;
-    return ok ? (uint32_t)(((f * g.H + y) * W + col) * PIX + 32 * lh) : 0u;
+    const int f = (ys > H) + (ys > 2 * H + 1) + (ys > 3 * H + 2);
+    const int y = ys - f * (H + 1);
+    ok = r < own && y < H && f < g.F && b * g.F + f < g.B;
+    return ok ? (uint32_t)(((f * H + y + strip.first) * W + col) * PIX + 32 * lh) : 0u;
   };
   const size_t stack_bytes = (size_t)g.F * g.H * W * PIX;
 
@@ -714,8 +737,8 @@ __global__ __launch_bounds__(kNT, 2) void res_stage32_kernel(StageArgs g) {
     for (int i = 0; i < 2; ++i) *(u32x4*)(o + lane_o[i]) = relu8(v[i]);
   };
 
-  const int stride = (int)gridDim.x;
-  int b = blockIdx.x;
+  const int stride = (int)gridDim.x / g.parts;
+  int b = (int)blockIdx.x / g.parts;
 #pragma unroll
   for (int r = 0; r < RT; ++r) load_tile(r, b, x[r]);
 #pragma unroll
@@ -745,7 +768,8 @@ __global__ __launch_bounds__(kNT, 2) void res_stage32_kernel(StageArgs g) {
           // after that is asked for
           bool ok;
           const uint32_t at = place(r, b, ok);
-          if (ok)
+          const int row = (int)(at / (W * PIX));  // (of the frame; a stack: all of them)
+          if (ok && (g.F > 1 || (row >= strip.r0 && row < strip.r1)))
 #pragma unroll
             for (int i = 0; i < 2; ++i) *(u32x4*)(dst + at + 16 * i) = g.relu_out ? relu8(x[r][i]) : x[r][i];
 #pragma unroll
@@ -777,12 +801,17 @@ hipError_t launch_stage_r(const StageArgs& g, size_t lds, hipStream_t st) {
   });
   if (attr_status != hipSuccess) return attr_status;
   // one workgroup per CU, each walking its share of the frames
-  const int groups = (g.B + g.F - 1) / g.F;
+  const int groups = (g.B + g.F - 1) / g.F * g.parts;
   const int blocks = groups < 256 ? groups : 256;
   kern<<<blocks, kNT, lds, st>>>(g);
   return hipGetLastError();
 }
 
+// rows of the largest strip
+int strip_rows(const StageArgs& g) {
+  const int own = (g.H + g.parts - 1) / g.parts, halo = g.n_convs * (g.parts > 2 ? 2 : g.parts - 1);
+  return own + halo < g.H ? own + halo : g.H;
+}
 // 32 channels with the filter banks in LDS: tiles per wave, 0 where it does not take the shape
 int stage32_rounds(int H, int W, int n_convs) {
   const int n_tiles = (H * W + 31) / 32, rows = (n_tiles * 32 + W - 1) / W + 2;
@@ -800,9 +829,9 @@ hipError_t launch_stage32(const StageArgs& g, hipStream_t st) {
   });
   if (attr_status != hipSuccess) return attr_status;
   constexpr int W = 1 << LW;
-  const int n_tiles = ((g.F * (g.H + 1) - 1) * W + 31) / 32, rows = (n_tiles * 32 + W - 1) / W + 2;
+  const int n_tiles = ((g.F * (strip_rows(g) + 1) - 1) * W + 31) / 32, rows = (n_tiles * 32 + W - 1) / W + 2;
   const size_t lds = 2 * (size_t)rows * (W + 2) * 64 + g.n_convs * (18 * 1024 + 32 * sizeof(float));
-  const int groups = (g.B + g.F - 1) / g.F;
+  const int groups = (g.B + g.F - 1) / g.F * g.parts;
   kern<<<groups < 256 ? groups : 256, kNT, lds, st>>>(g);  // one workgroup per CU, each walking its share
   return hipGetLastError();
 }
@@ -887,8 +916,23 @@ hipError_t launch_res_stage(const void* x, void* out, const uint16_t* const* wpk
   }
   g.B = B; g.H = H; g.n_convs = n_convs; g.relu_out = relu_out;
   g.F = stage_frames(c, H, W);
-  const size_t lds = stage_lds_bytes(c, g.F * (H + 1) - 1, W);
-  const int ppt = (g.F * H * W * c / 8 + kNT - 1) / kNT;
+  g.parts = 1;
+  // Few frames: small ones are not stacked while each has a CU of its own, and (see StageArgs::parts) two
+  // strips per frame, four of a tall one, while all workgroups run at once and a strip is a good part shorter
+  // than the frame.  Whole steps of the residual network, first pooling launches shared alike: 4 rows 92.9 ->
+  // 68.9 us, 64 rows 97.8 -> 73.2, 128 rows 104.5 -> 87.0.
+  if (n_convs <= 4 && B <= 256) {
+    if (c == 32 && g.F > 1 && stage32_rounds(H, W, n_convs)) g.F = 1;
+    if (x != out && g.F == 1 && (c == 16 || stage32_rounds(H, W, n_convs)))
+      for (int parts : {2, 4}) {
+        StageArgs t = g;
+        t.parts = parts;
+        if (B * parts <= 256 && 5 * strip_rows(t) <= 4 * strip_rows(g)) g.parts = parts;
+      }
+  }
+  const int HS = g.F * (strip_rows(g) + 1) - 1;  // rows in LDS
+  const size_t lds = stage_lds_bytes(c, HS, W);
+  const int ppt = (g.F * strip_rows(g) * W * c / 8 + kNT - 1) / kNT;
 #define SF_STAGE(C, LW)                                                    \
   do {                                                                     \
     if (ppt <= 2) return launch_stage_t<C, LW, 2>(g, lds, st);             \
@@ -900,7 +944,7 @@ hipError_t launch_res_stage(const void* x, void* out, const uint16_t* const* wpk
     if (W == 32) SF_STAGE(16, 5);
     SF_STAGE(16, 4);
   }
-  if (const int rounds = stage32_rounds(g.F * (H + 1) - 1, W, n_convs)) {
+  if (const int rounds = stage32_rounds(HS, W, n_convs)) {
     if (W == 64) return launch_stage32<6>(g, rounds, st);
     if (W == 32) return launch_stage32<5>(g, rounds, st);
     return launch_stage32<4>(g, rounds, st);

@@ -85,6 +85,7 @@ struct StemPoolArgs {
   int RP;              // LDS row pitch in bytes: (W + 4) pixels of 8 bytes
   int n_cg, n_seg;     // column groups of 16 pooled columns x row segments = a frame's wave units
   int n_items;         // H * W / 4
+  int parts;           // workgroups per frame (few frames): each a share of the pooled rows
   float obs_sub, obs_mul;
 };
 
@@ -95,6 +96,11 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (scalar: row loops branch uniformly)
   const int j = lane & 15, grp = lane >> 4;
   const size_t plane = (size_t)g.H * g.W;
+  // pooled rows [p0, p1) and the image rows [ya, yb) that they need
+  const int part = g.parts > 1 ? (int)blockIdx.x % g.parts : 0;
+  const int p0 = part * g.Ho / g.parts, p1 = (part + 1) * g.Ho / g.parts;
+  const int ya = max(2 * p0 - 2, 0), yb = min(2 * p1 + 1, g.H);
+  const int first_item = ya * (g.W >> 2), last_item = yb * (g.W >> 2) - 1;
 
   const u32x4 a_lo1 = g.wpk[lane], a_lo2 = g.wpk[64 + lane];
   const u32x4 a_hi1 = g.wpk[128 + lane], a_hi2 = g.wpk[192 + lane];
@@ -107,7 +113,7 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   int lds_off[kMaxIt];
 #pragma unroll
   for (int it = 0; it < kMaxIt; ++it) {
-    const int i = min(tid + it * kNT, g.n_items - 1);
+    const int i = min(first_item + tid + it * kNT, last_item);
     const int y = i / Q, jq = i - y * Q;
     lds_off[it] = (y + 1) * g.RP + (4 * jq + 2) * 8;
   }
@@ -116,8 +122,8 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
     const uint8_t* frame = g.obs + (size_t)b * 3 * plane;
 #pragma unroll
     for (int it = 0; it < kMaxIt; ++it) {
-      if (it * kNT >= g.n_items) break;  // uniform
-      const int i = min(tid + it * kNT, g.n_items - 1);
+      if (first_item + it * kNT > last_item) break;  // uniform
+      const int i = min(first_item + tid + it * kNT, last_item);
 #pragma unroll
       for (int c = 0; c < 3; ++c) nx[it][c] = *(const uint32_t*)(frame + c * plane + 4 * (size_t)i);
     }
@@ -125,7 +131,7 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   auto stage = [&]() {
 #pragma unroll
     for (int it = 0; it < kMaxIt; ++it) {
-      if (it * kNT >= g.n_items) break;  // uniform
+      if (first_item + it * kNT > last_item) break;  // uniform
       float c[4][3];
 #pragma unroll
       for (int k = 0; k < 4; ++k)
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
                         f16_bits(c[1][2])};
       const u32x4 hi = {pack_f16(c[2][0], c[2][1]), f16_bits(c[2][2]), pack_f16(c[3][0], c[3][1]),
                         f16_bits(c[3][2])};
-      if (tid + it * kNT < g.n_items) {
+      if (first_item + tid + it * kNT <= last_item) {
         u32x4* dst = (u32x4*)(patch + lds_off[it]);
         dst[0] = lo;
         dst[1] = hi;
@@ -149,7 +155,7 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   auto compute = [&](int b) {
     for (int u = wave; u < n_units; u += kNW) {
       const int cg = u % g.n_cg, seg = u / g.n_cg;
-      const int oy0 = seg * g.Ho / g.n_seg, oy1 = (seg + 1) * g.Ho / g.n_seg;
+      const int oy0 = p0 + seg * (p1 - p0) / g.n_seg, oy1 = p0 + (seg + 1) * (p1 - p0) / g.n_seg;
       const bool live = cg * 16 + j < g.Wo;
       const int x = live ? cg * 16 + j : g.Wo - 1;
       // window of pooled column x: image columns 2x-2 .. 2x+1 = LDS columns 2x .. 2x+3; lane group
@@ -212,7 +218,8 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
     }
   };
 
-  int b = blockIdx.x;
+  const int stride = (int)gridDim.x / g.parts;
+  int b = (int)blockIdx.x / g.parts;
   load_frame(b);
   // Parameters and first frame, requested together, have arrived before the loop (vmcnt(0), other counters
   // untouched).  Otherwise the compiler, which must assume the parameters' loads pending on some path,
@@ -220,10 +227,10 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   // frame's bytes right after they have been requested.
   __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();  // zeros in place
-  for (; b < g.B; b += gridDim.x) {
+  for (; b < g.B; b += stride) {
     stage();
     __syncthreads();
-    if (b + (int)gridDim.x < g.B) load_frame(b + (int)gridDim.x);
+    if (b + stride < g.B) load_frame(b + stride);
     compute(b);
     __syncthreads();  // every read of this frame done before the next one is staged
   }
@@ -278,6 +285,10 @@ hipError_t launch_stem_pool(const uint8_t* obs, const uint16_t* wpk, const float
   if (n_seg > g.Ho / 2) n_seg = g.Ho / 2;
   g.n_seg = n_seg < 1 ? 1 : n_seg;
   g.n_items = H * (W / 4);
+  // Few frames: a share of the pooled rows per workgroup while all run at once (two per CU), two rows or
+  // more per segment.
+  g.parts = 1;
+  while (2 * g.parts * B <= 512 && g.parts < 4 && g.Ho / (2 * g.parts) >= 2 * g.n_seg) g.parts *= 2;
   g.obs_sub = obs_sub; g.obs_mul = obs_mul;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
@@ -286,7 +297,7 @@ hipError_t launch_stem_pool(const uint8_t* obs, const uint16_t* wpk, const float
                                       (int)kMaxLds);
   });
   if (attr_status != hipSuccess) return attr_status;
-  const int blocks = B < 512 ? B : 512;  // two workgroups per CU, each walking its share of the frames
+  const int blocks = g.parts * B < 512 ? g.parts * B : 512 / g.parts * g.parts;  // two workgroups per CU, each walking its share of the frames
   stem_pool_kernel<<<blocks, kNT, stem_pool_lds_bytes(H, W), st>>>(g);
   return hipGetLastError();
 }

@@ -10,9 +10,11 @@ from tests.test_gpu_parity import RESNET_BF16_SMALL, _gpu_step
 pytestmark = pytest.mark.gpu
 
 # second stage frames (32 channels): 8 x 32 (one tile per wave), 12 x 32 with a ragged wave, 18 x 32 (three),
-# 11 x 16 stacked; 600 frames: several per workgroup; three blocks: the kernel that streams its banks
+# 11 x 16; 600 frames: several per workgroup; 131 frames of 13 x 16, stacked by two; up to 128 and 64 frames:
+# two and four strips per frame; three blocks: the kernel that streams its banks
 CASES = [((3, 32, 128), 2, 5), ((3, 45, 128), 2, 600), ((3, 72, 128), 1, 259), ((3, 44, 64), 2, 13),
-         ((3, 72, 128), 3, 3), ((3, 24, 256), 2, 4)]
+         ((3, 72, 128), 3, 3), ((3, 24, 256), 2, 4),
+         ((3, 100, 128), 2, 131), ((3, 72, 128), 2, 128), ((3, 72, 128), 2, 64), ((3, 71, 64), 1, 70), ((3, 41, 128), 2, 1)]
 
 
 @pytest.mark.parametrize("obs,blocks,B", CASES, ids=["%dx%d-%d-%d" % (o[1], o[2], n, b) for o, n, b in CASES])
@@ -34,6 +36,13 @@ def test_stage_with_its_banks_in_lds(torch_cuda, ref, monkeypatch, obs, blocks, 
     monkeypatch.delenv("SF_NO_RES_STAGE")
     g2 = _gpu_step(torch, old, o_, h_, d_, 7, 11)
     old.close()
+    if B > 64:  # (shared among workgroups or not, a frame has the same bits)
+        pol = binding.Policy(net, w)
+        for n in (min(128, B - 1), 64, 3):
+            part = _gpu_step(torch, pol, o_[:n], h_[:n], d_[:n], 7, 11)
+            for k in ("h_out", "value", "logits"):
+                assert np.array_equal(part[k], g[k][:n]), (n, k)
+        pol.close()
     for k in ("h_out", "value"):
         parity.assert_close(k, g[k][rows], o[k], 1e-2)
         # (fp16 streams rounded at different points, each about 1e-3 from the oracle)
