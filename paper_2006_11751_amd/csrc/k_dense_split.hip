@@ -852,10 +852,10 @@ bool dense_fc_supported(int K, int N) { return K > 0 && (K % 32) == 0 && N > 0 &
 bool dense_cell_supported(int I1, int I2, int H) {
   return I1 > 0 && (I1 % 32) == 0 && (I2 % 32) == 0 && H > 0 && (H % 32) == 0;
 }
-// FC layer on 16-bit rows: up to two rounds of the largest tile the tiled kernel (k_conv_bf16.hip),
-// whose time hardly depends on the batch, is the slower one: 2304 -> 512 in bf16 at 2048 rows 17
-// against 21 us, at 4096 rows 33 against 23; 4608 -> 256 in fp16 at 2048 rows 18 against 41 us, at
-// 8192 rows 62 against 45.
+// FC layer on 16-bit rows: up to two rounds of the largest tile; beyond, k_fc16.hip.  Whole steps, this kernel
+// against that one: bf16, 16 rows 24 against 29 us, 256 rows 32, 36, 2048 rows 95, 91; fp16 4608 -> 256, 101 rows
+// 83, 94, 1024 rows 253, 259, 2048 rows 477, 477, 4096 rows 870, 863.  (A handle keeps one of the two, and
+// a handle for 2048 rows also takes calls of few.)
 bool dense_fc_small(int M, int N) { return split_workgroups(M, N / 16, 4, 2) <= 512; }
 // Cells: up to two rounds of the 32-row tile.  Beyond, cell_tile_kernel in fp32 (GRU 512 -> 512 at
 // 512 rows 17.5 against 21 us, at 1024 rows 38 against 25) and k_rnn_bf16.hip in bf16 (at 512 rows 10

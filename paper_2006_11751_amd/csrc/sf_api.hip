@@ -702,6 +702,7 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
       conv_bf16_pack(u.data(), fb.data(), cfg->fc_dim, p->flat, 1, p->act_f16, wt, bb, &p->fc_Kpad);
       p->fc_wbf = bld.upload(wt);
       p->fc_bbf = bld.upload(bb);
+      p->fc16 = !p->stream_f32 && sw.conv_bf16_tc == 0 && fc16_supported(p->flat, cfg->fc_dim);
     }
     macs += (int64_t)p->flat * cfg->fc_dim;
     p->ops.push_back(Op{OP_FC, "fc", 2 * (int64_t)p->flat * cfg->fc_dim, -1, p->enc_buf, -1, -1, 0, 0, 0});
@@ -829,8 +830,8 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   for (int i = 0; i < 3; ++i)
     p->act[i] = i < n_act ? (float*)bld.dev_alloc(act_row_bytes * cfg->max_batch)
                           : nullptr;
-  p->seq_words = (unsigned*)bld.dev_alloc(256);
-  p->trash = (float*)bld.dev_alloc(256);
+  p->trash = (float*)bld.dev_alloc(512);
+  p->seq_words = (unsigned*)p->trash + 64;
   p->fc_out = (float*)bld.dev_alloc(sizeof(float) * (size_t)cfg->fc_dim * cfg->max_batch);
   p->h_new = (float*)bld.dev_alloc(sizeof(float) * (size_t)p->state_dim * cfg->max_batch);
   for (int l = 0; l < p->n_meas; ++l)
@@ -1342,6 +1343,9 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
         if (p->dense_fc)
           SF_LAUNCH(launch_dense_fc(buf(op.in_buf), !p->bf16_path ? 0 : p->act_f16 ? 2 : 1, p->fc_split_w, p->fc_b,
                                     p->fc_out, p->fc_out_bf16, B, p->flat, c.fc_dim, st));
+        else if (p->fc_wbf && p->fc16)
+          SF_LAUNCH(launch_fc16(buf(op.in_buf), p->fc_wbf, p->fc_bbf, p->fc_out, B, p->flat, c.fc_dim, p->act_f16,
+                                p->fc_out_bf16, st));
         else if (p->fc_wbf)
           SF_LAUNCH(launch_conv_bf16(buf(op.in_buf), p->fc_wbf, p->fc_bbf, nullptr, p->fc_out, B, 1, 1,
                                      p->flat, 1, 1, 0, 1, 1, c.fc_dim, p->fc_Kpad, 0, 1,

@@ -122,6 +122,7 @@ struct Policy {
   uint16_t* rnn_split_w = nullptr;  // dev: both matrices packed for k_dense_split.hip, or null
   uint16_t* fc_split_w = nullptr;   // dev: FC matrix packed for k_dense_split.hip, or null
   bool dense_fc = false, dense_core = false;  // the step's FC layer / core run on k_dense_split.hip
+  bool fc16 = false;  // fc_wbf on k_fc16.hip
   bool core_tile = false;           // ... the core on its kernel for many rows
   bool core_round = false;          // the step's core takes its features as bf16 numbers
   double conv1_ratio2 = 0, conv1_ratio3 = 0;  // admission test of the first convolution's digit planes
@@ -224,6 +225,10 @@ hipError_t launch_conv_bf16(const void* in, const uint16_t* wt, const float* bia
                             int stride, int pad, int Ho, int Wo, int N, int Kpad, int relu_in,
                             int relu_out, int in_f32, int resid_f32, int out_f32, int f16,
                             int tc_force, int tag, hipStream_t st);
+// FC layer on 16-bit rows (k_fc16.hip); w as conv_bf16_pack lays it out
+bool fc16_supported(int K, int N);
+hipError_t launch_fc16(const void* x, const uint16_t* w, const float* bias, void* out, int M, int K, int N, int f16,
+                       int out_bf16, hipStream_t st);
 hipError_t launch_maxpool_bf16(int B, int C, int H, int W, const void* in, void* out, int out_f32,
                                int f16, hipStream_t st);
 bool conv3x3_u8_bf16_supported(int cout);
