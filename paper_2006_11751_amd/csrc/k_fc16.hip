@@ -6,9 +6,10 @@
 // leave each CU 24 KB per 64 numbers of K to fetch and 256 cycles of products, so that the time is how much is
 // under way: with two chunks ahead in registers (k_conv_bf16.hip) a chunk took 1.5 k cycles, most of them
 // the trip of activations that another XCD wrote.  Here a ring of kDepth chunks in LDS is filled by loads
-// that go there directly (no registers, no LDS store instructions): all but one of them are on their way.
-// One barrier per chunk: it says that a chunk has come and that the one before it has been read.  Step of the
-// bf16 network at 4096 rows 156 -> 136 us.
+// that go there directly (no registers, no LDS store instructions): all but two of them are on their way.
+// One barrier per two chunks: it says that they have come and that the two before them have been read (one
+// per chunk: 18.0 against 17.6 us at 4096 rows).  2304 -> 512 in bf16 at
+// 4096 rows 25.4 -> 17.6 us (12.5 TB/s out of the L2s), 4608 -> 256 in fp16 at 8192 rows 45 -> 38.
 //
 // A load instruction writes 64 x 16 bytes in lane order, so rows (128 bytes) have no padding; instead the
 // 16-byte pieces of a row are exchanged by the row's number, on the side of the source: slot s of row r holds
@@ -52,7 +53,7 @@ struct Fc16Args {
 template <int BM>
 constexpr int chunk_bytes() { return (BM + kBN) * kRow; }
 template <int BM>
-constexpr int depth() { return 144 * 1024 / chunk_bytes<BM>(); }  // 6 (128 rows), 9, 12
+constexpr int depth() { return 144 * 1024 / chunk_bytes<BM>() / 2 * 2; }  // 6 (128 rows), 8, 12
 
 // 16 bytes per lane to LDS, in lane order (a function of its own: the host pass knows no such size)
 __device__ __attribute__((always_inline)) inline void load_lds(__amdgpu_buffer_rsrc_t from, LdsByte* to, int at, int k) {
@@ -64,7 +65,7 @@ template <int BM, bool F16, bool OUT_BF16>
 __global__ __launch_bounds__(4 * BM, 2) void fc16_kernel(Fc16Args g) {
   constexpr int NW = BM / 16, kDepth = depth<BM>(), CH = chunk_bytes<BM>();
   constexpr int L = CH / 1024 / NW;  // load instructions of a wave per chunk
-  static_assert(2 * NW == BM / 8 && L * NW * 1024 == CH && (kDepth - 2) * L < 64, "whole instructions, as many as the counter holds");
+  static_assert(2 * NW == BM / 8 && L * NW * 1024 == CH && (kDepth - 4) * L < 64, "whole instructions, as many as the counter holds");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(4 * BM, 2) void fc16_kernel(Fc16Args g) {
     }
   };
 #pragma unroll
-  for (int c = 0; c < kDepth - 1; ++c) request(c, c);
+  for (int c = 0; c < kDepth - 2; ++c) request(c, c);
 
   // this lane's piece of its row for each 16 numbers of a chunk; the same exchange for x and w
   const unsigned lds0 = (unsigned)(size_t)base;
@@ -123,31 +124,39 @@ __global__ __launch_bounds__(4 * BM, 2) void fc16_kernel(Fc16Args g) {
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
   };
 
-  int slot = 0;
-  for (int c = 0; c < n_chunks; ++c) {
-    constexpr int V = (kDepth - 2) * L;
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (V & 15) | (V >> 4) << 14);  // this wave's part of chunk c is there
-    __builtin_amdgcn_s_barrier();  // ... and the others'; chunk c - 1 has been read
-    __builtin_amdgcn_sched_barrier(0);
+  auto compute = [&](int slot) __attribute__((always_inline)) {
     const unsigned xb = slot * CH + x_at, wb = slot * CH + w_at;
-    request(c + kDepth - 1, slot == 0 ? kDepth - 1 : slot - 1);  // (past the end: the last one again, for no use)
-    __builtin_amdgcn_sched_barrier(0);
+    u32x4 x[4], w[4];
+    asm volatile(
+        "ds_read_b128 %0, %8\n\t"
+        "ds_read_b128 %1, %9\n\t"
+        "ds_read_b128 %2, %10\n\t"
+        "ds_read_b128 %3, %11\n\t"
+        "ds_read_b128 %4, %12\n\t"
+        "ds_read_b128 %5, %13\n\t"
+        "ds_read_b128 %6, %14\n\t"
+        "ds_read_b128 %7, %15\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(w[0]), "=&v"(x[0]), "=&v"(w[1]), "=&v"(x[1]), "=&v"(w[2]), "=&v"(x[2]), "=&v"(w[3]), "=&v"(x[3])
+        : "v"(from[0] + wb), "v"(from[0] + xb), "v"(from[1] + wb), "v"(from[1] + xb), "v"(from[2] + wb),
+          "v"(from[2] + xb), "v"(from[3] + wb), "v"(from[3] + xb)
+        : "memory");
 #pragma unroll
-    for (int s = 0; s < 4; s += 2) {
-      u32x4 x0, x1, w0, w1;
-      asm volatile(
-          "ds_read_b128 %0, %4\n\t"
-          "ds_read_b128 %1, %5\n\t"
-          "ds_read_b128 %2, %6\n\t"
-          "ds_read_b128 %3, %7\n\t"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(w0), "=&v"(x0), "=&v"(w1), "=&v"(x1)
-          : "v"(from[s] + wb), "v"(from[s] + xb), "v"(from[s + 1] + wb), "v"(from[s + 1] + xb)
-          : "memory");
-      mfma(w0, x0);
-      mfma(w1, x1);
-    }
-    slot = slot + 1 == kDepth ? 0 : slot + 1;
+    for (int s = 0; s < 4; ++s) mfma(w[s], x[s]);
+  };
+  int slot = 0;
+  for (int c = 0; c < n_chunks; c += 2) {
+    constexpr int V = (kDepth - 4) * L;
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (V & 15) | (V >> 4) << 14);  // this wave's parts of chunks c, c + 1 are there
+    __builtin_amdgcn_s_barrier();  // ... and the others'; chunks c - 2, c - 1 have been read
+    __builtin_amdgcn_sched_barrier(0);
+    const int before = slot == 0 ? kDepth - 2 : slot - 2;
+    request(c + kDepth - 2, before);  // (past the end: the last one again, for no use)
+    request(c + kDepth - 1, before + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(slot);
+    if (c + 1 < n_chunks) compute(slot + 1);
+    slot = slot + 2 == kDepth ? 0 : slot + 2;
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);  // (nothing writes to LDS behind this workgroup's end)
 
