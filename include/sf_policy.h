@@ -188,7 +188,8 @@ const char* sf_policy_op_pipe(const sf_policy* p, int i); /* static storage; "" 
 /* The kernel family launch i runs, for tests and benchmarks that must know which code path a
  * shape took: one of "generic", "conv1_mfma", "gemm_mfma", "conv1_i8", "conv_bf16",
  * "conv3x3_u8", "conv3x3_patch", "conv3x3_stem", "conv3x3_pool", "stem_pool", "conv_pool_regs", "res_block",
- * "res_stage", "conv_image_bf16", "conv_image_split", "conv12_fused" for a convolution launch, and "pool", "fc",
+ * "res_stage", "conv_image_bf16", "conv_image_split", "conv12_fused", "conv12_split" (the
+ * first two layers in the first one's launch) for a convolution launch, and "pool", "fc",
  * "meas", "rnn", "heads" for the others.  Static storage; "" if out of range or null. */
 const char* sf_policy_op_kernel(const sf_policy* p, int i);
 double sf_policy_conv1_fixed_point_ratio(const sf_policy* p, int planes);
@@ -268,8 +269,8 @@ int sf_policy_step_indexed(sf_policy* p, int32_t B, const uint8_t* obs, const fl
  *                state after step t (the last row is the state the trajectories end in)
  * The result is that of T calls of sf_policy_step, time t on rows [t][0..N) with the state
  * rows time t - 1 wrote, except that no action is drawn.  The launches: the encoder and the
- * FC layer once on all T * N frames, the core T times on N rows, the heads once on T * N
- * states; the features pass through the handle's workspace, hence T * N <= max_batch, and
+ * FC layer once on all T * N frames, the core in one launch over all steps (where the shape
+ * allows; else T times on N rows), the heads once on T * N states; the features pass through the handle's workspace, hence T * N <= max_batch, and
  * N rows of features and of state must be a multiple of 16 bytes.  Asynchronous on
  * hip_stream; allocates nothing.  N == 0 does nothing.  Errors: SF_ERR_ARG (null or
  * misaligned pointer), SF_ERR_BATCH (T < 1, N < 0, T * N > max_batch), SF_ERR_SHAPE (the
