@@ -44,6 +44,8 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+// a frame's address is a multiple of four bytes only; one load instruction all the same
+typedef u32x4 u32x4_any __attribute__((aligned(4)));
 
 constexpr int kNT = 512;
 constexpr int kCin = 3, kK1 = 8, kS1 = 4, kC1 = 32;  // first layer: planes, filter, stride, channels
@@ -119,7 +121,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
         const int plane = (f >= in_rows * row_pieces) + (f >= 2 * in_rows * row_pieces);
         at += (uint32_t)((plane * (g.H - in_rows) + kS1 * kS2 * row0) * g.W);
       }
-      fv[u] = *(const u32x4*)(src + at);
+      fv[u] = *(const u32x4_any*)(src + at);
     }
   };
   auto store_frame = [&]() {
@@ -423,12 +425,13 @@ bool conv12_split_supported(int cin, int H, int W, const sf_conv& a, const sf_co
   return layout(H, Ho1, Wo1, Wo2).bytes <= kMaxLds;
 }
 
-// L1 on three digit planes, L2 on split operands; obs 16-byte aligned; mid: room for L1's output, written
-// by the fallback only.
+// L1 on three digit planes, L2 on split operands; obs 4-byte aligned (the second layer's sums are this
+// kernel's own: frames at any address have to come here); mid: room for L1's output, written by the
+// fallback only.
 hipError_t launch_conv12_split(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs, float* mid, float* out,
                                hipStream_t st) {
   if (B == 0) return hipSuccess;
-  if (((uintptr_t)obs & 15) != 0 || L1.planes != 3 || (L2.Ho * L2.Wo + 15) / 16 != kMaxTiles) return hipErrorInvalidValue;
+  if (((uintptr_t)obs & 3) != 0 || L1.planes != 3 || (L2.Ho * L2.Wo + 15) / 16 != kMaxTiles) return hipErrorInvalidValue;
   const Layout L = layout(L1.H, L1.Ho, L1.Wo, L2.Wo);
   Args g;
   g.obs = obs; g.wpk1 = L1.ipk; g.scale1 = L1.spk; g.bias1 = L1.bpk8;

@@ -1138,8 +1138,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
              float* value, float* h_out, float* logits_opt, const int32_t* ids, float* h_table,
              int n_env, hipStream_t st, unsigned parts = PART_ALL, size_t feat_row = 0);
 
-// The first two convolutions of an fp32 plain stack in one launch, with the present parameters (16-byte
-// aligned frames).
+// The first two convolutions of an fp32 plain stack in one launch, with the present parameters.
 bool fuses_conv12(const Policy* p) {
   return p->conv12_split && p->convs[0].impl == CONV1_U8_I8 && p->convs[1].impl == CONV_IMAGE_SPLIT;
 }
@@ -1228,7 +1227,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
   const sf_policy_config& c = p->cfg;
   auto buf = [&](int i) -> float* { return i < 0 ? nullptr : p->act[i]; };
   const bool timing = p->timing && parts == PART_ALL;
-  const bool conv12 = fuses_conv12(p) && !misaligned(obs, 16);
+  const bool conv12 = fuses_conv12(p);
   if (timing) SF_LAUNCH(hipEventRecord(p->events[0], st));
   for (size_t i = 0; i < p->ops.size(); ++i) {
     const Op& op = p->ops[i];
