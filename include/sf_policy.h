@@ -268,10 +268,14 @@ int sf_policy_step_indexed(sf_policy* p, int32_t B, const uint8_t* obs, const fl
  *   h_seq   dev  [T][N][state_dim] fp32, 16-byte aligned, must not overlap h0: row t is the
  *                state after step t (the last row is the state the trajectories end in)
  * The result is that of T calls of sf_policy_step, time t on rows [t][0..N) with the state
- * rows time t - 1 wrote, except that no action is drawn.  The launches: the encoder and the
- * FC layer once on all T * N frames, the core in one launch over all steps (where the shape
- * allows; else T times on N rows), the heads once on T * N states; the features pass through the handle's workspace, hence T * N <= max_batch, and
- * N rows of features and of state must be a multiple of 16 bytes.  Asynchronous on
+ * rows time t - 1 wrote, except that no action is drawn and that the core may add its sums in
+ * another order.  The launches: the encoder and the FC layer once on all T * N frames, the core
+ * over all steps at once (where the shape allows; else T times on N rows), the heads once on
+ * T * N states; the features pass through the handle's workspace, hence T * N <= max_batch, and
+ * N rows of features and of state must be a multiple of 16 bytes.  In the core over all steps
+ * workgroups wait for one another, a bounded time: if other work keeps them from running
+ * together for longer than that, their trajectories are computed another way, whose results
+ * differ in rounding (repeated calls are bitwise the same otherwise).  Asynchronous on
  * hip_stream; allocates nothing.  N == 0 does nothing.  Errors: SF_ERR_ARG (null or
  * misaligned pointer), SF_ERR_BATCH (T < 1, N < 0, T * N > max_batch), SF_ERR_SHAPE (the
  * 16-byte rule), SF_ERR_ALIAS, SF_ERR_DEVICE. */

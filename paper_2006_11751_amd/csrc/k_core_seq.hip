@@ -21,10 +21,17 @@
 //
 // Progress.  A workgroup takes its row tile and its units by a ticket when it starts to run, so that the
 // row tiles are filled one after the other and a running workgroup waits only for workgroups that run
-// or are next to.  A wait ends after `limit` reads whatever happens: then a flag is set, the workgroups
-// leave, and core_seq_plain_kernel, launched behind this one, computes the pass in plain fp32 with
-// no exchange between workgroups (it returns at once otherwise).  The same where an infinity, a NaN or a sum
-// that overflows turns up, whose products the terms do not add up to.
+// or are next to.  A wait ends after `limit` reads whatever happens: then the trajectories of that row tile
+// are marked and its workgroups leave; the other tiles do not notice.
+//
+// What the terms cannot compute: the products of an infinity, a NaN or of numbers whose product overflows do
+// not add up to the product.  Such a sum is not finite; its trajectory, whose row is a column of the matrix
+// instructions of its own, is marked and goes on (a NaN of other bits than the pattern), and so does every
+// other one, with the same bits as without it.
+//
+// core_seq_plain_kernel, launched behind this one, computes the marked trajectories again, in plain fp32 and
+// without an exchange between workgroups: from the first such step to the episode's end behind the last one,
+// or all steps of a tile that was given up (the other trajectories' workgroups return at once).
 #include <type_traits>
 
 #include "sf_cell.h"
@@ -41,6 +48,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
+constexpr int kPlain = 1024;  // threads of core_seq_plain_kernel
+constexpr int kMaxX = 3 * 32 * kWaves, kMaxH = 2 * 32 * kWaves;  // see core_seq_supported
 constexpr unsigned kNotYet = 0xFFFFFFFFu;  // fills the h columns of h_seq ahead of the pass
 // cache policy of a buffer load: sc1 (device scope), volatile (repeated as often as it is written)
 constexpr int kDeviceScope = (int)0x80000010;
@@ -51,32 +60,27 @@ struct SeqArgs {
   const uint8_t* done;   // [T][N]
   float* seq;            // [T][N][S]
   int T, n_cg;
-  int limit;             // reads of a word that has not come (negative: the pass is given up at once)
-  unsigned* words;       // [0] ticket, [1] set where the pass was given up
+  int limit;             // reads of a word that has not come (negative: every tile is given up at once)
+  unsigned* ticket;
+  unsigned* mark;        // [N][2], see kNone
 };
+// A trajectory's marks: the first step with a sum that is not finite, plus one (0: its row tile was given
+// up; kNone: neither), and the last such step.
+constexpr unsigned kNone = 0xFFFFFFFFu;
 
 __device__ inline unsigned load_word(const unsigned* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ __launch_bounds__(256) void core_seq_fill_kernel(float* seq, long long rows, int H, int S, unsigned* words) {
+// also sets the n_words words of the ticket and the marks
+__global__ __launch_bounds__(256) void core_seq_fill_kernel(float* seq, long long rows, int H, int S, unsigned* words, int n_words) {
   const int per = H / 4;
   const long long n = rows * per;
-  if (blockIdx.x == 0 && threadIdx.x < 2) words[threadIdx.x] = 0;
+  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < n_words; i += (int)(256 * gridDim.x))
+    words[i] = i & 1 ? kNone : 0;
   const u32x4 v = {kNotYet, kNotYet, kNotYet, kNotYet};
   for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += 256ll * gridDim.x)
     *(u32x4*)(seq + i / per * S + 4 * (i % per)) = v;
-}
-
-// step t's rows for plain_sums
-template <int XT>
-__device__ inline DenseArgs step_args(const SeqArgs& g, int t) {
-  DenseArgs d = g.d;
-  const size_t r = (size_t)t * d.M;
-  d.x1 = (const uint8_t*)d.x1 + r * d.I1 * (XT == X_F32 ? 4 : 2);
-  if (d.x2) d.x2 += r * d.I2;
-  d.h_in = t == 0 ? g.h0 : g.seq + (r - d.M) * d.S;
-  return d;
 }
 
 // KX, KH: K steps (of 32) of a wave over the features / over the state; RT: row tiles of 16.
@@ -93,15 +97,17 @@ __global__ __launch_bounds__(kThreads, 2) void core_seq_kernel(SeqArgs g) {
   __shared__ __attribute__((aligned(16))) float red[2][kWaves][RT * NA][TILE];
   __shared__ unsigned first_word;
   __shared__ int lost[2];                        // a wait was given up, by step (a wave may be one step ahead)
+  __shared__ int odd[2][ROWS];                   // first (plus one) and last step of a row with a sum that is not finite
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
   const int M = g.d.M, H = g.d.H, S = g.d.S;
   if (tid == 0) {
-    first_word = __hip_atomic_fetch_add(g.words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    first_word = __hip_atomic_fetch_add(g.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     lost[0] = lost[1] = 0;
   }
+  if (tid < ROWS) odd[0][tid] = odd[1][tid] = 0;
   __syncthreads();
   const int ticket = __builtin_amdgcn_readfirstlane((int)first_word);
   const int row0 = ticket / g.n_cg * ROWS, cg = ticket % g.n_cg;
@@ -264,7 +270,7 @@ __global__ __launch_bounds__(kThreads, 2) void core_seq_kernel(SeqArgs g) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) missing |= (unsigned)(hv[i][j][e] == kNotYet);
       if (__all(missing == 0) && g.limit >= 0) break;
-      quit = tries >= g.limit || ((tries & 63) == 63 && load_word(g.words + 1) != 0);
+      quit = tries >= g.limit || ((tries & 63) == 63 && load_word(g.mark + 2 * row0) == 0);
       if (quit) break;
       load_h();
     }
@@ -291,7 +297,8 @@ __global__ __launch_bounds__(kThreads, 2) void core_seq_kernel(SeqArgs g) {
     if (quit) lost[t & 1] = 1;
     __syncthreads();
     if (__builtin_expect(lost[t & 1] != 0, 0)) {  // (the same for all threads)
-      if (tid == 0) __hip_atomic_store(g.words + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid < min(ROWS, M - row0))
+        __hip_atomic_fetch_min(g.mark + 2 * (row0 + tid), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
     // ---- the eight partial sums in wave order, gates, new state ----
@@ -323,46 +330,114 @@ __global__ __launch_bounds__(kThreads, 2) void core_seq_kernel(SeqArgs g) {
         const float n = tanh_acc(gate(v, Q2{}) + gate(a, Q0{}) * gate(v, Q3{}));
         h = prev[r] = (1.0f - z) * n + z * before;
       }
-      // (a sum with an infinity or a NaN in it, or of terms that overflow; the next step's flag, behind the
-      // barrier of this one's)
-      if (__builtin_expect(!finite(v) || h != h, 0)) lost[(t + 1) & 1] = 1;
       float* o = g.seq + ((size_t)t * M + m) * S + unit;
       if (m < M) {
         if (q == 0) __hip_atomic_store(o, h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (KIND == LSTM && q == 1) o[H] = prev[r];
       }
+      // a sum with an infinity or a NaN in it, or of terms that overflow (behind the store, which the others
+      // wait for: a NaN is stored again, with bits that no one waits for)
+      if (__builtin_expect(!finite(v) || h != h, 0)) {
+        if (odd[0][16 * r + erow] == 0) odd[0][16 * r + erow] = t + 1;  // (a row's threads are in one wave)
+        odd[1][16 * r + erow] = t;
+        if (h != h && q == 0 && m < M) __hip_atomic_store(o, __builtin_nanf(""), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
     }
   }
-  // (a sum of the last step that overflowed)
   __syncthreads();
-  if (tid == 0 && lost[g.T & 1] != 0) __hip_atomic_store(g.words + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid < min(ROWS, M - row0) && odd[0][tid] != 0) {
+    unsigned* at = g.mark + 2 * (row0 + tid);
+    __hip_atomic_fetch_min(at, (unsigned)odd[0][tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_max(at + 1, (unsigned)odd[1][tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
-// The same pass without an exchange: a workgroup per trajectory, every sum by its definition (slow; only
-// where core_seq_kernel gave up).
+// The marked trajectories without an exchange: a workgroup each, its state in LDS; a wave takes eight units, a
+// lane one of them and every eighth run of eight numbers of K (eight lanes' weights are one cache line).  Whole
+// passes on 64 trajectories of 32 steps, one of them never finite: LSTM 512 -> 512 4.2 ms, GRU 512 -> 512 3.4, in
+// bf16 1.5 (a launch per step, where k_dense_split.hip computes such a row by a lane per unit: 23.3, 18.5, 17.4);
+// all of them given up: 3.9, 3.0, 1.4.
 template <int KIND, int XT, int PB>
-__global__ __launch_bounds__(kThreads) void core_seq_plain_kernel(SeqArgs g) {
-  if (load_word(g.words + 1) == 0) return;
-  const int m = blockIdx.x, H = g.d.H, S = g.d.S;
-  for (int t = 0; t < g.T; ++t) {
-    const DenseArgs d = step_args<XT>(g, t);
-    const bool reset = g.done[(size_t)t * d.M + m] != 0;
-    float* o = g.seq + ((size_t)t * d.M + m) * S;
-    for (int unit = threadIdx.x; unit < H; unit += kThreads) {
-      float sum[4], bias[2][4] = {};
-      plain_sums<KIND, XT, PB>(d, m, reset, unit, sum);
-      for (int q = 0; q < (KIND == LSTM ? 4 : 3); ++q) {
-        bias[0][q] = d.b1[q * H + unit];
-        bias[1][q] = d.b2[q * H + unit];
-      }
-      const float prev = reset ? 0.0f : d.h_in[(size_t)m * S + (KIND == LSTM ? H : 0) + unit];
-      if (KIND == LSTM)
-        cell_lstm(o, H, unit, sum, bias, prev);
+__global__ __launch_bounds__(kPlain) void core_seq_plain_kernel(SeqArgs g) {
+  constexpr int GB = group_bytes(KIND), NG = KIND == LSTM ? 4 : 3;
+  __shared__ __attribute__((aligned(16))) float x[kMaxX], hs[2][kMaxH], cs[kMaxH];
+  const int m = blockIdx.x, M = g.d.M, H = g.d.H, S = g.d.S, k1 = g.d.k1, k2 = g.d.k2, kn = g.d.kn;
+  const unsigned first = load_word(g.mark + 2 * m);
+  if (first == kNone) return;
+  const int t0 = first == 0 ? 0 : (int)first - 1, last = first == 0 ? g.T : (int)load_word(g.mark + 2 * m + 1);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* before = t0 == 0 ? g.h0 + (size_t)m * S : g.seq + ((size_t)(t0 - 1) * M + m) * S;
+  for (int n = tid; n < H; n += kPlain) {
+    hs[t0 & 1][n] = before[n];
+    cs[n] = KIND == LSTM ? before[H + n] : 0.0f;
+  }
+  for (int t = t0; t < g.T; ++t) {
+    const size_t row = (size_t)t * M + m;
+    const bool reset = g.done[row] != 0;
+    if (reset && t > last) return;  // (nothing before this step matters to those behind it)
+    for (int k = tid; k < 32 * k2; k += kPlain) {
+      if constexpr (XT == X_F32)
+        x[k] = k < 32 * k1 ? ((const float*)g.d.x1)[row * g.d.I1 + k] : g.d.x2[row * g.d.I2 + (k - 32 * k1)];
       else
-        cell_gru(o, unit, sum, bias, prev);
+        x[k] = __builtin_bit_cast(float, (unsigned)((const uint16_t*)g.d.x1)[row * g.d.I1 + k] << 16);
     }
-    __threadfence();
-    __syncthreads();
+    __syncthreads();  // (the states of the step before, too)
+    float* const next = hs[(t + 1) & 1];
+    for (int cg = wave; cg < H / 8; cg += kPlain / 64) {
+      const int unit = 8 * cg + (lane & 7);
+      // GRU: r, z, the features' and the state's part of n; LSTM: i, f, g, o
+      float sum[4] = {};
+      const uint8_t* group = g.d.w + (size_t)cg * kn * PB * GB;
+      for (int i = lane >> 3; i < 4 * kn; i += 8) {
+        const int s = i >> 2, lg = i & 3;
+        const bool state = s >= k2;
+        const float* from = state ? hs[t & 1] + 8 * i - 32 * k2 : x + 8 * i;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = state && reset ? 0.0f : from[e];
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+          const int slot = KIND == LSTM || q < 2 ? (q >> 1) * 64 + lg * 16 + (q & 1) * 8 + (lane & 7) : 64 + lg * 8 + (lane & 7);
+          u32x4 w[PB];
+#pragma unroll
+          for (int p = 0; p < PB; ++p) w[p] = *(const u32x4*)(group + ((size_t)s * PB + p) * GB + slot * 16);
+          float a = 0.0f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            float we = 0.0f;
+#pragma unroll
+            for (int p = PB - 1; p >= 0; --p)
+              we += __builtin_bit_cast(float, e & 1 ? w[p][e / 2] & 0xFFFF0000u : w[p][e / 2] << 16);
+            a = fmaf(v[e], we, a);
+          }
+          if (KIND == GRU && q == 2)
+            sum[state ? 3 : 2] += a;
+          else
+            sum[q] += a;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int d = 8; d < 64; d *= 2) sum[q] += __shfl_xor(sum[q], d);
+      float bias[2][4] = {};
+#pragma unroll
+      for (int q = 0; q < NG; ++q) {
+        bias[0][q] = g.d.b1[q * H + unit];
+        bias[1][q] = g.d.b2[q * H + unit];
+      }
+      float* o = g.seq + row * S;
+      float h, cell = 0.0f;
+      if (KIND == LSTM)
+        h = lstm_gates(sum, bias, reset ? 0.0f : cs[unit], cell);
+      else
+        h = gru_gates(sum, bias, reset ? 0.0f : hs[t & 1][unit]);
+      if (lane < 8) {
+        next[unit] = o[unit] = h;
+        if (KIND == LSTM) cs[unit] = o[H + unit] = cell;
+      }
+    }
+    __syncthreads();  // the features are used up
   }
 }
 
@@ -372,7 +447,7 @@ hipError_t launch_rt(const SeqArgs& g, hipStream_t st) {
   core_seq_kernel<KIND, XT, PB, RT, KX, KH><<<blocks, kThreads, 0, st>>>(g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  core_seq_plain_kernel<KIND, XT, PB><<<g.d.M, kThreads, 0, st>>>(g);
+  core_seq_plain_kernel<KIND, XT, PB><<<g.d.M, kPlain, 0, st>>>(g);
   return hipGetLastError();
 }
 template <int KIND, int XT, int PB, int KX, int KH>
@@ -419,10 +494,10 @@ hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const 
   g.d.x1 = x1; g.d.x2 = x2; g.d.w = (const uint8_t*)w; g.d.b1 = b_ih; g.d.b2 = b_hh;
   g.d.M = N; g.d.I1 = I1; g.d.I2 = I2; g.d.H = H; g.d.S = lstm ? 2 * H : H;
   g.d.k1 = I1 / 32; g.d.k2 = (I1 + I2) / 32; g.d.kn = g.d.k2 + H / 32;
-  g.h0 = h0; g.done = done; g.seq = h_seq; g.T = T; g.n_cg = H / 8; g.words = words;
-  g.limit = limit;
+  g.h0 = h0; g.done = done; g.seq = h_seq; g.T = T; g.n_cg = H / 8;
+  g.ticket = words; g.mark = words + 1; g.limit = limit;
   const long long rows = (long long)T * N, pieces = rows * (H / 4);
-  core_seq_fill_kernel<<<(unsigned)(pieces < 256 * 1024 ? (pieces + 255) / 256 : 1024), 256, 0, st>>>(h_seq, rows, H, g.d.S, words);
+  core_seq_fill_kernel<<<(unsigned)(pieces < 256 * 1024 ? (pieces + 255) / 256 : 1024), 256, 0, st>>>(h_seq, rows, H, g.d.S, words, 1 + 2 * N);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (terms == 3) return lstm ? launch_kind<LSTM, X_F32, 3>(g, st) : launch_kind<GRU, X_F32, 3>(g, st);

@@ -830,8 +830,8 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   for (int i = 0; i < 3; ++i)
     p->act[i] = i < n_act ? (float*)bld.dev_alloc(act_row_bytes * cfg->max_batch)
                           : nullptr;
-  p->trash = (float*)bld.dev_alloc(512);
-  p->seq_words = (unsigned*)p->trash + 64;
+  p->trash = (float*)bld.dev_alloc(256);
+  p->seq_words = (unsigned*)bld.dev_alloc(sizeof(unsigned) * (1 + 2 * (size_t)cfg->max_batch));
   p->fc_out = (float*)bld.dev_alloc(sizeof(float) * (size_t)cfg->fc_dim * cfg->max_batch);
   p->h_new = (float*)bld.dev_alloc(sizeof(float) * (size_t)p->state_dim * cfg->max_batch);
   for (int l = 0; l < p->n_meas; ++l)

@@ -151,7 +151,7 @@ struct Policy {
   size_t act_elems;
   float* fc_out;      // dev [max_batch][fc_dim]
   float* h_new;       // dev [max_batch][state_dim]: new states of an indexed step before the scatter
-  unsigned* seq_words;  // dev, counters of the core over time (k_core_seq.hip)
+  unsigned* seq_words;  // dev, ticket and marks by trajectory of the core over time (k_core_seq.hip)
   float* trash;       // dev, 64 floats: target of stores that fall outside a tensor
   std::vector<void*> allocations;
   std::vector<size_t> alloc_bytes;   // size of each allocation, in allocation order
@@ -283,7 +283,7 @@ hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const f
 hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);
-// the core over all steps of N trajectories in one launch (k_core_seq.hip)
+// the core over all steps of N trajectories in one launch (k_core_seq.hip); words: 1 + 2 N
 bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type);
 hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                            const float* h0, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,

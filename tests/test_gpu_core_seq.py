@@ -21,16 +21,19 @@ CASES = {
     "bf16-gru-2-2-two-tiles": (4, 124, dict(fc=512, rnn=512, dtype="bf16")),
     "one-launch-per-step": (3, 20, dict(fc=96, rnn=32)),
     "bf16-lstm-1-1": (5, 24, dict(fc=128, rnn=96, rnn_type="lstm", dtype="bf16")),
+    "lstm-2-2-learner": (32, 64, dict(fc=512, rnn=512, rnn_type="lstm")),
 }
 
 
-def _pass(torch, net, w, T, N, env, monkeypatch, h0=None):
+def _pass(torch, net, w, T, N, env, monkeypatch, h0=None, ends=()):
     with monkeypatch.context() as m:
         for k, v in env.items():
             m.setenv(k, v)
         pol = binding.Policy(net, w, max_batch=T * N)
     obs, h, done, meas = wl.trajectory_inputs(net, T, N)
     h = h if h0 is None else h0
+    for at in ends:
+        done[at] = 1
     out = pol.unroll(*(torch.from_numpy(a).cuda() for a in (obs, h, done)),
                      meas=None if meas is None else torch.from_numpy(meas).cuda())
     torch.cuda.synchronize()
@@ -59,22 +62,34 @@ def test_one_launch_for_all_steps(torch_cuda, ref, monkeypatch, name):
             parity.assert_close(k, got[k], other[k], rtol)
 
 
-@pytest.mark.parametrize("kind", ["gru", "lstm"])
-def test_states_that_are_not_finite(torch_cuda, monkeypatch, kind):
-    """A row that starts with an infinity, a NaN or the NaN that marks a state as still to come: the same
-    kind of number everywhere as with a launch per step, and no other row is touched."""
+@pytest.mark.parametrize("kind,T,N,size", [("gru", 4, 24, (96, 64)), ("lstm", 4, 24, (96, 64)),
+                                           ("gru", 5, 116, (512, 512)), ("lstm", 32, 64, (512, 512))])
+def test_states_that_are_not_finite(torch_cuda, monkeypatch, kind, T, N, size):
+    """A row that starts with an infinity, a NaN, the NaN that marks a state as still to come, or a number
+    whose products overflow: the same kind of number everywhere as with a launch per step, also behind the
+    end of its episode, and every other row, of the same row tile too, has the bits that it has without such
+    neighbours."""
     torch = torch_cuda
-    T, N = 4, 24
-    net = wl.network(0, **dict(BASE, name="odd_" + kind, fc=96, rnn=64, rnn_type=kind, p_done=0.0))
+    net = wl.network(0, **dict(BASE, name="odd_" + kind, fc=size[0], rnn=size[1], rnn_type=kind, p_done=0.0))
     w = wl.weights(net)
-    h0 = wl.trajectory_inputs(net, T, N)[1].copy()
+    w["rnn_w_hh"] = w["rnn_w_hh"].copy()
+    w["rnn_w_hh"][:, 0] = np.where(w["rnn_w_hh"][:, 0] > 0, 4.0, -4.0)
+    clean = wl.trajectory_inputs(net, T, N)[1]
+    h0 = clean.copy()
     h0[3, 5] = np.inf
     h0[9, 60] = np.nan
     h0.view(np.uint32)[17, :] = 0xFFFFFFFF
-    got, _ = _pass(torch, net, w, T, N, {}, monkeypatch, h0)
-    other, _ = _pass(torch, net, w, T, N, {"SF_NO_RNN_SEQ": "1"}, monkeypatch, h0)
+    h0[20, 0] = 3e38
+    ends = [(2, 9), (T - 1, 17)]  # (step, row): a new episode
+    got, _ = _pass(torch, net, w, T, N, {}, monkeypatch, h0, ends)
+    other, _ = _pass(torch, net, w, T, N, {"SF_NO_RNN_SEQ": "1"}, monkeypatch, h0, ends)
+    without, _ = _pass(torch, net, w, T, N, {}, monkeypatch, clean, ends)
+    rows = [r for r in range(N) if r not in (3, 9, 17, 20)]
     for k in got:
         assert np.array_equal(np.isnan(got[k]), np.isnan(other[k])), k
         parity.assert_close(k, np.nan_to_num(got[k]), np.nan_to_num(other[k]), 1e-4)
-    rows = [r for r in range(N) if r not in (3, 9, 17)]
-    assert np.isfinite(got["h_seq"][:, rows]).all()
+        assert np.array_equal(got[k][:, rows], without[k][:, rows]), k
+    assert np.isfinite(without["h_seq"]).all()
+    for t, r in ends:
+        assert np.isnan(got["h_seq"][t - 1, r]).any() and np.isfinite(got["h_seq"][t:, r]).all()
+        assert np.array_equal(got["h_seq"][t:, r], without["h_seq"][t:, r])
