@@ -451,44 +451,47 @@ hipError_t launch_rt(const SeqArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 template <int KIND, int XT, int PB, int KX, int KH>
-hipError_t launch_k(const SeqArgs& g, hipStream_t st) {
+hipError_t launch_k(const SeqArgs& g, int cus, hipStream_t st) {
   if constexpr (KX <= 2)  // (more leave no registers for a second row tile)
-    if ((g.d.M + 15) / 16 * g.n_cg > 256) return launch_rt<KIND, XT, PB, 2, KX, KH>(g, st);
+    if ((g.d.M + 15) / 16 * g.n_cg > cus) return launch_rt<KIND, XT, PB, 2, KX, KH>(g, st);
   return launch_rt<KIND, XT, PB, 1, KX, KH>(g, st);
 }
 template <int KIND, int XT, int PB>
-hipError_t launch_kind(const SeqArgs& g, hipStream_t st) {
+hipError_t launch_kind(const SeqArgs& g, int cus, hipStream_t st) {
   const int kx = (g.d.k2 + kWaves - 1) / kWaves, kh = (g.d.kn - g.d.k2 + kWaves - 1) / kWaves;
-  if (kx <= 1 && kh <= 1) return launch_k<KIND, XT, PB, 1, 1>(g, st);
-  if (kx <= 2 && kh <= 2) return launch_k<KIND, XT, PB, 2, 2>(g, st);
+  if (kx <= 1 && kh <= 1) return launch_k<KIND, XT, PB, 1, 1>(g, cus, st);
+  if (kx <= 2 && kh <= 2) return launch_k<KIND, XT, PB, 2, 2>(g, cus, st);
   if constexpr (XT == X_F32)
-    if (kx <= 3 && kh <= 2) return launch_k<KIND, XT, PB, 3, 2>(g, st);
+    if (kx <= 3 && kh <= 2) return launch_k<KIND, XT, PB, 3, 2>(g, cus, st);
   return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 // Which passes run here.  Features and states of whole K steps, as many as a wave's registers hold the
-// weights of; four steps or more (the launches ahead and behind take 9 us, a step saves 1.7 to 4 us: 2
+// weights of; as many compute units as a row tile has workgroups (they wait for one another, and a unit holds one);
+// four steps or more (the launches ahead and behind take 9 us, a step saves 1.7 to 4 us: 2
 // steps of 64 rows of the bf16 network 38 against 35 us in all); and rows whose workgroups run at once,
-// 16 or 32 rows each (128 rows of 512 units), with three K steps of features per wave, which leave no room
+// 16 or 32 rows each (on 256 units 128 rows of 512), with three K steps of features per wave, which leave no room
 // for a second row tile, two rounds of 16.  Whole passes, 32 x 64 and 32 x 120 / 8 x 256 samples, against a
 // launch per step: GRU 512 342 -> 238, 550 -> 392 / 222 -> 235 us; with 128 measurement features 393 -> 259, 600 ->
 // 457 / 240 -> 271; in bf16 226 -> 172, 320 -> 247 / 129 -> 151; GRU 256 in bf16 656 -> 569, 1048 -> 961 / 548 -> 532,
 // 8 x 512 995 -> 1006.
-bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type) {
+// cus: compute units that the stream's workgroups may use.
+bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type, int cus) {
   if (I1 <= 0 || I1 % 32 || I2 % 32 || H <= 0 || H % 32 || (x_type == 1 && I2)) return false;
   const int kx = ((I1 + I2) / 32 + kWaves - 1) / kWaves, kh = (H / 32 + kWaves - 1) / kWaves;
   if (kx > (x_type == 1 ? 2 : 3) || kh > 2) return false;
   const long long tiles = (N + 15) / 16;
-  return T >= 4 && (kx <= 2 ? (tiles + 1) / 2 * (H / 8) <= 256 : tiles * (H / 8) <= 512);
+  if (H / 8 > cus) return false;
+  return T >= 4 && (kx <= 2 ? (tiles + 1) / 2 * (H / 8) <= cus : tiles * (H / 8) <= 2 * cus);
 }
 
 hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                            const float* h0, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
-                           const float* b_hh, float* h_seq, unsigned* words, int limit, hipStream_t st) {
+                           const float* b_hh, float* h_seq, unsigned* words, int limit, int cus, hipStream_t st) {
   if (!x2) I2 = 0;
-  if (!core_seq_supported(T, N, I1, I2, H, x_type) || (x_type != 0 && x_type != 1) || (x_type == 1 && terms != 1))
+  if (!core_seq_supported(T, N, I1, I2, H, x_type, cus) || (x_type != 0 && x_type != 1) || (x_type == 1 && terms != 1))
     return hipErrorInvalidValue;
   SeqArgs g{};
   g.d.x1 = x1; g.d.x2 = x2; g.d.w = (const uint8_t*)w; g.d.b1 = b_ih; g.d.b2 = b_hh;
@@ -500,9 +503,9 @@ hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const 
   core_seq_fill_kernel<<<(unsigned)(pieces < 256 * 1024 ? (pieces + 255) / 256 : 1024), 256, 0, st>>>(h_seq, rows, H, g.d.S, words, 1 + 2 * N);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (terms == 3) return lstm ? launch_kind<LSTM, X_F32, 3>(g, st) : launch_kind<GRU, X_F32, 3>(g, st);
-  if (x_type == 1) return lstm ? launch_kind<LSTM, X_BF16, 1>(g, st) : launch_kind<GRU, X_BF16, 1>(g, st);
-  return lstm ? launch_kind<LSTM, X_F32, 1>(g, st) : launch_kind<GRU, X_F32, 1>(g, st);
+  if (terms == 3) return lstm ? launch_kind<LSTM, X_F32, 3>(g, cus, st) : launch_kind<GRU, X_F32, 3>(g, cus, st);
+  if (x_type == 1) return lstm ? launch_kind<LSTM, X_BF16, 1>(g, cus, st) : launch_kind<GRU, X_BF16, 1>(g, cus, st);
+  return lstm ? launch_kind<LSTM, X_F32, 1>(g, cus, st) : launch_kind<GRU, X_F32, 1>(g, cus, st);
 }
 
 }  // namespace sf

@@ -280,6 +280,7 @@ Switches read_switches() {
   sw.no_conv_pool_regs = env_set("SF_NO_CONV_POOL_REGS");
   sw.no_rnn_seq = env_set("SF_NO_RNN_SEQ");
   sw.core_seq_limit = env_int("SF_CORE_SEQ_LIMIT");
+  sw.cus = env_int("SF_CUS");
   sw.act_bf16 = env_set("SF_ACT_BF16");
   sw.stream_f32 = env_set("SF_STREAM_F32");
   return sw;
@@ -992,6 +993,7 @@ extern "C" int sf_policy_create(const sf_policy_config* cfg, const sf_policy_wei
   }
   p->device = hip_device;
   p->sw = read_switches();
+  p->cus = p->sw.cus > 0 ? p->sw.cus : prop.multiProcessorCount;
   Builder bld{p, cfg->dtype == SF_DTYPE_BF16};
   bld.status = build_policy(p, cfg, w, bld, Cf, Hf, Wf);
   p->events.resize(p->ops.size() + 1, nullptr);
@@ -1141,6 +1143,18 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
 // The first two convolutions of an fp32 plain stack in one launch, with the present parameters.
 bool fuses_conv12(const Policy* p) {
   return p->conv12_split && p->convs[0].impl == CONV1_U8_I8 && p->convs[1].impl == CONV_IMAGE_SPLIT;
+}
+
+// Compute units that work on this stream may use: all of the device's, but for a stream with a mask.
+int stream_cus(const Policy* p, hipStream_t st) {
+  uint32_t mask[32] = {};
+  if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return p->cus;
+  }
+  int n = 0;
+  for (uint32_t m : mask) n += __builtin_popcount(m);
+  return n > 0 && n < p->cus ? n : p->cus;
 }
 
 bool misaligned(const void* q, uintptr_t a) { return (reinterpret_cast<uintptr_t>(q) & (a - 1)) != 0; }
@@ -1452,12 +1466,13 @@ extern "C" int sf_policy_unroll(sf_policy* handle, int32_t T, int32_t N, const u
                     nullptr, nullptr, 0, st, PART_ENCODER);
   // ... the core over all steps in one launch ...
   const int x_type = p->fc_out_bf16 ? 1 : 0;
-  if (rc == SF_OK && p->rnn_split_w && !p->sw.no_rnn_seq &&
-      core_seq_supported(T, N, c.fc_dim, p->meas_out_dim, c.rnn_dim, x_type)) {
+  auto one_launch = [&](int cus) { return core_seq_supported(T, N, c.fc_dim, p->meas_out_dim, c.rnn_dim, x_type, cus); };
+  int cus = p->cus;
+  if (rc == SF_OK && p->rnn_split_w && !p->sw.no_rnn_seq && one_launch(cus) && one_launch(cus = stream_cus(p, st))) {
     const int limit = p->sw.core_seq_limit ? p->sw.core_seq_limit : 1 << 17;
     hipError_t e = launch_core_seq(c.rnn_type == SF_RNN_LSTM, T, N, c.fc_dim, p->meas_out_dim, c.rnn_dim, p->fc_out, x_type,
                                    p->n_meas ? p->meas_buf[p->n_meas - 1] : nullptr, h0, done, p->rnn_split_w,
-                                   c.dtype == SF_DTYPE_BF16 ? 1 : 3, p->gru_bih, p->gru_bhh, h_seq, p->seq_words, limit, st);
+                                   c.dtype == SF_DTYPE_BF16 ? 1 : 3, p->gru_bih, p->gru_bhh, h_seq, p->seq_words, limit, cus, st);
     if (e != hipSuccess) {
       set_error("sf_policy_unroll: launch failed: %s", hipGetErrorString(e));
       rc = SF_ERR_DEVICE;

@@ -77,6 +77,7 @@ struct Switches {
   bool no_conv_pool_regs = false;  // SF_NO_CONV_POOL_REGS
   bool no_rnn_seq = false;         // SF_NO_RNN_SEQ
   int core_seq_limit = 0;          // SF_CORE_SEQ_LIMIT (0 = default; negative: the exchange is given up at once)
+  int cus = 0;                     // SF_CUS: compute units that core_seq_supported counts on (0 = the device's)
   bool act_bf16 = false;         // SF_ACT_BF16
   bool stream_f32 = false;       // SF_STREAM_F32
 };
@@ -101,6 +102,7 @@ struct Policy {
   sf_policy_config cfg;
   Switches sw;
   int device;
+  int cus;    // compute units of the device
   int flat;   // encoder output elements per row
   int sumA;   // total logits per row
   int max_head = 0;  // categories of the largest head
@@ -284,10 +286,10 @@ hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void*
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);
 // the core over all steps of N trajectories in one launch (k_core_seq.hip); words: 1 + 2 N
-bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type);
+bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type, int cus);
 hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                            const float* h0, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
-                           const float* b_hh, float* h_seq, unsigned* words, int limit, hipStream_t st);
+                           const float* b_hh, float* h_seq, unsigned* words, int limit, int cus, hipStream_t st);
 bool rnn_bf16_supported(int I1, int I2, int H);
 void rnn_bf16_pack(const float* w, size_t n, std::vector<uint16_t>& out);
 hipError_t launch_rnn_bf16(int lstm, int B, int I1, int I2, int H, const void* x1, int x1_bf16,

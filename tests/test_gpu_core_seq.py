@@ -1,6 +1,8 @@
 """The recurrent core over all time steps in one launch (k_core_seq.hip): every number of K steps per wave,
 one and two row tiles per workgroup, ragged rows, more workgroups than the chip has CUs, states that are
 not finite, and the pass that gives up its exchange and is computed again without one."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -93,3 +95,55 @@ def test_states_that_are_not_finite(torch_cuda, monkeypatch, kind, T, N, size):
     for t, r in ends:
         assert np.isnan(got["h_seq"][t - 1, r]).any() and np.isfinite(got["h_seq"][t:, r]).all()
         assert np.array_equal(got["h_seq"][t:, r], without["h_seq"][t:, r])
+
+
+def _same_as_single_steps(pol, args, stream=None):
+    """Whether a pass has the bits of passes of one step each (a launch per step), by step."""
+    obs, h0, done = args
+    got = {k: v.cpu().numpy() for k, v in pol.unroll(obs, h0, done, stream=stream).items()}
+    same, h = [], h0
+    for t in range(obs.shape[0]):
+        out = pol.unroll(obs[t:t + 1], h, done[t:t + 1])
+        same.append(all(np.array_equal(out[k][0].cpu().numpy(), got[k][t]) for k in got))
+        h = out["h_seq"][0].clone()
+    return same
+
+
+def test_compute_units_that_a_row_tile_needs(torch_cuda, monkeypatch):
+    """The workgroups of a row tile wait for one another: on fewer compute units than they are (SF_CUS), and
+    where the pass would take several rounds of workgroups, a launch per step."""
+    torch = torch_cuda
+    net = wl.network(0, **dict(BASE, name="few_units", fc=512, rnn=512))
+    w = wl.weights(net)
+    T = 5
+    for N, cus, one_launch in ((16, 0, True), (16, 64, True), (16, 63, False), (64, 128, True), (64, 127, False)):
+        with monkeypatch.context() as m:
+            if cus:
+                m.setenv("SF_CUS", str(cus))
+            pol = binding.Policy(net, w, max_batch=T * N)
+        same = _same_as_single_steps(pol, [torch.from_numpy(a).cuda() for a in wl.trajectory_inputs(net, T, N)[:3]])
+        pol.close()
+        assert all(same) != one_launch, (N, cus, same)
+
+
+def test_stream_with_a_mask(torch_cuda):
+    """The same for a stream that may not use all compute units: 128 rows of 512 units take 256 of them."""
+    torch = torch_cuda
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    if units != 256:
+        pytest.skip("sizes are those of 256 compute units")
+    hip = C.CDLL("libamdhip64.so")
+    mask, raw = (C.c_uint32 * 8)(*[0xFFFFFF00] + [0xFFFFFFFF] * 7), C.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(C.byref(raw), C.c_uint32(8), mask) == 0
+    net = wl.network(0, **dict(BASE, name="masked", fc=512, rnn=512))
+    T, N = 5, 128
+    pol = binding.Policy(net, wl.weights(net), max_batch=T * N)
+    args = [torch.from_numpy(a).cuda() for a in wl.trajectory_inputs(net, T, N)[:3]]
+    torch.cuda.synchronize()
+    assert not all(_same_as_single_steps(pol, args))
+    stream = torch.cuda.ExternalStream(raw.value)
+    with torch.cuda.stream(stream):
+        assert all(_same_as_single_steps(pol, args, stream))
+    stream.synchronize()
+    pol.close()
+    assert hip.hipStreamDestroy(raw) == 0
