@@ -469,22 +469,25 @@ hipError_t launch_kind(const SeqArgs& g, int cus, hipStream_t st) {
 }  // namespace
 
 // Which passes run here.  Features and states of whole K steps, as many as a wave's registers hold the
-// weights of; as many compute units as a row tile has workgroups (they wait for one another, and a unit holds one);
-// four steps or more (the launches ahead and behind take 9 us, a step saves 1.7 to 4 us: 2
-// steps of 64 rows of the bf16 network 38 against 35 us in all); and rows whose workgroups run at once,
-// 16 or 32 rows each (on 256 units 128 rows of 512), with three K steps of features per wave, which leave no room
-// for a second row tile, two rounds of 16.  Whole passes, 32 x 64 and 32 x 120 / 8 x 256 samples, against a
-// launch per step: GRU 512 342 -> 238, 550 -> 392 / 222 -> 235 us; with 128 measurement features 393 -> 259, 600 ->
-// 457 / 240 -> 271; in bf16 226 -> 172, 320 -> 247 / 129 -> 151; GRU 256 in bf16 656 -> 569, 1048 -> 961 / 548 -> 532,
-// 8 x 512 995 -> 1006.
+// weights of; as many compute units as a row tile has workgroups (they wait for one another, and a unit holds
+// one); rows whose workgroups run at once, 16 or 32 rows each (on 256 units 128 rows of 512), with three K steps of
+// features per wave, which leave no room for a second row tile, two rounds of 16.  Whole passes, 32 x 64 and
+// 32 x 120 / 8 x 256 samples, against a launch per step: GRU 512 342 -> 238, 550 -> 392 / 222 -> 235 us; with 128
+// measurement features 393 -> 259, 600 -> 457 / 240 -> 271; in bf16 226 -> 172, 320 -> 247 / 129 -> 151; GRU 256 in
+// bf16 656 -> 569, 1048 -> 961 / 548 -> 532, 8 x 512 995 -> 1006.
+// And steps enough: the launches ahead and behind and the weights' way into registers take 9 us and more, a step
+// saves 1.5 to 5.  From 16 to 256 rows of 32 to 512 units, both cells, both types: in one row tile 4 steps
+// are faster everywhere (45.9 against 50.6 us to 54.1 against 61.7); beyond, 4 are not (LSTM 512 on 32 rows 72.1 against
+// 64.8, GRU 256 on 128 rows 111.8 against 107.7), 5 with up to 256 units are (211.7 against 212.6 to 53.7
+// against 64.2) and with 512 not (82.1 against 79.7 on 48 rows in bf16), 6 are (106.6 against 114.4 on 64).
 // cus: compute units that the stream's workgroups may use.
 bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type, int cus) {
   if (I1 <= 0 || I1 % 32 || I2 % 32 || H <= 0 || H % 32 || (x_type == 1 && I2)) return false;
   const int kx = ((I1 + I2) / 32 + kWaves - 1) / kWaves, kh = (H / 32 + kWaves - 1) / kWaves;
   if (kx > (x_type == 1 ? 2 : 3) || kh > 2) return false;
   const long long tiles = (N + 15) / 16;
-  if (H / 8 > cus) return false;
-  return T >= 4 && (kx <= 2 ? (tiles + 1) / 2 * (H / 8) <= cus : tiles * (H / 8) <= 2 * cus);
+  if (H / 8 > cus || T < (tiles == 1 ? 4 : H <= 256 ? 5 : 6)) return false;
+  return (kx <= 2 ? (tiles + 1) / 2 * (H / 8) : (tiles * (H / 8) + 1) / 2) <= cus;
 }
 
 hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const void* x1, int x_type, const float* x2,

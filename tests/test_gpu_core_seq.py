@@ -15,12 +15,12 @@ BASE = dict(obs=(3, 36, 64), convs=[(16, 8, 4, 0), (32, 4, 2, 0)], p_done=0.2)
 # name, T, N, network: features + state -> K steps per wave (32 numbers each, eight waves)
 CASES = {
     "gru-1-1": (5, 20, dict(fc=96, rnn=32)),
-    "gru-1-1-two-tiles": (4, 500, dict(fc=128, rnn=128)),
+    "gru-1-1-two-tiles": (5, 500, dict(fc=128, rnn=128)),
     "lstm-2-1": (6, 7, dict(fc=288, rnn=64, rnn_type="lstm")),
-    "gru-2-2-two-tiles": (4, 116, dict(fc=512, rnn=512)),
+    "gru-2-2-two-tiles": (6, 116, dict(fc=512, rnn=512)),
     "lstm-2-2": (5, 12, dict(fc=512, rnn=288, rnn_type="lstm")),
-    "gru-3-2-two-rounds": (5, 120, dict(fc=512, rnn=512, meas_dim=23, meas_hidden=[64, 128])),
-    "bf16-gru-2-2-two-tiles": (4, 124, dict(fc=512, rnn=512, dtype="bf16")),
+    "gru-3-2-two-rounds": (6, 120, dict(fc=512, rnn=512, meas_dim=23, meas_hidden=[64, 128])),
+    "bf16-gru-2-2-two-tiles": (6, 124, dict(fc=512, rnn=512, dtype="bf16")),
     "one-launch-per-step": (3, 20, dict(fc=96, rnn=32)),
     "bf16-lstm-1-1": (5, 24, dict(fc=128, rnn=96, rnn_type="lstm", dtype="bf16")),
     "lstm-2-2-learner": (32, 64, dict(fc=512, rnn=512, rnn_type="lstm")),
@@ -64,8 +64,8 @@ def test_one_launch_for_all_steps(torch_cuda, ref, monkeypatch, name):
             parity.assert_close(k, got[k], other[k], rtol)
 
 
-@pytest.mark.parametrize("kind,T,N,size", [("gru", 4, 24, (96, 64)), ("lstm", 4, 24, (96, 64)),
-                                           ("gru", 5, 116, (512, 512)), ("lstm", 32, 64, (512, 512))])
+@pytest.mark.parametrize("kind,T,N,size", [("gru", 5, 24, (96, 64)), ("lstm", 5, 24, (96, 64)),
+                                           ("gru", 6, 116, (512, 512)), ("lstm", 32, 64, (512, 512))])
 def test_states_that_are_not_finite(torch_cuda, monkeypatch, kind, T, N, size):
     """A row that starts with an infinity, a NaN, the NaN that marks a state as still to come, or a number
     whose products overflow: the same kind of number everywhere as with a launch per step, also behind the
@@ -115,7 +115,7 @@ def test_compute_units_that_a_row_tile_needs(torch_cuda, monkeypatch):
     torch = torch_cuda
     net = wl.network(0, **dict(BASE, name="few_units", fc=512, rnn=512))
     w = wl.weights(net)
-    T = 5
+    T = 6
     for N, cus, one_launch in ((16, 0, True), (16, 64, True), (16, 63, False), (64, 128, True), (64, 127, False)):
         with monkeypatch.context() as m:
             if cus:
@@ -124,6 +124,18 @@ def test_compute_units_that_a_row_tile_needs(torch_cuda, monkeypatch):
         same = _same_as_single_steps(pol, [torch.from_numpy(a).cuda() for a in wl.trajectory_inputs(net, T, N)[:3]])
         pol.close()
         assert all(same) != one_launch, (N, cus, same)
+
+
+@pytest.mark.parametrize("H,N,shortest", [(32, 16, 4), (32, 17, 5), (256, 16, 4), (256, 40, 5), (512, 16, 4), (512, 17, 6)])
+def test_short_passes(torch_cuda, H, N, shortest):
+    """Passes of fewer steps than pay for the one launch take a launch per step."""
+    torch = torch_cuda
+    net = wl.network(0, **dict(BASE, name="short", fc=H, rnn=H))
+    pol = binding.Policy(net, wl.weights(net), max_batch=shortest * N)
+    for T in (shortest - 1, shortest):
+        same = _same_as_single_steps(pol, [torch.from_numpy(a).cuda() for a in wl.trajectory_inputs(net, T, N)[:3]])
+        assert all(same) == (T < shortest), (T, same)
+    pol.close()
 
 
 def test_stream_with_a_mask(torch_cuda):
@@ -136,7 +148,7 @@ def test_stream_with_a_mask(torch_cuda):
     mask, raw = (C.c_uint32 * 8)(*[0xFFFFFF00] + [0xFFFFFFFF] * 7), C.c_void_p()
     assert hip.hipExtStreamCreateWithCUMask(C.byref(raw), C.c_uint32(8), mask) == 0
     net = wl.network(0, **dict(BASE, name="masked", fc=512, rnn=512))
-    T, N = 5, 128
+    T, N = 6, 128
     pol = binding.Policy(net, wl.weights(net), max_batch=T * N)
     args = [torch.from_numpy(a).cuda() for a in wl.trajectory_inputs(net, T, N)[:3]]
     torch.cuda.synchronize()
