@@ -542,8 +542,10 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
         p->ops.erase(p->ops.begin() + 1);
       }
       // fp32: the first two layers run as one launch while the parameters admit both to their split
-      // arithmetic (see fuses_conv12); the operations stay two
-      p->conv12_split = cfg->n_conv >= 2 && !sw.no_conv12_fuse && !p->bf16_path && p->convs[0].ipk && p->convs[1].ssc &&
+      // arithmetic (see fuses_conv12); the operations stay two.  (Not with the switches of the first layer's own
+      // kernel, which it does not read.)
+      p->conv12_split = cfg->n_conv >= 2 && !sw.no_conv12_fuse && sw.conv1_waves == 0 && !sw.no_conv1_image &&
+                        !p->bf16_path && p->convs[0].ipk && p->convs[1].ssc &&
                         conv12_split_supported(cfg->obs_c, cfg->obs_h, cfg->obs_w, cfg->conv[0], cfg->conv[1]);
     } else {
       // buffer roles rotate: x holds the stage state, t and u are scratch

@@ -33,6 +33,7 @@ CASES = [
     ("SF_NO_CONV1_IMAGE", "1", dict(STD_SMALL, B=2060)),  # (the frame-resident kernel is for 2048 frames and more)
     ("SF_NO_BF16_PATH", "1", STD_BF16_SMALL),
     ("SF_NO_RNN_BF16", "1", STD_BF16_SMALL),
+    ("SF_NO_CONV12_FUSE", "1", STD_SMALL),
     ("SF_CONV_BF16_TC", "2", STD_BF16_SMALL),
     ("SF_FC_OUT_F32", "1", STD_BF16_SMALL),
     ("SF_NO_CONV_IMAGE", "1", STD_BF16_SMALL),
@@ -56,6 +57,9 @@ def test_switch(torch_cuda, ref, monkeypatch, var, val, net):
     monkeypatch.setenv(var, val)
     pol, w = _make(torch, net)
     monkeypatch.delenv(var)
+    if var in ("SF_CONV1_WAVES", "SF_NO_CONV1_IMAGE", "SF_NO_CONV12_FUSE") and net["dtype"] == "fp32":
+        # (they are about the first convolution's own kernel)
+        assert pol.op_kernels()[:2] == ["conv1_i8", "conv_image_split"]
     d = pol.device
     B = net["B"]
     obs, state, done = wl.observations(net, 0, B), wl.initial_state(net, B), wl.done_mask(net, 0, B)
