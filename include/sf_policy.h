@@ -188,8 +188,8 @@ const char* sf_policy_op_pipe(const sf_policy* p, int i); /* static storage; "" 
 /* The kernel family launch i runs, for tests and benchmarks that must know which code path a
  * shape took: one of "generic", "conv1_mfma", "gemm_mfma", "conv1_i8", "conv_bf16",
  * "conv3x3_u8", "conv3x3_patch", "conv3x3_stem", "conv3x3_pool", "stem_pool", "conv_pool_regs", "res_block",
- * "res_stage", "conv_image_bf16", "conv_image_split", "conv12_fused", "conv12_split" (the
- * first two layers in the first one's launch) for a convolution launch, and "pool", "fc",
+ * "res_stage", "conv_image_bf16", "conv_image_split", "conv12_fused", "conv12_split" (of
+ * the first two operations, which are then one launch) for a convolution launch, and "pool", "fc",
  * "meas", "rnn", "heads" for the others.  Static storage; "" if out of range or null. */
 const char* sf_policy_op_kernel(const sf_policy* p, int i);
 double sf_policy_conv1_fixed_point_ratio(const sf_policy* p, int planes);
@@ -320,10 +320,12 @@ int64_t sf_policy_flops_per_row(const sf_policy* p);
 
 /* ---- measurement aids (used by the benchmark; not part of the step) ----------
  * The step is a fixed sequence of kernel launches ("ops": the convolutions, the
- * FC layer, the GRU cell, the heads).  With timing enabled sf_policy_step records
+ * FC layer, the GRU cell, the heads), one each; where the kernel of ops 0 and 1 is
+ * "conv12_split", the launch of op 0 does both.  With timing enabled sf_policy_step records
  * a HIP event on its stream before the first and after every launch;
  * sf_policy_last_op_times waits for the last recorded step and writes the
- * duration of each launch in milliseconds to ms_out[0..op_count).  Errors:
+ * duration of each launch in milliseconds to ms_out[0..op_count) (0 for an op that the launch
+ * before did).  Errors:
  * SF_ERR_ARG (null handle or buffer, n < op_count), SF_ERR_DEVICE (nothing
  * recorded yet). */
 int sf_policy_op_count(const sf_policy* p);

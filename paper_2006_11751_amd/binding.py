@@ -475,7 +475,7 @@ class Policy:
         return int(load_library().sf_policy_flops_per_row(self.handle))
 
     def ops(self):
-        """[(name, flops_per_row)] for each kernel launch of the step."""
+        """[(name, flops_per_row)] for each operation of the step (see op_kernels)."""
         L = load_library()
         return [(L.sf_policy_op_name(self.handle, i).decode(),
                  int(L.sf_policy_op_flops_per_row(self.handle, i)))
@@ -489,7 +489,8 @@ class Policy:
                 for i in range(L.sf_policy_op_count(self.handle))]
 
     def op_kernels(self):
-        """The kernel family of each launch ("stem_pool", "res_stage", "gemm_mfma", ...)."""
+        """The kernel family of each operation ("stem_pool", "res_stage", "gemm_mfma", ...); "conv12_split" for
+        the first two where they are one launch, whose time is the first one's."""
         L = load_library()
         return [L.sf_policy_op_kernel(self.handle, i).decode()
                 for i in range(L.sf_policy_op_count(self.handle))]

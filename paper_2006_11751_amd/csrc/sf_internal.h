@@ -170,6 +170,7 @@ struct Policy {
   // optional per-launch timing (measurement aid)
   bool timing = false;
   std::vector<hipEvent_t> events;  // ops.size() + 1
+  bool timed_conv12 = false;       // the timed step ran the first two operations as one launch
 };
 
 void set_error(const char* fmt, ...);

@@ -20,7 +20,7 @@ def test_one_launch_and_two(torch_cuda, ref, monkeypatch, height):
     with monkeypatch.context() as m:
         m.setenv("SF_NO_CONV12_FUSE", "1")
         two = binding.Policy(net, w, max_batch=B)
-    assert one.op_kernels()[0] == "conv12_split" and two.op_kernels()[0] == "conv1_i8"
+    assert one.op_kernels()[:2] == ["conv12_split"] * 2 and two.op_kernels()[:2] == ["conv1_i8", "conv_image_split"]
     o_, s_, d_ = wl.observations(net, 0, B), wl.initial_state(net, B), wl.done_mask(net, 0, B)
     raw = torch.empty(o_.size + 4, dtype=torch.uint8, device="cuda")
     shifted = raw[4:].view(o_.shape).copy_(torch.from_numpy(o_))
@@ -40,6 +40,13 @@ def test_one_launch_and_two(torch_cuda, ref, monkeypatch, height):
             part = step(one, n, x)
             for k in full:
                 assert np.array_equal(part[k], full[k][:n]), (n, k)
+    # the second layer is in the first one's launch
+    for pol in (one, two):
+        pol.set_op_timing(True)
+        step(pol, 300, obs)
+        ms = pol.last_op_times_ms()
+        assert (ms[1] == 0.0) == (pol is one) and min(ms[:1] + ms[2:]) > 0.0, ms
+        pol.set_op_timing(False)
     one.close()
     two.close()
 

@@ -1,6 +1,7 @@
-"""fp32 convolutions on operands split into two fp16 terms (k_conv_image_split.hip): rounds of one
-and two frames with a ragged last one, several rounds per workgroup, another frame size, channels of
-very different size, and the admission test that sends a layer back to the fp32 kernel."""
+"""fp32 convolutions on operands split into two fp16 terms (k_conv_image_split.hip, and k_conv12_split.hip for
+the first two layers in one launch): rounds of one and two frames with a ragged last one, several rounds
+per workgroup, another frame size, channels of very different size, and the admission test that sends a
+layer back to the fp32 kernel.  The second layer on either kernel."""
 import numpy as np
 import pytest
 
@@ -22,14 +23,22 @@ def _net(**kw):
     return wl.network(1, fc=64, rnn=64, name="conv_split", **kw)
 
 
+@pytest.fixture(params=["conv12_split", "conv_image_split"])
+def second(request, monkeypatch):
+    """The second layer's kernel on frames of 72 x 128."""
+    if request.param == "conv_image_split":
+        monkeypatch.setenv("SF_NO_CONV12_FUSE", "1")
+    return request.param
+
+
 @pytest.mark.parametrize("obs,kernels", [((3, 72, 128), ["conv_image_split", "conv_image_split"]),
                                          ((3, 68, 132), ["conv_image_split", "gemm_mfma"])])
-def test_rounds_and_frame_sizes(torch_cuda, ref, obs, kernels):
+def test_rounds_and_frame_sizes(torch_cuda, ref, second, obs, kernels):
     torch = torch_cuda
     net = _net(obs=obs)
     w = wl.weights(net)
     pol = binding.Policy(net, w, max_batch=1100)
-    assert pol.op_kernels()[1:3] == kernels
+    assert pol.op_kernels()[1:3] == ([second] if obs == (3, 72, 128) else kernels[:1]) + kernels[1:]
     full = None
     for B in (1100, 515, 3, 2, 1):  # 1100 frames: three and two rounds per workgroup
         g, (o_, s_, d_) = _run(torch, pol, net, B)
@@ -45,7 +54,7 @@ def test_rounds_and_frame_sizes(torch_cuda, ref, obs, kernels):
 
 
 @pytest.mark.parametrize("spread", [0, 12, 40])
-def test_channels_of_different_size(torch_cuda, ref, spread):
+def test_channels_of_different_size(torch_cuda, ref, second, spread):
     """Channel c of a layer 2^s larger and the next layer's weights on it 2^s smaller: the network
     is the same, and the split's errors follow each channel's own size."""
     torch = torch_cuda
@@ -58,13 +67,13 @@ def test_channels_of_different_size(torch_cuda, ref, spread):
         w["conv_b"][l] = w["conv_b"][l] * s
         w["conv_w"][l + 1] = w["conv_w"][l + 1] / s[None, :, None, None]
     pol = binding.Policy(net, w, max_batch=33)
-    assert pol.op_kernels()[1:3] == ["conv_image_split"] * 2
+    assert pol.op_kernels()[1:3] == [second, "conv_image_split"]
     g, (o_, s_, d_) = _run(torch, pol, net, 33)
     parity.check_against_oracle(net, g, ref.policy_step(net, w, o_, s_, d_, 7, 11), ref, 7, 11)
     pol.close()
 
 
-def test_admission_follows_the_parameters(torch_cuda, ref):
+def test_admission_follows_the_parameters(torch_cuda, ref, second):
     """Activations near the end of fp32's range go to the fp32 kernel; a weight update moves the
     layer there and back, each state with the bits of a fresh policy."""
     torch = torch_cuda
@@ -81,7 +90,7 @@ def test_admission_follows_the_parameters(torch_cuda, ref):
     g, (o_, s_, d_) = _run(torch, pol, net, 5)
     parity.check_against_oracle(net, g, ref.policy_step(net, huge, o_, s_, d_, 7, 11), ref, 7, 11)
     pol.update_weights(w)
-    assert pol.op_kernels()[1:3] == ["conv_image_split"] * 2
+    assert pol.op_kernels()[1:3] == [second, "conv_image_split"]
     again, _ = _run(torch, pol, net, 5)
     for k in first:
         assert np.array_equal(first[k], again[k]), k
@@ -89,7 +98,7 @@ def test_admission_follows_the_parameters(torch_cuda, ref):
 
 
 @pytest.mark.parametrize("factor", [-110, 110])
-def test_recorded_step_after_an_update(torch_cuda, ref, factor):
+def test_recorded_step_after_an_update(torch_cuda, ref, second, factor):
     """A graph keeps its kernels: recorded with the split admitted and replayed with parameters for
     which it is not (factor < 0: the other way round), it computes the new parameters' network."""
     torch = torch_cuda
@@ -165,14 +174,14 @@ def test_sums_that_fp32_hardly_rounds(torch_cuda, ref, what):
         else:
             a[:] = _thin(w, [l], int(what.split()[0].replace("one", "1")))["conv_w"][l][ch]
         pol = binding.Policy(net, v, max_batch=5)
-        assert pol.op_kernels()[1:3] == [("gemm_mfma" if i == l else "conv_image_split") for i in (1, 2)], l
+        assert pol.op_kernels()[1:3] == [["gemm_mfma", "conv_image_split"], ["conv12_split", "gemm_mfma"]][l - 1], l
         g, (o_, s_, d_) = _run(torch, pol, net, 5)
         parity.check_against_oracle(net, g, ref.policy_step(net, v, o_, s_, d_, 7, 11), ref, 7, 11)
         pol.close()
 
 
 @pytest.mark.parametrize("case", ["normal", "laplace", "uniform", "430 taps", "early taps"])
-def test_error_against_64_bits(torch_cuda, monkeypatch, case):
+def test_error_against_64_bits(torch_cuda, monkeypatch, second, case):
     """About as far from the exact result as with the fp32 kernel that adds K in four pieces, the most exact
     one (a small handle): measured 0.99 to 1.06 times as far over such networks, 0.8 of the kernel
     that adds it in one piece."""
@@ -191,7 +200,7 @@ def test_error_against_64_bits(torch_cuda, monkeypatch, case):
             if switch:
                 m.setenv("SF_NO_CONV_IMAGE", "1")
             pol = binding.Policy(net, w, max_batch=64)
-        assert pol.op_kernels()[1:3] == ["gemm_mfma" if switch else "conv_image_split"] * 2
+        assert pol.op_kernels()[1:3] == (["gemm_mfma"] * 2 if switch else [second, "conv_image_split"])
         g, (o_, s_, d_) = _run(torch, pol, net, 64)
         pol.close()
         want = _exact_h(net, w, o_, s_, d_)
