@@ -34,9 +34,38 @@ HBM_PEAK_GBPS = 8000.0
 
 
 def peak_of(pipe):
-    """Peak for a launch; a launch that runs two layers on two pipes ("i8x2+bf16") is held
-    against the slower pipe's peak (a lower bound of its fraction)."""
+    """Peak of a pipe; an operation that runs two layers on two pipes ("i8x2+bf16") is held
+    against the slower pipe's peak."""
     return min(PEAK_TOPS[p] for p in pipe.split("+"))
+
+
+def launches(ops, pipes, kernels):
+    """The step's kernel launches, from its operations (name, operations per row), their pipes and kernels:
+    dicts of name, flops (per row), pipe, kernel, peak (flops over the time they take at their pipes' peaks) and
+    index (those of the operations).  Neighbours on "conv12_split" are one launch."""
+    out = []
+    for i, ((name, flops), pipe, kernel) in enumerate(zip(ops, pipes, kernels)):
+        if out and kernel == "conv12_split" == out[-1]["kernel"]:
+            e = out[-1]
+            e.update(name=e["name"] + "+" + name, flops=e["flops"] + flops, pipe=e["pipe"] + "+" + pipe,
+                     t_peak=e["t_peak"] + flops / peak_of(pipe), index=e["index"] + [i])
+        else:
+            out.append(dict(name=name, flops=flops, pipe=pipe, kernel=kernel, t_peak=flops / peak_of(pipe), index=[i]))
+    for e in out:
+        t = e.pop("t_peak")
+        e["peak"] = e["flops"] / t if t > 0 else peak_of(e["pipe"])
+    return out
+
+
+def launch_times(event_ms, ms_per_step):
+    """(time of each launch, cost of an event): event_ms are the intervals between events, one after every launch.
+    An event between two launches costs time of its own (the first launch must have drained and its time
+    stamp be written before the next one starts), which the untimed steps do not pay: there the launches follow
+    one another without a gap (the kernel trace's durations add up to the step).  That cost, (sum of the
+    intervals - untimed step) / number of launches, is taken off every interval."""
+    cost = float(np.clip((event_ms.sum() - ms_per_step) / len(event_ms), 0.0, 0.5 * event_ms.min()))
+    return event_ms - cost, cost
+
 
 BLOCKS = 5
 PREWARM_SECONDS = 0.3
@@ -55,7 +84,7 @@ def source_hash():
     return h.hexdigest()[:16]
 
 
-def load_traffic(workload, B, ops, pipes):
+def load_traffic(workload, B, names, pipes):
     """HBM bytes per launch from the tracked table of rocprofv3 counter runs, or None when the
     table has no entry measured on these sources for this workload, batch and launch sequence."""
     try:
@@ -66,7 +95,7 @@ def load_traffic(workload, B, ops, pipes):
     src = source_hash()
     for e in table:
         if (e["workload"] == workload and e["B"] == B and e["source_hash"] == src and
-                [o["op"] for o in e["ops"]] == [n for n, _ in ops] and [o["pipe"] for o in e["ops"]] == pipes):
+                [o["op"] for o in e["ops"]] == names and [o["pipe"] for o in e["ops"]] == pipes):
             return {o["op"]: o for o in e["ops"]}, "profiles/hbm_traffic_table.txt (%s)" % e.get("profile", "")
     return None, "no table entry for these kernels (sources %s)" % src
 
@@ -201,7 +230,7 @@ def measure_learner_forward(torch, binding, wl, net, w, reps):
     pol.close()
     return {"T": T, "N": N, "ms_per_pass": round(ms, 4), "samples_per_s": round(T * N / ms * 1e3, 1),
             "algorithmic_tflops": round(flops / ms / 1e9, 2), "as_32_single_steps_ms": round(ms_steps, 4),
-            "launches": "encoder and FC once on 2048 frames, the core 32 times on 64 rows, the heads once on 2048 states"}
+            "launches": "encoder and FC once on 2048 frames, the core over all steps, the heads once on 2048 states"}
 
 
 def main():
@@ -282,7 +311,8 @@ def main():
     fps = B / (ms_per_step * 1e-3)
 
     ops = pol.ops()
-    pipes = pol.op_pipes()
+    runs = launches(ops, pol.op_pipes(), pol.op_kernels())
+    names, pipes = [r["name"] for r in runs], [r["pipe"] for r in runs]
     dtype = net["dtype"]
     roofline = None
     graph = None
@@ -297,42 +327,37 @@ def main():
             samples[t] = pol.last_op_times_ms()
         t_next += n_timed
         pol.set_op_timing(False)
-        event_ms = samples.mean(axis=0)
-        # An event between two launches costs time of its own (the first launch must have drained
-        # and its time stamp be written before the next one starts), which the untimed steps do
-        # not pay: there the launches follow one another without a gap (the kernel trace's
-        # durations add up to the step).  That cost, (sum of the intervals - untimed step) / number
-        # of launches, is taken off every interval; the raw intervals are kept as "event_ms".
-        event_cost = float(np.clip((event_ms.sum() - ms_per_step) / len(ops), 0.0, 0.5 * event_ms.min()))
-        op_ms = event_ms - event_cost
+        event_ms = np.array([samples.mean(axis=0)[r["index"]].sum() for r in runs])
+        op_ms, event_cost = launch_times(event_ms, ms_per_step)  # (the raw intervals are kept as "event_ms")
         i_dom = int(np.argmax(op_ms))
-        traffic, traffic_src = load_traffic(net["name"], B, ops, pipes)
+        traffic, traffic_src = load_traffic(net["name"], B, names, pipes)
         per_op = {}
-        for (name, fl), pipe, ms, ems in zip(ops, pipes, op_ms, event_ms):
+        for r, ms, ems in zip(runs, op_ms, event_ms):
+            name, pipe, fl = r["name"], r["pipe"], r["flops"]
             tops = fl * B / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
             e = {"ms": round(float(ms), 5), "event_ms": round(float(ems), 5), "pipe": pipe, "tops": round(tops, 3),
-                 "frac_of_pipe_peak": round(tops / peak_of(pipe), 5)}
+                 "frac_of_pipe_peak": round(tops / r["peak"], 5)}
             if traffic is not None:
                 byts = 1024.0 * traffic[name]["hbm_kib"]
                 e["hbm_bytes"] = int(byts)
                 e["hbm_frac"] = round(byts / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 5) if ms > 0 else None
             per_op[name] = e
-        dom = per_op[ops[i_dom][0]]
+        dom = per_op[names[i_dom]]
         whole_tops = pol.flops_per_row() * B / (ms_per_step * 1e-3) / 1e12
         # the step against a roof of its own: every launch at the peak of its pipe
-        t_roof_ms = sum(fl * B / (peak_of(p) * 1e12) * 1e3 for (_, fl), p in zip(ops, pipes))
+        t_roof_ms = sum(r["flops"] * B / (r["peak"] * 1e12) * 1e3 for r in runs)
         whole = {"algorithmic_tops": round(whole_tops, 3), "ms_at_pipe_peaks": round(t_roof_ms, 5),
                  "frac": round(t_roof_ms / ms_per_step, 5)}
-        f32 = [(fl, ms) for (_, fl), p, ms in zip(ops, pipes, op_ms) if p == "f32"]
+        f32 = [(r["flops"], ms) for r, ms in zip(runs, op_ms) if r["pipe"] == "f32"]
         if f32:
             tf = sum(fl for fl, _ in f32) * B / (sum(ms for _, ms in f32) * 1e-3) / 1e12
             whole["fp32_mfma_launches"] = {"tflops": round(tf, 3), "frac": round(tf / PEAK_TOPS["f32"], 5),
                                            "ms": round(float(sum(ms for _, ms in f32)), 5)}
         if traffic is not None:
-            hbm = sum(1024.0 * traffic[name]["hbm_kib"] for name, _ in ops) / (ms_per_step * 1e-3) / 1e9
+            hbm = sum(1024.0 * traffic[name]["hbm_kib"] for name in names) / (ms_per_step * 1e-3) / 1e9
             whole.update({"hbm_GBps": round(hbm, 1), "hbm_frac": round(hbm / HBM_PEAK_GBPS, 4)})
-        roofline = {"bound": "mfma", "kernel": ops[i_dom][0], "pipe": dom["pipe"], "achieved": dom["tops"],
-                    "peak": peak_of(dom["pipe"]), "unit": "TFLOP/s" if not dom["pipe"].startswith("i8") else "TOP/s",
+        roofline = {"bound": "mfma", "kernel": names[i_dom], "pipe": dom["pipe"], "achieved": dom["tops"],
+                    "peak": round(runs[i_dom]["peak"], 1), "unit": "TFLOP/s" if not dom["pipe"].startswith("i8") else "TOP/s",
                     "frac": dom["frac_of_pipe_peak"],
                     "traffic": dom.get("hbm_bytes"), "traffic_source": traffic_src,
                     "avg_launch_ms": dom["ms"], "event_cost_ms_per_launch": round(event_cost, 5),
@@ -407,8 +432,8 @@ def main():
             net["name"], B, *net["obs"], net["encoder"], net["fc"], net["rnn_type"].upper(), net["rnn"],
             net["heads"], ", %d measurements -> FC%s" % (net["meas_dim"], net["meas_hidden"]) if net["meas_dim"] else ""),
             "name": net["name"], "B": B, "conv1": conv1 or pipes[0],
-            "launch_pipes": dict(zip((n for n, _ in ops), pipes)),
-            "launch_kernels": dict(zip((n for n, _ in ops), pol.op_kernels())),
+            "launch_pipes": dict(zip(names, pipes)),
+            "launch_kernels": {r["name"]: r["kernel"] for r in runs},
             "paper_accounting_x4_frameskip_fps": round(4 * fps, 1),
             "inputs": "device-resident; host-to-device transfer excluded",
             "timing": "median of %d blocks of %d steps after %d uncounted pre-warm-up steps (>= %.1f s) and %d "
