@@ -1,6 +1,7 @@
 """The first two convolutions of an fp32 network in one launch (k_conv12_split.hip) against the two separate
 launches and the oracle: one and several frames per workgroup, a frame height that leaves rows over, frames
-at an address that is a multiple of four bytes only."""
+at an address that is a multiple of four bytes only, a graph recorded before an update that the second layer's
+split does not take."""
 import numpy as np
 import pytest
 
@@ -49,6 +50,44 @@ def test_one_launch_and_two(torch_cuda, ref, monkeypatch, height):
         pol.set_op_timing(False)
     one.close()
     two.close()
+
+
+@pytest.mark.parametrize("B", [37, 300, 600])
+def test_recorded_step_whose_second_layer_is_refused(torch_cuda, ref, B):
+    """A graph keeps the one launch; with parameters that the second layer's split does not take, it computes
+    that layer in fp32: frames shared by four and by two workgroups, and several whole frames per workgroup."""
+    torch = torch_cuda
+    net = wl.network(1, fc=64, rnn=64, name="conv12_recorded")
+    w = wl.weights(net)
+    huge = {k: [a.copy() for a in v] if isinstance(v, list) else v.copy() for k, v in w.items()}
+    huge["conv_w"][0] *= np.float32(2.0 ** 110)
+    huge["conv_b"][0] *= np.float32(2.0 ** 110)
+    huge["conv_w"][1] *= np.float32(2.0 ** -110)
+    pol = binding.Policy(net, w, max_batch=B)
+    assert pol.op_kernels()[0] == "conv12_split"
+    o_, s_, d_ = wl.observations(net, 0, B), wl.initial_state(net, B), wl.done_mask(net, 0, B)
+    obs, st, dn = (torch.from_numpy(a).cuda() for a in (o_, s_, d_))
+    out = pol.step(obs, st, dn, 7, 11)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pol.step(obs, st, dn, 7, 11, out=out, stream=torch.cuda.current_stream())
+    pol.update_weights(huge)
+    assert pol.op_kernels()[:2] == ["conv1_i8", "gemm_mfma"]
+    rows = np.unique(np.array([0, 1, B // 3, B // 2, B - 2, B - 1]))
+    want = ref.policy_step(net, huge, o_[rows], s_[rows], d_[rows], 7, 11)
+    for _ in range(2):
+        for v in out.values():
+            v.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        recorded = {k: v.cpu().numpy() for k, v in out.items()}
+        for k in ("logits", "value", "h_out"):
+            parity.assert_close(k, recorded[k][rows], want[k], 1e-4)
+        eager = {k: v.cpu().numpy() for k, v in pol.step(obs, st, dn, 7, 11).items()}  # (the fp32 kernel)
+        for k in ("logits", "value", "h_out"):
+            parity.assert_close(k, recorded[k], eager[k], 1e-4)
+    pol.close()
 
 
 @pytest.mark.parametrize("height", [72, 74])

@@ -159,3 +159,27 @@ def test_stream_with_a_mask(torch_cuda):
     stream.synchronize()
     pol.close()
     assert hip.hipStreamDestroy(raw) == 0
+
+
+def test_two_passes_at_once(torch_cuda, monkeypatch):
+    """Two handles on two streams, each with as many workgroups as the chip has compute units: the bits of a
+    pass alone."""
+    torch = torch_cuda
+    T, N = 32, 64
+    pair = []
+    for kind in ("gru", "lstm"):
+        net = wl.network(0, **dict(BASE, name="pair_" + kind, fc=512, rnn=512, rnn_type=kind))
+        pol = binding.Policy(net, wl.weights(net), max_batch=T * N)
+        args = tuple(torch.from_numpy(a).cuda() for a in wl.trajectory_inputs(net, T, N)[:3])
+        alone = {k: v.clone() for k, v in pol.unroll(*args).items()}
+        out = {k: torch.zeros_like(v) for k, v in alone.items()}
+        pair.append((pol, args, alone, out, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for pol, args, _, out, stream in pair:
+            pol.unroll(*args, out=out, stream=stream)
+    torch.cuda.synchronize()
+    for pol, _, alone, out, _ in pair:
+        for k in alone:
+            assert torch.equal(alone[k], out[k]), k
+        pol.close()
