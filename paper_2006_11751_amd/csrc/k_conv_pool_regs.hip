@@ -93,8 +93,10 @@ struct Rows {
   f32x16 e, o;  // accumulators of a convolution row: columns 2x and 2x+1
 };
 
-// CIN channels in; PPT 16-byte pieces per thread and frame; FPW frames per workgroup round.
-template <int CIN, int PPT, int FPW>
+// CIN channels in; PPT 16-byte pieces per thread and frame; FPW frames per workgroup round.  SHARED: g.parts
+// workgroups per round; an instantiation of its own (whole frames through that one: 8192 of 36 x 64 with 16 channels
+// 257 us, of 18 x 32 with 32 channels 153.7; this one 252, 151.2).
+template <int CIN, int PPT, int FPW, bool SHARED>
 __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
   constexpr int NS = CIN / 16, C8 = CIN / 8;
   constexpr int P = CIN == 16 ? 48 : 80;
@@ -129,9 +131,9 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
   // plane x%2, row y + 1, plane column x/2 (even plane) or x/2 + 1 (odd plane: its column 0 is
   // image column -1).  Threads past step_rows * row_pieces idle.
   // pooled rows [p0, p1) and the image rows [ya, yb) that they need
-  const int part = g.parts > 1 ? (int)blockIdx.x % g.parts : 0;
-  const int p0 = part * g.Ho / g.parts, p1 = (part + 1) * g.Ho / g.parts;
-  const int ya = max(2 * p0 - 2, 0), yb = min(2 * p1 + 1, g.H);
+  const int part = SHARED ? (int)blockIdx.x % g.parts : 0;
+  const int p0 = SHARED ? part * g.Ho / g.parts : 0, p1 = SHARED ? (part + 1) * g.Ho / g.parts : g.Ho;
+  const int ya = SHARED ? max(2 * p0 - 2, 0) : 0, yb = SHARED ? min(2 * p1 + 1, g.H) : g.H;
   const int srow = tid / g.row_pieces, scol = tid - srow * g.row_pieces;
   const bool loader = srow < g.step_rows;
   const int pieces = g.H * g.row_pieces;
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
         int p = tid;
         asm volatile("" : "+v"(p));
         p += k * g.step_rows * g.row_pieces;
-        const bool here = loader && p < (yb - ya) * g.row_pieces;
+        const bool here = loader && p < (SHARED ? (yb - ya) * g.row_pieces : pieces);
         nx[f][k] = src[here ? p + ya * g.row_pieces : pieces - 1];
       }
     }
@@ -263,8 +265,8 @@ __global__ __launch_bounds__(kNT, 2) void conv_pool_regs_kernel(CprArgs g) {
     }
   };
 
-  const int stride = (int)gridDim.x / g.parts * FPW;
-  int b0 = (int)blockIdx.x / g.parts * FPW;
+  const int stride = (SHARED ? (int)gridDim.x / g.parts : (int)gridDim.x) * FPW;
+  int b0 = (SHARED ? (int)blockIdx.x / g.parts : (int)blockIdx.x) * FPW;
   load_frames(b0);
 #pragma unroll
   for (int k = 0; k < NBP; ++k)
@@ -298,11 +300,13 @@ size_t lds_bytes_of(int cin, int H, int W) {
 
 template <int CIN, int PPT, int FPW>
 hipError_t launch_t(CprArgs g, size_t lds_bytes, hipStream_t st) {
-  auto kern = conv_pool_regs_kernel<CIN, PPT, FPW>;
+  auto whole = conv_pool_regs_kernel<CIN, PPT, FPW, false>, shared = conv_pool_regs_kernel<CIN, PPT, FPW, true>;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
-    attr_status = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+    for (auto k : {whole, shared})
+      if (attr_status == hipSuccess)
+        attr_status = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   });
   if (attr_status != hipSuccess) return attr_status;
   const int rounds = (g.B + FPW - 1) / FPW;
@@ -313,7 +317,7 @@ hipError_t launch_t(CprArgs g, size_t lds_bytes, hipStream_t st) {
   g.n_seg = g.Ho / g.parts < kNW ? (g.parts > 1 ? g.Ho / g.parts : rows) : kNW;
   // one workgroup per CU, each walking its share of the frames
   const int blocks = g.parts * rounds < 256 ? g.parts * rounds : 256;
-  kern<<<blocks, kNT, lds_bytes, st>>>(g);
+  (g.parts > 1 ? shared : whole)<<<blocks, kNT, lds_bytes, st>>>(g);
   return hipGetLastError();
 }
 

@@ -594,7 +594,7 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
 // rows of the weights are dealt so that a lane's 16 accumulators are 16 neighbouring channels (32 bytes: two
 // pieces) of its pixel, conv_b adds to them and writes relu of the sum for the next block: no pass of its
 // own for the sum, one barrier fewer per block.
-// Cycles per frame and launch times: see launch_res_stage.
+// At 8192 frames: 18 x 32 pixels 439 -> 362 us, 9 x 16 (stacked by three) 138 -> 111.
 template <int LW, int RT>
 __global__ __launch_bounds__(kNT, 2) void res_stage32_kernel(StageArgs g) {
   constexpr int W = 1 << LW, PIX = 64, ROW = (W + 2) * PIX, S = 18;

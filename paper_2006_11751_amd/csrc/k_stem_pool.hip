@@ -90,6 +90,9 @@ struct StemPoolArgs {
 };
 
 // (second launch bound: waves per SIMD; four = two workgroups of eight waves per CU, 128 VGPRs)
+// SHARED: g.parts workgroups per frame; an instantiation of its own, which asks for its first frame together
+// with the parameters (whole frames through that one: 8192 of them 243.9 us, this one 242.2, before there were parts 240.6).
+template <bool SHARED>
 __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char patch[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -97,23 +100,34 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   const int j = lane & 15, grp = lane >> 4;
   const size_t plane = (size_t)g.H * g.W;
   // pooled rows [p0, p1) and the image rows [ya, yb) that they need
-  const int part = g.parts > 1 ? (int)blockIdx.x % g.parts : 0;
-  const int p0 = part * g.Ho / g.parts, p1 = (part + 1) * g.Ho / g.parts;
-  const int ya = max(2 * p0 - 2, 0), yb = min(2 * p1 + 1, g.H);
-  const int first_item = ya * (g.W >> 2), last_item = yb * (g.W >> 2) - 1;
+  const int part = SHARED ? (int)blockIdx.x % g.parts : 0;
+  const int p0 = SHARED ? part * g.Ho / g.parts : 0, p1 = SHARED ? (part + 1) * g.Ho / g.parts : g.Ho;
+  const int ya = SHARED ? max(2 * p0 - 2, 0) : 0, yb = SHARED ? min(2 * p1 + 1, g.H) : g.H;
+  const int first_item = SHARED ? ya * (g.W >> 2) : 0, end_item = SHARED ? yb * (g.W >> 2) : g.n_items;
 
+  // zeros once: the ring is never written again
+  auto clear = [&]() {
+    for (int i = tid; i < (g.H + 2) * g.RP / 16; i += kNT) ((u32x4*)patch)[i] = u32x4{0u, 0u, 0u, 0u};
+  };
+  if (!SHARED) clear();
   const u32x4 a_lo1 = g.wpk[lane], a_lo2 = g.wpk[64 + lane];
   const u32x4 a_hi1 = g.wpk[128 + lane], a_hi2 = g.wpk[192 + lane];
   const f32x4 bias = *(const f32x4*)(g.bias + 4 * grp);
-  // zeros once: the ring is never written again
-  for (int i = tid; i < (g.H + 2) * g.RP / 16; i += kNT) ((u32x4*)patch)[i] = u32x4{0u, 0u, 0u, 0u};
+  // The parameters have arrived before the loop, whole frames: before the first frame is requested (vmcnt(0), other
+  // counters untouched).  Otherwise the compiler, which must assume their loads pending on some path, drains
+  // the load counter ahead of every row loop that uses them, and that wait would catch the next frame's
+  // bytes right after they have been requested.
+  if (SHARED)
+    clear();
+  else
+    __builtin_amdgcn_s_waitcnt(0x0F70);
   // Item i = tid + it * kNT is the four pixels at byte 4*i of each colour plane: image row
   // i / (W/4), columns 4*(i % (W/4)) ..; in LDS, row + 1 and column + 2.
   const int Q = g.W >> 2;
   int lds_off[kMaxIt];
 #pragma unroll
   for (int it = 0; it < kMaxIt; ++it) {
-    const int i = min(first_item + tid + it * kNT, last_item);
+    const int i = min(first_item + tid + it * kNT, end_item - 1);
     const int y = i / Q, jq = i - y * Q;
     lds_off[it] = (y + 1) * g.RP + (4 * jq + 2) * 8;
   }
@@ -122,8 +136,8 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
     const uint8_t* frame = g.obs + (size_t)b * 3 * plane;
 #pragma unroll
     for (int it = 0; it < kMaxIt; ++it) {
-      if (first_item + it * kNT > last_item) break;  // uniform
-      const int i = min(first_item + tid + it * kNT, last_item);
+      if (first_item + it * kNT >= end_item) break;  // uniform
+      const int i = min(first_item + tid + it * kNT, end_item - 1);
 #pragma unroll
       for (int c = 0; c < 3; ++c) nx[it][c] = *(const uint32_t*)(frame + c * plane + 4 * (size_t)i);
     }
@@ -131,7 +145,7 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   auto stage = [&]() {
 #pragma unroll
     for (int it = 0; it < kMaxIt; ++it) {
-      if (first_item + it * kNT > last_item) break;  // uniform
+      if (first_item + it * kNT >= end_item) break;  // uniform
       float c[4][3];
 #pragma unroll
       for (int k = 0; k < 4; ++k)
@@ -142,7 +156,7 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
                         f16_bits(c[1][2])};
       const u32x4 hi = {pack_f16(c[2][0], c[2][1]), f16_bits(c[2][2]), pack_f16(c[3][0], c[3][1]),
                         f16_bits(c[3][2])};
-      if (first_item + tid + it * kNT <= last_item) {
+      if (first_item + tid + it * kNT < end_item) {
         u32x4* dst = (u32x4*)(patch + lds_off[it]);
         dst[0] = lo;
         dst[1] = hi;
@@ -218,14 +232,10 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
     }
   };
 
-  const int stride = (int)gridDim.x / g.parts;
-  int b = (int)blockIdx.x / g.parts;
+  const int stride = SHARED ? (int)gridDim.x / g.parts : (int)gridDim.x;
+  int b = SHARED ? (int)blockIdx.x / g.parts : (int)blockIdx.x;
   load_frame(b);
-  // Parameters and first frame, requested together, have arrived before the loop (vmcnt(0), other counters
-  // untouched).  Otherwise the compiler, which must assume the parameters' loads pending on some path,
-  // drains the load counter ahead of every row loop that uses them, and that wait would catch the next
-  // frame's bytes right after they have been requested.
-  __builtin_amdgcn_s_waitcnt(0x0F70);
+  if (SHARED) __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();  // zeros in place
   for (; b < g.B; b += stride) {
     stage();
@@ -293,12 +303,15 @@ hipError_t launch_stem_pool(const uint8_t* obs, const uint16_t* wpk, const float
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
-    attr_status = hipFuncSetAttribute((const void*)stem_pool_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)kMaxLds);
+    for (const void* k : {(const void*)stem_pool_kernel<false>, (const void*)stem_pool_kernel<true>})
+      if (attr_status == hipSuccess)
+        attr_status = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
   });
   if (attr_status != hipSuccess) return attr_status;
-  const int blocks = g.parts * B < 512 ? g.parts * B : 512 / g.parts * g.parts;  // two workgroups per CU, each walking its share of the frames
-  stem_pool_kernel<<<blocks, kNT, stem_pool_lds_bytes(H, W), st>>>(g);
+  // two workgroups per CU, each walking its share of the frames
+  const int blocks = g.parts * B < 512 ? g.parts * B : 512 / g.parts * g.parts;
+  auto kern = g.parts > 1 ? stem_pool_kernel<true> : stem_pool_kernel<false>;
+  kern<<<blocks, kNT, stem_pool_lds_bytes(H, W), st>>>(g);
   return hipGetLastError();
 }
 
