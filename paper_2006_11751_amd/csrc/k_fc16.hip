@@ -8,8 +8,8 @@
 // the trip of activations that another XCD wrote.  Here a ring of kDepth chunks in LDS is filled by loads
 // that go there directly (no registers, no LDS store instructions): all but two of them are on their way.
 // One barrier per two chunks: it says that they have come and that the two before them have been read (one
-// per chunk: 18.0 against 17.6 us at 4096 rows).  2304 -> 512 in bf16 at
-// 4096 rows 25.4 -> 17.6 us (12.5 TB/s out of the L2s), 4608 -> 256 in fp16 at 8192 rows 45 -> 38.
+// per chunk: 2 % slower at 4096 rows).  Medians of a kernel trace: 2304 -> 512 in bf16 at 4096 rows 24.4 -> 18.7 us
+// (12.1 TB/s out of the L2s), 4608 -> 256 in fp16 at 8192 rows 45.1 -> 37.8.
 //
 // A load instruction writes 64 x 16 bytes in lane order, so rows (128 bytes) have no padding; instead the
 // 16-byte pieces of a row are exchanged by the row's number, on the side of the source: slot s of row r holds
