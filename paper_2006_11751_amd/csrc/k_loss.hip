@@ -12,9 +12,9 @@
 // A sample's logits are reduced to the joint log-probability and the entropy; the backward recursion
 // over time runs across the 32 or 64 lanes of a trajectory (the coefficient pairs are broadcast one
 // by one, last step first); longer trajectories are walked in chunks from the end, carrying the
-// recursion's value.  Targets, advantages, gradients and a workgroup's partial sums follow.  A second,
-// single-workgroup launch adds the partial sums in a fixed order, so the result does not depend on
-// scheduling.
+// recursion's value.  Targets, advantages, gradients and a workgroup's partial sums follow.  The
+// partial sums are added in a fixed order, so the result does not depend on scheduling: by the
+// workgroup that finds them all there (see publish), or by a second, single-workgroup launch.
 //
 // Memory side: the arrays are time-major, so the samples of a trajectory lie N * sumA floats apart
 // and per-lane reads of a sample's logits touch a cache line per lane and element.  A workgroup
@@ -23,6 +23,8 @@
 // conflicts), and the gradients leave for memory as contiguous runs again.  Tiles that do not fit
 // LDS take the direct kernel (one wave per trajectory, one lane per time step).
 #include <math.h>
+#include <sys/random.h>
+#include <time.h>
 
 #include <mutex>
 
@@ -52,7 +54,9 @@ struct LossArgs {
   float* adv;             // [T][N]
   float* dlogits;         // [T][N][sumA] or null
   float* dvalues;         // [T][N] or null
-  float* partials;        // [workgroups of the trajectory kernel][4], at most [N][4]
+  float* partials;        // [workgroups of the trajectory kernel][4], at most [N][4]; 16-byte aligned
+  float* loss;            // [4]
+  uint32_t key;           // of the partial sums' check words; 0: a second launch adds them
   int T, N, n_heads, sumA;
   int head_sizes[SF_MAX_HEADS];
   int head_off[SF_MAX_HEADS];    // first logit of each head
@@ -236,6 +240,116 @@ __device__ inline void copy_tile_vec4(const float* mem, float* tile, int t0, int
   }
 }
 
+// ---- adding the partial sums without a second launch ----
+//
+// A workgroup publishes its three sums with a check word (two 64-bit stores with device scope, past the
+// caches that are not coherent across the XCDs; a store that has been waited for is seen by all) and then
+// looks at the entries of all workgroups.  Stores and looks meet in memory in some order, so that the
+// workgroup whose store came last finds all entries there.  The first to find them adds the sums in the
+// fixed order, writes the losses and takes the entries back.  Nobody waits for another workgroup, and
+// there is no counter: nothing of the caller's workspace has to be set ahead.  One wave does this while
+// the others write the gradients: behind their stores it would wait for these.
+//
+// An entry that is taken back, or whose workgroup has begun, never passes for a published one: both its
+// words differ from any published word, so half of it does not either.  What the workspace held before
+// could only pass if its check word, a function of the sums and of a key drawn once per process,
+// happened to fit, and only as long as its workgroup has not begun while all others are done.
+//
+// Whole calls, 41 logits in 7 heads, 32 steps (us, against the second launch, which is dependent on the
+// first and costs 3.5 of the host's time, 13 us per call with it): 64 trajectories 12.3 -> 10.6, 256 12.3 -> 11.2,
+// 512 13.1 -> 12.9, 700 13.4 -> 12.4, 1024 14.1 -> 13.4, 2048 17.4 -> 15.9, 4096 (512 workgroups) 23.7 -> 21.9.
+typedef unsigned long long u64;
+constexpr u64 kNoSums = ~0ull, kNoCheck = 0;
+__device__ inline uint32_t check_word(uint32_t a, uint32_t b, uint32_t c, uint32_t key) {
+  uint32_t h = a * 0x85EBCA6Bu + key;
+  h = (h ^ (h >> 15) ^ b) * 0xC2B2AE35u;
+  h = (h ^ (h >> 13) ^ c) * 0x9E3779B1u;
+  return (h ^ (h >> 16)) | 1u;
+}
+__device__ inline void take_back(float* partials, int at) {
+  u64* e = (u64*)partials + 2 * (size_t)at;
+  __hip_atomic_store(e, kNoSums, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(e + 1, kNoCheck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// by one lane; returns when the entry is in memory
+__device__ inline void publish(float* partials, int at, const float (&sum)[3], uint32_t key) {
+  uint32_t u[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) u[i] = sum[i] != sum[i] ? 0x7FC00000u : __builtin_bit_cast(uint32_t, sum[i]);
+  u64* e = (u64*)partials + 2 * (size_t)at;
+  __hip_atomic_store(e, u[0] | (u64)u[1] << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(e + 1, u[2] | (u64)check_word(u[0], u[1], u[2], key) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// The order of the sums: 256 threads (i: entries i, i + 256, ...), then a binary tree over them.
+constexpr int kReduceThreads = 256;
+__device__ inline void write_losses(float pi, float v, float ent, float inv_m, float critic_coef, float entropy_coef,
+                                    float* loss) {
+  const float l_pi = pi * inv_m, l_v = critic_coef * v * inv_m, l_h = entropy_coef * ent * inv_m;
+  loss[0] = l_pi;
+  loss[1] = l_v;
+  loss[2] = l_h;
+  loss[3] = l_pi + l_v + l_h;
+}
+
+// The look of one wave at the n <= 256 * kLooks entries; lane l stands for threads l, l + 64, l + 128, l + 192.
+// Many workgroups find all entries (they end at about the same time): the first of them, by an exchange,
+// goes on (all of them taking all entries back made the call 3 to 10 us longer).  With more than kFew
+// workgroups a look at sixteen neighbours comes first, since looks queue for the entries' few lines of
+// memory: 512 workgroups 12.9 us per call against 14.8, 256 workgroups 11.5 against 11.2.
+constexpr int kLooks = 2, kNear = 16, kFew = 256;
+__device__ inline void entry(const LossArgs& g, int at, u64 (&w)[2]) {
+  const u64* e = (const u64*)g.partials + 2 * (size_t)at;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) w[q] = __hip_atomic_load(e + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline bool is_published(const LossArgs& g, const u64 (&w)[2]) {
+  return w[0] != kNoSums && w[1] != kNoCheck &&
+         (uint32_t)(w[1] >> 32) == check_word((uint32_t)w[0], (uint32_t)(w[0] >> 32), (uint32_t)w[1], g.key);
+}
+__device__ inline void add_if_complete(const LossArgs& g, int n, float inv_m) {
+  const int lane = threadIdx.x & (kWave - 1);
+  if (n > kFew) {
+    u64 near[2];
+    entry(g, min((int)blockIdx.x / kNear * kNear + lane % kNear, n - 1), near);
+    if (!__all(is_published(g, near))) return;
+  }
+  u64 w[kLooks][4][2];
+#pragma unroll
+  for (int i = 0; i < kLooks; ++i)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) entry(g, min(kReduceThreads * i + kWave * k + lane, n - 1), w[i][k]);
+  float sum[4][3] = {};
+  bool there = true;
+#pragma unroll
+  for (int i = 0; i < kLooks; ++i)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      there = there && is_published(g, w[i][k]);
+      if (kReduceThreads * i + kWave * k + lane < n) {
+        sum[k][0] += __builtin_bit_cast(float, (uint32_t)w[i][k][0]);
+        sum[k][1] += __builtin_bit_cast(float, (uint32_t)(w[i][k][0] >> 32));
+        sum[k][2] += __builtin_bit_cast(float, (uint32_t)w[i][k][1]);
+      }
+    }
+  if (!__all(there)) return;
+  // the first of those who find all entries: it takes the first check word
+  u64 first = 0;
+  if (lane == 0) first = __hip_atomic_exchange((u64*)g.partials + 1, kNoCheck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!__any(first != kNoCheck)) return;
+  float all[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    float a = (sum[0][q] + sum[2][q]) + (sum[1][q] + sum[3][q]);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) a += __shfl_down(a, m, kWave);
+    all[q] = a;
+  }
+  if (lane == 0) write_losses(all[0], all[1], all[2], inv_m, g.critic_coef, g.entropy_coef, g.loss);
+  for (int i = lane; i < n; i += kWave) take_back(g.partials, i);
+}
+
 // A workgroup of NT threads owns TPB trajectories, LW (32 when T <= 32, else 64) time steps of them
 // at a time.  What bounds it is the latency of a few dependent stretches, so each of them is spread
 // over all threads:
@@ -244,7 +358,7 @@ __device__ inline void copy_tile_vec4(const float* mem, float* tile, int t0, int
 //   3. one thread per sample: ratio, the backward recursion across the lanes of a trajectory,
 //      targets, advantages, partial sums;
 //   4. one thread per logit (four neighbouring ones where the rows allow): gradients straight from
-//      the tile to memory.
+//      the tile to memory; the partial sums meanwhile by the first wave (publish, add_if_complete).
 // (One lane per sample through all of it, two waves per workgroup, took 14.5 us at 64 trajectories of
 // 32 steps and seven heads, 19.6 at 2048; now 9.4 and 15.7, 1.6 TB/s of logits, actions and gradients:
 // see pick_tile for whole calls.)
@@ -293,6 +407,7 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
   }
   float sum_pi = 0.0f, sum_v = 0.0f, sum_ent = 0.0f;
   float carry = 0.0f;
+  if (g.key && tid == 0) take_back(g.partials, blockIdx.x);
   const int n_chunks = (g.T + LW - 1) / LW;
   for (int ch = n_chunks - 1; ch >= 0; --ch) {
     const int t0 = ch * LW;
@@ -391,9 +506,40 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
         if (g.dvalues) g.dvalues[s] = 2.0f * g.critic_coef * dv * inv_m;
         t_dlp[smp] = a <= b ? -adv * ratio * inv_m : 0.0f;
       }
+      if (ch == 0) {
+#pragma unroll
+        for (int m = LW / 2; m >= 1; m >>= 1) {
+          sum_pi += __shfl_xor(sum_pi, m, LW);
+          sum_v += __shfl_xor(sum_v, m, LW);
+          sum_ent += __shfl_xor(sum_ent, m, LW);
+        }
+        if (lane == 0) {
+          t_sum[j * 4] = sum_pi;
+          t_sum[j * 4 + 1] = sum_v;
+          t_sum[j * 4 + 2] = sum_ent;
+        }
+      }
     }
     __syncthreads();
-    if (g.dlogits) {
+    // one entry per workgroup, trajectories in order
+    const bool adds = ch == 0 && g.key != 0;
+    if (ch == 0 && (adds ? tid < kWave : tid == 0)) {
+      if (tid == 0) {
+        float sum[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          sum[i] = 0.0f;
+          for (int q = 0; q < nb; ++q) sum[i] += t_sum[q * 4 + i];
+        }
+        if (adds)
+          publish(g.partials, blockIdx.x, sum, g.key);
+        else
+          *(f32x4*)(g.partials + (size_t)blockIdx.x * 4) = f32x4{sum[0], sum[1], sum[2], 0.0f};
+      }
+      if (adds) add_if_complete(g, (int)gridDim.x, inv_m);
+    }
+    const int gt0 = adds ? tid - kWave : tid, gnt = adds ? NT - kWave : NT;  // threads of the gradients
+    if (g.dlogits && gt0 >= 0) {
       auto gradient = [&](int smp, int i) {
         const int k = head_of[i], at = smp * hp + k;
         const float ls = ltile[smp * plan.pitch + i] - t_lse[at];
@@ -402,7 +548,7 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
       };
       if (vec4) {
         const int row4 = TPB * g.sumA / 4;
-        for (int e = tid; e < nt * row4; e += NT) {
+        for (int e = gt0; e < nt * row4; e += gnt) {
           const int gt = (int)div_magic((uint32_t)e, (uint32_t)row4, plan.m_row4), q = e - gt * row4;
           int jj = (int)div_magic((uint32_t)(4 * q), (uint32_t)g.sumA, plan.m_sumA), i = 4 * q - jj * g.sumA;
           f32x4 d;
@@ -418,7 +564,7 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
         }
       } else {
         const int row = nb * g.sumA;
-        for (int e = tid; e < nt * row; e += NT) {
+        for (int e = gt0; e < nt * row; e += gnt) {
           const int gt = (int)div_magic((uint32_t)e, (uint32_t)row, m_row), q = e - gt * row;
           const int jj = (int)div_magic((uint32_t)q, (uint32_t)g.sumA, plan.m_sumA), i = q - jj * g.sumA;
           g.dlogits[((size_t)(t0 + gt) * g.N + n0) * g.sumA + q] = gradient(gt * TPB + jj, i);
@@ -427,33 +573,11 @@ __global__ __launch_bounds__(NT) void appo_traj_lds_kernel(LossArgs g, LdsPlan p
     }
     if (ch) __syncthreads();  // the tiles are free for the next chunk
   }
-  if (have) {
-#pragma unroll
-    for (int m = LW / 2; m >= 1; m >>= 1) {
-      sum_pi += __shfl_xor(sum_pi, m, LW);
-      sum_v += __shfl_xor(sum_v, m, LW);
-      sum_ent += __shfl_xor(sum_ent, m, LW);
-    }
-    if (lane == 0) {
-      t_sum[j * 4] = sum_pi;
-      t_sum[j * 4 + 1] = sum_v;
-      t_sum[j * 4 + 2] = sum_ent;
-    }
-  }
-  __syncthreads();
-  if (tid < 4) {  // one entry per workgroup, trajectories in order
-    float a = 0.0f;
-    if (tid < 3)
-      for (int q = 0; q < nb; ++q) a += t_sum[q * 4 + tid];
-    g.partials[(size_t)blockIdx.x * 4 + tid] = a;
-  }
 }
 
 // Adds the partial sums (one entry per workgroup of the first launch) in an order that depends on
-// their number only: thread i takes
-// entries i, i + 256, ... (independent 16-byte loads), then a fixed binary tree over the 256
-// threads' sums in LDS.
-constexpr int kReduceThreads = 256;
+// their number only: thread i takes entries i, i + 256, ... (independent 16-byte loads), then a
+// fixed binary tree over the 256 threads' sums in LDS (add_if_complete's order).
 __global__ __launch_bounds__(kReduceThreads) void appo_reduce_kernel(const float* __restrict__ partials, int N,
                                                                      float inv_m, float critic_coef,
                                                                      float entropy_coef, float* __restrict__ loss) {
@@ -478,14 +602,7 @@ __global__ __launch_bounds__(kReduceThreads) void appo_reduce_kernel(const float
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    const float l_pi = red[0][0] * inv_m, l_v = critic_coef * red[1][0] * inv_m,
-                l_h = entropy_coef * red[2][0] * inv_m;
-    loss[0] = l_pi;
-    loss[1] = l_v;
-    loss[2] = l_h;
-    loss[3] = l_pi + l_v + l_h;
-  }
+  if (tid == 0) write_losses(red[0][0], red[1][0], red[2][0], inv_m, critic_coef, entropy_coef, loss);
 }
 
 int check_loss_config(const sf_loss_config* c, const char* fn, int* sumA) {
@@ -586,7 +703,26 @@ const LossTile* pick_tile(int T, int N, int n_heads, int sumA) {
   return nullptr;
 }
 
-// Argument checks and the two launches shared by the entry points; `partials` is device
+// The check words' key: drawn once, never zero.
+const char g_key_tag = 0;  // (its address differs from process to process)
+uint32_t process_key() {
+  static const uint32_t key = [] {
+    uint32_t k = 0;
+    if (getrandom(&k, sizeof(k), GRND_NONBLOCK) != (ssize_t)sizeof(k)) {
+      timespec t{};
+      (void)clock_gettime(CLOCK_REALTIME, &t);
+      k = (uint32_t)t.tv_nsec * 0x9E3779B1u ^ (uint32_t)t.tv_sec ^ (uint32_t)((uintptr_t)&g_key_tag >> 12);
+    }
+    return k | 1u;
+  }();
+  return key;
+}
+
+// Up to this many workgroups add the partial sums themselves (see add_if_complete; more take several
+// rounds, where the second launch is the smaller part).
+constexpr unsigned kOneLaunch = kLooks * kReduceThreads;
+
+// Argument checks and the launches shared by the entry points; `partials` is 16-byte aligned device
 // memory for N x 4 floats.
 int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const float* logits,
                   const int32_t* actions, const float* logp_mu, const float* values, const float* rewards,
@@ -607,7 +743,7 @@ int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const flo
   LossArgs g;
   g.logits = logits; g.actions = actions; g.logp_mu = logp_mu; g.values = values; g.rewards = rewards;
   g.dones = dones; g.vs = vs; g.adv = adv; g.dlogits = dlogits_opt; g.dvalues = dvalues_opt;
-  g.partials = partials;
+  g.partials = partials; g.loss = loss; g.key = 0;
   g.T = cfg->T; g.N = cfg->N; g.n_heads = cfg->n_heads; g.sumA = sumA;
   for (int k = 0; k < SF_MAX_HEADS; ++k) g.head_sizes[k] = k < cfg->n_heads ? cfg->head_sizes[k] : 0;
   g.gamma = cfg->gamma; g.rho_bar = cfg->rho_bar; g.c_bar = cfg->c_bar; g.clip = cfg->clip;
@@ -650,13 +786,14 @@ int run_appo_loss(const char* fn, const sf_loss_config* cfg, int sumA, const flo
   }
   unsigned n_partials = (unsigned)((cfg->N + TPB - 1) / TPB);
   if (tile) {
+    if (n_partials <= kOneLaunch) g.key = process_key();
     tile->kernel<<<n_partials, tile->threads, tile_lds(*tile, cfg->n_heads, sumA), st>>>(g, plan);
   } else {
     n_partials = (unsigned)cfg->N;
     appo_traj_kernel<<<(unsigned)((cfg->N + kTrajPerBlock - 1) / kTrajPerBlock), kLossThreads, 0, st>>>(g);
   }
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) {
+  if (e == hipSuccess && g.key == 0) {
     appo_reduce_kernel<<<1, kReduceThreads, 0, st>>>(g.partials, (int)n_partials, 1.0f / ((float)cfg->T * (float)cfg->N),
                                             cfg->critic_coef, cfg->entropy_coef, loss);
     e = hipGetLastError();
