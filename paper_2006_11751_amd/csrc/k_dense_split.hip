@@ -67,15 +67,27 @@ __device__ inline void state_rows(const DenseArgs& g, int (&row)[N], int (&flag)
   }
 }
 
-// DA, DB: K steps of rows / weights a wave has in flight; 1: in turn with a second workgroup of the CU.
+// Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2: an XCD gets a block of
+// neighbouring row tiles and column groups (deal(), below).
+__device__ inline bool tile_of(const DenseArgs& g, int& rt, int& cg) {
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  rt = xcd % g.xcd_rows * g.per_rt + slot / g.per_cg;
+  cg = xcd / g.xcd_rows * g.per_cg + slot % g.per_cg;
+  return rt < g.n_rt && cg < g.n_cg;
+}
+
+// DA, DB: K steps of rows / weights a wave has in flight; DA = 1: in turn with a second workgroup of the CU, or
+// for want of registers.
 template <int KIND, int XT, int PB, int RT, int U, int DA, int DB, bool OUT16>
-__global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(DenseArgs g) {
+__global__ __launch_bounds__(kThreads, DA == 1 && RT * U <= 4 ? 4 : 2) void dense_split_kernel(DenseArgs g) {
   constexpr int GB = group_bytes(KIND);
-  constexpr int NB = KIND == FC ? U : KIND == GRU ? U + 1 : 2 * U;  // weight tiles per K step and term
-  constexpr int NA = KIND == FC ? U : KIND == GRU ? U + 2 : 2 * U;  // accumulators per row tile
+  constexpr int UN = (U + 1) / 2;                                   // GRU: tiles of n columns
+  constexpr int NB = KIND == FC ? U : KIND == GRU ? U + UN : 2 * U;  // weight tiles per K step and term
+  constexpr int NA = KIND == FC ? U : KIND == GRU ? U + 2 * UN : 2 * U;  // accumulators per row tile
   constexpr bool LATE = DA == 1;
   constexpr int R16 = 0, R32 = 1, R32_ONE = 2;                      // kinds of rows of a K step: see load_a
   constexpr int RR = RT * NA <= 8 ? RT : 8 / NA;                    // row tiles per round of the sum
+  static_assert(KIND == FC || RR * U <= 4, "a thread per unit");
   static_assert(RT % RR == 0, "whole rounds");
   constexpr int TURN = kWaves * 16 * RT * 36, RED = kWaves * RR * NA * 64 * 4;  // floats
   __shared__ __attribute__((aligned(16))) float lds[TURN > RED ? TURN : RED];
@@ -85,18 +97,8 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
-  // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2: an XCD gets column
-  // groups of its own (its share of the weights stays in its L2) or row tiles of its own,
-  // whichever leaves the smaller operand to be read by all of them.
   int rt0, cg;
-  {
-    const int id = blockIdx.x, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt, n_out = g.rows_per_xcd ? g.n_rt : g.n_cg;
-    const int per = (n_out + 7) / 8, slot = id >> 3;
-    const int o = (id & 7) * per + slot / n_in, i = slot % n_in;
-    if (slot >= per * n_in || o >= n_out) return;
-    rt0 = g.rows_per_xcd ? o : i;
-    cg = g.rows_per_xcd ? i : o;
-  }
+  if (!tile_of(g, rt0, cg)) return;
   const int row0 = rt0 * 16 * RT;
 
   // Rows are loaded with neighbouring lanes on neighbouring bytes (fp32: eight lanes per row, 128
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
     else if (t < U)
       woff[t] = (uint32_t)(t * group_stride) + lane * 16;
     else  // the n columns: 8 per group (one group: twice the same eight)
-      woff[t] = (uint32_t)((U == 2 ? (li >> 3) : 0) * group_stride) + 1024 + (lg * 8 + (li & 7)) * 16;
+      woff[t] = (uint32_t)((U == 1 ? 0 : 2 * (t - U) + (li >> 3)) * group_stride) + 1024 + (lg * 8 + (li & 7)) * 16;
   }
 
   f32x4 acc[RT][NA];
@@ -280,14 +282,16 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
     }
   };
   // The GRU's n gate needs its sums over the features and over the state apart: at the border
-  // the first moves aside (acc[U] -> acc[U + 1]) and acc[U] starts again.
+  // the first moves aside (acc[U ..] -> acc[U + UN ..]) and acc[U ..] starts again.
   auto move_n = [&]() __attribute__((always_inline)) {
     if constexpr (KIND == GRU) {
 #pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        acc[r][U + 1] = acc[r][U];
-        acc[r][U] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      }
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int t = U; t < U + UN; ++t) {
+          acc[r][t + UN] = acc[r][t];
+          acc[r][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
     }
   };
   auto each = [&](auto f) __attribute__((always_inline)) {
@@ -398,11 +402,11 @@ __global__ __launch_bounds__(kThreads, DA == 1 ? 4 : 2) void dense_split_kernel(
           ln[1] = ln[3] = 2 + hq;
         } else {
           tl[0] = tl[1] = gq;
-          tl[2] = U + 1;
-          tl[3] = U;
+          tl[2] = U + UN + (eq >> 2);
+          tl[3] = U + (eq >> 2);
           ln[0] = hq;
           ln[1] = 2 + hq;
-          ln[2] = ln[3] = eq;
+          ln[2] = ln[3] = eq & 3;
         }
         float sum[4];
 #pragma unroll
@@ -457,14 +461,7 @@ __global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
   const int kw = wave & 3, half = wave >> 2;
   const int li = lane & 15, lg = lane >> 4;
   int rt0, cg;
-  {
-    const int id = blockIdx.x, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt, n_out = g.rows_per_xcd ? g.n_rt : g.n_cg;
-    const int per = (n_out + 7) / 8, slot = id >> 3;
-    const int o = (id & 7) * per + slot / n_in, i = slot % n_in;
-    if (slot >= per * n_in || o >= n_out) return;
-    rt0 = g.rows_per_xcd ? o : i;
-    cg = g.rows_per_xcd ? i : o;
-  }
+  if (!tile_of(g, rt0, cg)) return;
   const int row0 = rt0 * 64;
   const int group0 = (cg * 2 + half) * U;      // this wave's first column group
 
@@ -708,16 +705,31 @@ __global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
   }
 }
 
+// Which block of tiles an XCD gets: of the divisions that give the XCDs the fewest rounds of workgroups
+// the one whose block has the fewest bytes of rows and weights, which its L2 has to fetch.  (Rows or
+// columns only, as before: FC 2304 -> 512 at 1024 rows 17.9, 19.5 against 17.1 us, GRU 512 at 1024 rows 24.8,
+// 23.6 against 22.6.)
+unsigned deal(DenseArgs& g, long long tile_row_bytes, long long group_bytes) {
+  long long least = -1;
+  for (int rows = 1; rows <= 8; rows *= 2) {
+    const int per_rt = (g.n_rt + rows - 1) / rows, per_cg = (g.n_cg * rows + 7) / 8;
+    const long long rounds = ((long long)per_rt * per_cg + 31) / 32;
+    const long long cost = (rounds << 40) + per_rt * tile_row_bytes + per_cg * group_bytes;
+    if (least >= 0 && cost >= least) continue;
+    least = cost;
+    g.xcd_rows = rows;
+    g.per_rt = per_rt;
+    g.per_cg = per_cg;
+  }
+  return 8u * g.per_rt * g.per_cg;
+}
+
 template <int KIND, int XT, int PB, int RT, int U, int DA, int DB, bool OUT16>
 hipError_t launch_cfg(DenseArgs g, hipStream_t st) {
   g.n_rt = (g.M + 16 * RT - 1) / (16 * RT);
   g.n_cg = KIND == FC ? g.N / (16 * U) : g.H / (8 * U);
-  // bytes of the rows against bytes of the weights
-  const long long xb = (long long)g.M * g.kn * 32 * (in_f32(XT) ? 4 : 2);
-  const long long wb = (long long)g.n_cg * U * g.kn * PB * group_bytes(KIND);
-  g.rows_per_xcd = xb > wb;
-  const int n_out = g.rows_per_xcd ? g.n_rt : g.n_cg, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt;
-  const unsigned blocks = 8u * ((n_out + 7) / 8) * n_in;
+  const long long row_bytes = 16LL * RT * g.kn * 32 * (in_f32(XT) ? 4 : 2);
+  const unsigned blocks = deal(g, row_bytes, (long long)U * g.kn * PB * group_bytes(KIND));
   dense_split_kernel<KIND, XT, PB, RT, U, DA, DB, OUT16><<<blocks, kThreads, 0, st>>>(g);
   return hipGetLastError();
 }
@@ -726,10 +738,8 @@ template <int KIND>
 hipError_t launch_tile(DenseArgs g, hipStream_t st) {
   g.n_rt = (g.M + 63) / 64;
   g.n_cg = g.H / 32;
-  const long long xb = (long long)g.M * g.kn * 128, wb = (long long)(g.H / 8) * g.kn * 3 * group_bytes(KIND);
-  g.rows_per_xcd = xb > wb;
-  const int n_out = g.rows_per_xcd ? g.n_rt : g.n_cg, n_in = g.rows_per_xcd ? g.n_cg : g.n_rt;
-  cell_tile_kernel<KIND><<<8u * ((n_out + 7) / 8) * n_in, kThreads, 0, st>>>(g);
+  const unsigned blocks = deal(g, 64LL * g.kn * 128, 4LL * g.kn * 3 * group_bytes(KIND));
+  cell_tile_kernel<KIND><<<blocks, kThreads, 0, st>>>(g);
   return hipGetLastError();
 }
 
@@ -737,37 +747,50 @@ long long split_workgroups(long long M, int n_col, int rt, int u) {
   return ((M + 16 * rt - 1) / (16 * rt)) * (n_col / u);
 }
 
-// Rows and columns per workgroup: the smallest tile whose grid is one round of workgroups (256, one
-// per CU), since a round takes about as long with one workgroup as with 256.  Launch times (us) of
-// the FC layer 2304 -> 512 / the GRU 512 -> 512 in fp32, one CU tile per column:
-//   rows   16 x 1      32 x 1      32 x 2      64 x 2
-//     64   6.2 /  5.7  8.4 /  8.0 10.0 /  8.3 18.2 / 14.3
-//    256  11.8 / 21.2  9.8 / 16.6 10.9 /  9.5 18.8 / 15.4
-//    512  24.0 / 40    16  / 32   12.3 / 18   19   / 16
-//   1024  62   / 85    35  / 68   25   / 38   23   / 35
-// Beyond one round two workgroups of the 32 x 2 tile share a CU (DA = DB = 1, 128 registers), so that
-// one's loads run behind the other's products.  The cells in fp32 do not quite fit: the GRU spills 14
-// registers, the LSTM 20, and both read some of them back in every K step.  Launch times (us, the launch's own few included)
-// against the tile that was there, one workgroup per CU with two or three steps in flight:
-//   FC in fp32, 600 / 1024 / 2048 rows: 24 -> 21.5, 26.8 -> 24.6, 47 -> 46 (was 64 x 2)
-//   GRU 512 -> 512 in fp32, 333 / 512 rows: 21.4 -> 19.8, 22.6 -> 21.3
-//   LSTM 512 -> 512 in fp32, 300 / 400 / 512 rows: 22.6 -> 22.5, 23.2 -> 23.6, 24.0 -> 24.9; with 128
-//   measurement features more 25.7 -> 24.7, 26.4 -> 25.5, 27.5 -> 27.1: a draw, and one form for both
-//   GRU 512 -> 512 in bf16, 512 rows: 16.5 -> 13.3
-//   GRU 256 -> 256 on 16-bit features, 512 / 1000 rows: 9.4 -> 8.6, 14.0 -> 11.4
-// Within one round it is worse in fp32 (GRU at 160 rows 14.1 against 12.9), better for cells in 16 bits
-// (the figure at 512 rows is one).  FC rows in 16 bits keep 64 x 2.
+// Rows and columns per workgroup, in units of 16 rows x 16 outputs or 8 hidden units.  A round of
+// workgroups (256, one per CU) takes about as long with one workgroup as with 256, the longer the
+// larger the tile; a larger tile needs fewer bytes per product out of the L2, which is what bounds many
+// rows.  So it is the smallest tile whose grid is one round.  Launch times (us, the launch's own 2.7 included):
+//   FC 2304 -> 512, fp32     1 x 1   2 x 1   2 x 2   2 x 4   4 x 4
+//          64 rows             6.2     8.4    10.0    14.6
+//         256                 11.8    10.2    10.3    14.6    24.0
+//         512                 24.0    16.0    10.8    14.9    24.4
+//        1024                                 20.5    17.5    24.6
+//        2048                                 34.7    32.0    27.4   (with the division by deal(); 39.3 before)
+//   GRU 512 -> 512, fp32      1 x 1   2 x 1   2 x 2   2 x 4
+//          64 rows             6.6     8.0     8.3    12.1
+//         256                 21.2    16.6     9.4    12.1
+//         333                                 15.2    12.2
+//         512                                 17.3    12.9
+//   LSTM 512 -> 512, fp32, 512 rows           21.3    15.5
+//   FC 2304 -> 512, bf16: 600 rows 2 x 2 8.6, 2 x 4 6.8, 4 x 4 8.2; 2048 rows 15.8, 12.5, 10.9 (before 15.6)
+//   FC 4608 -> 256, fp16: 512 rows 2 x 1 8.2, 2 x 2 6.9; 2048 rows 2 x 2 15.8, 2 x 4 13.1, 4 x 4 18.4 (15.9)
+// Beyond one round of all of them the FC takes the one of 2 x 4 and 4 x 4 with the less time over its
+// rounds, one of 4 x 4 counted as 1.6 (fp32 at 2600 rows 45.0, 48.5; at 4096 65, 56).  Weights in 16 bits leave room
+// for two workgroups of 2 x 2 on a CU, one's loads behind the other's products: cells with one
+// term stay with that (GRU 512 rows 9.3, 2 x 4 9.0; 1000 rows 16.2, 16.1).
+// DA, DB by what fits the registers: all tiles but those with two workgroups per CU have 256, none spills
+// but the LSTM's and GRU's of three terms would at 2 x 4 with two steps in flight.
 // The bits of a result do not depend on any of this.
 template <int KIND, int XT, int PB, bool OUT16>
 hipError_t launch_kind(const DenseArgs& g, hipStream_t st) {
   const int n_col = KIND == FC ? g.N / 16 : g.H / 8;
-  const bool one_round = split_workgroups(g.M, n_col, 2, 2) <= 256;
-  if (split_workgroups(g.M, n_col, 1, 1) <= 256) return launch_cfg<KIND, XT, PB, 1, 1, 4, 4, OUT16>(g, st);
-  if (split_workgroups(g.M, n_col, 2, 1) <= 256) return launch_cfg<KIND, XT, PB, 2, 1, 3, 3, OUT16>(g, st);
-  if constexpr (KIND == FC || PB == 3)
-    if (one_round) return launch_cfg<KIND, XT, PB, 2, 2, 2, 2, OUT16>(g, st);
-  if constexpr (KIND == FC && XT != X_F32) return launch_cfg<KIND, XT, PB, 4, 2, 3, 3, OUT16>(g, st);
-  else return launch_cfg<KIND, XT, PB, 2, 2, 1, 1, OUT16>(g, st);
+  auto rounds = [&](int rt, int u) { return (split_workgroups(g.M, n_col, rt, u) + 255) / 256; };
+  constexpr bool F32 = XT == X_F32;
+  if (rounds(1, 1) <= 1) return launch_cfg<KIND, XT, PB, 1, 1, 4, 4, OUT16>(g, st);
+  if constexpr (KIND != FC || F32)
+    if (rounds(2, 1) <= 1) return launch_cfg<KIND, XT, PB, 2, 1, 3, 3, OUT16>(g, st);
+  if constexpr (KIND == FC) {
+    constexpr int D = F32 ? 1 : 2;
+    if (rounds(2, 2) <= 1 || n_col % 4 != 0) return launch_cfg<KIND, XT, PB, 2, 2, D, D, OUT16>(g, st);
+    if (rounds(2, 4) <= 1 || 5 * rounds(2, 4) < 8 * rounds(4, 4)) return launch_cfg<KIND, XT, PB, 2, 4, 2, D, OUT16>(g, st);
+    return launch_cfg<KIND, XT, PB, 4, 4, 1, 1, OUT16>(g, st);
+  } else if constexpr (PB == 3) {
+    if (rounds(2, 2) <= 1) return launch_cfg<KIND, XT, PB, 2, 2, 2, 2, OUT16>(g, st);
+    return launch_cfg<KIND, XT, PB, 2, 4, 1, 1, OUT16>(g, st);
+  } else {
+    return launch_cfg<KIND, XT, PB, 2, 2, 1, 1, OUT16>(g, st);
+  }
 }
 
 // Packing runs at every weight update, 24 results per eight weights: two builds of the loops, the

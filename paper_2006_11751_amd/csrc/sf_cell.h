@@ -18,18 +18,20 @@ __device__ inline float tanh_acc(float a) {
   return copysignf((1.0f - e) / (1.0f + e), a);
 }
 
+// (The contractions are written out: left to the compiler, a cell's bits would depend on the tile it is
+// computed in.)
 __device__ inline float gru_gates(const float (&sum)[4], const float (&bias)[2][4], float prev) {
   const float rg = sigmoid_acc(sum[0] + (bias[0][0] + bias[1][0]));
   const float z = sigmoid_acc(sum[1] + (bias[0][1] + bias[1][1]));
-  const float n = tanh_acc(sum[2] + bias[0][2] + rg * (sum[3] + bias[1][2]));
-  return (1.0f - z) * n + z * prev;
+  const float n = tanh_acc(fmaf(rg, sum[3] + bias[1][2], sum[2] + bias[0][2]));
+  return fmaf(z, prev, (1.0f - z) * n);
 }
 __device__ inline float lstm_gates(const float (&sum)[4], const float (&bias)[2][4], float prev, float& cell) {
   const float ig = sigmoid_acc(sum[0] + (bias[0][0] + bias[1][0]));
   const float fg = sigmoid_acc(sum[1] + (bias[0][1] + bias[1][1]));
   const float gg = tanh_acc(sum[2] + (bias[0][2] + bias[1][2]));
   const float og = sigmoid_acc(sum[3] + (bias[0][3] + bias[1][3]));
-  cell = fg * prev + ig * gg;
+  cell = fmaf(fg, prev, ig * gg);
   return og * tanh_acc(cell);
 }
 // a state row: [h] (GRU), [h | c] (LSTM); prev: the unit's h or c
@@ -64,7 +66,8 @@ struct DenseArgs {
   int N;                // FC outputs
   int k1, k2, kn;       // K steps (of 32): of x1, of x1 and x2, all
   int n_rt, n_cg;       // workgroups along the rows / the columns
-  int rows_per_xcd;     // deal row tiles (1) or column groups (0) to the XCDs
+  int xcd_rows;         // the 8 XCDs as xcd_rows x 8 / xcd_rows blocks of
+  int per_rt, per_cg;   // per_rt x per_cg workgroups
 };
 
 // The sums of one row that holds an infinity or a NaN, or of a row whose sum came out as one, in plain

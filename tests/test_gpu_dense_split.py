@@ -21,8 +21,8 @@ def _net(**kw):
     return n
 
 
-# (network, max_batch, batch sizes).  512 hidden units: one round of 16 x 8, 32 x 8, 32 x 16 tiles up
-# to 64, 128, 256 rows; the kernel for many rows from max_batch 513 on (64 rows x 32 units).
+# (network, max_batch, batch sizes).  512 hidden units: one round of 16 x 8, 32 x 8, 32 x 16, 32 x 32 tiles up
+# to 64, 128, 256, 512 rows; the kernel for many rows from max_batch 513 on (64 rows x 32 units).
 CASES = [
     (_net(fc=512, rnn=512), 512, [1, 16, 17, 64, 65, 128, 129, 257, 512]),
     (_net(fc=512, rnn=512), 513, [1, 64, 65, 513]),
@@ -35,6 +35,12 @@ CASES = [
     (_net(fc=128, rnn=128, dtype="bf16"), 70, [1, 70]),
     (_net(fc=128, rnn=128, rnn_type="lstm", dtype="bf16", meas_dim=5, meas_hidden=[64]), 33, [33]),
     (_net(fc=64, rnn=96, dtype="bf16"), 50, [50]),
+    # the FC layer's tiles: 512 outputs, one round of 32 x 32, 32 x 64, 64 x 64 up to 512, 1024, 2048 rows;
+    # outputs that are no multiple of 64
+    (_net(fc=512, rnn=32), 2600, [512, 513, 1024, 1025, 2048, 2049, 2600]),
+    (_net(fc=512, rnn=32, dtype="bf16"), 2048, [128, 129, 512, 513, 1024, 1025, 2048]),
+    (_net(fc=544, rnn=32), 500, [480, 481, 500]),
+    (_net(fc=544, rnn=32, dtype="bf16"), 500, [480, 481, 500]),
 ]
 
 
@@ -68,7 +74,7 @@ def test_tiles(torch_cuda, ref, net, max_batch, sizes):
     pol.close()
 
 
-@pytest.mark.parametrize("max_batch,B", [(64, 64), (256, 200), (600, 600)])
+@pytest.mark.parametrize("max_batch,B", [(64, 64), (256, 200), (300, 300), (600, 600)])
 @pytest.mark.parametrize("rnn_type", ["gru", "lstm"])
 def test_gathered_states(torch_cuda, max_batch, B, rnn_type):
     """Rows that index a state table give the bits of the plain step; an id outside the table
@@ -91,7 +97,7 @@ def test_gathered_states(torch_cuda, max_batch, B, rnn_type):
     pol.close()
 
 
-@pytest.mark.parametrize("max_batch,B", [(40, 40), (200, 200), (600, 600)])
+@pytest.mark.parametrize("max_batch,B", [(40, 40), (200, 200), (300, 300), (600, 600)])
 @pytest.mark.parametrize("rnn_type", ["gru", "lstm"])
 def test_states_without_terms(torch_cuda, ref, max_batch, B, rnn_type):
     """An infinity, a NaN and a number that would round up to an infinity in bf16: their rows
