@@ -35,6 +35,7 @@
 
 #include "sf_cell.h"
 #include "sf_internal.h"
+#include "sf_meas.h"
 #include "sf_split.h"
 
 namespace sf {
@@ -70,15 +71,17 @@ __device__ inline void state_rows(const DenseArgs& g, int (&row)[N], int (&flag)
 // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2: an XCD gets a block of
 // neighbouring row tiles and column groups (deal(), below).
 __device__ inline bool tile_of(const DenseArgs& g, int& rt, int& cg) {
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  rt = xcd % g.xcd_rows * g.per_rt + slot / g.per_cg;
-  cg = xcd / g.xcd_rows * g.per_cg + slot % g.per_cg;
+  const uint32_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int i = (int)(g.per_cg == 1 ? slot : __umulhi(slot, g.rcp_cg));  // slot / per_cg
+  rt = (int)(xcd & ((1u << g.xcd_rows) - 1)) * g.per_rt + i;
+  cg = (int)(xcd >> g.xcd_rows) * g.per_cg + (int)slot - i * g.per_cg;
   return rt < g.n_rt && cg < g.n_cg;
 }
 
 // DA, DB: K steps of rows / weights a wave has in flight; DA = 1: in turn with a second workgroup of the CU, or
 // for want of registers.
-template <int KIND, int XT, int PB, int RT, int U, int DA, int DB, bool OUT16>
+// MEAS: with workgroups of the measurement layers (an instantiation of its own: 0.2 us of 24 at 60 rows).
+template <int KIND, int XT, int PB, int RT, int U, int DA, int DB, bool OUT16, bool MEAS>
 __global__ __launch_bounds__(kThreads, DA == 1 && RT * U <= 4 ? 4 : 2) void dense_split_kernel(DenseArgs g) {
   constexpr int GB = group_bytes(KIND);
   constexpr int UN = (U + 1) / 2;                                   // GRU: tiles of n columns
@@ -97,6 +100,11 @@ __global__ __launch_bounds__(kThreads, DA == 1 && RT * U <= 4 ? 4 : 2) void dens
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
+  if constexpr (MEAS)
+    if ((int)blockIdx.x >= g.blocks) {  // the measurement layers (kMeasThreads threads)
+      meas_rows(g.meas, (int)blockIdx.x - g.blocks, lds);
+      return;
+    }
   int rt0, cg;
   if (!tile_of(g, rt0, cg)) return;
   const int row0 = rt0 * 16 * RT;
@@ -717,10 +725,11 @@ unsigned deal(DenseArgs& g, long long tile_row_bytes, long long group_bytes) {
     const long long cost = (rounds << 40) + per_rt * tile_row_bytes + per_cg * group_bytes;
     if (least >= 0 && cost >= least) continue;
     least = cost;
-    g.xcd_rows = rows;
+    g.xcd_rows = rows == 8 ? 3 : rows / 2;
     g.per_rt = per_rt;
     g.per_cg = per_cg;
   }
+  g.rcp_cg = (uint32_t)((0x100000000ull + g.per_cg - 1) / g.per_cg);  // (exact: per_rt * per_cg^2 is far below 2^32)
   return 8u * g.per_rt * g.per_cg;
 }
 
@@ -730,7 +739,14 @@ hipError_t launch_cfg(DenseArgs g, hipStream_t st) {
   g.n_cg = KIND == FC ? g.N / (16 * U) : g.H / (8 * U);
   const long long row_bytes = 16LL * RT * g.kn * 32 * (in_f32(XT) ? 4 : 2);
   const unsigned blocks = deal(g, row_bytes, (long long)U * g.kn * PB * group_bytes(KIND));
-  dense_split_kernel<KIND, XT, PB, RT, U, DA, DB, OUT16><<<blocks, kThreads, 0, st>>>(g);
+  if constexpr (KIND == FC)
+    if (g.meas.B > 0) {
+      g.blocks = (int)blocks;
+      dense_split_kernel<KIND, XT, PB, RT, U, DA, DB, OUT16, true>
+          <<<blocks + (g.meas.B + kMeasRows - 1) / kMeasRows, kThreads, 0, st>>>(g);
+      return hipGetLastError();
+    }
+  dense_split_kernel<KIND, XT, PB, RT, U, DA, DB, OUT16, false><<<blocks, kThreads, 0, st>>>(g);
   return hipGetLastError();
 }
 
@@ -905,13 +921,20 @@ void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lst
   (host_avx2() ? pack_cell_avx2 : pack_cell_plain)(w_ih, w_hh, I, H, lstm, terms, out);
 }
 
+// The smallest tile's LDS has to hold the rows of a workgroup.
+static_assert(kMeasThreads == kThreads, "workgroups of the FC layer's launch");
+bool dense_fc_takes_meas(int n0, int n1) { return meas_lds(n0, n1) <= kWaves * 16 * 36; }
+
+// meas: measurement layers to be computed by further workgroups of the launch, or null: their time passes
+// beside the FC layer's (as a launch of their own 6.4 us at 333 rows, latency for the most part).
 // x [M][K] (x_type 0 fp32, 1 bf16, 2 fp16), w packed with three terms for fp32 rows and one for
 // 16-bit rows; out [M][N] = relu(x w^T + bias), fp32 or (out_bf16) bf16.
 hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const float* bias, void* out, int out_bf16,
-                           int M, int K, int N, hipStream_t st) {
+                           int M, int K, int N, const MeasArgs* meas, hipStream_t st) {
   if (M == 0) return hipSuccess;
-  if (!dense_fc_supported(K, N)) return hipErrorInvalidValue;
+  if (!dense_fc_supported(K, N) || (meas && !dense_fc_takes_meas(meas->n0, meas->n1))) return hipErrorInvalidValue;
   DenseArgs g{};
+  if (meas) g.meas = *meas;
   g.x1 = x; g.w = (const uint8_t*)w; g.b1 = bias; g.out = out;
   g.M = M; g.I1 = K; g.N = N; g.k1 = g.k2 = g.kn = K / 32;
   if (x_type == X_F32) return out_bf16 ? hipErrorInvalidValue : launch_kind<FC, X_F32, 3, false>(g, st);

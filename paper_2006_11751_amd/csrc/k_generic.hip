@@ -93,90 +93,9 @@ __global__ __launch_bounds__(kThreads) void linear_generic_kernel(
   out[(size_t)b * n_out + o] = acc;
 }
 
-// Measurement encoder of the full architecture: one or two fully connected + ReLU layers
-// in one launch.  A workgroup handles kMeasRows rows; the rows' inputs and the hidden activations
-// sit in LDS, every weight is read once per workgroup.  The time is the latency of the weight
-// loads, so four groups of threads share the inputs of a layer and the first weights of both layers
-// are requested at once; the partial sums meet in LDS.  (One group, eight loads in flight: 10 us for 23 -> 128 -> 128 on
-// 333 rows; now 5.9.)
-constexpr int kMeasRows = 4;
-constexpr int kMeasCols = 128;   // outputs at a time
-constexpr int kMeasParts = 4;    // groups of threads along the inputs
-constexpr int kMeasThreads = kMeasCols * kMeasParts;
-
-// A thread's first weights of a layer, and its bias: requested for both layers at the kernel's start.
-template <int BATCH>
-struct MeasFirst {
-  float w[BATCH], bias;
-  __device__ inline void load(const float* __restrict__ w_t, const float* __restrict__ b, int n_in, int n_out) {
-    const int o = min((int)threadIdx.x % kMeasCols, n_out - 1), q = threadIdx.x / kMeasCols;
-    const int k0 = n_in * q / kMeasParts, k1 = n_in * (q + 1) / kMeasParts;
-#pragma unroll
-    for (int u = 0; u < BATCH; ++u) w[u] = w_t[(size_t)max(min(k0 + u, k1 - 1), 0) * n_out + o];
-    bias = b[o];
-  }
-};
-
-template <int BATCH>
-__device__ inline void meas_layer(const float* in, int n_in, const float* __restrict__ w_t, const float* __restrict__ b,
-                                  int n_out, MeasFirst<BATCH>& first, float* part, float* hidden, float* out, int rows) {
-  const int tid = threadIdx.x, c = tid % kMeasCols, q = tid / kMeasCols;
-  const int k0 = n_in * q / kMeasParts, k1 = n_in * (q + 1) / kMeasParts;
-  for (int o0 = 0; o0 < n_out; o0 += kMeasCols) {
-    const int o = min(o0 + c, n_out - 1);
-    if (o0) first.bias = b[o];
-    float acc[kMeasRows];
-#pragma unroll
-    for (int r = 0; r < kMeasRows; ++r) acc[r] = 0.0f;
-    for (int i = k0; i < k1; i += BATCH) {
-      if (o0 || i != k0)
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) first.w[u] = w_t[(size_t)min(i + u, k1 - 1) * n_out + o];
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        // past the end: 0 times the last weight again (the input is the one to leave out: it may be infinite)
-        const int at = min(i + u, k1 - 1);
-#pragma unroll
-        for (int r = 0; r < kMeasRows; ++r) acc[r] = fmaf(i + u < k1 ? in[r * n_in + at] : 0.0f, first.w[u], acc[r]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kMeasRows; ++r) part[(q * kMeasRows + r) * kMeasCols + c] = acc[r];
-    __syncthreads();
-    const int r = q;  // (as many groups as rows)
-    float v = first.bias;
-#pragma unroll
-    for (int p = 0; p < kMeasParts; ++p) v += part[(p * kMeasRows + r) * kMeasCols + c];
-    v = fmaxf(v, 0.0f);
-    if (o0 + c < n_out) {
-      if (hidden)
-        hidden[r * n_out + o] = v;
-      else if (r < rows)
-        out[(size_t)r * n_out + o] = v;
-    }
-    __syncthreads();
-  }
-}
-
-__global__ __launch_bounds__(kMeasThreads) void meas_mlp_kernel(
-    const float* __restrict__ meas, int B, int n0, const float* __restrict__ w1_t,
-    const float* __restrict__ b1, int n1, const float* __restrict__ w2_t,
-    const float* __restrict__ b2, int n2, float* __restrict__ out) {
-  static_assert(kMeasParts == kMeasRows, "a group finishes a row");
-  __shared__ float part[kMeasParts * kMeasRows * kMeasCols];
+__global__ __launch_bounds__(kMeasThreads) void meas_mlp_kernel(MeasArgs g) {
   extern __shared__ float sm[];
-  float* s_in = sm;                   // [kMeasRows][n0]
-  float* s_h = sm + kMeasRows * n0;   // [kMeasRows][n1]
-  const int r0 = blockIdx.x * kMeasRows, rows = min(B - r0, kMeasRows);
-  MeasFirst<8> first1;
-  MeasFirst<32> first2;
-  first1.load(w1_t, b1, n0, n1);
-  if (n2 > 0) first2.load(w2_t, b2, n1, n2);
-  for (int i = threadIdx.x; i < kMeasRows * n0; i += kMeasThreads)
-    s_in[i] = i < rows * n0 ? meas[(size_t)r0 * n0 + i] : 0.0f;
-  __syncthreads();
-  meas_layer(s_in, n0, w1_t, b1, n1, first1, part, n2 > 0 ? s_h : nullptr, out + (size_t)r0 * n1, rows);
-  if (n2 > 0) meas_layer(s_h, n1, w2_t, b2, n2, first2, part, nullptr, out + (size_t)r0 * n2, rows);
+  meas_rows(g, (int)blockIdx.x, sm);
 }
 
 __device__ inline float sigmoidf_acc(float a) { return 1.0f / (1.0f + expf(-a)); }
@@ -291,17 +210,13 @@ hipError_t launch_linear_generic(int B, int n_in, int n_out, const float* in, co
   return hipGetLastError();
 }
 
-bool meas_mlp_supported(int n0, int n1) { return (size_t)kMeasRows * (n0 + n1) * sizeof(float) <= 48 * 1024; }
+bool meas_mlp_supported(int n0, int n1) { return (size_t)meas_lds(n0, n1) * sizeof(float) <= 56 * 1024 + 128; }
 
-// w1_t [n0][n1], w2_t [n1][n2] (transposed weights); n2 == 0: a single layer.
-// out [B][n2 ? n2 : n1].
-hipError_t launch_meas_mlp(int B, int n0, const float* meas, const float* w1_t, const float* b1, int n1,
-                           const float* w2_t, const float* b2, int n2, float* out, hipStream_t st) {
-  if (B == 0) return hipSuccess;
-  if (!meas_mlp_supported(n0, n1)) return hipErrorInvalidValue;
-  const unsigned blocks = (unsigned)((B + kMeasRows - 1) / kMeasRows);
-  const size_t lds = (size_t)kMeasRows * (n0 + n1) * sizeof(float);
-  meas_mlp_kernel<<<blocks, kMeasThreads, lds, st>>>(meas, B, n0, w1_t, b1, n1, w2_t, b2, n2, out);
+hipError_t launch_meas_mlp(const MeasArgs& g, hipStream_t st) {
+  if (g.B == 0) return hipSuccess;
+  if (!meas_mlp_supported(g.n0, g.n1)) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)((g.B + kMeasRows - 1) / kMeasRows);
+  meas_mlp_kernel<<<blocks, kMeasThreads, meas_lds(g.n0, g.n1) * sizeof(float), st>>>(g);
   return hipGetLastError();
 }
 

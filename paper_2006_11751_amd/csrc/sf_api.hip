@@ -731,6 +731,7 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
       }
       n_prev = n_out;
     }
+    p->meas_fused = fused;
     if (fused) p->ops.push_back(Op{OP_MEAS, "meas.fc", 2 * m_all, -1, -1, -1, -1, 0, 0, 0});
     if (p->n_meas) p->meas_out_dim = n_prev;
   }
@@ -1244,6 +1245,17 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
   auto buf = [&](int i) -> float* { return i < 0 ? nullptr : p->act[i]; };
   const bool timing = p->timing && parts == PART_ALL;
   const bool conv12 = fuses_conv12(p);
+  // the measurement layers, where they are one launch, in the FC layer's (timed: a launch of their own)
+  const bool meas_in_fc = !timing && p->n_meas && p->dense_fc && p->meas_fused && dense_fc_takes_meas(c.meas_dim, c.meas_hidden[0]);
+  auto meas_args = [&] {
+    const bool two = p->n_meas == 2;
+    MeasArgs m{};
+    if (!p->n_meas) return m;
+    m.in = meas; m.w1 = p->meas_w_t[0]; m.b1 = p->meas_b[0]; m.out = p->meas_buf[p->n_meas - 1];
+    m.w2 = two ? p->meas_w_t[1] : nullptr; m.b2 = two ? p->meas_b[1] : nullptr;
+    m.B = B; m.n0 = c.meas_dim; m.n1 = c.meas_hidden[0]; m.n2 = two ? c.meas_hidden[1] : 0;
+    return m;
+  };
   if (timing) {
     p->timed_conv12 = conv12;
     SF_LAUNCH(hipEventRecord(p->events[0], st));
@@ -1358,10 +1370,11 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
           SF_LAUNCH(launch_maxpool3x3s2p1(B, op.C, op.H, op.W, buf(op.in_buf), buf(op.out_buf), st));
         break;
       case OP_FC:
-        if (p->dense_fc)
+        if (p->dense_fc) {
+          const MeasArgs m = meas_args();
           SF_LAUNCH(launch_dense_fc(buf(op.in_buf), !p->bf16_path ? 0 : p->act_f16 ? 2 : 1, p->fc_split_w, p->fc_b,
-                                    p->fc_out, p->fc_out_bf16, B, p->flat, c.fc_dim, st));
-        else if (p->fc_wbf && p->fc16)
+                                    p->fc_out, p->fc_out_bf16, B, p->flat, c.fc_dim, meas_in_fc ? &m : nullptr, st));
+        } else if (p->fc_wbf && p->fc16)
           SF_LAUNCH(launch_fc16(buf(op.in_buf), p->fc_wbf, p->fc_bbf, p->fc_out, B, p->flat, c.fc_dim, p->act_f16,
                                 p->fc_out_bf16, st));
         else if (p->fc_wbf)
@@ -1379,10 +1392,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
       case OP_MEAS: {
         const int l = op.conv;
         if (l < 0) {  // every layer in one launch
-          const bool two = p->n_meas == 2;
-          SF_LAUNCH(launch_meas_mlp(B, c.meas_dim, meas, p->meas_w_t[0], p->meas_b[0], c.meas_hidden[0],
-                                    two ? p->meas_w_t[1] : nullptr, two ? p->meas_b[1] : nullptr,
-                                    two ? c.meas_hidden[1] : 0, p->meas_buf[p->n_meas - 1], st));
+          if (!meas_in_fc) SF_LAUNCH(launch_meas_mlp(meas_args(), st));
           break;
         }
         SF_LAUNCH(launch_linear_generic(B, p->meas_in_dim[l], c.meas_hidden[l],

@@ -6,6 +6,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "sf_meas.h"
+
 namespace sf {
 
 enum Kind { FC = 0, GRU = 1, LSTM = 2 };
@@ -66,8 +68,11 @@ struct DenseArgs {
   int N;                // FC outputs
   int k1, k2, kn;       // K steps (of 32): of x1, of x1 and x2, all
   int n_rt, n_cg;       // workgroups along the rows / the columns
-  int xcd_rows;         // the 8 XCDs as xcd_rows x 8 / xcd_rows blocks of
+  int xcd_rows;         // the 8 XCDs as 2^xcd_rows x 2^(3 - xcd_rows) blocks of
   int per_rt, per_cg;   // per_rt x per_cg workgroups
+  uint32_t rcp_cg;      // 2^32 / per_cg, rounded up
+  int blocks;           // FC: workgroups ahead of those of the measurement layers
+  MeasArgs meas;        // B = 0: none
 };
 
 // The sums of one row that holds an infinity or a NaN, or of a row whose sum came out as one, in plain

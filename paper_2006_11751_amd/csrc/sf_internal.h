@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "sf_meas.h"
 #include "sf_policy.h"
 
 namespace sf {
@@ -140,6 +141,7 @@ struct Policy {
   // measurement encoder of the full architecture (n_meas = 0: none)
   int n_meas;
   int meas_out_dim;
+  bool meas_fused = false;  // all layers in one launch
   int meas_in_dim[SF_MAX_MEAS_LAYERS];
   float* meas_w_t[SF_MAX_MEAS_LAYERS];  // dev [in][out]
   float* meas_b[SF_MAX_MEAS_LAYERS];
@@ -184,8 +186,7 @@ hipError_t launch_maxpool3x3s2p1(int B, int C, int H, int W, const float* in, fl
 hipError_t launch_linear_generic(int B, int n_in, int n_out, const float* in, const float* w_t,
                                  const float* bias, int relu, float* out, hipStream_t st);
 bool meas_mlp_supported(int n0, int n1);
-hipError_t launch_meas_mlp(int B, int n0, const float* meas, const float* w1_t, const float* b1, int n1,
-                           const float* w2_t, const float* b2, int n2, float* out, hipStream_t st);
+hipError_t launch_meas_mlp(const MeasArgs& g, hipStream_t st);
 hipError_t launch_rnn_generic(int lstm, int B, int n1, int n2, int H, const float* x1, const float* x2,
                               const float* h_in, const uint8_t* done, const float* wih_t,
                               const float* whh_t, const float* bih, const float* bhh, float* h_out,
@@ -281,8 +282,9 @@ size_t dense_fc_pack_size(int N, int K, int terms);  // elements
 size_t dense_cell_pack_size(int I, int H, int lstm, int terms);
 void dense_pack_fc(const float* w, int N, int K, int terms, bool f16, uint16_t* out);
 void dense_pack_cell(const float* w_ih, const float* w_hh, int I, int H, int lstm, int terms, uint16_t* out);
+bool dense_fc_takes_meas(int n0, int n1);  // the measurement layers in the FC layer's launch
 hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const float* bias, void* out, int out_bf16,
-                           int M, int K, int N, hipStream_t st);
+                           int M, int K, int N, const MeasArgs* meas, hipStream_t st);
 hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);

@@ -1,4 +1,4 @@
-"""Measurement layers (meas_mlp_kernel): an infinite measurement, or an infinite hidden value, at every
+"""Measurement layers (sf_meas.h, in the FC layer's launch or, hidden layers too large for that, their own): an infinite measurement, or an infinite hidden value, at every
 place of a layer's inputs, against the oracle."""
 import numpy as np
 import pytest
@@ -19,7 +19,7 @@ def _net(hidden, dtype):
 
 @pytest.mark.parametrize("sign", [1, -1])
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("hidden", [[32], [64], [40, 32], [33, 64], [150, 64]])
+@pytest.mark.parametrize("hidden", [[32], [64], [40, 32], [33, 64], [150, 64], [660, 32]])
 def test_infinite_measurement(torch_cuda, ref, hidden, dtype, sign):
     """Rows 0 .. 22 hold an infinity at measurement 0 .. 22.  Each layer has one unit per input with a
     weight of the sign that makes it infinite; the others go to zero, so that one feature is infinite and the
