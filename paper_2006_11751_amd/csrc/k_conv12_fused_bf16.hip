@@ -69,6 +69,7 @@ struct Conv12Args {
   int image_at;         // LDS offset of the two images
   int rcp_wo2, rcp_row; // x / d = x * rcp >> 16 for Wo2, W / 16
   int parts;            // workgroups per frame
+  ExchangePrep prep;    // with several workgroups per frame: work for a later launch (sf_exchange.h)
 };
 
 int reciprocal(int d) { return (65536 + d - 1) / d; }  // exact for x * d < 65536
@@ -263,6 +264,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_fused_bf16_kernel(Conv12Args g)
   int b = first_frame;
   store_frame();
   __syncthreads();
+  if (!WHOLE) exchange_prepare(g.prep, (int)blockIdx.x * kNT + tid, (int)gridDim.x * kNT);
   if (WHOLE || b + stride < g.B) load_frame(min(b + stride, g.B - 1));  // (no frame left: one for no use)
   first_layer(image);
   __syncthreads();
@@ -325,7 +327,7 @@ bool conv12_fused_bf16_supported(int cin, int H, int W, const sf_conv& c1, const
 // L1, L2: the two layers as executed separately (L1's digit planes, scales and bias, L2's
 // image-kernel fragments and bias); out: bf16 [B][Ho2*Wo2][64].
 hipError_t launch_conv12_fused_bf16(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs,
-                                    void* out, hipStream_t st) {
+                                    void* out, ExchangePrep& prep, hipStream_t st) {
   if (B == 0) return hipSuccess;
   if (((uintptr_t)obs & 15) != 0 || L1.planes != 2 || (L2.Ho * L2.Wo + 15) / 16 != kMaxTiles) return hipErrorInvalidValue;
   Conv12Args g;
@@ -349,6 +351,8 @@ hipError_t launch_conv12_fused_bf16(const ConvLayer& L1, const ConvLayer& L2, in
     return !flat(L1.W) && B * parts <= 256 && (L2.Ho + parts - 1) / parts * L2.Wo <= 16 * tiles;
   };
   g.parts = fits(4, 2) ? 4 : fits(2, 4) ? 2 : 1;
+  prep.done = g.parts > 1;
+  g.prep = prep;
   auto kern = flat(L1.W) ? conv12_fused_bf16_kernel<true, 7>
               : g.parts == 4 ? conv12_fused_bf16_kernel<false, 2>
               : g.parts == 2 ? conv12_fused_bf16_kernel<false, 4>

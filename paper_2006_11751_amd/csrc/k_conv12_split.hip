@@ -78,6 +78,7 @@ struct Args {
   int image_at, sums_at, bank_at; // LDS offsets
   int rcp_wo2, rcp_row;  // x / d = x * rcp >> 16 for Wo2, W / 16
   int parts;             // workgroups per frame
+  ExchangePrep prep;     // with several workgroups per frame: work for a later launch (sf_exchange.h)
 };
 
 int reciprocal(int d) { return (65536 + d - 1) / d; }  // exact for x * d < 65536
@@ -203,6 +204,7 @@ __global__ __launch_bounds__(kNT, 2) void conv12_split_kernel(Args g) {
 
   store_frame();
   __syncthreads();
+  if (!WHOLE) exchange_prepare(g.prep, (int)blockIdx.x * kNT + tid, (int)gridDim.x * kNT);
   int done = -1;  // the frame whose sums wait to be finished
   for (int b = first_frame; b < g.B; b += frame_step) {
     const bool more = WHOLE || b + frame_step < g.B;
@@ -427,9 +429,9 @@ bool conv12_split_supported(int cin, int H, int W, const sf_conv& a, const sf_co
 
 // L1 on three digit planes, L2 on split operands; obs 4-byte aligned (the second layer's sums are this
 // kernel's own: frames at any address have to come here); mid: room for L1's output, written by the
-// fallback only.
+// fallback only; prep: see Args, marked as done if it is.
 hipError_t launch_conv12_split(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs, float* mid, float* out,
-                               hipStream_t st) {
+                               ExchangePrep& prep, hipStream_t st) {
   if (B == 0) return hipSuccess;
   if (((uintptr_t)obs & 3) != 0 || L1.planes != 3 || (L2.Ho * L2.Wo + 15) / 16 != kMaxTiles) return hipErrorInvalidValue;
   const Layout L = layout(L1.H, L1.Ho, L1.Wo, L2.Wo);
@@ -458,6 +460,8 @@ hipError_t launch_conv12_split(const ConvLayer& L1, const ConvLayer& L2, int B, 
     blocks = items < 256 ? items : 256;
     least = time;
   }
+  prep.done = g.parts > 1;
+  g.prep = prep;
   auto kern = g.parts == 4 ? conv12_split_kernel<2> : g.parts == 2 ? conv12_split_kernel<4> : conv12_split_kernel<7>;
   kern<<<blocks, kNT, L.bytes, st>>>(g);
   return hipGetLastError();

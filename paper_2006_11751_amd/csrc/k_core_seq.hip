@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "sf_cell.h"
+#include "sf_exchange.h"
 #include "sf_internal.h"
 #include "sf_split.h"
 
@@ -50,9 +51,6 @@ constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kPlain = 1024;  // threads of core_seq_plain_kernel
 constexpr int kMaxX = 3 * 32 * kWaves, kMaxH = 2 * 32 * kWaves;  // see core_seq_supported
-constexpr unsigned kNotYet = 0xFFFFFFFFu;  // fills the h columns of h_seq ahead of the pass
-// cache policy of a buffer load: sc1 (device scope), volatile (repeated as often as it is written)
-constexpr int kDeviceScope = (int)0x80000010;
 
 struct SeqArgs {
   DenseArgs d;    // x1, x2, w, b1, b2, I1, I2, H, S, k1, k2, kn; M = N trajectories
@@ -67,10 +65,6 @@ struct SeqArgs {
 // A trajectory's marks: the first step with a sum that is not finite, plus one (0: its row tile was given
 // up; kNone: neither), and the last such step.
 constexpr unsigned kNone = 0xFFFFFFFFu;
-
-__device__ inline unsigned load_word(const unsigned* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // also sets the n_words words of the ticket and the marks
 __global__ __launch_bounds__(256) void core_seq_fill_kernel(float* seq, long long rows, int H, int S, unsigned* words, int n_words) {

@@ -16,42 +16,18 @@
 // Other shapes: heads_kernel, one 64-lane wavefront per row, whose dot products, ten cross-lane moves
 // per eight outputs, took 16.5 us for seven heads on 333 rows and 16 us for one head of 15 on 8192
 // rows (now 8.4 and 8.1).
+#include "sf_heads.h"
 #include "sf_internal.h"
-#include "sf_split.h"
 
 namespace sf {
 
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;
 constexpr int kRowsPerBlock = 4;
 constexpr int kMaxLogits = 1024;  // per row, value included (LDS staging)
-
-__device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                     uint32_t k0, uint32_t k1, uint32_t out[4]) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    const uint32_t m0 = 0xD2511F53u, m1 = 0xCD9E8D57u;
-    uint32_t hi0 = __umulhi(m0, c0), lo0 = m0 * c0;
-    uint32_t hi1 = __umulhi(m1, c2), lo1 = m1 * c2;
-    uint32_t n0 = hi1 ^ c1 ^ k0;
-    uint32_t n2 = hi0 ^ c3 ^ k1;
-    c0 = n0;
-    c1 = lo1;
-    c2 = n2;
-    c3 = lo0;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  out[0] = c0;
-  out[1] = c1;
-  out[2] = c2;
-  out[3] = c3;
-}
 
 __device__ inline float wave_sum(float v) {
 #pragma unroll
@@ -209,43 +185,14 @@ __global__ __launch_bounds__(kWave* kRowsPerBlock) void heads_kernel(
   if (lane == 0) logp[b] = lp_total;
 }
 
-struct HeadsArgs {
-  const float* h;         // [B][S], the first H floats of a row
-  const uint8_t* w;       // packed weights [NT][H / 32][PB][64][8] (rows past the value head: zeros)
-  const float* head_w;    // [sumA + 1][H]
-  const float* head_b;    // [sumA + 1]
-  const int32_t* head_off;
-  int32_t* actions;       // null: logits and value only
-  float* logp;
-  float* value;
-  float* logits;          // or null
-  const int32_t* ids;     // or null
-  float* h_table;         // or null: row ids[b] receives row b's state
-  uint32_t seed_lo, seed_hi, step_lo, step_hi;
-  int B, H, S, n_heads, sumA, n_env;
-};
-
-constexpr int kHeadWaves = 8;
-constexpr int kHeadRows = 16;
-constexpr int kHeadThreads = kWave * kHeadWaves;
-
 template <int NT, int PB>
 __global__ __launch_bounds__(kHeadThreads) void heads_split_kernel(HeadsArgs g) {
-  constexpr int P32 = 36;                       // pitch of a row in LDS (floats)
-  constexpr int TURN = kHeadWaves * kHeadRows * P32, RED = kHeadWaves * NT * 64 * 4;
-  constexpr int LP = NT * 16 + 1;               // pitch of a row of logits
-  __shared__ __attribute__((aligned(16))) float lds[TURN > RED ? TURN : RED];
-  __shared__ float s_lg[kHeadRows][LP], s_pt[kHeadRows][LP], s_lp[kHeadRows][SF_MAX_HEADS];
-  __shared__ int s_off[SF_MAX_HEADS + 1], odd_row[kHeadRows];
-  f32x4(*red)[NT][64] = (f32x4(*)[NT][64])lds;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li = lane & 15, lg = lane >> 4;
+  __shared__ HeadsLds<NT> lds;
   // With a state table, the rows' new states go back to rows ids[b] of it (ids outside it write
   // nothing): workgroups of their own, a wave per row, on CUs that the contraction leaves free.
   const int n_blocks = (g.B + kHeadRows - 1) / kHeadRows;
   if ((int)blockIdx.x >= n_blocks) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int b = ((int)blockIdx.x - n_blocks) * kHeadWaves + wave;
     if (b >= g.B) return;
     const uint32_t env = (uint32_t)g.ids[b];
@@ -255,156 +202,7 @@ __global__ __launch_bounds__(kHeadThreads) void heads_split_kernel(HeadsArgs g) 
     }
     return;
   }
-  const int row0 = blockIdx.x * kHeadRows;
-  if (tid < kHeadRows) odd_row[tid] = 0;
-  if (tid <= g.n_heads) s_off[tid] = g.head_off[tid];
-
-  const int kn = g.H / 32;
-  const int s_begin = kn * wave / kHeadWaves, s_end = kn * (wave + 1) / kHeadWaves;
-  // rows with eight lanes side by side on a K step, turned into operand order in the wave's corner
-  // of LDS; two K steps in flight
-  const uint8_t* src[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-    src[j] = (const uint8_t*)(g.h + (size_t)min(row0 + 8 * j + (lane >> 3), g.B - 1) * g.S) + (lane & 7) * 16;
-  float* turn = lds + wave * (kHeadRows * P32);
-  f32x4 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  float left = 0.0f;
-  for (int s0 = s_begin; s0 < s_end; s0 += 2) {
-    f32x4 a[2][2];
-    u32x4 b[2][PB][NT];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int s = min(s0 + u, s_end - 1);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) a[u][j] = *(const f32x4*)(src[j] + (size_t)s * 128);
-#pragma unroll
-      for (int q = 0; q < PB; ++q)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) b[u][q][t] = *(const u32x4*)(g.w + (((size_t)t * kn + s) * PB + q) * 1024 + lane * 16);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (s0 + u >= s_end) break;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) *(f32x4*)(turn + (8 * j + (lane >> 3)) * P32 + (lane & 7) * 4) = a[u][j];
-      const f32x4 v0 = *(const f32x4*)(turn + li * P32 + lg * 8), v1 = *(const f32x4*)(turn + li * P32 + lg * 8 + 4);
-      u32x4 x[3];
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        unsigned t0, t1, t2;
-        split_pair(p < 2 ? v0[2 * p] : v1[2 * p - 4], p < 2 ? v0[2 * p + 1] : v1[2 * p - 3], t0, t1, t2, left);
-        x[0][p] = t0;
-        x[1][p] = t1;
-        x[2][p] = t2;
-      }
-      auto term = [&](int wq, int xq) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[u][wq][t]),
-                                                           __builtin_bit_cast(bf16x8, x[xq]), acc[t], 0, 0, 0);
-      };
-      if constexpr (PB == 3) {
-        term(2, 0);
-        term(0, 2);
-        term(1, 1);
-        term(1, 0);
-      } else {
-        term(0, 2);
-      }
-      term(0, 1);
-      term(0, 0);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < NT; ++t) red[wave][t][lane] = acc[t];
-  if (left != left) odd_row[li] = 1;
-  __syncthreads();
-  if (tid < NT * 64) {  // sums in wave order: thread -> row li, four outputs
-    f32x4 v = red[0][tid >> 6][lane];
-#pragma unroll
-    for (int w = 1; w < kHeadWaves; ++w) v += red[w][tid >> 6][lane];
-    bool odd = odd_row[li] != 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) odd |= !(fabsf(v[e]) < INFINITY);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int a = (tid >> 6) * 16 + 4 * lg + e;
-      const int ac = min(a, g.sumA);
-      if (__builtin_expect(odd, 0)) {  // an infinity or a NaN in the state or as a sum: plain arithmetic
-        const float* hr = g.h + (size_t)min(row0 + li, g.B - 1) * g.S;
-        float sum = 0.0f;
-        for (int k = 0; k < g.H; ++k) sum = fmaf(hr[k], g.head_w[(size_t)ac * g.H + k], sum);
-        v[e] = sum;
-      }
-      s_lg[li][a] = v[e] + g.head_b[ac];
-    }
-  }
-  __syncthreads();
-  const int rows = min(g.B - row0, kHeadRows);
-  if (tid < rows) g.value[row0 + tid] = s_lg[tid][g.sumA];
-  if (g.logits)
-    for (int i = tid; i < rows * g.sumA; i += kHeadThreads) {
-      const int r = i / g.sumA;
-      g.logits[(size_t)row0 * g.sumA + i] = s_lg[r][i - r * g.sumA];
-    }
-  if (!g.actions) return;  // (the learner's pass wants logits and value only)
-
-  // Gumbel perturbation: thread -> row, block of four categories of a head (at most 27 blocks)
-  const int r = tid & 15, b = row0 + r;
-  {
-    int q = tid >> 4, k = 0;
-    while (k < g.n_heads && q >= (s_off[k + 1] - s_off[k] + 3) / 4) {
-      q -= (s_off[k + 1] - s_off[k] + 3) / 4;
-      ++k;
-    }
-    if (k < g.n_heads && r < rows) {
-      // with ids, the row stands for environment ids[b]: that is the sampler's counter word
-      const uint32_t env = g.ids ? (uint32_t)g.ids[b] : (uint32_t)b;
-      uint32_t wd[4];
-      philox4x32_10(env, g.step_lo, g.step_hi, ((uint32_t)k << 16) | (uint32_t)q, g.seed_lo, g.seed_hi, wd);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int idx = s_off[k] + 4 * q + e;
-        if (idx < s_off[k + 1]) {
-          const float u = ((float)(wd[e] >> 9) + 0.5f) * 0x1.0p-23f;
-          s_pt[r][idx] = s_lg[r][idx] + -logf(-logf(u));
-        }
-      }
-    }
-  }
-  __syncthreads();
-  // thread -> row, head: categories in ascending order, so that the first maximum wins ties
-  const int k = tid >> 4;
-  if (k < g.n_heads && r < rows) {
-    const int off = s_off[k], A = s_off[k + 1] - off;
-    const float *pt = &s_pt[r][off], *l = &s_lg[r][off];
-    float best = pt[0], lmax = l[0];
-    int arg = 0;
-#pragma unroll 4
-    for (int i = 1; i < A; ++i) {
-      const float pert = pt[i];
-      if (pert > best) {
-        best = pert;
-        arg = i;
-      }
-      lmax = fmaxf(lmax, l[i]);
-    }
-    float se = 0.0f;
-#pragma unroll 4
-    for (int i = 0; i < A; ++i) se += expf(l[i] - lmax);
-    s_lp[r][k] = l[arg] - (lmax + logf(se));
-    g.actions[(size_t)b * g.n_heads + k] = arg;
-  }
-  __syncthreads();
-  if (tid < rows) {
-    float lp = 0.0f;
-    for (int q = 0; q < g.n_heads; ++q) lp += s_lp[tid][q];
-    g.logp[row0 + tid] = lp;
-  }
+  heads_rows<NT, PB, false>(g, blockIdx.x * kHeadRows, lds);
 }
 
 template <int PB>

@@ -87,6 +87,7 @@ struct StemPoolArgs {
   int n_items;         // H * W / 4
   int parts;           // workgroups per frame (few frames): each a share of the pooled rows
   float obs_sub, obs_mul;
+  ExchangePrep prep;   // few frames: work for a later launch (sf_exchange.h)
 };
 
 // (second launch bound: waves per SIMD; four = two workgroups of eight waves per CU, 128 VGPRs)
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(kNT, 4) void stem_pool_kernel(StemPoolArgs g) {
   load_frame(b);
   if (SHARED) __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();  // zeros in place
+  if (SHARED) exchange_prepare(g.prep, (int)blockIdx.x * kNT + tid, (int)gridDim.x * kNT);
   for (; b < g.B; b += stride) {
     stage();
     __syncthreads();
@@ -282,7 +284,7 @@ void stem_pool_pack(const float* w, bool f16, std::vector<uint16_t>& wpk) {
 // obs: planar bytes [B][3][H][W]; wpk as stem_pool_pack lays it out; bias: 16 floats;
 // out: fp16 [B][(H-1)/2+1][(W-1)/2+1][16].
 hipError_t launch_stem_pool(const uint8_t* obs, const uint16_t* wpk, const float* bias, void* out, int B,
-                            int H, int W, float obs_sub, float obs_mul, hipStream_t st) {
+                            int H, int W, float obs_sub, float obs_mul, ExchangePrep& prep, hipStream_t st) {
   if ((long long)B * H * W == 0) return hipSuccess;
   if (!stem_pool_supported(3, 16, H, W)) return hipErrorInvalidValue;
   StemPoolArgs g;
@@ -300,6 +302,8 @@ hipError_t launch_stem_pool(const uint8_t* obs, const uint16_t* wpk, const float
   g.parts = 1;
   while (2 * g.parts * B <= 512 && g.parts < 4 && g.Ho / (2 * g.parts) >= 2 * g.n_seg) g.parts *= 2;
   g.obs_sub = obs_sub; g.obs_mul = obs_mul;
+  prep.done = g.parts > 1;
+  g.prep = prep;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {

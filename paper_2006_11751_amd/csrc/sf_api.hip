@@ -280,6 +280,8 @@ Switches read_switches() {
   sw.no_conv_pool_regs = env_set("SF_NO_CONV_POOL_REGS");
   sw.no_rnn_seq = env_set("SF_NO_RNN_SEQ");
   sw.core_seq_limit = env_int("SF_CORE_SEQ_LIMIT");
+  sw.no_tail = env_set("SF_NO_TAIL");
+  sw.tail_skip = env_int("SF_TAIL_SKIP");
   sw.cus = env_int("SF_CUS");
   sw.act_bf16 = env_set("SF_ACT_BF16");
   sw.stream_f32 = env_set("SF_STREAM_F32");
@@ -302,6 +304,10 @@ void free_policy(Policy* p) {
 using namespace sf;
 
 namespace {
+
+// Types of the FC layer's input (fp32, bf16, fp16) and of the core's features (fp32, bf16, fp32 to be rounded).
+int fc_type(const Policy* p) { return !p->bf16_path ? 0 : p->act_f16 ? 2 : 1; }
+int core_type(const Policy* p) { return p->fc_out_bf16 ? 1 : p->core_round ? 2 : 0; }
 
 // Chooses the kernels, packs the weights and sizes the workspace of `p` for `cfg` under the
 // switches in p->sw.  Shared by create (bld allocates) and by a weight update (bld replays into
@@ -834,6 +840,17 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   for (int i = 0; i < 3; ++i)
     p->act[i] = i < n_act ? (float*)bld.dev_alloc(act_row_bytes * cfg->max_batch)
                           : nullptr;
+  // FC layer, core and heads in one launch: the three on their kernels for few rows, features of a type that
+  // it is instantiated for, and a first launch that can prepare it.
+  const int types = 4 * fc_type(p) + core_type(p);
+  const bool prepared = cfg->encoder == SF_ENCODER_RESNET ? p->convs[0].impl == STEM_POOL
+                                                          : p->conv12_split || p->ops[0].mid_buf >= 0;
+  if (prepared && !sw.no_tail && p->dense_fc && p->dense_core && !p->core_tile && p->head_split_w && p->n_meas == 0 &&
+      (bld.bf16 ? types == 4 * 1 + 1 || types == 4 * 2 + 2 : types == 0)) {
+    const int rows = tail_max_rows(cfg->fc_dim, cfg->rnn_dim);
+    p->tail_rows = rows < cfg->max_batch ? rows : cfg->max_batch;
+    p->tail_area = bld.dev_alloc(tail_bytes(p->tail_rows, cfg->fc_dim, p->state_dim));
+  }
   p->trash = (float*)bld.dev_alloc(256);
   p->seq_words = (unsigned*)bld.dev_alloc(sizeof(unsigned) * (1 + 2 * (size_t)cfg->max_batch));
   p->fc_out = (float*)bld.dev_alloc(sizeof(float) * (size_t)cfg->fc_dim * cfg->max_batch);
@@ -1078,7 +1095,7 @@ extern "C" int sf_policy_update_weights(sf_policy* handle, const sf_policy_weigh
                    scratch.core_tile == p->core_tile && scratch.core_round == p->core_round &&
                    scratch.rnn_split_w == p->rnn_split_w && scratch.fc_split_w == p->fc_split_w &&
                    scratch.head_split_w == p->head_split_w &&
-                   scratch.dense_fc == p->dense_fc && scratch.dense_core == p->dense_core &&
+                   scratch.tail_rows == p->tail_rows && scratch.dense_fc == p->dense_fc && scratch.dense_core == p->dense_core &&
                    (scratch.rnn_wih_bf != nullptr) == (p->rnn_wih_bf != nullptr);
   for (size_t i = 0; same_plan && i < p->convs.size(); ++i) {
     const ConvLayer &a = scratch.convs[i], &b = p->convs[i];
@@ -1245,6 +1262,10 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
   auto buf = [&](int i) -> float* { return i < 0 ? nullptr : p->act[i]; };
   const bool timing = p->timing && parts == PART_ALL;
   const bool conv12 = fuses_conv12(p);
+  // few rows: FC layer, core and heads in one launch, whose exchange buffers the first launch prepares
+  ExchangePrep prep{};
+  if (parts == PART_ALL && !timing && B <= p->tail_rows)
+    prep = tail_prep(p->tail_area, B, c.fc_dim, p->state_dim, p->fc_out_bf16);
   // the measurement layers, where they are one launch, in the FC layer's (timed: a launch of their own)
   const bool meas_in_fc = !timing && p->n_meas && p->dense_fc && p->meas_fused && dense_fc_takes_meas(c.meas_dim, c.meas_hidden[0]);
   auto meas_args = [&] {
@@ -1275,7 +1296,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
               // planes, 16-byte aligned frames), else the two kernels in sequence (same bits)
               const ConvLayer& L2 = p->convs[op.conv + 1];
               if (L.planes == 2 && !misaligned(obs, 16)) {
-                SF_LAUNCH(launch_conv12_fused_bf16(L, L2, B, obs, buf(op.out_buf), st));
+                SF_LAUNCH(launch_conv12_fused_bf16(L, L2, B, obs, buf(op.out_buf), prep, st));
               } else {
                 SF_LAUNCH(launch_conv1_i8(L, B, obs, L.ipk, L.spk, L.bpk8, buf(op.mid_buf), 1, L.planes,
                                           p->conv1_waves, p->conv1_image, st));
@@ -1286,7 +1307,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
               break;
             }
             if (conv12) {
-              SF_LAUNCH(launch_conv12_split(L, p->convs[1], B, obs, buf(op.out_buf), buf(p->ops[1].out_buf), st));
+              SF_LAUNCH(launch_conv12_split(L, p->convs[1], B, obs, buf(op.out_buf), buf(p->ops[1].out_buf), prep, st));
               break;
             }
             SF_LAUNCH(launch_conv1_i8(L, B, obs, L.ipk, L.spk, L.bpk8, buf(op.out_buf), p->bf16_path,
@@ -1329,7 +1350,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
             SF_LAUNCH(launch_conv_pool_regs(in, L.wbf, L.bbf, buf(op.out_buf), B, L.H, L.W, L.cin, st));
             break;
           case STEM_POOL:
-            SF_LAUNCH(launch_stem_pool(obs, L.wsp, L.bbf, buf(op.out_buf), B, L.H, L.W, c.obs_sub, c.obs_mul, st));
+            SF_LAUNCH(launch_stem_pool(obs, L.wsp, L.bbf, buf(op.out_buf), B, L.H, L.W, c.obs_sub, c.obs_mul, prep, st));
             break;
           case RES_STAGE: {
             const uint16_t* wpk[SF_MAX_CONV_TENSORS];
@@ -1370,9 +1391,22 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
           SF_LAUNCH(launch_maxpool3x3s2p1(B, op.C, op.H, op.W, buf(op.in_buf), buf(op.out_buf), st));
         break;
       case OP_FC:
+        if (prep.claims && prep.done) {
+          TailCall t{};
+          t.B = B; t.flat = p->flat; t.fc = c.fc_dim; t.lstm = c.rnn_type == SF_RNN_LSTM; t.H = c.rnn_dim;
+          t.n_heads = c.n_heads; t.sumA = p->sumA; t.n_env = n_env;
+          t.x = buf(op.in_buf); t.fc_type = fc_type(p); t.x_type = core_type(p);
+          t.fc_w = p->fc_split_w; t.fc_b = p->fc_b; t.cell_w = p->rnn_split_w; t.b_ih = p->gru_bih; t.b_hh = p->gru_bhh;
+          t.head_split_w = p->head_split_w; t.head_w = p->head_w; t.head_b = p->head_b; t.head_off = p->head_off;
+          t.h_in = h_in; t.done = done; t.ids = ids; t.h_out = h_out; t.h_table = h_table;
+          t.seed = seed; t.step = step; t.actions = actions; t.logp = logp; t.value = value; t.logits = logits_opt;
+          t.area = p->tail_area; t.skip = p->sw.tail_skip;
+          SF_LAUNCH(launch_tail(t, st));
+          return SF_OK;
+        }
         if (p->dense_fc) {
           const MeasArgs m = meas_args();
-          SF_LAUNCH(launch_dense_fc(buf(op.in_buf), !p->bf16_path ? 0 : p->act_f16 ? 2 : 1, p->fc_split_w, p->fc_b,
+          SF_LAUNCH(launch_dense_fc(buf(op.in_buf), fc_type(p), p->fc_split_w, p->fc_b,
                                     p->fc_out, p->fc_out_bf16, B, p->flat, c.fc_dim, meas_in_fc ? &m : nullptr, st));
         } else if (p->fc_wbf && p->fc16)
           SF_LAUNCH(launch_fc16(buf(op.in_buf), p->fc_wbf, p->fc_bbf, p->fc_out, B, p->flat, c.fc_dim, p->act_f16,
@@ -1408,7 +1442,7 @@ int run_step(Policy* p, int32_t B, const uint8_t* obs, const float* meas, const 
         // (PART_CORE alone: one time step of the pass over trajectories, few rows; the step's own
         // kernel there too if the switch asks for it)
         const bool few = parts == PART_CORE && !p->sw.no_rnn_seq;
-        const int x_type = p->fc_out_bf16 ? 1 : p->core_round && !few ? 2 : 0;
+        const int x_type = few && !p->fc_out_bf16 ? 0 : core_type(p);
         if (p->dense_core || (few && p->rnn_split_w))
           SF_LAUNCH(launch_dense_cell(lstm, B, c.fc_dim, p->meas_out_dim, c.rnn_dim, x1, x_type, x2, h_in, done,
                                       p->rnn_split_w, c.dtype == SF_DTYPE_BF16 ? 1 : 3, p->gru_bih, p->gru_bhh, h_out,

@@ -6,6 +6,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "sf_exchange.h"
 #include "sf_meas.h"
 
 namespace sf {
@@ -79,9 +80,9 @@ struct DenseArgs {
 // fp32 arithmetic: the products of such a number with the terms of a weight do not add up to its
 // product with the weight, and neither do those of terms whose largest product overflows.  q: gate
 // (FC: 0), n: unit (FC: output); the n gate of a GRU has its sums over the features (n_x) and the
-// state (n_h) apart.
-template <int KIND, int XT, int PB>
-__device__ inline float plain_sum(const DenseArgs& g, int m, int sm, bool reset, int q, int n, int k_from, int k_to) {
+// state (n_h) apart.  EX: the features are another workgroup's of the same launch (sf_exchange.h).
+template <int KIND, int XT, int PB, bool EX = false>
+__device__ inline __attribute__((always_inline)) float plain_sum(const DenseArgs& g, int m, int sm, bool reset, int q, int n, int k_from, int k_to) {
   constexpr int GB = group_bytes(KIND);
   constexpr int C = KIND == FC ? 16 : 8;
   float sum = 0.0f;
@@ -89,7 +90,11 @@ __device__ inline float plain_sum(const DenseArgs& g, int m, int sm, bool reset,
     const int s = k >> 5, lg = (k >> 3) & 3, e = k & 7;
     float x;
     if (s < g.k1) {
-      if (in_f32(XT))
+      if (EX && in_f32(XT))
+        x = load_float((const float*)g.x1 + (size_t)m * g.I1 + k);
+      else if (EX)
+        x = __builtin_bit_cast(float, load_word((const unsigned*)g.x1 + ((size_t)m * g.I1 + k) / 2) << (k & 1 ? 0 : 16) & 0xFFFF0000u);
+      else if (in_f32(XT))
         x = ((const float*)g.x1)[(size_t)m * g.I1 + k];
       else if (XT == X_BF16)
         x = __builtin_bit_cast(float, (unsigned)((const uint16_t*)g.x1)[(size_t)m * g.I1 + k] << 16);
@@ -118,16 +123,16 @@ __device__ inline float plain_sum(const DenseArgs& g, int m, int sm, bool reset,
   }
   return sum;
 }
-template <int KIND, int XT, int PB>
-__device__ inline void plain_sums(const DenseArgs& g, int m, bool reset, int n, float (&sum)[4]) {
+template <int KIND, int XT, int PB, bool EX = false>
+__device__ inline __attribute__((always_inline)) void plain_sums(const DenseArgs& g, int m, bool reset, int n, float (&sum)[4]) {
   const int sm = g.ids && !reset ? g.ids[m] : m;  // (a reset row's state is not read)
   if (KIND == FC) {
-    sum[0] = plain_sum<KIND, XT, PB>(g, m, sm, reset, 0, n, 0, g.kn);
+    sum[0] = plain_sum<KIND, XT, PB, EX>(g, m, sm, reset, 0, n, 0, g.kn);
   } else {
-    for (int q = 0; q < (KIND == LSTM ? 4 : 2); ++q) sum[q] = plain_sum<KIND, XT, PB>(g, m, sm, reset, q, n, 0, g.kn);
+    for (int q = 0; q < (KIND == LSTM ? 4 : 2); ++q) sum[q] = plain_sum<KIND, XT, PB, EX>(g, m, sm, reset, q, n, 0, g.kn);
     if (KIND == GRU) {
-      sum[2] = plain_sum<KIND, XT, PB>(g, m, sm, reset, 2, n, 0, g.k2);
-      sum[3] = plain_sum<KIND, XT, PB>(g, m, sm, reset, 2, n, g.k2, g.kn);
+      sum[2] = plain_sum<KIND, XT, PB, EX>(g, m, sm, reset, 2, n, 0, g.k2);
+      sum[3] = plain_sum<KIND, XT, PB, EX>(g, m, sm, reset, 2, n, g.k2, g.kn);
     }
   }
 }

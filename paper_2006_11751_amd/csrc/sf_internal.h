@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "sf_exchange.h"
 #include "sf_meas.h"
 #include "sf_policy.h"
 
@@ -81,6 +82,8 @@ struct Switches {
   int cus = 0;                     // SF_CUS: compute units that core_seq_supported counts on (0 = the device's)
   bool act_bf16 = false;         // SF_ACT_BF16
   bool stream_f32 = false;       // SF_STREAM_F32
+  bool no_tail = false;          // SF_NO_TAIL
+  int tail_skip = 0;             // SF_TAIL_SKIP: workgroups of that launch that leave at once
 };
 
 // One kernel launch of the step, fixed at create time.
@@ -126,6 +129,8 @@ struct Policy {
   uint16_t* fc_split_w = nullptr;   // dev: FC matrix packed for k_dense_split.hip, or null
   bool dense_fc = false, dense_core = false;  // the step's FC layer / core run on k_dense_split.hip
   bool fc16 = false;  // fc_wbf on k_fc16.hip
+  int tail_rows = 0;                // up to so many rows: FC layer, core and heads in one launch (k_tail.hip)
+  void* tail_area = nullptr;        // dev: its claims and exchange buffers
   bool core_tile = false;           // ... the core on its kernel for many rows
   bool core_round = false;          // the step's core takes its features as bf16 numbers
   double conv1_ratio2 = 0, conv1_ratio3 = 0;  // admission test of the first convolution's digit planes
@@ -262,7 +267,7 @@ uint16_t conv_weight_bits(float v, bool f16);
 bool stem_pool_supported(int cin, int cout, int H, int W);
 void stem_pool_pack(const float* w, bool f16, std::vector<uint16_t>& wpk);
 hipError_t launch_stem_pool(const uint8_t* obs, const uint16_t* wpk, const float* bias, void* out, int B,
-                            int H, int W, float obs_sub, float obs_mul, hipStream_t st);
+                            int H, int W, float obs_sub, float obs_mul, ExchangePrep& prep, hipStream_t st);
 bool conv_pool_regs_supported(int cin, int cout, int H, int W);
 hipError_t launch_conv_pool_regs(const void* in, const uint16_t* wpk, const float* bias32, void* out, int B,
                                  int H, int W, int cin, hipStream_t st);
@@ -288,6 +293,32 @@ hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const f
 hipError_t launch_dense_cell(int lstm, int B, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
                              const float* h_in, const uint8_t* done, const uint16_t* w, int terms, const float* b_ih,
                              const float* b_hh, float* h_out, const int32_t* ids, int n_env, int tile, hipStream_t st);
+// FC layer, cell and heads on few rows in one launch (k_tail.hip)
+struct TailCall {
+  int B, flat, fc, lstm, H, n_heads, sumA, n_env;
+  const void* x;          // [B][flat]
+  int fc_type, x_type;    // as for launch_dense_fc, launch_dense_cell
+  const uint16_t* fc_w;   // the weights of the three as they take them
+  const float* fc_b;
+  const uint16_t* cell_w;
+  const float *b_ih, *b_hh;
+  const uint16_t* head_split_w;
+  const float *head_w, *head_b;
+  const int32_t* head_off;
+  const float* h_in;
+  const uint8_t* done;
+  const int32_t* ids;     // with a table: rows ids[b] of h_in = h_table
+  float *h_out, *h_table;
+  uint64_t seed, step;
+  int32_t* actions;
+  float *logp, *value, *logits;
+  void* area;             // tail_bytes, prepared by an earlier launch
+  int skip;
+};
+int tail_max_rows(int fc, int H);
+size_t tail_bytes(int rows, int fc, int S);
+ExchangePrep tail_prep(void* area, int B, int fc, int S, int out_bf16);
+hipError_t launch_tail(const TailCall& t, hipStream_t st);
 // the core over all steps of N trajectories in one launch (k_core_seq.hip); words: 1 + 2 N
 bool core_seq_supported(int T, int N, int I1, int I2, int H, int x_type, int cus);
 hipError_t launch_core_seq(int lstm, int T, int N, int I1, int I2, int H, const void* x1, int x_type, const float* x2,
@@ -308,7 +339,7 @@ hipError_t launch_conv_image_bf16(const void* in, const uint16_t* wpk, const flo
                                   int Wo, int N, int relu, hipStream_t st);
 bool conv12_fused_bf16_supported(int cin, int H, int W, const sf_conv& c1, const sf_conv& c2);
 hipError_t launch_conv12_fused_bf16(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs,
-                                    void* out, hipStream_t st);
+                                    void* out, ExchangePrep& prep, hipStream_t st);
 // fp32 convolution on operands split into two fp16 terms (k_conv_image_split.hip)
 bool conv_image_split_supported(int Cin, int ksize, int stride, int pad, int H, int W, int N);
 void conv_activation_range(const float* w, const float* bias, int cout, int cin, int k, std::vector<double>& bound,
@@ -321,7 +352,7 @@ hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const f
 // the first two convolutions of an fp32 plain stack in one launch (k_conv12_split.hip)
 bool conv12_split_supported(int cin, int H, int W, const sf_conv& c1, const sf_conv& c2);
 hipError_t launch_conv12_split(const ConvLayer& L1, const ConvLayer& L2, int B, const uint8_t* obs, float* mid, float* out,
-                               hipStream_t st);
+                               ExchangePrep& prep, hipStream_t st);
 bool gemm_mfma_supported(int Cin, int ksize, int pad, int N);
 int gemm_mfma_pick_tile(long long M, int N, int K, int seg_len);
 hipError_t launch_gemm_mfma(const float* A, const float* Wt, const float* bias, float* out, int B,

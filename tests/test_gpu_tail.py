@@ -1,0 +1,99 @@
+"""FC layer, core and heads of few rows in one launch (k_tail.hip): the bits of the three launches, at the edges of
+the row tiles and on both sides of the limit, plain and with a state table, for both cells and every type of
+features, with states that have no bf16 terms, and with workgroups that never start."""
+import numpy as np
+import pytest
+
+from paper_2006_11751_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+_STD = dict(obs=(3, 72, 128), encoder="conv", convs=[(32, 8, 4, 0), (64, 4, 2, 0), (128, 3, 2, 0)], fc=512, rnn=512,
+            dtype="fp32", rnn_type="gru", heads=[7], p_done=0.2, steps=1, obs_sub=0.0, obs_mul=wl.OBS_MUL, meas_dim=0,
+            meas_hidden=[], index=5, name="tail")
+_RES = dict(_STD, encoder="resnet", stages=[16, 32, 32], blocks_per_stage=2, fc=256, rnn=256, dtype="bf16", heads=[15])
+NETS = {
+    "gru": (_STD, 64), "lstm": (dict(_STD, rnn_type="lstm"), 64), "bf16": (dict(_STD, dtype="bf16"), 64),
+    "bf16-lstm": (dict(_STD, dtype="bf16", rnn_type="lstm", rnn=256, heads=[3, 3, 2, 2, 2, 8, 21]), 128),
+    "resnet": (_RES, 128), "resnet-lstm": (dict(_RES, rnn_type="lstm", heads=[30, 33]), 128),
+    "heads": (dict(_STD, heads=[3, 3, 2, 2, 2, 8, 21]), 64), "narrow": (dict(_STD, fc=32, rnn=32, heads=[17, 5]), 1200),
+    "wide": (dict(_STD, fc=480, rnn=1024), 32),
+}
+
+
+def _policy(monkeypatch, net, max_batch, w, **env):
+    for k, v in env.items():
+        monkeypatch.setenv(k, str(v))
+    pol = binding.Policy(net, w, max_batch=max_batch)
+    for k in env:
+        monkeypatch.delenv(k)
+    return pol
+
+
+def _inputs(torch, net, B, odd=False):
+    x = dict(obs=wl.observations(net, 0, B), h=wl.initial_state(net, B), done=wl.done_mask(net, 0, B))
+    if odd and B > 12:
+        x["h"][3, 5], x["h"][7, 0], x["h"][11, 31] = np.inf, np.nan, 3.39e38
+        x["h"][9].view(np.uint32)[2] = 0xFFFFFFFF
+    return {k: torch.from_numpy(v).cuda() for k, v in x.items()}
+
+
+def _step(torch, pol, x, B):
+    out = pol.step(x["obs"][:B], x["h"][:B], x["done"][:B], 7, 11)
+    torch.cuda.synchronize()
+    return {k: v.cpu().numpy() for k, v in out.items()}
+
+
+def _indexed(torch, pol, x, B, ids, n_env):
+    table = torch.full((n_env, pol.H), 3.0, device="cuda")
+    ok = (ids >= 0) & (ids < n_env)
+    table[ids[ok].long()] = x["h"][:B][ok]
+    out = pol.step_indexed(x["obs"][:B], table, ids, x["done"][:B], 7, 11)
+    torch.cuda.synchronize()
+    return dict({k: v.cpu().numpy() for k, v in out.items()}, table=table.cpu().numpy())
+
+
+def _same(a, b, what):
+    for k in a:
+        assert np.array_equal(a[k], b[k], equal_nan=a[k].dtype.kind == "f"), (what, k)
+
+
+@pytest.mark.parametrize("name", NETS)
+def test_bits_of_the_three_launches(torch_cuda, monkeypatch, name):
+    torch = torch_cuda
+    net, limit = NETS[name]
+    B = min(limit, 150) + 2
+    w = wl.weights(net)
+    one, three = _policy(monkeypatch, net, B, w), _policy(monkeypatch, net, B, w, SF_NO_TAIL=1)
+    x = _inputs(torch, net, B)
+    odd = _inputs(torch, net, B, odd=True)
+    for n in sorted({1, 2, 15, 16, 17, 31, 33, min(limit, B) - 1, min(limit, B), B}):
+        if n <= B:
+            print(name, n, flush=True)
+            _same(_step(torch, one, x, n), _step(torch, three, x, n), n)
+    _same(_step(torch, one, odd, B - 2), _step(torch, three, odd, B - 2), "states without terms")
+    ids = torch.from_numpy(np.random.default_rng(3).permutation(2 * B)[:B].astype(np.int32)).cuda()
+    ids[0], ids[B - 3] = -1, 2 * B
+    for n in (1, 17, B - 2):
+        _same(_indexed(torch, one, x, n, ids[:n], 2 * B), _indexed(torch, three, x, n, ids[:n], 2 * B), ("table", n))
+    one.close()
+    three.close()
+
+
+@pytest.mark.parametrize("name,B", [("gru", 33), ("bf16", 60), ("resnet-lstm", 100)])
+def test_workgroups_that_never_start(torch_cuda, monkeypatch, name, B):
+    """The others take over the roles of the first workgroups, down to one that computes everything."""
+    torch = torch_cuda
+    net, _ = NETS[name]
+    w = wl.weights(net)
+    x = _inputs(torch, net, B)
+    pol = _policy(monkeypatch, net, B, w)
+    want = _step(torch, pol, x, B)
+    pol.close()
+    tiles, fc, cell = (B + 15) // 16, net["fc"] // 16, net["rnn"] // 8
+    for skip in (1, tiles * fc - 1, tiles * fc + 3, tiles * (fc + cell) - 1):
+        print(name, "without the first", skip, flush=True)
+        pol = _policy(monkeypatch, net, B, w, SF_TAIL_SKIP=skip)
+        for _ in range(2):
+            _same(_step(torch, pol, x, B), want, skip)
+        pol.close()
