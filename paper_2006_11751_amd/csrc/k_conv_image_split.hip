@@ -26,7 +26,8 @@
 // walks rounds of FR frames: the image goes through registers, where it is scaled and split, into
 // LDS, and after one barrier each wave computes 16 output channels of all pixels, its filter bank
 // (both terms: 128 or 144 registers) resident.  Two workgroups share a CU, one loading while the
-// other computes.  Launch times at B = 1024: see launch_conv_image_split.
+// other computes; or one of eight waves and two images does both at once (AHEAD).  Launch times: see
+// launch_conv_image_split.
 //
 // v_mfma_f32_16x16x32_f16: lane l supplies A[i = l%16][k = 8*(l/16) + e] and B[k][j = l%16], e =
 // 0..7 (16 bytes each); D[i][j] sits in lane j + 16*(i/4), register i%4.  A = weights (i = output
@@ -75,8 +76,11 @@ int reciprocal(int d) { return (65536 + d - 1) / d; }
 
 // FR frames per round; their FR*Ho*Wo <= 16*MT output pixels form one row-major sequence of MT
 // 16-pixel tiles, computed MP at a time.  NW: waves, 16 output channels each; NV: 16-byte pieces of a
-// round's input per thread.
-template <int CIN, int KS, int FR, int MT, int MP, int NW, int NV>
+// round's input per thread.  AHEAD: a CU's only workgroup, with two images in LDS: the pieces of the next round are
+// fetched, scaled, split and stored between a round's products (four at a time: with more the registers of the
+// filter bank spill, and a reload waits for the pieces).  A round takes 4.2 us, bound by the products and, over the
+// chip, by the frames' 25 KB each.
+template <int CIN, int KS, int FR, int MT, int MP, int NW, int NV, bool AHEAD>
 __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs g) {
   constexpr int kNT = 64 * NW;
   constexpr int STRIDE = 2;
@@ -87,6 +91,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
   constexpr int G = KS * KS * HALVES;
   extern __shared__ __attribute__((aligned(16))) u32x4 img[];  // [FR][frame_stride] pieces
 
+  static_assert(!AHEAD || (MT == MP && NV <= 8 && G >= 14), "one pass over the taps, with room for the pieces");
   static_assert(FR <= 2 && kNT % C4 == 0, "a thread's pieces: two frames at most, the same channels throughout");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lp = lane & 15, lg = lane >> 4;
@@ -97,13 +102,19 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
   const int frame_stride = g.H * row_stride + g.frame_pad;
 
   u32x4 wf[G][2];
+  auto load_bank = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int t = 0; t < G; ++t)
+    for (int t = 0; t < G; ++t)
 #pragma unroll
-    for (int q = 0; q < 2; ++q) wf[t][q] = g.wpk[((size_t)(n0 / 16) * G + t) * 128 + q * 64 + lane];
+      for (int q = 0; q < 2; ++q) wf[t][q] = g.wpk[((size_t)(n0 / 16) * G + t) * 128 + q * 64 + lane];
+  };
+  if constexpr (!AHEAD) load_bank();
   const f32x4 scale = *(const f32x4*)(g.scale + (tid % C4) * 4);  // (a thread's pieces: the same channels)
-  const f32x4 inv = *(const f32x4*)(g.scale + CIN + n0 + 4 * lg);
-  const f32x4 bias = *(const f32x4*)(g.bias + n0 + 4 * lg);
+  f32x4 inv, bias;
+  if constexpr (!AHEAD) {
+    inv = *(const f32x4*)(g.scale + CIN + n0 + 4 * lg);
+    bias = *(const f32x4*)(g.bias + n0 + 4 * lg);
+  }
   const float refused = g.scale[CIN + g.N];
   const int wave_n0 = __builtin_amdgcn_readfirstlane(n0);  // (kept in a scalar register for the fallback)
 
@@ -121,40 +132,67 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
   for (int m = 0; m < MT; ++m) abase[m] = origin(m);
 
   const int n_rounds = (g.B + FR - 1) / FR;
-  for (int it = blockIdx.x; it < n_rounds; it += gridDim.x) {
-    const int frames = min(g.B - it * FR, FR);
-    {
-      // a last round with fewer frames re-reads its last piece instead of reading past the batch
-      const uint8_t* src = (const uint8_t*)(g.in + (size_t)it * FR * frame_pieces);
-      const uint32_t last = 16u * (uint32_t)(frames * frame_pieces - 1);
-      // (opaque: computed ahead of the loop the places of all pieces would have to be spilled)
-      int first = tid;
-      asm volatile("" : "+v"(first));
-      f32x4 v[NV];
+  constexpr int NR = AHEAD ? 4 : NV;  // pieces in registers
+  f32x4 v[NR];
+  // piece u of a round
+  auto load = [&](int it, int u) __attribute__((always_inline)) {
+    // a last round with fewer frames re-reads its last piece instead of reading past the batch
+    const uint8_t* src = (const uint8_t*)(g.in + (size_t)it * FR * frame_pieces);
+    const uint32_t last = 16u * (uint32_t)(min(g.B - it * FR, FR) * frame_pieces - 1);
+    // (opaque: computed ahead of the loop the places of all pieces would have to be spilled)
+    int first = tid;
+    asm volatile("" : "+v"(first));
+    v[u % NR] = *(const f32x4*)(src + min(16u * (uint32_t)(first + kNT * u), last));
+  };
+  auto put = [&](int u, u32x4* image) __attribute__((always_inline)) {
+    int first = tid;
+    asm volatile("" : "+v"(first));
+    const int f = first + kNT * u;
+    const bool second = FR == 2 && f >= frame_pieces;
+    const int pix = (f - (second ? frame_pieces : 0)) / C4;
+    int at = (second ? frame_stride : 0) + pix * P4 + (pix * g.rcp_w >> 16) * g.row_pad;
+    at = min(at, FR * frame_stride);  // (past the end: a pixel behind the images, for no use)
+    u32x2 t0, t1;
 #pragma unroll
-      for (int u = 0; u < NV; ++u) v[u] = *(const f32x4*)(src + min(16u * (uint32_t)(first + kNT * u), last));
+    for (int p = 0; p < 2; ++p) {
+      const f32x2 s = {v[u % NR][2 * p] * scale[2 * p], v[u % NR][2 * p + 1] * scale[2 * p + 1]};
+      const f16x2 h = __builtin_convertvector(s, f16x2);
+      const f32x2 rest = {fmaf((float)h[0], -1.0f, s[0]), fmaf((float)h[1], -1.0f, s[1])};
+      t0[p] = __builtin_bit_cast(unsigned, h);
+      t1[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(rest, f16x2));
+    }
+    u32x2* dst = (u32x2*)(image + at) + tid % C4;
+    dst[0] = t0;
+    dst[2 * C8] = t1;
+  };
+  if constexpr (AHEAD)
 #pragma unroll
-      for (int u = 0; u < NV; ++u) {
-        const int f = first + kNT * u;
-        const bool second = FR == 2 && f >= frame_pieces;
-        const int pix = (f - (second ? frame_pieces : 0)) / C4;
-        int at = (second ? frame_stride : 0) + pix * P4 + (pix * g.rcp_w >> 16) * g.row_pad;
-        at = min(at, FR * frame_stride);  // (past the end: a pixel behind the images, for no use)
-        u32x2 t0, t1;
+    for (int u = 0; u < NR; ++u) load(blockIdx.x, u);
+  if constexpr (AHEAD) load_bank();
+  const int image_stride = FR * frame_stride + P4;
+  f32x4* const affine = (f32x4*)(img + 2 * image_stride);  // AHEAD: [2][N / 4] inverse scales, biases
+  if constexpr (AHEAD) {
+    if (tid < g.N / 2) affine[tid] = ((const f32x4*)(tid < g.N / 4 ? g.scale + CIN : g.bias))[tid % (g.N / 4)];
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          const f32x2 s = {v[u][2 * p] * scale[2 * p], v[u][2 * p + 1] * scale[2 * p + 1]};
-          const f16x2 h = __builtin_convertvector(s, f16x2);
-          const f32x2 rest = {fmaf((float)h[0], -1.0f, s[0]), fmaf((float)h[1], -1.0f, s[1])};
-          t0[p] = __builtin_bit_cast(unsigned, h);
-          t1[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(rest, f16x2));
-        }
-        u32x2* dst = (u32x2*)(img + at) + tid % C4;
-        dst[0] = t0;
-        dst[2 * C8] = t1;
-      }
+    for (int u = 0; u < NV; ++u) {
+      put(u, img);
+      if (u + NR < NV) load(blockIdx.x, u + NR);
     }
     __syncthreads();
+  }
+  int odd_round = 0;
+  for (int it = blockIdx.x; it < n_rounds; it += gridDim.x) {
+    const int frames = min(g.B - it * FR, FR), next_it = it + (int)gridDim.x;
+    const u32x4* const image = img + (AHEAD && odd_round ? image_stride : 0);
+    u32x4* const other = img + (AHEAD && odd_round ? 0 : image_stride);
+    odd_round ^= 1;
+    if constexpr (!AHEAD) {
+#pragma unroll
+      for (int u = 0; u < NV; ++u) load(it, u);
+#pragma unroll
+      for (int u = 0; u < NV; ++u) put(u, img);
+      __syncthreads();
+    }
     asm volatile("" ::"s"(refused));  // (requested with the scales, here long since)
 
     float* dst = g.out + (size_t)it * FR * npix * g.N + n0 + 4 * lg;
@@ -163,7 +201,8 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
       const int tp = t / HALVES, half = t % HALVES;
       return (tp / KS) * row_stride + (tp % KS) * P4 + 4 * half;
     };
-    auto tiles = [&](auto m0c, auto mnc) __attribute__((always_inline)) {
+    auto tiles = [&](auto m0c, auto mnc, auto morec) __attribute__((always_inline)) {
+      constexpr bool MORE = decltype(morec)::value;
       constexpr int M0 = decltype(m0c)::value, MN = decltype(mnc)::value;
       // (the small products in an accumulator of their own: added to the large ones they would have
       // them rounded three times as often)
@@ -172,27 +211,64 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
 #pragma unroll
       for (int m = 0; m < MN; ++m) {
         acc[m] = low[m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        x0[m] = img[abase[M0 + m] + tap(0)];
-        x1[m] = img[abase[M0 + m] + tap(0) + C8];
+        x0[m] = image[abase[M0 + m] + tap(0)];
+        x1[m] = image[abase[M0 + m] + tap(0) + C8];
       }
+      if constexpr (MORE)
+#pragma unroll
+        for (int u = 0; u < NR; ++u) load(next_it, u);
 #pragma unroll
       for (int t = 0; t < G; ++t) {
         const int next = tap(t + 1 < G ? t + 1 : t);
+        auto mfma = [&](const u32x4& w, const u32x4& x, f32x4& c) __attribute__((always_inline)) {
+          c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
+        };
+        if constexpr (AHEAD) {
+          // a term of the next tap is requested behind its last use (left alone, the scheduler sinks each
+          // read to its use)
 #pragma unroll
-        for (int m = 0; m < MN; ++m) {
-          auto mfma = [&](const u32x4& w, const u32x4& x, f32x4& c) __attribute__((always_inline)) {
-            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
-          };
-          mfma(wf[t][1], x0[m], low[m]);
-          mfma(wf[t][0], x0[m], acc[m]);
-          mfma(wf[t][0], x1[m], low[m]);
-          // the operands of the next tap, MN tiles ahead of their use
-          if (t + 1 < G) {
-            x0[m] = img[abase[M0 + m] + next];
-            x1[m] = img[abase[M0 + m] + next + C8];
+          for (int m = 0; m < MN; ++m) {
+            mfma(wf[t][1], x0[m], low[m]);
+            __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_sched_barrier(0);  // (left alone, the scheduler sinks each read to its use)
+#pragma unroll
+          for (int m = 0; m < MN; ++m) {
+            mfma(wf[t][0], x0[m], acc[m]);
+            if (t + 1 < G) x0[m] = image[abase[M0 + m] + next];
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int m = 0; m < MN; ++m) {
+            mfma(wf[t][0], x1[m], low[m]);
+            if (t + 1 < G) x1[m] = image[abase[M0 + m] + next + C8];
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+#pragma unroll
+          for (int m = 0; m < MN; ++m) {
+            mfma(wf[t][1], x0[m], low[m]);
+            mfma(wf[t][0], x0[m], acc[m]);
+            mfma(wf[t][0], x1[m], low[m]);
+            // the operands of the next tap, MN tiles ahead of their use
+            if (t + 1 < G) {
+              x0[m] = image[abase[M0 + m] + next];
+              x1[m] = image[abase[M0 + m] + next + C8];
+            }
+            __builtin_amdgcn_sched_barrier(0);  // (left alone, the scheduler sinks each read to its use)
+          }
         }
+        if constexpr (MORE) {
+          // the first pieces, asked for ahead of the taps, behind six of them, the others behind the last
+          if (t >= 6 && t < 6 + NR) {
+            put(t - 6, other);
+            if (t - 6 + NR < NV) load(next_it, t - 6 + NR);
+          }
+          if (t >= G - (NV - NR)) put(t - (G - NV), other);
+        }
+      }
+      if constexpr (AHEAD) {
+        inv = affine[(n0 >> 2) + lg];
+        bias = affine[((g.N + n0) >> 2) + lg];
       }
 #pragma unroll
       for (int m = 0; m < MN; ++m) {
@@ -203,8 +279,17 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
         if (FR == 1 || n < live) *(f32x4*)(dst + (size_t)n * g.N) = r;
       }
     };
-    tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, MP>{});
-    if constexpr (MT > MP) tiles(std::integral_constant<int, MP>{}, std::integral_constant<int, MT - MP>{});
+    using All = std::integral_constant<int, MP>;
+    using Zero = std::integral_constant<int, 0>;
+    if constexpr (AHEAD) {
+      if (next_it < n_rounds)
+        tiles(Zero{}, All{}, std::true_type{});
+      else
+        tiles(Zero{}, All{}, std::false_type{});
+    } else {
+      tiles(Zero{}, All{}, std::false_type{});
+      if constexpr (MT > MP) tiles(All{}, std::integral_constant<int, MT - MP>{}, std::false_type{});
+    }
     __syncthreads();  // every wave is done with this round's images
   }
   // The host launches this kernel while the split is admitted; a graph recorded then may run it after
@@ -266,7 +351,7 @@ int variant(int Cin, int ksize, int stride, int pad, int H, int W, int N) {
   return 0;
 }
 
-template <int CIN, int KS, int FR, int MT, int MP, int NW, int NV>
+template <int CIN, int KS, int FR, int MT, int MP, int NW, int NV, bool AHEAD = false>
 hipError_t launch_t(SplitArgs g, hipStream_t st) {
   const Layout L = layout(CIN, FR, g.H, g.W, g.Ho, g.Wo);
   g.row_pad = L.row_pad;
@@ -274,18 +359,26 @@ hipError_t launch_t(SplitArgs g, hipStream_t st) {
   g.rcp_w = reciprocal(g.W);
   g.rcp_wo = reciprocal(g.Wo);
   g.rcp_npix = reciprocal(g.Ho * g.Wo);
-  auto kern = conv_image_split_kernel<CIN, KS, FR, MT, MP, NW, NV>;
+  auto kern = conv_image_split_kernel<CIN, KS, FR, MT, MP, NW, NV, AHEAD>;
   static std::once_flag once;
   static hipError_t attr_status = hipSuccess;
   std::call_once(once, [&] {
-    attr_status = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+    attr_status = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)(AHEAD ? 2 * kMaxLds : kMaxLds));
   });
   if (attr_status != hipSuccess) return attr_status;
   const int n_rounds = (g.B + FR - 1) / FR, ny = g.N / (16 * NW);
   // eight waves per CU, each workgroup walking its share of the rounds
   const int per_chip = 2048 / NW, slots = ny >= per_chip ? 1 : per_chip / ny;
-  kern<<<dim3((unsigned)(n_rounds < slots ? n_rounds : slots), (unsigned)ny), 64 * NW, L.lds_bytes, st>>>(g);
+  const size_t lds = AHEAD ? 2 * L.lds_bytes + 8 * (size_t)g.N : L.lds_bytes;
+  kern<<<dim3((unsigned)(n_rounds < slots ? n_rounds : slots), (unsigned)ny), 64 * NW, lds, st>>>(g);
   return hipGetLastError();
+}
+
+// Two images and the affine table in LDS, a vector of the table per thread.
+bool ahead_fits(const SplitArgs& g) {
+  return g.N % 128 == 0 && g.N <= 1024 &&
+         2 * layout(64, 2, g.H, g.W, g.Ho, g.Wo).lds_bytes + 8 * (size_t)g.N <= 2 * kMaxLds;
 }
 
 // the power of two that takes v into [2^14, 2^15)
@@ -490,6 +583,13 @@ hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const f
       // few frames: one per round and two waves, so that a CU has half of the filter bank to fetch (16 rows
       // 5.6 -> 4.0 us; beyond 256 workgroups no faster: whole steps at 128 / 256 rows 38.2, 37.6 / 45.4, 46.9)
       if ((long long)B * (N / 32) <= 256) return launch_t<64, 3, 1, 2, 2, 2, 13>(g, st);
+      // From half the chip in workgroups of eight waves to a second round of few of them: the next round on the way
+      // under this one's products.  Steps of the standard network at 128 output channels, us, without / with:
+      // 258 rows 53.7 / 53.3, 400 rows 57.0 / 56.6, 512 rows 62.0 / 61.1, 514 rows 82.0 / 78.7, 640 rows 83.7 / 82.4,
+      // 768 rows 87.7 / 87.5, 896 rows 93.6 / 95.2, 1500 rows 142 / 147.  (Alone the kernel is the faster one there
+      // too, 2048 rows 25 / 23, but the launches around it are not; below 256 rows it is not, 200 rows 6.0 / 7.6.)
+      if (const long long work = (long long)((B + 1) / 2) * (N / 128); ahead_fits(g) && work > 128 && work <= 320)
+        return launch_t<64, 3, 2, 3, 3, 8, 7, true>(g, st);
       return launch_t<64, 3, 2, 3, 3, 4, 13>(g, st);
     default: return hipErrorInvalidValue;
   }

@@ -207,3 +207,43 @@ def test_error_against_64_bits(torch_cuda, monkeypatch, second, case):
         err.append(np.linalg.norm(g["h_out"] - want) / np.linalg.norm(want))
     print(case, "error: split %.3g, fp32 %.3g" % tuple(err))
     assert err[0] <= 1.1 * err[1] and err[0] < 2e-6, err
+
+
+@pytest.mark.parametrize("rows", [257, 300, 513, 640])
+def test_rounds_under_way_during_products(torch_cuda, ref, rows):
+    """More than 256 frames, up to 640: the third layer's next round is put into LDS during a round's products.  One
+    round per workgroup and several, with a last one of one frame; and a recorded launch whose split an update
+    no longer admits, its workgroups with several rounds too."""
+    torch = torch_cuda
+    net = _net()
+    w = wl.weights(net)
+    pol = binding.Policy(net, w, max_batch=640)
+    g, (o_, s_, d_) = _run(torch, pol, net, rows)
+    few, _ = _run(torch, pol, net, 256)  # a round at a time
+    for k in g:
+        assert np.array_equal(g[k][:256], few[k]), k
+    at = np.r_[0:2, 254:257, rows - 2:rows]
+    o = ref.policy_step(net, w, o_[at], s_[at], d_[at], 7, 11)
+    for k in ("logits", "value", "h_out"):
+        parity.assert_close(k, g[k][at], o[k], 1e-4)
+
+    obs, st, dn = (torch.from_numpy(a).cuda() for a in (o_, s_, d_))
+    out = pol.step(obs, st, dn, 7, 11)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pol.step(obs, st, dn, 7, 11, out=out, stream=torch.cuda.current_stream())
+    after = {k: [a.copy() for a in v] if isinstance(v, list) else v.copy() for k, v in w.items()}
+    after["conv_w"][1] *= np.float32(2.0 ** 110)
+    after["conv_b"][1] *= np.float32(2.0 ** 110)
+    after["conv_w"][2] *= np.float32(2.0 ** -110)
+    pol.update_weights(after)
+    want = ref.policy_step(net, after, o_[at], s_[at], d_[at], 7, 11)
+    for _ in range(2):
+        for v in out.values():
+            v.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in ("logits", "value", "h_out"):
+            parity.assert_close(k, out[k].cpu().numpy()[at], want[k], 1e-4)
+    pol.close()
