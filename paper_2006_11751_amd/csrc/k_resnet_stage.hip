@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     }
   };
   // A operands of a convolution: nine taps x NS channel groups for the 32x32x16 MFMA; five tap
-  // pairs for the 16x16x32 MFMA that runs the 16-channel stages (see conv16 below)
+  // pairs for the 16x16x32 MFMA that runs the 16-channel stages (see walk below)
   constexpr bool M16 = C == 16;
   constexpr int NB = M16 ? 5 : 9;
   u32x4 wA[NB][NS], wB[NB][NS];
@@ -292,169 +292,105 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     }
   };
 
-  // The same for 16 channels on v_mfma_f32_16x16x32_f16 (a 32x32 tile would compute 16 output
-  // rows of zeros): lane l supplies A[i = l%16][k = 8*(l/16) + e] and B[k][j = l%16]; D[i][j] sits
-  // in lane j + 16*(i/4), register i%4.  A tile is 16 neighbouring pixels of a row; K = 32 is two
-  // filter taps x 16 channels, lane group g = l/16 holding tap g%2 of the pair, channels
-  // 8*(g/2)..: with the two taps side by side in a filter row, the 64 lanes' 16-byte reads are
-  // free of bank conflicts (4 cycles measured; 8 with the channel half in the low bit of g, and 8
-  // for two taps of different rows).  Five MFMAs: taps (0,1), (3,4), (6,7), (2,5), (8, none: zero
-  // weights, the lanes re-read tap 8).
-  const int j16 = lane & 15, g16 = lane >> 4;
-  int lane_m[5], lane_o16;
-  {
-    constexpr int pair[5][2] = {{0, 1}, {3, 4}, {6, 7}, {2, 5}, {8, 8}};
-#pragma unroll
-    for (int m = 0; m < 5; ++m) {
-      const int tap = pair[m][g16 & 1], p = tap / 3, q = tap % 3;
-      lane_m[m] = p * ROW + (j16 + q) * PITCH + (((g16 >> 1) * 16) ^ swz(j16 + q));
-    }
-    // channels 4*g .. 4*g+3 of ring pixel (y + 1, x + 1)
-    lane_o16 = ROW + (j16 + 1) * PITCH + ((((g16 >> 1) * 16) ^ swz(j16 + 1)) + (g16 & 1) * 8);
-  }
-  auto conv16 = [&](const u32x4 (&wreg)[NB][NS], int kconv, const unsigned char* src, unsigned char* dst,
-                    bool relu) {
-    const f32x4 init = *(const f32x4*)(bias_lds + 32 * kconv + 4 * g16);
-    const int n16 = npix >> 4;  // (the width is a multiple of 16: no partial tiles)
-    auto tile_off = [&](int t) { return ((t << 4) >> LW) * ROW + ((t << 4) & (W - 1)) * PITCH; };
-    auto run = [&](auto cnt, int t0) {
-      constexpr int N = decltype(cnt)::value;
-      f32x4 acc[N];
-      const unsigned char* base[N];
-#pragma unroll
-      for (int n = 0; n < N; ++n) {
-        acc[n] = init;
-        base[n] = src + tile_off(t0 + n * kNW);
-      }
-      // the pixel fragment of step k + 2 is requested right behind the MFMA of step k
-      u32x4 pf[2][N];
-#pragma unroll
-      for (int n = 0; n < N; ++n)
-#pragma unroll
-        for (int d = 0; d < 2; ++d) pf[d][n] = *(const u32x4*)(base[n] + lane_m[d]);
-#pragma unroll
-      for (int k = 0; k < 5; ++k) {
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-          acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wreg[k][0]),
-                                                          __builtin_bit_cast(f16x8, pf[k & 1][n]), acc[n], 0, 0, 0);
-          if (k + 2 < 5) pf[k & 1][n] = *(const u32x4*)(base[n] + lane_m[k + 2]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-#pragma unroll
-      for (int n = 0; n < N; ++n) {
-        u32x2 ov;
-        ov[0] = pk_f16(acc[n][0], acc[n][1]);
-        ov[1] = pk_f16(acc[n][2], acc[n][3]);
-        if (relu) {
-          ov[0] = pk_max0(ov[0]);
-          ov[1] = pk_max0(ov[1]);
-        }
-        *(u32x2*)(dst + tile_off(t0 + n * kNW) + lane_o16) = ov;
-      }
-    };
-    if constexpr (M16) {
-      int t = wave;
-      // (four tiles in flight, two where the resident filter banks leave no room for more)
-      if constexpr (!(RES && PPT >= 9))
-        for (; t + 3 * kNW < n16; t += 4 * kNW) run(std::integral_constant<int, 4>{}, t);
-      for (; t + kNW < n16; t += 2 * kNW) run(std::integral_constant<int, 2>{}, t);
-      for (; t < n16; t += kNW) run(std::integral_constant<int, 1>{}, t);
-    }
-  };
-  auto conv = [&](const u32x4 (&wreg)[NB][NS], int kconv, const unsigned char* src, unsigned char* dst,
-                  bool relu) {
-    if constexpr (M16) conv16(wreg, kconv, src, dst, relu);
-    else conv32(wreg, kconv, src, dst, relu);
-  };
-
   if constexpr (M16) {
-    // 16 channels: the residual stream lives in the accumulator layout of the wave that owns the
-    // tile (lane j + 16*g: channels 4g..4g+3 of pixel j, 8 bytes; tiles wave, wave + 8, ...), so
-    // conv_b's epilogue adds it in registers and writes relu(x) for the next block straight into
-    // X: no separate pass over the frame, one barrier fewer per block.  Same arithmetic as the
+    // 16 channels on v_mfma_f32_16x16x32_f16 (a 32x32 tile would compute 16 output rows of zeros): lane l supplies
+    // A[i = l%16][k = 8*(l/16) + e] and B[k][j = l%16]; D[i][j] sits in lane j + 16*(i/4), register i%4.
+    // A tile is 16 neighbouring pixels of a row; K = 32 is two filter taps x 16 channels, lane group g = l/16
+    // holding tap g%2 of the pair, channels 8*(g/2)..: with the two taps side by side in a filter row, the
+    // 64 lanes' 16-byte reads are free of bank conflicts (4 cycles measured; 8 with the channel half in the low
+    // bit of g, and 8 for two taps of different rows).
+    //
+    // A wave owns a run of rows of one 16-pixel column group and walks down it: image row i gives two operands, P
+    // (columns 0 and 1 of the windows) and Q (column 2 of rows i - 1 and i).  P is the first two taps of all
+    // three filter rows, for the three output rows that see it; Q is taps (2, 5) of one output row and (none, 8) of
+    // the one above: five MFMAs per output row on two reads, into three accumulators in turn, the operands of the
+    // next row requested ahead of them.  A tile by itself took five reads, with nothing to cover its first
+    // ones and its epilogue.  Two blocks on 36 x 64 pixels: 8192 frames 495 -> 389 us (3.1 TB/s; the matrix pipe
+    // is busy 0.4 of the time), 2048 frames 131 -> 103, 101 frames 18.5 -> 15.1.  (Q's two rows cost its reads
+    // 8 cycles; rows of a multiple of 256 bytes would not, but do not fit twice.)
+    const int j16 = lane & 15, g16 = lane >> 4;
+    constexpr int CG = W / 16, SEGS = kNW / CG;
+    const int cg = wave % CG, seg = wave / CG;
+    const int y0 = seg * strip.H / SEGS, n = (seg + 1) * strip.H / SEGS - y0;  // the wave's rows
+    constexpr int RT = 2 * PPT;  // ... at most
+    // channels 4*g .. 4*g+3 of ring pixel (y0 + 1, x + 1), and the two operands
+    const int own = y0 * ROW + cg * 16 * PITCH;
+    const int lane_o16 = own + ROW + (j16 + 1) * PITCH + ((((g16 >> 1) * 16) ^ swz(j16 + 1)) + (g16 & 1) * 8);
+    const int lane_p = own + (j16 + (g16 & 1)) * PITCH + (((g16 >> 1) * 16) ^ swz(j16 + (g16 & 1)));
+    const int lane_q16 = own + (g16 & 1) * ROW + (j16 + 2) * PITCH + (((g16 >> 1) * 16) ^ swz(j16 + 2));
+    // done(r, acc): output row y0 + r is complete
+    auto walk = [&](const u32x4 (&w)[NB][NS], int kconv, const unsigned char* src, auto&& done) __attribute__((always_inline)) {
+      const f32x4 init = *(const f32x4*)(bias_lds + 32 * kconv + 4 * g16);
+      auto mfma = [&](int k, const u32x4& x, const f32x4& c) __attribute__((always_inline)) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[k][0]), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
+      };
+      // (opaque: computed ahead of the frame loop all rows' places and conditions would be spilled)
+      int from_p = lane_p, from_q = lane_q16, rows = n;
+      asm volatile("" : "+v"(from_p), "+v"(from_q), "+s"(rows));
+      const unsigned char *at_p = src + from_p, *at_q = src + from_q;
+      u32x4 p[2], q[2];
+      f32x4 acc[3];
+      p[0] = *(const u32x4*)at_p;
+      auto step = [&](auto self, auto ic) __attribute__((always_inline)) {  // image row y0 + i
+        constexpr int i = decltype(ic)::value;
+        if (i >= rows + 2) return;
+        if (i + 1 < RT + 2) {
+          at_p += i < rows + 1 ? ROW : 0;  // (behind the last row: that one again, for no use)
+          p[(i + 1) & 1] = *(const u32x4*)at_p;
+          if (i > 0) at_q += i < rows + 1 ? ROW : 0;
+          q[(i + 1) & 1] = *(const u32x4*)at_q;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 &a0 = acc[i % 3], &a1 = acc[(i + 2) % 3], &a2 = acc[(i + 1) % 3];  // of output rows i, i - 1, i - 2
+        // (a2 first: its two products are back when it is rounded, 398 -> 389 us)
+        if (i > 1) a2 = mfma(2, p[i & 1], a2);
+        if (i > 0 && i < RT + 1) a1 = mfma(1, p[i & 1], a1);
+        if (i > 1) a2 = mfma(4, q[i & 1], a2);
+        if (i > 0 && i < RT + 1) a1 = mfma(3, q[i & 1], a1);
+        if (i < RT) a0 = mfma(0, p[i & 1], init);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (i > 1) done(i - 2, a2);
+        if constexpr (i + 1 < RT + 2) self(self, std::integral_constant<int, i + 1>{});
+      };
+      step(step, std::integral_constant<int, 0>{});
+    };
+    // conv_a of a block: X -> T, ReLU
+    auto conv16_a = [&](const u32x4 (&w)[NB][NS], int kconv) __attribute__((always_inline)) {
+      walk(w, kconv, X, [&](int r, const f32x4& acc) __attribute__((always_inline)) {
+        *(u32x2*)(T + lane_o16 + r * ROW) = u32x2{pk_max0(pk_f16(acc[0], acc[1])), pk_max0(pk_f16(acc[2], acc[3]))};
+      });
+    };
+
+    // The residual stream lives in the accumulator layout of the wave that owns the tile (lane j + 16*g: channels
+    // 4g..4g+3 of pixel j, 8 bytes), so conv_b's epilogue adds it in registers and writes relu(x) for the next block
+    // straight into X: no separate pass over the frame, one barrier fewer per block.  Same arithmetic as the
     // piece form: conv_b's result is rounded to fp16, then added to x in fp16.
-    constexpr int RT = 2 * PPT;  // 16-pixel tiles per wave at most
-    const int n16 = npix >> 4;
     u32x2 xt[RT], nt[RT];
-    auto tile_off16 = [&](int t) { return ((t << 4) >> LW) * ROW + ((t << 4) & (W - 1)) * PITCH; };
     const int lane_g = j16 * 32 + g16 * 8;  // the lane's 8 bytes within a tile's 512 in memory
-    // (part p of `parts`: rounds p, p + parts, ...)
+    // (part p of `parts`: rows p, p + parts, ...)
     auto load_tiles = [&](int bb, u32x2 (&dst)[RT], int part = 0, int parts = 1) {
-      const unsigned char* src = (const unsigned char*)g.x + (size_t)bb * pieces * 16 + (size_t)strip.first * W * 32;
+      const unsigned char* src =
+          (const unsigned char*)g.x + (size_t)bb * pieces * 16 + ((size_t)(strip.first + y0) * CG + cg) * 512;
+      int last = n > 0 ? n - 1 : 0;
+      asm volatile("" : "+s"(last));
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         if (r % parts != part) continue;
         // (an opaque move keeps the offsets from being computed ahead of the frame loop and spilled)
         int o = lane_g;
         asm volatile("" : "+v"(o));
-        const int t = wave + kNW * r;
-        dst[r] = *(const u32x2*)(src + (size_t)(t < n16 ? t : n16 - 1) * 512 + o);
+        dst[r] = *(const u32x2*)(src + (size_t)(r < last ? r : last) * (CG * 512) + o);
       }
     };
     auto relu2 = [](u32x2 v) { return u32x2{pk_max0(v[0]), pk_max0(v[1])}; };
-    // conv_b of a block: T -> x += conv + bias; X <- relu(x) if another block follows.  The tile
-    // rounds are unrolled (the stream's registers are indexed by the round).
-    auto conv16_b = [&](const u32x4 (&wreg)[NB][NS], int kconv, bool more) {
-      const f32x4 init = *(const f32x4*)(bias_lds + 32 * kconv + 4 * g16);
-      auto run = [&](auto cnt, auto r0c) {
-        constexpr int N = decltype(cnt)::value, R0 = decltype(r0c)::value;
-        f32x4 acc[N];
-        const unsigned char* base[N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-          acc[n] = init;
-          base[n] = T + tile_off16(wave + kNW * (R0 + n));
-        }
-        u32x4 pf[2][N];
-#pragma unroll
-        for (int n = 0; n < N; ++n)
-#pragma unroll
-          for (int d = 0; d < 2; ++d) pf[d][n] = *(const u32x4*)(base[n] + lane_m[d]);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-#pragma unroll
-          for (int n = 0; n < N; ++n) {
-            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wreg[k][0]),
-                                                            __builtin_bit_cast(f16x8, pf[k & 1][n]), acc[n], 0, 0, 0);
-            if (k + 2 < 5) pf[k & 1][n] = *(const u32x4*)(base[n] + lane_m[k + 2]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-          if (R0 + n < RT) {  // (constant once unrolled)
-            u32x2& x = xt[R0 + n < RT ? R0 + n : RT - 1];
-            x[0] = pk_add(x[0], pk_f16(acc[n][0], acc[n][1]));
-            x[1] = pk_add(x[1], pk_f16(acc[n][2], acc[n][3]));
-            if (more) *(u32x2*)(X + tile_off16(wave + kNW * (R0 + n)) + lane_o16) = relu2(x);
-          }
-        }
-      };
-      if constexpr (RES && PPT >= 9) {
-        static_for<RT, 2>([&](auto r0c) {
-          constexpr int R0 = decltype(r0c)::value;
-          const int t0 = wave + kNW * R0;
-          if (t0 + kNW < n16 && R0 + 1 < RT) run(std::integral_constant<int, 2>{}, r0c);
-          else if (t0 < n16) run(std::integral_constant<int, 1>{}, r0c);
-        });
-      } else {
-        static_for<RT, 4>([&](auto r0c) {
-          constexpr int R0 = decltype(r0c)::value;
-          const int t0 = wave + kNW * R0;
-          if (t0 + 3 * kNW < n16 && R0 + 3 < RT) {
-            run(std::integral_constant<int, 4>{}, r0c);
-          } else if (t0 < n16) {
-            if (t0 + kNW < n16 && R0 + 1 < RT) {
-              run(std::integral_constant<int, 2>{}, r0c);
-              if (t0 + 2 * kNW < n16 && R0 + 2 < RT) run(std::integral_constant<int, 1>{}, std::integral_constant<int, R0 + 2>{});
-            } else {
-              run(std::integral_constant<int, 1>{}, r0c);
-            }
-          }
-        });
-      }
+    // conv_b of a block: T -> x += conv + bias; X <- relu(x) if another block follows
+    auto conv16_b = [&](const u32x4 (&w)[NB][NS], int kconv, bool more) __attribute__((always_inline)) {
+      walk(w, kconv, T, [&](int r, const f32x4& acc) __attribute__((always_inline)) {
+        u32x2& x = xt[r];
+        x[0] = pk_add(x[0], pk_f16(acc[0], acc[1]));
+        x[1] = pk_add(x[1], pk_f16(acc[2], acc[3]));
+        if (more) *(u32x2*)(X + lane_o16 + r * ROW) = relu2(x);
+      });
     };
 
     const int stride = (int)gridDim.x / g.parts;
@@ -481,8 +417,7 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     for (; b < g.B; b += stride) {
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        const int t = wave + kNW * r;
-        if (t < n16) *(u32x2*)(X + tile_off16(t) + lane_o16) = relu2(xt[r]);
+        if (r < n) *(u32x2*)(X + lane_o16 + r * ROW) = relu2(xt[r]);
       }
       __syncthreads();
       const int bn = b + stride < g.B ? b + stride : b;  // (last round: its own again)
@@ -490,14 +425,14 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
         // the next frame is requested in three parts between the convolutions: the requests of
         // all workgroups in one burst kept the last waves of a workgroup 10 k cycles at issuing theirs
         load_tiles(bn, nt, 0, 3);
-        conv16(wk[0], 0, X, T, true);
+        conv16_a(wk[0], 0);
         load_tiles(bn, nt, 1, 3);
         __syncthreads();
         conv16_b(wk[1], 1, g.n_convs > 2);
         load_tiles(bn, nt, 2, 3);
         __syncthreads();  // X complete for the next block / T free for the next frame
         if (g.n_convs > 2) {
-          conv16(wk[2], 2, X, T, true);
+          conv16_a(wk[2], 2);
           __syncthreads();
           conv16_b(wk[3], 3, false);
           __syncthreads();
@@ -506,21 +441,20 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
         load_tiles(bn, nt);
         for (int k = 0; k < g.n_convs; k += 2) {
           load_bank(k + 1, wB);
-          conv16(wA, k, X, T, true);
+          conv16_a(wA, k);
           __syncthreads();
           load_bank(k + 2 < g.n_convs ? k + 2 : 0, wA);
           conv16_b(wB, k + 1, k + 2 < g.n_convs);
           __syncthreads();
         }
       }
-      unsigned char* dst = (unsigned char*)g.out + (size_t)b * pieces * 16 + (size_t)strip.first * W * 32;
-      const int t0 = (strip.r0 - strip.first) * (W / 16), t1 = (strip.r1 - strip.first) * (W / 16);  // its own rows
+      unsigned char* dst = (unsigned char*)g.out + (size_t)b * pieces * 16 + ((size_t)(strip.first + y0) * CG + cg) * 512;
+      const int first = strip.r0 - strip.first - y0, last = min(strip.r1 - strip.first - y0, n);  // its own rows
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         int o = lane_g;
         asm volatile("" : "+v"(o));
-        const int t = wave + kNW * r;
-        if (t >= t0 && t < t1) *(u32x2*)(dst + (size_t)t * 512 + o) = g.relu_out ? relu2(xt[r]) : xt[r];
+        if (r >= first && r < last) *(u32x2*)(dst + (size_t)r * (CG * 512) + o) = g.relu_out ? relu2(xt[r]) : xt[r];
       }
 #pragma unroll
       for (int r = 0; r < RT; ++r) xt[r] = nt[r];
@@ -542,11 +476,11 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     for (int k = 0; k < g.n_convs; k += 2) {
       // conv_a of the block: X -> T, ReLU; conv_b's bank arrives meanwhile
       load_bank(k + 1, wB);
-      conv(wA, k, X, T, true);
+      conv32(wA, k, X, T, true);
       __syncthreads();
       // conv_b: T -> X; the next conv_a's bank (the next block's, or the first of the next frame)
       load_bank(k + 2 < g.n_convs ? k + 2 : 0, wA);
-      conv(wB, k + 1, T, X, false);
+      conv32(wB, k + 1, T, X, false);
       __syncthreads();
       // x <- x + branch; X <- relu(x) unless this was the last block.  Three pieces at a time:
       // their reads first, then the arithmetic and the writes (one LDS latency per three pieces).
@@ -852,9 +786,9 @@ hipError_t launch_stage_t(const StageArgs& g, size_t lds, hipStream_t st) {
 
 // A operands of a 16 -> 16 channel convolution for the tap-pair MFMAs of the stage kernel:
 // wpk[(m * 64 + lane) * 8 + e] = w[n = lane%16][c = 8*(lane/32) + e][tap], tap = pair m's first
-// (lane/16 even) or second (odd) member; pair 4 has no second member (zeros).
+// (lane/16 even) or second (odd) member; pair 4 has no first member (zeros).
 void res_stage_pack16(const float* w, bool f16, std::vector<uint16_t>& wpk) {
-  static const int pair[5][2] = {{0, 1}, {3, 4}, {6, 7}, {2, 5}, {8, -1}};
+  static const int pair[5][2] = {{0, 1}, {3, 4}, {6, 7}, {2, 5}, {-1, 8}};
   wpk.assign((size_t)5 * 64 * 8, 0);
   for (int m = 0; m < 5; ++m)
     for (int lane = 0; lane < 64; ++lane)

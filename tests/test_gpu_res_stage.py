@@ -47,3 +47,15 @@ def test_stage_with_its_banks_in_lds(torch_cuda, ref, monkeypatch, obs, blocks, 
         parity.assert_close(k, g[k][rows], o[k], 1e-2)
         # (fp16 streams rounded at different points, each about 1e-3 from the oracle)
         parity.assert_close(k + " vs per-block kernels", g[k], g2[k], 1e-2)
+
+
+# first stage frames (16 channels): rows that the waves share unevenly in four, two and one column groups; the fewest
+# that are taken (one row per wave at 16 columns: strips leave waves without any); three blocks, and several frames
+# per workgroup
+CASES16 = [((3, 34, 128), 2, 5), ((3, 10, 128), 1, 4), ((3, 71, 128), 2, 300), ((3, 45, 64), 2, 261), ((3, 37, 32), 2, 3),
+           ((3, 32, 32), 2, 270), ((3, 33, 32), 1, 64), ((3, 45, 64), 3, 260), ((3, 71, 128), 3, 2)]
+
+
+@pytest.mark.parametrize("obs,blocks,B", CASES16, ids=["%dx%d-%d-%d" % (o[1], o[2], n, b) for o, n, b in CASES16])
+def test_rows_of_a_column_group(torch_cuda, ref, monkeypatch, obs, blocks, B):
+    test_stage_with_its_banks_in_lds(torch_cuda, ref, monkeypatch, obs, blocks, B)
