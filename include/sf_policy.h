@@ -325,7 +325,8 @@ int64_t sf_policy_flops_per_row(const sf_policy* p);
  * a HIP event on its stream before the first and after every launch;
  * sf_policy_last_op_times waits for the last recorded step and writes the
  * duration of each launch in milliseconds to ms_out[0..op_count) (0 for an op that the launch
- * before did).  Errors:
+ * before did).  Without timing the measurement layers run in the launch of the FC layer, and the FC layer, the cell
+ * and the heads of few rows are one launch, with the same results bit for bit.  Errors:
  * SF_ERR_ARG (null handle or buffer, n < op_count), SF_ERR_DEVICE (nothing
  * recorded yet). */
 int sf_policy_op_count(const sf_policy* p);
