@@ -445,23 +445,23 @@ __global__ __launch_bounds__(kThreads, DA == 1 && RT * U <= 4 ? 4 : 2) void dens
   }
 }
 
-// The cell of an fp32 configuration on many rows: a workgroup owns 64 rows and 32 hidden units in
-// two halves.  Four waves share a half and take every fourth K step; the rows of a chunk of four K
+// The cell of an fp32 configuration in handles for many rows: a workgroup owns 16 * RT rows (64; fewer in calls of
+// few, see launch_tile: the bits of a row are the same) and 32 hidden units in two halves.  Four waves share a half and take every fourth K step; the rows of a chunk of four K
 // steps are split once for all eight waves and wait in LDS in operand order (two buffers, one
 // barrier per chunk), the weights go from memory to the one wave that needs them.
-template <int KIND>
+template <int KIND, int RT>
 __global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
   constexpr int XT = X_F32, PB = 3;
   constexpr int GB = group_bytes(KIND);
   constexpr int U = 2;                         // column groups per wave
   constexpr int NB = KIND == GRU ? U + 1 : 2 * U, NA = 2 * U;
-  constexpr int RT = 4, KW = 4;                // row tiles; K steps per chunk
-  constexpr int RR = 2;                        // row tiles per round of the sum
+  constexpr int KW = 4;                        // K steps per chunk
+  constexpr int RR = RT < 2 ? 1 : 2;           // row tiles per round of the sum
   constexpr int NP = 3;                        // terms of a row element
   constexpr int BUF = NP * RT * KW * 1024;     // bytes of a chunk in LDS
   constexpr int RED = kWaves * RR * NA * 1024;
   __shared__ __attribute__((aligned(16))) uint8_t lds[2 * BUF > RED ? 2 * BUF : RED];
-  __shared__ int odd_row[64];                  // rows with an infinity or a NaN
+  __shared__ int odd_row[16 * RT];             // rows with an infinity or a NaN
   f32x4(*red)[RR * NA][64] = (f32x4(*)[RR * NA][64])lds;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -470,11 +470,11 @@ __global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
   const int li = lane & 15, lg = lane >> 4;
   int rt0, cg;
   if (!tile_of(g, rt0, cg)) return;
-  const int row0 = rt0 * 64;
+  const int row0 = rt0 * 16 * RT;
   const int group0 = (cg * 2 + half) * U;      // this wave's first column group
 
   // rows of a chunk: thread -> (row tid/32 + 16 j, four floats)
-  constexpr int NL = 4;
+  constexpr int NL = RT;
   int xm[NL], hm[NL], dn[NL];
 #pragma unroll
   for (int j = 0; j < NL; ++j) {
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(kThreads, 2) void cell_tile_kernel(DenseArgs g) {
     dn[j] = g.done[xm[j]];
   }
   state_rows(g, hm, dn);
-  if (tid < 64) odd_row[tid] = 0;
+  if (tid < 16 * RT) odd_row[tid] = 0;
 
   const size_t group_stride = (size_t)g.kn * PB * GB;
   const uint8_t* wbase = g.w + (size_t)group0 * group_stride;
@@ -750,13 +750,24 @@ hipError_t launch_cfg(DenseArgs g, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int KIND>
-hipError_t launch_tile(DenseArgs g, hipStream_t st) {
-  g.n_rt = (g.M + 63) / 64;
+template <int KIND, int RT>
+hipError_t launch_tile_t(DenseArgs g, hipStream_t st) {
+  g.n_rt = (g.M + 16 * RT - 1) / (16 * RT);
   g.n_cg = g.H / 32;
-  const unsigned blocks = deal(g, 64LL * g.kn * 128, 4LL * g.kn * 3 * group_bytes(KIND));
-  cell_tile_kernel<KIND><<<blocks, kThreads, 0, st>>>(g);
+  const unsigned blocks = deal(g, 16LL * RT * g.kn * 128, 4LL * g.kn * 3 * group_bytes(KIND));
+  cell_tile_kernel<KIND, RT><<<blocks, kThreads, 0, st>>>(g);
   return hipGetLastError();
+}
+template <int KIND>
+hipError_t launch_tile(const DenseArgs& g, hipStream_t st) {
+  // The smallest tile whose grid is one round of workgroups: what a workgroup takes grows with its rows.  512
+  // units, us, 16 / 32 / 64 rows per workgroup: GRU, 256 rows 11.0 / 13.8 / 19.5, 512 rows 19.9 / 14.4 / 19.3, 768 rows 28.6 / 25.4 /
+  // 20.0, 1024 rows 39 / 27 / 22.1, 1536 rows 58 / 39.6 / 39.8; LSTM, 256 rows 13.4 / 16.6 / 24.7, 512 rows 23.9 / 17.3 / 25.3, 1024
+  // rows 47 / 33 / 27.3.
+  auto one_round = [&](int rt) { return (long long)((g.M + 16 * rt - 1) / (16 * rt)) * (g.H / 32) <= 256; };
+  if (one_round(1)) return launch_tile_t<KIND, 1>(g, st);
+  if (one_round(2)) return launch_tile_t<KIND, 2>(g, st);
+  return launch_tile_t<KIND, 4>(g, st);
 }
 
 long long split_workgroups(long long M, int n_col, int rt, int u) {
@@ -896,8 +907,8 @@ bool dense_cell_supported(int I1, int I2, int H) {
 // 83, 94, 1024 rows 253, 259, 2048 rows 477, 477, 4096 rows 870, 863.  (A handle keeps one of the two, and
 // a handle for 2048 rows also takes calls of few.)
 bool dense_fc_small(int M, int N) { return split_workgroups(M, N / 16, 4, 2) <= 512; }
-// Cells: up to two rounds of the 32-row tile.  Beyond, cell_tile_kernel in fp32 (GRU 512 -> 512 at
-// 512 rows 17.5 against 21 us, at 1024 rows 38 against 25) and k_rnn_bf16.hip in bf16 (at 512 rows 10
+// Cells: up to two rounds of the 32-row tile.  Beyond, cell_tile_kernel in fp32 (GRU 512 -> 512, us: 256
+// rows 9.7 against 11.0, 512 rows 13.4, 14.4, 768 rows 23.4, 20, 1024 rows 25.2, 22.1, 2048 rows 48, 42.5) and k_rnn_bf16.hip in bf16 (at 512 rows 10
 // against 20 us, at 1024 rows 24 against 21; 256 -> 256 at 1000 rows 8 against 14).  The kernels'
 // sums run in different orders (and the state enters k_rnn_bf16.hip in two terms), so that this is
 // settled once, by the largest batch.

@@ -171,3 +171,13 @@ def test_sums_that_overflow(torch_cuda, ref, max_batch, rnn_type):
             assert (weights is u and k != "h_out") or np.max(np.abs(a[m] - b[m])) < 1e-4, k
     if rnn_type == "gru":
         assert np.isinf(o["logits"][rows]).all() and np.isfinite(o["logits"]).sum() == (B - 4) * 6
+
+
+@pytest.mark.parametrize("rnn_type", ["gru", "lstm"])
+def test_few_rows_of_a_handle_for_many(torch_cuda, ref, rnn_type):
+    """The kernel for many rows on 16, 32 and 64 rows per workgroup: one round of them up to 256 and 512 rows of 512
+    hidden units; gathered states, and rows whose sums are computed by the definition."""
+    test_tiles(torch_cuda, ref, _net(fc=128, rnn=512, rnn_type=rnn_type), 600, [1, 16, 17, 255, 256, 257, 511, 512, 513, 600])
+    for B in (200, 400):
+        test_gathered_states(torch_cuda, 600, B, rnn_type)
+        test_states_without_terms(torch_cuda, ref, 600, B, rnn_type)
