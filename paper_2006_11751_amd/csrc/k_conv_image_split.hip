@@ -135,18 +135,19 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
   constexpr int NR = AHEAD ? 4 : NV;  // pieces in registers
   f32x4 v[NR];
   // piece u of a round
-  auto load = [&](int it, int u) __attribute__((always_inline)) {
+  // (opaque: computed ahead of the loop the places of all pieces would have to be spilled)
+  auto thread = [&]() __attribute__((always_inline)) {
+    int first = tid;
+    asm volatile("" : "+v"(first));
+    return first;
+  };
+  auto load = [&](int it, int u, int first) __attribute__((always_inline)) {
     // a last round with fewer frames re-reads its last piece instead of reading past the batch
     const uint8_t* src = (const uint8_t*)(g.in + (size_t)it * FR * frame_pieces);
     const uint32_t last = 16u * (uint32_t)(min(g.B - it * FR, FR) * frame_pieces - 1);
-    // (opaque: computed ahead of the loop the places of all pieces would have to be spilled)
-    int first = tid;
-    asm volatile("" : "+v"(first));
     v[u % NR] = *(const f32x4*)(src + min(16u * (uint32_t)(first + kNT * u), last));
   };
-  auto put = [&](int u, u32x4* image) __attribute__((always_inline)) {
-    int first = tid;
-    asm volatile("" : "+v"(first));
+  auto put = [&](int u, u32x4* image, int first) __attribute__((always_inline)) {
     const int f = first + kNT * u;
     const bool second = FR == 2 && f >= frame_pieces;
     const int pix = (f - (second ? frame_pieces : 0)) / C4;
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
   };
   if constexpr (AHEAD)
 #pragma unroll
-    for (int u = 0; u < NR; ++u) load(blockIdx.x, u);
+    for (int u = 0; u < NR; ++u) load(blockIdx.x, u, thread());
   if constexpr (AHEAD) load_bank();
   const int image_stride = FR * frame_stride + P4;
   f32x4* const affine = (f32x4*)(img + 2 * image_stride);  // AHEAD: [2][N / 4] inverse scales, biases
@@ -175,8 +176,8 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
     if (tid < g.N / 2) affine[tid] = ((const f32x4*)(tid < g.N / 4 ? g.scale + CIN : g.bias))[tid % (g.N / 4)];
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
-      put(u, img);
-      if (u + NR < NV) load(blockIdx.x, u + NR);
+      put(u, img, thread());
+      if (u + NR < NV) load(blockIdx.x, u + NR, thread());
     }
     __syncthreads();
   }
@@ -187,10 +188,11 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
     u32x4* const other = img + (AHEAD && odd_round ? 0 : image_stride);
     odd_round ^= 1;
     if constexpr (!AHEAD) {
+      const int first = thread();
 #pragma unroll
-      for (int u = 0; u < NV; ++u) load(it, u);
+      for (int u = 0; u < NV; ++u) load(it, u, first);
 #pragma unroll
-      for (int u = 0; u < NV; ++u) put(u, img);
+      for (int u = 0; u < NV; ++u) put(u, img, first);
       __syncthreads();
     }
     asm volatile("" ::"s"(refused));  // (requested with the scales, here long since)
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
       }
       if constexpr (MORE)
 #pragma unroll
-        for (int u = 0; u < NR; ++u) load(next_it, u);
+        for (int u = 0; u < NR; ++u) load(next_it, u, thread());
 #pragma unroll
       for (int t = 0; t < G; ++t) {
         const int next = tap(t + 1 < G ? t + 1 : t);
@@ -260,10 +262,10 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_image_split_kernel(SplitArgs 
         if constexpr (MORE) {
           // the first pieces, asked for ahead of the taps, behind six of them, the others behind the last
           if (t >= 6 && t < 6 + NR) {
-            put(t - 6, other);
-            if (t - 6 + NR < NV) load(next_it, t - 6 + NR);
+            put(t - 6, other, thread());
+            if (t - 6 + NR < NV) load(next_it, t - 6 + NR, thread());
           }
-          if (t >= G - (NV - NR)) put(t - (G - NV), other);
+          if (t >= G - (NV - NR)) put(t - (G - NV), other, thread());
         }
       }
       if constexpr (AHEAD) {
