@@ -302,12 +302,16 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     //
     // A wave owns a run of rows of one 16-pixel column group and walks down it: image row i gives two operands, P
     // (columns 0 and 1 of the windows) and Q (column 2 of rows i - 1 and i).  P is the first two taps of all
-    // three filter rows, for the three output rows that see it; Q is taps (2, 5) of one output row and (none, 8) of
-    // the one above: five MFMAs per output row on two reads, into three accumulators in turn, the operands of the
-    // next row requested ahead of them.  A tile by itself took five reads, with nothing to cover its first
-    // ones and its epilogue.  Two blocks on 36 x 64 pixels: 8192 frames 495 -> 389 us (3.1 TB/s; the matrix pipe
-    // is busy 0.4 of the time), 2048 frames 131 -> 103, 101 frames 18.5 -> 15.1.  (Q's two rows cost its reads
-    // 8 cycles; rows of a multiple of 256 bytes would not, but do not fit twice.)
+    // three filter rows, for the three output rows that see it; Q is (none, 8) of output row i - 2 and, kept for the
+    // next image row, (2, 5) of row i - 1: five MFMAs per output row on two reads, into three accumulators in turn,
+    // the operands of the next row requested ahead of them.  The products of an output row are added in the order
+    // (0, 1), (3, 4), (6, 7), (2, 5), (8), the order of a tile computed by itself: results are rounded to fp16 between
+    // convolutions, so that another one shows (as much as 0.5 % at the network's end; adding (2, 5) an image row
+    // earlier is no faster: 8192 rows 1580 and 1581 us a step).
+    // A tile by itself took five reads, with nothing to cover its first ones and its epilogue.  Two blocks on
+    // 36 x 64 pixels: 8192 frames 495 -> 389 us (3.1 TB/s; the matrix pipe is busy 0.4 of the time), 2048 frames
+    // 131 -> 103, 101 frames 18.5 -> 15.1.  (Q's two rows cost its reads 8 cycles; rows of a multiple of 256
+    // bytes would not, but do not fit twice.)
     const int j16 = lane & 15, g16 = lane >> 4;
     constexpr int CG = W / 16, SEGS = kNW / CG;
     const int cg = wave % CG, seg = wave / CG;
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
       int from_p = lane_p, from_q = lane_q16, rows = n;
       asm volatile("" : "+v"(from_p), "+v"(from_q), "+s"(rows));
       const unsigned char *at_p = src + from_p, *at_q = src + from_q;
-      u32x4 p[2], q[2];
+      u32x4 p[2], q[3];
       f32x4 acc[3];
       p[0] = *(const u32x4*)at_p;
       auto step = [&](auto self, auto ic) __attribute__((always_inline)) {  // image row y0 + i
@@ -338,16 +342,15 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
           at_p += i < rows + 1 ? ROW : 0;  // (behind the last row: that one again, for no use)
           p[(i + 1) & 1] = *(const u32x4*)at_p;
           if (i > 0) at_q += i < rows + 1 ? ROW : 0;
-          q[(i + 1) & 1] = *(const u32x4*)at_q;
+          q[(i + 1) % 3] = *(const u32x4*)at_q;
         }
         __builtin_amdgcn_sched_barrier(0);
         f32x4 &a0 = acc[i % 3], &a1 = acc[(i + 2) % 3], &a2 = acc[(i + 1) % 3];  // of output rows i, i - 1, i - 2
-        // (a2 first: its two products are back when it is rounded, 398 -> 389 us)
         if (i > 1) a2 = mfma(2, p[i & 1], a2);
         if (i > 0 && i < RT + 1) a1 = mfma(1, p[i & 1], a1);
-        if (i > 1) a2 = mfma(4, q[i & 1], a2);
-        if (i > 0 && i < RT + 1) a1 = mfma(3, q[i & 1], a1);
+        if (i > 1) a2 = mfma(3, q[(i + 2) % 3], a2);
         if (i < RT) a0 = mfma(0, p[i & 1], init);
+        if (i > 1) a2 = mfma(4, q[i % 3], a2);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (i > 1) done(i - 2, a2);
         if constexpr (i + 1 < RT + 2) self(self, std::integral_constant<int, i + 1>{});

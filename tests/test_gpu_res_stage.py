@@ -59,3 +59,26 @@ CASES16 = [((3, 34, 128), 2, 5), ((3, 10, 128), 1, 4), ((3, 71, 128), 2, 300), (
 @pytest.mark.parametrize("obs,blocks,B", CASES16, ids=["%dx%d-%d-%d" % (o[1], o[2], n, b) for o, n, b in CASES16])
 def test_rows_of_a_column_group(torch_cuda, ref, monkeypatch, obs, blocks, B):
     test_stage_with_its_banks_in_lds(torch_cuda, ref, monkeypatch, obs, blocks, B)
+
+
+@pytest.mark.parametrize("obs,blocks", [((3, 32, 32), 1), ((3, 40, 64), 2), ((3, 72, 128), 2), ((3, 32, 64), 3)])
+def test_order_of_the_taps(torch_cuda, ref, obs, blocks):
+    """The products of a 16-channel convolution are added in the order (0, 1), (3, 4), (6, 7), (2, 5), (8): a small
+    one of tap 5 is kept if the large ones of taps 4 and 7, which cancel, are both there before it."""
+    net = dict(RESNET_BF16_SMALL, name="taps_%dx%d" % obs[1:], B=3, obs=obs, stages=[16], blocks_per_stage=blocks)
+    w = wl.weights(net)
+    w["conv_w"] = [np.zeros_like(a) for a in w["conv_w"]]
+    w["conv_b"] = [np.zeros_like(b) for b in w["conv_b"]]
+    w["conv_b"][0][:] = 1.0  # every pixel is 1, and a multiple of 2^-9 below 2 behind each block
+    for k in range(blocks):
+        a, b = w["conv_w"][1 + 2 * k], w["conv_w"][2 + 2 * k]
+        a[0, 0, 1, 1], a[0, 0, 2, 1], a[0, 0, 1, 2] = -2.0 ** 14, 2.0 ** 14, 2.0 ** -13
+        b[:, 0, 1, 1] = 2.0 ** 10
+    o_, h_, d_ = wl.observations(net, 0, 3), wl.initial_state(net, 3), wl.done_mask(net, 0, 3)
+    pol = binding.Policy(net, w)
+    assert "res_stage" in pol.op_kernels(), pol.op_kernels()
+    g = _gpu_step(torch_cuda, pol, o_, h_, d_, 7, 11)
+    pol.close()
+    o = ref.policy_step(net, w, o_, h_, d_, 7, 11)
+    for k in ("h_out", "value"):
+        parity.assert_close(k, g[k], o[k], 1e-2)
