@@ -8,16 +8,16 @@
 // exchange buffer (sf_exchange.h), which the step's first launch prepares.  What a role needs of its own
 // (weights, flags, the incoming state) it asks for before it waits.
 //
-// Progress.  Roles are numbered level by level: FC tiles, cell tiles, heads.  A role waits only for roles
-// of lower levels, FC tiles for nobody.  Each workgroup has a role of its own, by its number, and marks it
-// as claimed when it starts.  A wait that has lasted a while is given up; the workgroup then looks for a role
+// Progress.  Roles are numbered level by level: FC tiles, cell tiles, then heads and the state table's writers.  A role
+// waits only for roles of lower levels, FC tiles for nobody.  Each workgroup has a role of its own, by its number, and
+// marks it as claimed when it starts.  A wait that has lasted a while is given up; the workgroup then looks for a role
 // of a lower level that nobody has claimed (the device or the stream's compute units are full of others, so
 // that its workgroup has not started), claims it, computes it and begins its own again.  With all of them
 // claimed, each is computed by a workgroup that runs, and it waits as long as it takes.  So a wait never
 // depends on a workgroup that has not started, however few of them run at a time.  A workgroup that starts
-// late and finds its cell tile claimed leaves (the state table may be new by then); an FC tile is computed
-// once more, with the same bits, since waiting for the answer to a claim, 2 us with many at a time, would
-// be part of every step.
+// late and finds its cell tile claimed leaves: the state table may be new by then, since it is written as soon as
+// all cell tiles, each computed once, are marked as complete.  An FC tile is computed once more, with the same
+// bits, since waiting for the answer to a claim, 2 us with many at a time, would be part of every step.
 //
 // What many waiting workgroups read over and over holds up the stores that they wait for (a look of all waves at all
 // their features, and at the claims first: the features came 3 us later).  So a wave looks at one word of each
@@ -52,13 +52,14 @@ constexpr int kD = 4;               // K steps in flight of a cell tile
 constexpr int kFD = 9;              // ... of an FC tile: all that a wave has of 2304 inputs
 constexpr int kP32 = 36, kP16 = 20;  // pitch of a row in LDS (floats)
 constexpr int kPatience = 64;        // looks, about 1 us each, before a wait is given up
+constexpr unsigned kComplete = 2;    // with a state table: in a cell tile's claim when it is through with the old states
 
 struct TailArgs {
   DenseArgs fc;    // x1, w, b1, M, I1, N, kn; out: exchange buffer of the features
-  DenseArgs cell;  // x1: exchange buffer of the features; out: state rows, or null (a state table: the heads write it)
+  DenseArgs cell;  // x1: exchange buffer of the features; out: state rows, or null (a state table)
   HeadsArgs heads; // h: exchange buffer of the new states
   unsigned* claims;
-  int n_fc, n_cell, n_heads;  // roles
+  int n_fc, n_cell, n_heads;  // roles; with a state table as many writers of it as heads (8 bytes more here: 0.2 us)
   int fc_cg, cell_cg;         // workgroups along the columns
   int skip;                   // workgroups that leave at once (0; the tests' stand-in for ones that never start)
 };
@@ -71,6 +72,10 @@ union TailLds {
     int lost;
   } dense;
   HeadsLds<NT> heads;
+  struct {
+    int later[16];  // a later row of the batch names the same environment
+    int lost;
+  } table;
 };
 
 template <bool F16>
@@ -405,6 +410,61 @@ __device__ inline __attribute__((always_inline)) bool cell_tile(const DenseArgs&
   return true;
 }
 
+// The new states of rows row0 .. go to the table once all cell tiles have read its old ones, those of other rows, too:
+// two rows of the batch may name one environment, and both are computed from its old state.  The last of them leaves
+// its state there.  False if the wait was given up after `limit` looks.  Workgroups of their own: done by the heads at
+// their end, indexed steps were 1.0 to 1.7 us longer without waiting for other rows' tiles (16 rows of the standard
+// network 26.7 us, now 25.0; 60 rows 31.4, 29.9; LSTM, 33 rows 30.8, 29.9), and 0.8 us more with it.
+template <typename Lds>
+__device__ inline __attribute__((always_inline)) bool table_rows(const HeadsArgs& g, const unsigned* cells, int n_cell, int row0, int limit, Lds& lds) {
+  const int tid = role_thread();
+  const int rows = min(g.B - row0, 16), r = tid & 15;
+  if (tid < 16) lds.later[tid] = 0;
+  __syncthreads();
+  if (r < rows) {
+    const int env = g.ids[row0 + r];
+    for (int j = row0 + r + 1 + (tid >> 4); j < g.B; j += kThreads / 16)
+      if (g.ids[j] == env) lds.later[r] = 1;
+  }
+  for (int at = tid; at < n_cell; at += kThreads)
+    for (int tries = 0; !(load_word(cells + at) & kComplete); ++tries) {
+      if (tries >= limit) {
+        lds.lost = 1;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(16);
+    }
+  __syncthreads();
+  if (__builtin_expect(lds.lost, 0)) return false;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)g.h, 0, 4 * g.B * g.S, 0x00027000);
+  const int per = g.S / 4;
+  constexpr int kPieces = 4;  // in flight (one by one: 2 us more with an LSTM's states)
+  for (int i0 = tid; i0 < rows * per; i0 += kPieces * kThreads) {
+    u32x4 v[kPieces];
+    bool missing;
+    do {  // (the tiles are complete: their words are here or on their way)
+      missing = false;
+#pragma unroll
+      for (int u = 0; u < kPieces; ++u) {
+        const int i = min(i0 + u * kThreads, rows * per - 1), q = i / per;
+        v[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 4 * ((row0 + q) * g.S + 4 * (i - q * per)), 0, kDeviceScope);
+      }
+#pragma unroll
+      for (int u = 0; u < kPieces; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) missing |= v[u][e] == kNotYet;
+    } while (missing);
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+      const int i = i0 + u * kThreads, q = i / per;
+      if (i >= rows * per) break;
+      const uint32_t env = (uint32_t)g.ids[row0 + q];
+      if (env < (uint32_t)g.n_env && !lds.later[q]) *((u32x4*)(g.h_table + (size_t)env * g.S) + i - q * per) = v[u];
+    }
+  }
+  return true;
+}
+
 // The kernel's argument, each time opaque: a role's part of it is loaded when the role begins.  (Loaded for all
 // roles ahead of the loop over them, as the compiler has it otherwise, it does not fit the scalar registers; 190
 // of them were spilled to lanes and read back, 2 us of each role.)
@@ -414,7 +474,8 @@ __device__ inline const TailArgs& tail_args() {
   return *(const TailArgs*)p;
 }
 
-template <int KIND, int FT, int XT, int PB, int NT>
+// TABLE: with a state table (an instantiation of its own: 0.1 to 0.25 us of a step without one).
+template <int KIND, int FT, int XT, int PB, int NT, bool TABLE>
 __global__ __launch_bounds__(kThreads, 2) void tail_kernel(TailArgs) {
   const TailArgs& g = tail_args();
   __shared__ __attribute__((aligned(16))) TailLds<NT> lds;
@@ -423,17 +484,19 @@ __global__ __launch_bounds__(kThreads, 2) void tail_kernel(TailArgs) {
   const int own = (int)blockIdx.x;
   if (own < g.skip) return;
   auto claim = [&](int role) {  // by one lane: whether it is this workgroup's now
-    return __hip_atomic_exchange(g.claims + role, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    return __hip_atomic_fetch_or(g.claims + role, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
   };
   auto begin = [&](int role) {  // by one thread, ahead of a barrier
     if (role < g.n_fc + g.n_cell)
       lds.dense.lost = 0;
-    else
+    else if (!TABLE || role < g.n_fc + g.n_cell + g.n_heads)
       lds.heads.lost = 0;
+    else
+      lds.table.lost = 0;
   };
   if (own >= g.n_fc) {
     if (threadIdx.x == 0) {
-      s_run = claim(own);
+      s_run = (TABLE && own >= g.n_fc + g.n_cell + g.n_heads) || claim(own);  // (the table's writers have no claims)
       begin(own);
     }
     __syncthreads();
@@ -449,9 +512,16 @@ __global__ __launch_bounds__(kThreads, 2) void tail_kernel(TailArgs) {
       const TailArgs& t = tail_args();
       const int r = run - t.n_fc;
       complete = cell_tile<KIND, XT, PB>(t.cell, r / t.cell_cg, r % t.cell_cg, (float*)t.heads.h, run == own ? limit : INT_MAX, lds.dense);
-    } else {
+      if (TABLE && complete) {
+        __syncthreads();  // every wave has stored what it computed from the table
+        if (threadIdx.x == 0) store_word(t.claims + run, 1u | kComplete);
+      }
+    } else if (!TABLE || run < g.n_fc + g.n_cell + g.n_heads) {
       const TailArgs& t = tail_args();
       complete = heads_rows<NT, PB, true>(t.heads, (run - t.n_fc - t.n_cell) * kHeadRows, lds.heads, limit);
+    } else {
+      const TailArgs& t = tail_args();
+      complete = table_rows(t.heads, t.claims + t.n_fc, t.n_cell, (run - t.n_fc - t.n_cell - t.n_heads) * 16, limit, lds.table);
     }
     if (run == own && complete) return;
     __syncthreads();  // LDS is free
@@ -481,14 +551,21 @@ __global__ __launch_bounds__(kThreads, 2) void tail_kernel(TailArgs) {
   }
 }
 
+template <int KIND, int FT, int XT, int PB, int NT>
+void launch_t(const TailArgs& g, hipStream_t st) {
+  const int blocks = g.n_fc + g.n_cell + g.n_heads;
+  if (g.heads.h_table)
+    tail_kernel<KIND, FT, XT, PB, NT, true><<<blocks + g.n_heads, kThreads, 0, st>>>(g);
+  else
+    tail_kernel<KIND, FT, XT, PB, NT, false><<<blocks, kThreads, 0, st>>>(g);
+}
 template <int KIND, int FT, int XT, int PB>
 hipError_t launch_nt(const TailArgs& g, hipStream_t st) {
-  const int blocks = g.n_fc + g.n_cell + g.n_heads;
   switch ((g.heads.sumA + 16) / 16) {
-    case 1: tail_kernel<KIND, FT, XT, PB, 1><<<blocks, kThreads, 0, st>>>(g); break;
-    case 2: tail_kernel<KIND, FT, XT, PB, 2><<<blocks, kThreads, 0, st>>>(g); break;
-    case 3: tail_kernel<KIND, FT, XT, PB, 3><<<blocks, kThreads, 0, st>>>(g); break;
-    default: tail_kernel<KIND, FT, XT, PB, 4><<<blocks, kThreads, 0, st>>>(g); break;
+    case 1: launch_t<KIND, FT, XT, PB, 1>(g, st); break;
+    case 2: launch_t<KIND, FT, XT, PB, 2>(g, st); break;
+    case 3: launch_t<KIND, FT, XT, PB, 3>(g, st); break;
+    default: launch_t<KIND, FT, XT, PB, 4>(g, st); break;
   }
   return hipGetLastError();
 }

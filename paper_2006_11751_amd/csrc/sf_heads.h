@@ -283,22 +283,6 @@ __device__ inline __attribute__((always_inline)) bool heads_rows(const HeadsArgs
     for (int q = 0; q < g.n_heads; ++q) lp += lds.s_lp[tid][q];
     g.logp[row0 + tid] = lp;
   }
-  // The rows' new states go to the table: all cell tiles of these rows have read the old ones (their results are
-  // there, the waits above).
-  if constexpr (EX)
-    if (g.h_table) {
-      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)g.h, 0, 4 * g.B * g.S, 0x00027000);
-      const int per = g.S / 4;
-      for (int i = tid; i < rows * per; i += kHeadThreads) {
-        const int q = i / per, at = i - q * per;
-        heads_u32x4 v;
-        do
-          v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 4 * ((row0 + q) * g.S + 4 * at), 0, kDeviceScope);
-        while (v[0] == kNotYet || v[1] == kNotYet || v[2] == kNotYet || v[3] == kNotYet);
-        const uint32_t env = (uint32_t)g.ids[row0 + q];
-        if (env < (uint32_t)g.n_env) *((heads_u32x4*)(g.h_table + (size_t)env * g.S) + at) = v;
-      }
-    }
   return true;
 }
 

@@ -97,3 +97,37 @@ def test_workgroups_that_never_start(torch_cuda, monkeypatch, name, B):
         for _ in range(2):
             _same(_step(torch, pol, x, B), want, skip)
         pol.close()
+
+
+@pytest.mark.parametrize("name", ["gru", "lstm", "bf16", "resnet-lstm", "narrow"])
+def test_two_rows_of_one_environment(torch_cuda, monkeypatch, name):
+    """Rows of the batch that name the same environment, in one row tile and in several: each is computed from the
+    environment's old state, and the table receives the state of one of them, the last."""
+    torch = torch_cuda
+    net, limit = NETS[name]
+    B = min(limit, 100) - 3
+    w = wl.weights(net)
+    pol, three = _policy(monkeypatch, net, B, w), _policy(monkeypatch, net, B, w, SF_NO_TAIL=1)
+    x = _inputs(torch, net, B)
+    n_env = 2 * B
+    ids = np.random.default_rng(5).permutation(n_env)[:B].astype(np.int32)
+    ids[40], ids[7], ids[20], ids[B - 1], ids[B - 2], ids[17] = ids[3], ids[5], ids[1], ids[1], ids[0], n_env
+    last = {int(e): b for b, e in enumerate(ids) if e < n_env}
+    ids = torch.from_numpy(ids).cuda()
+    old = 0.1 * torch.randn(n_env, pol.H, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    h = torch.where((ids < n_env)[:, None], old[ids.clamp(max=n_env - 1).long()], torch.zeros((), device="cuda"))
+    state = pol.step(x["obs"], h, x["done"], 7, 11)["h_out"]
+    new = old.clone()
+    for e, b in last.items():
+        new[e] = state[b]
+    table = old.clone()
+    want = three.step_indexed(x["obs"], table, ids, x["done"], 7, 11)
+    for _ in range(10):
+        table = old.clone()
+        got = pol.step_indexed(x["obs"], table, ids, x["done"], 7, 11)
+        torch.cuda.synchronize()
+        for k in got:
+            assert torch.equal(got[k], want[k]), k
+        assert torch.equal(table, new)
+    pol.close()
+    three.close()
