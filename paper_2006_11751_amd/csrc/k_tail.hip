@@ -625,7 +625,7 @@ hipError_t launch_tail(const TailCall& t, hipStream_t st) {
   const int n_rt = (rows + 15) / 16;
   g.fc_cg = fc / 16; g.cell_cg = t.H / 8;
   g.n_fc = n_rt * g.fc_cg; g.n_cell = n_rt * g.cell_cg; g.n_heads = n_rt;
-  g.skip = t.skip;
+  g.skip = t.skip < 0 ? 0 : t.skip < g.n_fc + g.n_cell ? t.skip : g.n_fc + g.n_cell;  // (what the others can take over)
   if (t.fc_type == X_F32) return t.x_type == 0 ? launch_kind<X_F32, X_F32, 3>(t.lstm, g, st) : hipErrorInvalidValue;
   if (t.fc_type == X_BF16)
     return t.x_type == 1 ? launch_kind<X_BF16, X_BF16, 1>(t.lstm, g, st) : hipErrorInvalidValue;
