@@ -405,7 +405,8 @@ int sf_pipeline_destroy(sf_pipeline* pl);
  *   values   [T+1][N] fp32, row T = bootstrap value;  rewards [T][N] fp32;  dones [T][N] bytes
  *   vs, adv  [T][N] fp32 out;  loss [4] fp32 out = {L_pi, L_v, L_ent, their sum}
  *   dlogits_opt [T][N][sum(head_sizes)], dvalues_opt [T][N] (d/dV_t of L_v) fp32 out, or NULL
- *   workspace   sf_appo_loss_workspace_bytes(cfg) bytes (16 N + 16), owned by the caller
+ *   workspace   sf_appo_loss_workspace_bytes(cfg) bytes (16 N + 16), owned by the caller; its contents
+ *               do not matter, but calls that may run at the same time need one each
  * Asynchronous on hip_stream, allocation-free, and bitwise reproducible (the partial sums
  * are added in a fixed order).  Errors: SF_ERR_ARG (null or misaligned pointer, struct_size),
  * SF_ERR_SHAPE (sizes or hyperparameters out of range), SF_ERR_DEVICE. */
@@ -428,10 +429,12 @@ int sf_appo_loss(const sf_loss_config* cfg, const float* logits, const int32_t* 
  * per GPU for as long as the process runs, so N is limited to
  * sf_appo_loss_static_max_trajectories() = 16384; a larger N is refused with SF_ERR_SHAPE.  The
  * call allocates and frees nothing, runs on the current HIP device, and is otherwise
- * sf_appo_loss (same kernels, same bits).  All calls on one GPU share the one array, which
- * keeps the last call's contents (every slot a call reads is written by that call first): two
- * calls that overlap on one GPU, on different streams or from different threads, race; calls
- * on one stream are safe.  Errors: as sf_appo_loss, plus SF_ERR_SHAPE for N beyond the limit
+ * sf_appo_loss (same kernels, same bits).  All calls on one GPU share the one array, which keeps what
+ * the last call left there.  A call may look at slots that it has not written yet; a check word in
+ * each (31 bits, of its values and the call) tells its own entries from older ones.  Two
+ * calls that overlap on one GPU, on different streams or from different threads, race: their
+ * losses may be wrong or not be written at all (the other outputs are not affected); calls on one
+ * stream are safe.  Errors: as sf_appo_loss, plus SF_ERR_SHAPE for N beyond the limit
  * and SF_ERR_DEVICE if the array's address cannot be obtained. */
 int32_t sf_appo_loss_static_max_trajectories(void);
 int sf_appo_loss_static(const sf_loss_config* cfg, const float* logits, const int32_t* actions,
