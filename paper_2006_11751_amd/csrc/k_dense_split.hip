@@ -739,7 +739,7 @@ hipError_t launch_cfg(DenseArgs g, hipStream_t st) {
   g.n_cg = KIND == FC ? g.N / (16 * U) : g.H / (8 * U);
   const long long row_bytes = 16LL * RT * g.kn * 32 * (in_f32(XT) ? 4 : 2);
   const unsigned blocks = deal(g, row_bytes, (long long)U * g.kn * PB * group_bytes(KIND));
-  if constexpr (KIND == FC)
+  if constexpr (KIND == FC && !OUT16)  // (features leave in bf16 only where there are no measurements)
     if (g.meas.B > 0) {
       g.blocks = (int)blocks;
       dense_split_kernel<KIND, XT, PB, RT, U, DA, DB, OUT16, true>
@@ -943,7 +943,7 @@ bool dense_fc_takes_meas(int n0, int n1) { return meas_lds(n0, n1) <= kWaves * 1
 hipError_t launch_dense_fc(const void* x, int x_type, const uint16_t* w, const float* bias, void* out, int out_bf16,
                            int M, int K, int N, const MeasArgs* meas, hipStream_t st) {
   if (M == 0) return hipSuccess;
-  if (!dense_fc_supported(K, N) || (meas && !dense_fc_takes_meas(meas->n0, meas->n1))) return hipErrorInvalidValue;
+  if (!dense_fc_supported(K, N) || (meas && (out_bf16 || !dense_fc_takes_meas(meas->n0, meas->n1)))) return hipErrorInvalidValue;
   DenseArgs g{};
   if (meas) g.meas = *meas;
   g.x1 = x; g.w = (const uint8_t*)w; g.b1 = bias; g.out = out;
