@@ -588,8 +588,9 @@ hipError_t launch_conv_image_split(const float* in, const uint16_t* wpk, const f
       // From half the chip in workgroups of eight waves to a second round of few of them: the next round on the way
       // under this one's products.  Steps of the standard network at 128 output channels, us, without / with:
       // 258 rows 53.7 / 53.3, 400 rows 57.0 / 56.6, 512 rows 62.0 / 61.1, 514 rows 82.0 / 78.7, 640 rows 83.7 / 82.4,
-      // 768 rows 87.7 / 87.5, 896 rows 93.6 / 95.2, 1500 rows 142 / 147.  (Alone the kernel is the faster one there
-      // too, 2048 rows 25 / 23, but the launches around it are not; below 256 rows it is not, 200 rows 6.0 / 7.6.)
+      // 768 rows 87.7 / 87.5, 896 rows 93.6 / 95.2, 1500 rows 142 / 147.  (A measured window, without a cause: alone the
+      // kernel is the faster one beyond it, too, 2048 rows 25 / 23, but the launches around it get longer there, which
+      // has not been explained.  Below 256 rows it is not faster, 200 rows 6.0 / 7.6.)
       if (const long long work = (long long)((B + 1) / 2) * (N / 128); ahead_fits(g) && work > 128 && work <= 320)
         return launch_t<64, 3, 2, 3, 3, 8, 7, true>(g, st);
       return launch_t<64, 3, 2, 3, 3, 4, 13>(g, st);

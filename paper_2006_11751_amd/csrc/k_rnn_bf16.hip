@@ -301,8 +301,12 @@ __global__ __launch_bounds__(256) void rnn_bf16_kernel(RnnBf16Args g) {
 // way and two barriers' worth of conversions per chunk: 3.2 k cycles per chunk and CU at 768 of products.  Taking
 // these rows, too, it made steps of a network of 512 features and units 59.6 us at 700 rows (52.9 with this one), 65.5 at 1024
 // (58.8), 80.8 at 1500 (77.3), 92.6 at 2048 (89.6), 143.8 at 4096 (141.3; the launch 34.6 -> 31.2), 274 at
-// 8192 (269).  What bounds it now is the way from L2 into LDS: 7 to 10 TB/s.  Here
-// chunks of 32 numbers of K go straight to LDS, two per barrier, kDepth - 2 ahead: bf16 features, then the fp32 state, which is
+// 8192 (269).  What bounds it now: with few rows the way from L2 into LDS (7 to 10 TB/s).  In the tile of most rows (128 x 64:
+// beyond 2048 rows of 512 units, 6.5 TB/s) the ring is four chunks deep, since a slot has room for a chunk of the fp32
+// state, of which features fill half: two chunks are on their way, and each barrier waits for both.  k_fc16.hip draws 12
+// TB/s over the same path, so that this is exposed latency.  Here
+// chunks of 32 numbers of K go straight to LDS, two per barrier, kDepth - 2 ahead (kDepth 8, 8, 4 in the tiles of 64 x 32, 64 x 64,
+// 128 x 64; LSTM 8, 6, 4): bf16 features, then the fp32 state, which is
 // split into its two bf16 numbers by the wave that reads it (twice: two tiles of units) and zeroed there where
 // an episode begins; each with the weights of its columns.  RT x UT waves of 32 rows x 32 units x all gates.
 // Rows of features and weights are 64 bytes (four pieces, exchanged by r / 4), of the state 128 (eight, by

@@ -467,7 +467,7 @@ __device__ inline __attribute__((always_inline)) bool table_rows(const HeadsArgs
 
 // The kernel's argument, each time opaque: a role's part of it is loaded when the role begins.  (Loaded for all
 // roles ahead of the loop over them, as the compiler has it otherwise, it does not fit the scalar registers; 190
-// of them were spilled to lanes and read back, 2 us of each role.)
+// of them were spilled to lanes and read back, 2 us of each role.  14 to 20 still are with fp16 rows.)
 __device__ inline const TailArgs& tail_args() {
   auto p = (const __attribute__((address_space(4))) TailArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));

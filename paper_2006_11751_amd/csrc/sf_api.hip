@@ -840,8 +840,9 @@ int build_policy(Policy* p, const sf_policy_config* cfg, const sf_policy_weights
   for (int i = 0; i < 3; ++i)
     p->act[i] = i < n_act ? (float*)bld.dev_alloc(act_row_bytes * cfg->max_batch)
                           : nullptr;
-  // FC layer, core and heads in one launch: the three on their kernels for few rows, features of a type that
-  // it is instantiated for, and a first launch that can prepare it.
+  // FC layer, core and heads in one launch: the three on their kernels for few rows (so not in a handle for many rows, whose
+  // core is fixed to a kernel with another order of sums: beyond 512 rows of 512 units), no measurements, features
+  // of a type that it is instantiated for, and a first launch that can prepare it.
   const int types = 4 * fc_type(p) + core_type(p);
   const bool prepared = cfg->encoder == SF_ENCODER_RESNET ? p->convs[0].impl == STEM_POOL
                                                           : p->conv12_split || p->ops[0].mid_buf >= 0;
