@@ -303,11 +303,12 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     // A wave owns a run of rows of one 16-pixel column group and walks down it: image row i gives two operands, P
     // (columns 0 and 1 of the windows) and Q (column 2 of rows i - 1 and i).  P is the first two taps of all
     // three filter rows, for the three output rows that see it; Q is (none, 8) of output row i - 2 and, kept for the
-    // next image row, (2, 5) of row i - 1: five MFMAs per output row on two reads, into three accumulators in turn,
+    // next image row, (2, 5) of row i - 1: five MFMAs per output row on two reads, into four accumulators in turn,
     // the operands of the next row requested ahead of them.  The products of an output row are added in the order
     // (0, 1), (3, 4), (6, 7), (2, 5), (8), the order of a tile computed by itself: results are rounded to fp16 between
-    // convolutions, so that another one shows (as much as 0.5 % at the network's end; adding (2, 5) an image row
-    // earlier is no faster: 8192 rows 1580 and 1581 us a step).
+    // convolutions, so that another one shows (as much as 0.5 % at the network's end).  Its last three then follow one
+    // another, and the row is rounded behind the next row's products: steps of 8192 rows 1651 -> 1635 us, of 101 rows
+    // 78.9 -> 78.8; adding (2, 5) an image row earlier, 1645.
     // A tile by itself took five reads, with nothing to cover its first ones and its epilogue.  Two blocks on
     // 36 x 64 pixels: 8192 frames 495 -> 389 us (3.1 TB/s; the matrix pipe is busy 0.4 of the time), 2048 frames
     // 131 -> 103, 101 frames 18.5 -> 15.1.  (Q's two rows cost its reads 8 cycles; rows of a multiple of 256
@@ -333,11 +334,11 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
       asm volatile("" : "+v"(from_p), "+v"(from_q), "+s"(rows));
       const unsigned char *at_p = src + from_p, *at_q = src + from_q;
       u32x4 p[2], q[3];
-      f32x4 acc[3];
+      f32x4 acc[4];
       p[0] = *(const u32x4*)at_p;
       auto step = [&](auto self, auto ic) __attribute__((always_inline)) {  // image row y0 + i
         constexpr int i = decltype(ic)::value;
-        if (i >= rows + 2) return;
+        if (i >= rows + 3) return;
         if (i + 1 < RT + 2) {
           at_p += i < rows + 1 ? ROW : 0;  // (behind the last row: that one again, for no use)
           p[(i + 1) & 1] = *(const u32x4*)at_p;
@@ -345,15 +346,15 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
           q[(i + 1) % 3] = *(const u32x4*)at_q;
         }
         __builtin_amdgcn_sched_barrier(0);
-        f32x4 &a0 = acc[i % 3], &a1 = acc[(i + 2) % 3], &a2 = acc[(i + 1) % 3];  // of output rows i, i - 1, i - 2
-        if (i > 1) a2 = mfma(2, p[i & 1], a2);
+        f32x4 &a0 = acc[i % 4], &a1 = acc[(i + 3) % 4], &a2 = acc[(i + 2) % 4], &a3 = acc[(i + 1) % 4];  // of output rows i, i - 1, ...
+        if (i > 1 && i < RT + 2) a2 = mfma(2, p[i & 1], a2);
         if (i > 0 && i < RT + 1) a1 = mfma(1, p[i & 1], a1);
-        if (i > 1) a2 = mfma(3, q[(i + 2) % 3], a2);
+        if (i > 1 && i < RT + 2) a2 = mfma(3, q[(i + 2) % 3], a2);
         if (i < RT) a0 = mfma(0, p[i & 1], init);
-        if (i > 1) a2 = mfma(4, q[i % 3], a2);
+        if (i > 1 && i < RT + 2) a2 = mfma(4, q[i % 3], a2);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (i > 1) done(i - 2, a2);
-        if constexpr (i + 1 < RT + 2) self(self, std::integral_constant<int, i + 1>{});
+        if constexpr (i > 2) done(i - 3, a3);
+        if constexpr (i + 1 < RT + 3) self(self, std::integral_constant<int, i + 1>{});
       };
       step(step, std::integral_constant<int, 0>{});
     };
