@@ -364,8 +364,8 @@ __device__ inline void add_if_complete(const LossArgs& g, int n, float inv_m) {
 //      the tile to memory; the partial sums meanwhile by the first wave (publish, add_if_complete).
 // (One lane per sample through all of it, two waves per workgroup, took 14.5 us at 64 trajectories of
 // 32 steps and seven heads, 19.6 at 2048; now 9.4 and 15.7, 1.6 TB/s of logits, actions and gradients:
-// see pick_tile for whole calls.  The argument's three arrays of 16 and the addresses do not fit the scalar registers: 104 to 119
-// of them are spilled to lanes with 32 lanes per trajectory, 42 to 56 with 64; what that costs has not been measured.)
+// see pick_tile for whole calls.  The argument's three arrays of 16 and the addresses do not fit the scalar registers: 103 to 118
+// of them are spilled to lanes with 32 lanes per trajectory, 41 to 55 with 64; what that costs has not been measured.)
 // Per head one exponential per logit forward,
 //   d_i = l_i - max, e_i = exp(d_i), se = sum e_i, sd = sum e_i d_i
 //   lse = max + log se,  entropy = log se - sd / se   (= -sum p_i (l_i - lse))

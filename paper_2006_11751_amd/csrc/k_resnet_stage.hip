@@ -310,8 +310,8 @@ __global__ __launch_bounds__(kNT, 1) void res_stage_kernel(StageArgs g) {
     // another, and the row is rounded behind the next row's products: steps of 8192 rows 1651 -> 1635 us, of 101 rows
     // 78.9 -> 78.8; adding (2, 5) an image row earlier, 1645.
     // A tile by itself took five reads, with nothing to cover its first ones and its epilogue.  Two blocks on
-    // 36 x 64 pixels: 8192 frames 495 -> 389 us (3.1 TB/s; the matrix pipe is busy 0.4 of the time), 2048 frames
-    // 131 -> 103, 101 frames 18.5 -> 15.1.  (Q's two rows cost its reads 8 cycles; rows of a multiple of 256
+    // 36 x 64 pixels: 8192 frames 495 -> 383 us (3.2 TB/s; the matrix pipe is busy 0.4 of the time), 2048 frames
+    // 131 -> 101, 101 frames 18.5 -> 15.1.  (Q's two rows cost its reads 8 cycles; rows of a multiple of 256
     // bytes would not, but do not fit twice.)
     const int j16 = lane & 15, g16 = lane >> 4;
     constexpr int CG = W / 16, SEGS = kNW / CG;
