@@ -136,7 +136,7 @@ def test_workgroups_that_never_start(torch_cuda, monkeypatch, name, B):
 @pytest.mark.parametrize("name", ["gru", "lstm", "bf16", "resnet-lstm", "narrow"])
 def test_two_rows_of_one_environment(torch_cuda, monkeypatch, name):
     """Rows of the batch that name the same environment, in one row tile and in several: each is computed from the
-    environment's old state, and the table receives the state of one of them, the last."""
+    environment's old state, and the table receives the state of one of them, the last; recorded, too."""
     torch = torch_cuda
     net, in_one, _ = NETS[name]
     B = min(in_one[-1], 100) - 3
@@ -157,12 +157,27 @@ def test_two_rows_of_one_environment(torch_cuda, monkeypatch, name):
     table = old.clone()
     want = three.step_indexed(x["obs"], table, ids, x["done"], 7, 11)
     assert _launches(torch, three, x, B) - _launches(torch, pol, x, B) == 2
-    for _ in range(10):
-        table = old.clone()
-        got = pol.step_indexed(x["obs"], table, ids, x["done"], 7, 11)
+
+    def check(got):
         torch.cuda.synchronize()
         for k in got:
             assert torch.equal(got[k], want[k]), k
         assert torch.equal(table, new)
+
+    for _ in range(10):
+        table.copy_(old)
+        check(pol.step_indexed(x["obs"], table, ids, x["done"], 7, 11))
+    out = pol.alloc_outputs(B)
+    del out["h_out"]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pol.step_indexed(x["obs"], table, ids, x["done"], 7, 11, out=out, stream=torch.cuda.current_stream())
+    for _ in range(4):  # with eager work and synchronisations between the replays
+        table.copy_(old)
+        for v in out.values():
+            v.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        check(out)
     pol.close()
     three.close()
